@@ -240,7 +240,9 @@ int build_plan(const char* spec, int batch, int dtype, int bn_mode, Plan* plan) 
       if (S[q].kind == ST_CONV) { if (fc < 0) fc = (int)q; lc = (int)q; }
     if (fc >= 0 && (fc == 0 || (fc == 1 && S[0].kind == ST_TRANSPOSE && S[0].last_token == -1))) {
       Step& st = S[fc];
-      if (st.cin <= 4 && thin_in_supported(st.cin, st.cout, st.k, st.up)) {
+      // (the thin kernels write no binary32 copy of a sigmoid output, which the backward pass of a bfloat16 model reads)
+      const bool needs_aux = dtype == AE_BF16 && st.act == ACT_SIGMOID && !st.has_bn && !st.pool;
+      if (st.cin <= 4 && !needs_aux && thin_in_supported(st.cin, st.cout, st.k, st.up)) {
         st.thin = 1;
         if (fc == 1) { S.erase(S.begin()); --lc; }
       }
