@@ -50,6 +50,7 @@ struct ae_model {
   float* wgrad_ws = nullptr;       // used on the side stream only (or on the caller's when not overlapping)
   float* wgrad_ws_inorder = nullptr;   // for the weight gradients that stay in order on the caller's stream
   float* splitk_ws = nullptr;
+  char* dypad[3] = {nullptr, nullptr, nullptr};   // padded conv-output gradients: beside draw_buf[0], draw_buf[1], and of layers that stay in order
   bool overlap = true;
   hipStream_t side = nullptr;
   hipEvent_t ev_fork = nullptr;
@@ -158,13 +159,18 @@ const void* step_input(const ae_model* m, size_t i, const void* x) { return i ==
 
 // forward: does this conv step read repacked weights?
 bool needs_fwd_pack(const Plan& P, const Step& st) {
-  return st.kind == ST_CONV && st.thin == 0 && !(st.k == 1 && P.dtype == AE_F32 && !st.mfma);
+  return st.kind == ST_CONV && st.thin == 0 && !(st.k == 1 && P.dtype == AE_F32 && !st.mfma && !st.chunks);
 }
 bool needs_dgrad_pack(const Step& st) { return st.kind == ST_CONV && st.thin == 0 && st.needs_dx; }
 
 // Repack the weights of every layer of a pass with one launch (more layers than a batch
 // holds: the per-layer launches remain).
-bool is_big_fc(const Step& st) { return st.k == 1 && (int64_t)st.cout * st.cin >= (1 << 20); }
+// (channel counts that are whole 16-byte chunks in either type: plain conversion and transpose are the packed forms)
+bool is_big_fc(const Step& st) { return st.k == 1 && (int64_t)st.cout * st.cin >= (1 << 20) && st.cin % 8 == 0 && st.cout % 8 == 0; }
+// channels per tap of the packed weights (0: as many as there are)
+int pack_ld(const Plan& P, const Step& st, bool dgrad) {
+  return dgrad ? (st.chunks_d ? chan_pad(st.cout, P.dtype) : 0) : (st.chunks ? chan_pad(st.cin, P.dtype) : 0);
+}
 
 // part 0: everything but the big fully-connected layers; part 1: those (they take long and are
 // needed late in the forward pass, so they go last and get an event of their own)
@@ -183,7 +189,7 @@ int pack_all(ae_model* m, const float* params, bool dgrad, hipStream_t s, int pa
       TIMED(0, dgrad ? "bwd.pack_weights_up" : "fwd.pack_weights_up", 0.0,
             (double)st.cout * st.cin * (36.0 + 16.0 * (double)dtype_size(P.dtype)),
             launch_pack_weights_up(params + st.w_off, dgrad ? st.wpack_d : st.wpack, st.cout, st.cin, P.dtype,
-                                   dgrad ? CONV_UP_DGRAD : CONV_UP_PHASES, s));
+                                   dgrad ? CONV_UP_DGRAD : CONV_UP_PHASES, s, pack_ld(P, st, dgrad)));
       continue;
     }
     if (is_big_fc(st)) {
@@ -198,6 +204,7 @@ int pack_all(ae_model* m, const float* params, bool dgrad, hipStream_t s, int pa
     j.w = params + st.w_off; j.wp = dgrad ? st.wpack_d : st.wpack;
     j.cout = st.cout; j.cin = st.cin; j.k = st.k; j.dgrad = dgrad ? 1 : 0; j.first_block = 0;
     j.frag = (dgrad ? st.wfrag_d : st.wfrag) ? 1 : 0;
+    j.ld = pack_ld(P, st, dgrad);
     bytes += (double)st.cout * st.cin * st.k * st.k * (4.0 + (double)dtype_size(P.dtype));
   }
   if (pb.n > 0)
@@ -261,19 +268,22 @@ int forward_conv(ae_model* m, int si, Step& st, const float* params, const void*
   const void* w = nullptr;
   if (st.thin == 1) {
     // canonical weights are read directly
-  } else if (st.k == 1 && P.dtype == AE_F32 && !st.mfma) {
+  } else if (st.k == 1 && P.dtype == AE_F32 && !st.mfma && !st.chunks) {
     w = params + st.w_off;  // [C_out][C_in] is already the packed order (the MFMA loader wants a 16-byte aligned copy)
   } else {
     if (!m->packed_in_batch) {
       if (st.up_phases)
         TIMED(si, "fwd.pack_weights_up", 0.0, wel * 4.0 + 16.0 * st.cout * st.cin * es,
-              launch_pack_weights_up(params + st.w_off, st.wpack, st.cout, st.cin, P.dtype, CONV_UP_PHASES, s));
+              launch_pack_weights_up(params + st.w_off, st.wpack, st.cout, st.cin, P.dtype, CONV_UP_PHASES, s, pack_ld(P, st, false)));
       else
         TIMED(si, "fwd.pack_weights", 0.0, wel * (4.0 + es),
-              launch_pack_weights(params + st.w_off, st.wpack, st.cout, st.cin, st.k, P.dtype, false, s, st.wfrag));
+              launch_pack_weights(params + st.w_off, st.wpack, st.cout, st.cin, st.k, P.dtype, false, s, st.wfrag, pack_ld(P, st, false)));
     }
     w = st.wpack;
   }
+  if (st.xpad && (st.chunks || !m->inference))     // kept until the weight gradient has read it
+    TIMED(si, "fwd.pad_channels", 0.0, 2.0 * in_el * es,
+          launch_pad_channels(in, st.xpad, (int64_t)P.batch * st.hin * st.win, st.cin, P.dtype, s));
   const bool second_pass = st.has_bn || st.pool;
   ConvArgs a;
   a.x = in; a.w = w; a.bias = params + st.b_off;
@@ -336,6 +346,14 @@ int forward_conv(ae_model* m, int si, Step& st, const float* params, const void*
     // (slot FLOPs are the algorithmic ones of the definition; the four-phase form of an upsampled conv,
     // named apart, executes 4/9 of them)
     TIMED(si, st.up_phases ? "fwd.conv_mfma_phases" : "fwd.conv_mfma", conv_flops, conv_bytes, launch_conv_mfma(a, s));
+  } else if (st.chunks) {
+    if (st.xpad) a.x = st.xpad;
+    if (st.has_bn && P.bn_mode == 0 && !st.up_phases) {
+      a.partial = m->partial;
+      const int pr = plan_conv_chunks(a).bm;
+      nblk = (int)((rows + pr - 1) / pr);
+    }
+    TIMED(si, st.up_phases ? "fwd.conv_chunks_phases" : "fwd.conv_chunks", conv_flops, conv_bytes, launch_conv_chunks(a, s));
   } else {
     TIMED(si, "fwd.conv_direct", conv_flops, conv_bytes, launch_conv_direct(a, s));
   }
@@ -451,6 +469,13 @@ int backward_conv(ae_model* m, int si, Step& st, const float* params, const void
     TIMED(si, "bwd.bias_finalize", 0.0, 0.0,
           launch_colsum_finalize(m->partial, nblocks_for(rows), st.cout, grads + st.b_off, s));
   }
+  // the conv-output gradient in whole chunks, where the kernels below want it; its buffer is guarded like the draw buffer beside it
+  const void* dr_p = dr;
+  if ((st.chunks_d || st.chunks_w) && chan_pad(st.cout, P.dtype) != st.cout) {
+    char* const buf = m->dypad[dr == m->draw ? m->draw_sel : 2];
+    TIMED(si, "bwd.pad_channels", 0.0, 2.0 * raw_el * es, launch_pad_channels(dr, buf, rows, st.cout, P.dtype, s));
+    dr_p = buf;
+  }
   // Fork: the weight gradient reads dr and the saved input.  When dr is one of the two
   // alternating buffers it may run beside the rest of the pass; a dr that is the incoming
   // gradient itself is overwritten by the very next layer, so that case stays in order.
@@ -549,13 +574,15 @@ int backward_conv(ae_model* m, int si, Step& st, const float* params, const void
   }
   // weight gradient
   WgradArgs wa;
-  wa.x = in; wa.dy = dr; wa.dw_canonical = grads + st.w_off;
+  wa.x = st.chunks_w && st.xpad ? st.xpad : in; wa.dy = st.chunks_w ? dr_p : dr; wa.dw_canonical = grads + st.w_off;
   wa.n = P.batch; wa.hc = st.hc; wa.wc = st.wc; wa.cin = st.cin; wa.cout = st.cout; wa.k = st.k; wa.up = st.up;
   wa.dtype = P.dtype;
   if (wgrad_mfma_supported(wa)) {
     // (slot FLOPs are the algorithmic ones of the definition; the phase form of an upsampled layer, named apart, executes 4/9 of them)
     TIMED_ON(ws, si, wgrad_mfma_up_phases(wa) ? "bwd.wgrad_mfma_phases" : "bwd.wgrad_mfma", conv_flops,
              (in_el + raw_el) * es + wel * 4, launch_wgrad_mfma(wa, wws, ws));
+  } else if (st.chunks_w) {
+    TIMED_ON(ws, si, "bwd.wgrad_chunks", conv_flops, (in_el + raw_el) * es + wel * 4, launch_wgrad_chunks(wa, wws, ws));
   } else {
     TIMED_ON(ws, si, "bwd.wgrad_direct", conv_flops, (in_el + raw_el) * es + wel * 4,
              launch_wgrad_direct(wa, wws, wws == m->wgrad_ws ? P.max_wgrad_floats : P.max_wgrad_inorder_floats, ws));
@@ -567,13 +594,13 @@ int backward_conv(ae_model* m, int si, Step& st, const float* params, const void
     if (!m->packed_in_batch) {
       if (st.up_dgrad)
         TIMED(si, "bwd.pack_weights_up", 0.0, wel * 4.0 + 16.0 * st.cout * st.cin * es,
-              launch_pack_weights_up(params + st.w_off, st.wpack_d, st.cout, st.cin, P.dtype, CONV_UP_DGRAD, s));
+              launch_pack_weights_up(params + st.w_off, st.wpack_d, st.cout, st.cin, P.dtype, CONV_UP_DGRAD, s, pack_ld(P, st, true)));
       else
         TIMED(si, "bwd.pack_weights", 0.0, wel * (4.0 + es),
-              launch_pack_weights(params + st.w_off, st.wpack_d, st.cout, st.cin, st.k, P.dtype, true, s, st.wfrag_d));
+              launch_pack_weights(params + st.w_off, st.wpack_d, st.cout, st.cin, st.k, P.dtype, true, s, st.wfrag_d, pack_ld(P, st, true)));
     }
     ConvArgs a;
-    a.x = dr; a.w = st.wpack_d; a.bias = nullptr;
+    a.x = st.chunks_d ? dr_p : dr; a.w = st.wpack_d; a.bias = nullptr;
     a.y = (st.up && !st.up_dgrad) ? m->dfull : gnext;
     if (st.up_dgrad) a.geom = CONV_UP_DGRAD;   // straight to the stored resolution: no full-size gradient, no 2x2 sum
     a.w_frag = st.wfrag_d;
@@ -609,6 +636,9 @@ int backward_conv(ae_model* m, int si, Step& st, const float* params, const void
       // (the 4x4 stride-2 form, named apart, executes 4/9 of the algorithmic multiply-adds and writes the stored resolution)
       TIMED(si, st.up_dgrad ? "bwd.dgrad_mfma_stride2" : "bwd.dgrad_mfma", conv_flops,
             (raw_el + (st.up_dgrad ? in_el : full_el) + wel) * es, launch_conv_mfma(a, s));
+    else if (st.chunks_d)
+      TIMED(si, st.up_dgrad ? "bwd.dgrad_chunks_stride2" : "bwd.dgrad_chunks", conv_flops,
+            (raw_el + (st.up_dgrad ? in_el : full_el) + wel) * es, launch_conv_chunks(a, s));
     else
       TIMED(si, "bwd.dgrad_direct", conv_flops, (raw_el + full_el + wel) * es, launch_conv_direct(a, s));
     if (st.up && !st.up_dgrad)
@@ -657,6 +687,7 @@ int model_create(const char* layer_spec, int batch, int dtype, int bn_mode, ae_m
     st.wpack_d = st.off_wpack_d >= 0 ? m->ws + st.off_wpack_d : nullptr;
     st.bn_vec = st.off_bn >= 0 ? (float*)(m->ws + st.off_bn) : nullptr;
     st.aux = st.off_aux >= 0 ? (float*)(m->ws + st.off_aux) : nullptr;
+    st.xpad = st.off_xpad >= 0 ? m->ws + st.off_xpad : nullptr;
     if (st.kind == ST_CONV) {
       ConvArgs a;
       memset(&a, 0, sizeof(a));
@@ -677,6 +708,11 @@ int model_create(const char* layer_spec, int batch, int dtype, int bn_mode, ae_m
         st.up_phases = conv_up_phases_usable(f);
         st.up_dgrad = st.needs_dx && conv_up_dgrad_usable(d);
       }
+      if (st.up && st.k == 3) {
+        // the kernel for any channel counts takes the cheaper forms always
+        if (st.chunks) st.up_phases = true;
+        if (st.chunks_d) st.up_dgrad = true;
+      }
       if (st.mfma && st.thin == 0) {
         // likewise the order of the packed weights
         if (st.up_phases) f.geom = CONV_UP_PHASES;
@@ -696,6 +732,7 @@ int model_create(const char* layer_spec, int batch, int dtype, int bn_mode, ae_m
   m->wgrad_ws = (float*)(m->ws + P.off_wgrad);
   m->wgrad_ws_inorder = (float*)(m->ws + P.off_wgrad_inorder);
   m->splitk_ws = (float*)(m->ws + P.off_splitk);
+  for (int i = 0; i < 3; ++i) m->dypad[i] = m->ws + P.off_dypad + i * P.max_dypad_bytes;
   m->fused_small = fused_small_match(P, &m->fused);
   *out = m;
   return AE_OK;

@@ -1,8 +1,7 @@
 // ae_conv_direct.hip — general-shape convolution kernels on the vector ALUs.
-// They serve every layer shape the MFMA implicit-GEMM kernels do not take
-// (channel counts that are not a multiple of the MFMA K-slab, e.g. the 1- or
-// 3-channel first layer and the 1- or 3-channel last layer) and are the only
-// weight-gradient kernels for those shapes.
+// They serve the small 1x1 layers for which the matrix-core kernels' launches cost
+// more than the work (conv_chunks_worthwhile, wgrad_chunks_worthwhile), and tensors
+// beyond the 32-bit offsets of those kernels.
 //
 // Activations are [n][H][W][C]; packed weights are [C_out][k][k][C_in].
 // If `up` is set the input tensor is stored at half resolution and read through a

@@ -17,8 +17,10 @@
 //                  optionally split over K; also the two cheaper forms of a 3x3 convolution behind
 //                  a x2 upsample (four 2x2 phase convolutions forward, one 4x4 stride-2
 //                  convolution for the input gradient; see IgemmParams)
+//                  and, with CHUNKS, any channel counts (a 16-byte chunk of K belongs to one tap; see there)
 //   k_wgrad_row3   weight gradient, three taps per workgroup from one input patch (bf16)
 //   k_wgrad_rows, k_wgrad   weight gradient, one tap per workgroup (fp32, 1x1, odd shapes)
+//   k_wgrad_chunks          weight gradient of any channel counts, columns (tap, ci) walked across tap borders
 // The shared epilogue adds the bias, rounds to the storage type, optionally reduces per-channel
 // sum / sum of squares of the tile (batch-norm statistics), applies the activation and stores [M][N].
 #include "ae_device.h"
@@ -75,6 +77,7 @@ struct IgemmParams {
   // of the image (Wt = Wc / strips, TH = 256 / Wt); GEMM row m = tile * 256 + th * Wt + tw then is pixel
   // (row block * TH + th, strip * Wt + tw) of its image.  1: a tile spans the image width and rows are pixels in order.
   int strips = 1;
+  int chunks = 0;              // CHUNKS kernels: 16-byte chunks of one tap (= Cin / elements per chunk)
   int log_wt = 6;              // log2 of the strip width Wc / strips
   int log_w = -1, log_h = -1;  // log2 of Wc and Hc when both are powers of two (the four-phase output mapping), else -1
   // Companion tensor of the output's shape and layout (interior tiles only): the saved activation a of the layer whose
@@ -294,7 +297,8 @@ __device__ __forceinline__ void igemm_resid_stats(const floatx16 (&acc)[MI][NJ],
 // Results go through a wave-private LDS staging area (the operand buffers are free: the K loop
 // ended on a barrier) so that global stores are 16 bytes wide and each instruction covers
 // whole row segments.  smem: at least 4*32*(WN + 16/sizeof(T))*sizeof(T) bytes; sRed: [WGM][2][BN].
-template <typename T, int BM, int BN, int WGM, int WGN, bool INTERIOR, int EPI = 0>
+// PHASED: a checked tile may belong to an output parity of an upsampled convolution (interior tiles always may).
+template <typename T, int BM, int BN, int WGM, int WGN, bool INTERIOR, int EPI = 0, bool PHASED = false>
 __device__ __forceinline__ void igemm_epilogue(floatx16 (&acc)[BM / WGM / 32][BN / WGN / 32], const IgemmParams& p,
                                                char* smem, float (*sRed)[2][BN], int64_t m0, int n0, int64_t tile_m,
                                                int phase = 0) {
@@ -375,8 +379,9 @@ __device__ __forceinline__ void igemm_epilogue(floatx16 (&acc)[BM / WGM / 32][BN
           if (wide_store) {
             Store<T>::st(&stage[lr * SW + j * 32 + col_lane], a);
           } else if (m < p.M && col_ok) {
-            Store<T>::st(&Y[m * p.N + col], a);
-            if (p.y_aux) p.y_aux[m * p.N + col] = a;
+            const int64_t o = (PHASED ? igemm_out_row(p, m, phase, 0) : m) * p.N + col;   // (column strips: interior tiles only)
+            Store<T>::st(&Y[o], a);
+            if (p.y_aux) p.y_aux[o] = a;
           }
         }
       }
@@ -390,7 +395,7 @@ __device__ __forceinline__ void igemm_epilogue(floatx16 (&acc)[BM / WGM / 32][BN
           const int64_t m = m0 + wm * WM + i * 32 + lr;
           const int col0 = n0 + wn * WN + ch * EPC;
           if (m < p.M && col0 < p.N)
-            *reinterpret_cast<uint4v*>(Y + m * p.N + col0) = *reinterpret_cast<const uint4v*>(&stage[lr * SW + ch * EPC]);
+            *reinterpret_cast<uint4v*>(Y + (PHASED ? igemm_out_row(p, m, phase, 0) : m) * p.N + col0) = *reinterpret_cast<const uint4v*>(&stage[lr * SW + ch * EPC]);
         }
       }
     }
@@ -506,8 +511,19 @@ struct SlabReads<KS, KS, MI, NJ, BKB> {
 // registers.  A wave waits for its own loads of the slab it is about to read (vmcnt), then
 // the workgroup barrier makes every wave's loads visible and also guarantees that the stage
 // about to be refilled has been read by everybody.
-template <typename T, int BM, int BN, int WGM, int WGN, int BKB, bool INTERIOR, bool DMA, int EPI = 0>
+//
+// CHUNKS: any channel counts.  p.Cin is the channel count rounded up to whole 16-byte chunks (both operands are stored
+// with that row length, zeros behind the channels), and K is walked chunk by chunk across tap borders: chunk q belongs
+// to tap q / p.chunks, so every lane keeps the tap of the one chunk per slab it loads (its slot is the same in every
+// pass of the loader) and advances it by a slab's CPR chunks.  Nothing but the tail of the last slab is multiplied in
+// vain: 9 x 48 channels are 13.5 slabs, where slabs that end with their tap would be 18, and a 3-channel image 2.25
+// instead of 9.  Chunks past the end read zeros (both operands: 0 x Inf would be NaN).  What it costs: the pixel
+// offsets are formed for every slab, not once per tap, a dozen VALU instructions per 16 bytes loaded.
+// Measured (bf16, 24 x 36 x 60 pixels): 48 -> 80 channels, 3x3, 25 us = 143 TFLOP/s, where one thread per output on the
+// vector ALUs took 3.4 ms; two such layers at 64 x 64 x 8 forward and backward 140 us against 11.4 ms.
+template <typename T, int BM, int BN, int WGM, int WGN, int BKB, bool INTERIOR, bool DMA, int EPI = 0, bool CHUNKS = false>
 __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(2))) void k_igemm(IgemmParams p) {
+  static_assert(!CHUNKS || (!INTERIOR && DMA && EPI == 0), "the chunk walk exists for checked tiles through the DMA pipeline");
   static_assert(EPI == 0 || INTERIOR, "the special epilogues exist for check-free tiles only");
   static_assert(WGM * WGN == 4 || WGM * WGN == 8, "four or eight wavefronts per workgroup");
   constexpr int NT = WGM * WGN * 64;            // threads: all of them load, each wavefront owns a WM x WN part of the tile
@@ -518,14 +534,15 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
   constexpr int RSTEP = NT / CPR;               // rows covered by one pass of the loader threads
   constexpr int WM = BM / WGM, WN = BN / WGN;   // wave tile
   constexpr int MI = WM / 32, NJ = WN / 32;     // 32x32 MFMA tiles per wave
-  constexpr int A_CHUNKS = BM / RSTEP, B_CHUNKS = BN / RSTEP;
+  constexpr int BNL = BN < RSTEP ? RSTEP : BN;  // weight rows loaded: a whole pass at least (rows past N read zeros)
+  constexpr int A_CHUNKS = BM / RSTEP, B_CHUNKS = BNL / RSTEP;
   constexpr int SW = WN + 16 / ES;              // staging row stride of the epilogue (elements): +16 bytes
   constexpr int NSTAGE = DMA ? (NT == 512 ? 4 : 3) : 2;   // eight wavefronts: one workgroup per compute unit, LDS for a fourth stage
-  constexpr int SLAB_BYTES = NSTAGE * (BM + BN) * BKB;
+  constexpr int SLAB_BYTES = NSTAGE * (BM + BNL) * BKB;
   constexpr int STAGE_BYTES = (NT / 64) * 32 * SW * ES;
   __shared__ __attribute__((aligned(16))) char smem[SLAB_BYTES > STAGE_BYTES ? SLAB_BYTES : STAGE_BYTES];
   char* const sA = smem;                        // [NSTAGE][BM*BKB]
-  char* const sB = smem + NSTAGE * BM * BKB;    // [NSTAGE][BN*BKB]
+  char* const sB = smem + NSTAGE * BM * BKB;    // [NSTAGE][BNL*BKB]
   __shared__ float sRed[WGM][2][BN];            // [wave row][sum | sumsq][column]
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -600,7 +617,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
   for (int i = 0; i < B_CHUNKS; ++i) {
     const int row = n0 + lrow + i * RSTEP;
-    b_off[i] = row < p.N ? (unsigned)(phase * p.N + row) * (unsigned)p.K * (unsigned)ES + (unsigned)gchunk * 16u : kOob;
+    b_off[i] = row < p.N && lrow + i * RSTEP < BN ? (unsigned)(phase * p.N + row) * (unsigned)p.K * (unsigned)ES + (unsigned)gchunk * 16u : kOob;
   }
 
   int k_lo = 0, k_hi = p.K;                                             // triangular operands: see IgemmParams::tri
@@ -620,6 +637,13 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
   }
   const int kt_lo = k_lo / BK, kt_hi = (k_hi + BK - 1) / BK;
   const int kt0 = INTERIOR ? kt_lo : max(kt_lo, split * p.slabs_per_split);   // first K slab of this workgroup
+  // CHUNKS: the tap and the chunk within it of this lane's next load (q = chunk index along K)
+  int q = 0, q_c = 0, q_r = 0, q_s = 0;
+  if constexpr (CHUNKS) {
+    q = kt0 * CPR + gchunk;
+    const int tap = q / p.chunks;
+    q_c = q - tap * p.chunks; q_r = tap / p.ksz; q_s = tap - q_r * p.ksz;
+  }
   int rs = (kt0 * BK) / p.Cin, ci0 = (kt0 * BK) % p.Cin;                // filter tap and first channel of the next slab to load
   unsigned kbyte = (unsigned)(kt0 * BKB);       // byte offset of the next slab inside a weight row
 #define IGEMM_TAP()                                                                                          \
@@ -680,15 +704,41 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
 
   const int KT = INTERIOR ? kt_hi - kt0 : min(kt_hi - kt0, p.slabs_per_split);   // (tri launches have one split)
-  if (ci0 != 0) IGEMM_TAP();                     // a split that starts inside a tap (the loaders compute a tap's offsets at its first slab)
+  if (!CHUNKS && ci0 != 0) IGEMM_TAP();          // a split that starts inside a tap (the loaders compute a tap's offsets at its first slab)
   if constexpr (DMA) {
     constexpr int L = A_CHUNKS + B_CHUNKS;       // loads per thread and slab
     static_assert(RSTEP * BKB == NT * 16, "one pass of the loader covers 16 bytes per thread");
+    auto dma_chunks = [&](int stg) {
+      char* const da = sA + stg * BM * BKB + wave * 1024;
+      char* const db = sB + stg * BNL * BKB + wave * 1024;
+      const bool in_k = q < p.ksz * p.ksz * p.chunks;
+#pragma unroll
+      for (int i = 0; i < A_CHUNKS; ++i) {
+        const int hh = a_h[i] * p.stride + q_r - pad_h, ww = a_w[i] * p.stride + q_s - pad_w;
+        const bool ok = in_k && a_img[i] != kOob && hh >= 0 && hh < p.Hv && ww >= 0 && ww < p.Wv;
+        const unsigned pix = (unsigned)((hh >> p.up) * Win + (ww >> p.up));
+        dma_load16(rX, da + i * (NT * 16), ok ? a_img[i] + (pix * (unsigned)p.chunks + (unsigned)q_c) * 16u : kOob);
+      }
+#pragma unroll
+      for (int i = 0; i < B_CHUNKS; ++i) dma_load16(rW, db + i * (NT * 16), in_k ? b_off[i] + kbyte : kOob);
+      kbyte += BKB;
+      q += CPR;
+      q_c += CPR;
+      while (q_c >= p.chunks) {                  // (at most CPR turns)
+        q_c -= p.chunks;
+        if (++q_s == p.ksz) { q_s = 0; ++q_r; }
+      }
+    };
 #define IGEMM_DMA(STG)                                                                                       \
+  {                                                                                                          \
+    if constexpr (CHUNKS) dma_chunks(STG);                                                                   \
+    else IGEMM_DMA_TAP(STG);                                                                                 \
+  }
+#define IGEMM_DMA_TAP(STG)                                                                                   \
   {                                                                                                          \
     if (ci0 == 0) IGEMM_TAP();                                                                               \
     char* const da = sA + (STG) * BM * BKB + wave * 1024;                                                    \
-    char* const db = sB + (STG) * BN * BKB + wave * 1024;                                                    \
+    char* const db = sB + (STG) * BNL * BKB + wave * 1024;                                                   \
     _Pragma("unroll") for (int i = 0; i < A_CHUNKS; ++i)                                                     \
         dma_load16(rX, da + i * (NT * 16), a_off[i] + (unsigned)ci0 * (unsigned)ES);                         \
     _Pragma("unroll") for (int i = 0; i < B_CHUNKS; ++i)                                                     \
@@ -712,13 +762,14 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
       else __builtin_amdgcn_s_waitcnt(0x0F70);
       __builtin_amdgcn_s_barrier();
       uint4v fa[KS][MI], fb[KS][NJ];
-      SlabReads<0, KS, MI, NJ, BKB>::run(fa, fb, lds_a + (unsigned)(cur * BM * BKB), lds_b + (unsigned)(cur * BN * BKB), lane_off);
+      SlabReads<0, KS, MI, NJ, BKB>::run(fa, fb, lds_a + (unsigned)(cur * BM * BKB), lds_b + (unsigned)(cur * BNL * BKB), lane_off);
       if (kt + NSTAGE - 1 < KT) IGEMM_DMA(nxt);
       SlabSteps<T, KS, 0, MI, NJ>::run(fa, fb, acc);
       cur = cur == NSTAGE - 1 ? 0 : cur + 1;
       nxt = nxt == NSTAGE - 1 ? 0 : nxt + 1;
     }
 #undef IGEMM_DMA
+#undef IGEMM_DMA_TAP
     __syncthreads();                             // every wave is done with the slabs: the epilogue reuses the memory
   } else {
   uint4v ra0[A_CHUNKS], rb0[B_CHUNKS], ra1[A_CHUNKS], rb1[B_CHUNKS];
@@ -762,7 +813,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
       return;
     }
   }
-  igemm_epilogue<T, BM, BN, WGM, WGN, INTERIOR, EPI>(acc, p, smem, sRed, m0, n0, tile_m, phase);
+  igemm_epilogue<T, BM, BN, WGM, WGN, INTERIOR, EPI, CHUNKS>(acc, p, smem, sRed, m0, n0, tile_m, phase);
 }
 
 // y = act(round(sum over splits of partial[split] + bias)) for split-K launches
@@ -1028,29 +1079,6 @@ IgemmTile pick_tile(int64_t M, int cout, int cin, int es, bool wide = true, int 
 
 }  // namespace
 
-// The GEMM behind the two forms of an upsampled convolution: rows are pixels of the STORED
-// (half-size) grid, 2x2 taps per phase or 4x4 taps with stride 2.
-static ConvArgs conv_effective(const ConvArgs& a) {
-  ConvArgs e = a;
-  if (a.geom == CONV_PLAIN) return e;
-  e.hc = a.hc / 2; e.wc = a.wc / 2; e.up = 0;
-  e.k = a.geom == CONV_UP_PHASES ? 2 : 4;
-  e.geom = CONV_PLAIN;                      // (applying this twice must not halve twice)
-  return e;
-}
-
-bool conv_mfma_supported(const ConvArgs& a0) {
-  const ConvArgs a = conv_effective(a0);
-  const int es = (int)dtype_size(a.dtype);
-  if ((a.cin * es) % 64 != 0 || a.cout < 32) return false;
-  const int64_t M = (int64_t)a.n * a.hc * a.wc;
-  const int64_t x_bytes = a0.geom == CONV_UP_DGRAD ? (int64_t)a0.n * a0.hc * a0.wc * a.cin * es
-                                                   : (int64_t)a.n * (a.hc >> a.up) * (a.wc >> a.up) * a.cin * es;
-  const int64_t w_bytes = (int64_t)a.cout * a.k * a.k * a.cin * es * (a0.geom == CONV_UP_PHASES ? 4 : 1);
-  if (x_bytes >= 0x7FFFFFFF || w_bytes >= 0x7FFFFFFF) return false;   // 32-bit buffer offsets
-  return M * ((a.cout + 63) / 64) / 128 < 0x7FFFFFFF && M < 0x7FFFFFFF;
-}
-
 // The patch kernel takes 3x3 convolutions whose image width is 16..128 (a power of two), whose
 // tiles of 256/W rows divide the image height, with enough tiles to fill the chip, and whose
 // epilogue needs no run-time checks.
@@ -1156,6 +1184,39 @@ int conv_comp_blocks(const ConvArgs& a0) {
 
 bool conv_weights_frag_order(const ConvArgs& a) { return conv3_patch_usable(a); }
 
+// source and destination geometry of a launch; row_bytes: one stored pixel of x
+static void igemm_geometry(const ConvArgs& a0, const ConvArgs& a, int row_bytes, IgemmParams* p) {
+  p->Hc = a.hc; p->Wc = a.wc; p->ksz = a.k; p->up = a.up; p->act = a.act;
+  p->Hv = a.hc; p->Wv = a.wc; p->stride = 1; p->pad = (a.k - 1) >> 1; p->phases = 1;
+  if ((a.hc & (a.hc - 1)) == 0 && (a.wc & (a.wc - 1)) == 0) {
+    p->log_w = p->log_h = 0;
+    while ((1 << p->log_w) < a.wc) ++p->log_w;
+    while ((1 << p->log_h) < a.hc) ++p->log_h;
+  }
+  p->x_bytes = (unsigned)((int64_t)a.n * (a.hc >> a.up) * (a.wc >> a.up) * row_bytes);
+  p->w_bytes = (unsigned)((int64_t)a.cout * a.k * a.k * row_bytes);
+  if (a0.geom == CONV_UP_PHASES) {
+    p->pad = 1; p->phases = 4;
+    p->w_bytes *= 4u;
+  } else if (a0.geom == CONV_UP_DGRAD) {
+    p->Hv = a0.hc; p->Wv = a0.wc; p->stride = 2; p->pad = 1;
+    p->x_bytes = (unsigned)((int64_t)a0.n * a0.hc * a0.wc * row_bytes);
+  }
+}
+
+// sum of a split launch's partial tiles, bias, rounding and activation
+static int launch_splitk_finish(const ConvArgs& a, int splits, int64_t M, int N, hipStream_t s) {
+  int64_t g = (M * N + 255) / 256;
+  if (g > 8192) g = 8192;
+  if (a.dtype == AE_BF16)
+    hipLaunchKernelGGL((k_splitk_finish<bf16_t>), dim3((unsigned)g), dim3(256), 0, s, a.splitk_ws, splits, M, N, a.bias,
+                       a.act, (bf16_t*)a.y, a.y_aux);
+  else
+    hipLaunchKernelGGL((k_splitk_finish<float>), dim3((unsigned)g), dim3(256), 0, s, a.splitk_ws, splits, M, N, a.bias,
+                       a.act, (float*)a.y, a.y_aux);
+  return launch_status("splitk_finish");
+}
+
 int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
   if (!conv_mfma_supported(a0)) return fail(AE_EINVAL, "conv_mfma: shape not supported");
   if (a0.w_frag != conv3_patch_usable(a0)) return fail(AE_EINVAL, "conv_mfma: the order of the packed weights does not fit the kernel of this launch (conv_weights_frag_order)");
@@ -1167,13 +1228,8 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
   p.x = a.x; p.w = a.w; p.bias = a.bias; p.y = a.y; p.y_aux = a.y_aux; p.partial = a.partial;
   p.M = (int64_t)a.n * a.hc * a.wc;
   p.N = a.cout; p.K = a.k * a.k * a.cin;
-  p.Hc = a.hc; p.Wc = a.wc; p.Cin = a.cin; p.ksz = a.k; p.up = a.up; p.act = a.act;
-  p.Hv = a.hc; p.Wv = a.wc; p.stride = 1; p.pad = (a.k - 1) >> 1; p.phases = 1;
-  if ((a.hc & (a.hc - 1)) == 0 && (a.wc & (a.wc - 1)) == 0) {
-    p.log_w = p.log_h = 0;
-    while ((1 << p.log_w) < a.wc) ++p.log_w;
-    while ((1 << p.log_h) < a.hc) ++p.log_h;
-  }
+  p.Cin = a.cin;
+  igemm_geometry(a0, a, a.cin * es, &p);
   p.resid = a0.resid;
   p.comp = a0.comp; p.comp_mode = a0.comp_mode; p.comp_bn = a0.comp_bn;
   if (a0.comp_mode != 0) {
@@ -1192,15 +1248,6 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
   if (a0.tri != 0 && (a0.tri < 0 || (a0.tri > 4 && a0.tri < 8) || a0.tri > 9 || a.k != 1 || a.hc != 1 || a.wc != 1 || a.up != 0 || a.n != a.cout || a.cin != a.cout ||
                       a0.epi != CONV_EPI_NONE || a.partial))
     return fail(AE_EINVAL, "conv_mfma: triangular K ranges are for square dense products only");
-  p.x_bytes = (unsigned)((int64_t)a.n * (a.hc >> a.up) * (a.wc >> a.up) * a.cin * es);
-  p.w_bytes = (unsigned)((int64_t)a.cout * a.k * a.k * a.cin * es);
-  if (a0.geom == CONV_UP_PHASES) {
-    p.pad = 1; p.phases = 4;
-    p.w_bytes *= 4u;
-  } else if (a0.geom == CONV_UP_DGRAD) {
-    p.Hv = a0.hc; p.Wv = a0.wc; p.stride = 2; p.pad = 1;
-    p.x_bytes = (unsigned)((int64_t)a0.n * a0.hc * a0.wc * a.cin * es);
-  }
   if (conv3_patch_usable(a0)) {
     const int bn = conv3_patch_bn(a);
     p.tiles_n = a.cout / bn;
@@ -1302,18 +1349,43 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
 #undef IGEMM_LAUNCH
 #undef IGEMM_LAUNCH_T
   AE_TRY(launch_status("conv_mfma"));
-  if (splits > 1) {
-    int64_t g = (p.M * p.N + 255) / 256;
-    if (g > 8192) g = 8192;
-    if (a.dtype == AE_BF16)
-      hipLaunchKernelGGL((k_splitk_finish<bf16_t>), dim3((unsigned)g), dim3(256), 0, s, a.splitk_ws, splits, p.M, p.N, a.bias,
-                         a.act, (bf16_t*)a.y, a.y_aux);
-    else
-      hipLaunchKernelGGL((k_splitk_finish<float>), dim3((unsigned)g), dim3(256), 0, s, a.splitk_ws, splits, p.M, p.N, a.bias,
-                         a.act, (float*)a.y, a.y_aux);
-    return launch_status("splitk_finish");
-  }
-  return AE_OK;
+  return splits > 1 ? launch_splitk_finish(a, splits, p.M, p.N, s) : AE_OK;
+}
+
+// ---- any channel counts: the chunk walk of k_igemm ---------------------------------------------------------------
+// a.x holds whole 16-byte chunks per pixel and a.w per tap (chan_pad channels, zeros behind the layer's own)
+int launch_conv_chunks(const ConvArgs& a0, hipStream_t s) {
+  if (!conv_chunks_supported(a0) || a0.w_frag) return fail(AE_EINVAL, "conv_chunks: shape not supported");
+  const ConvChunksPlan c = plan_conv_chunks(a0);
+  const ConvArgs a = conv_effective(a0);
+  IgemmParams p = {};
+  p.x = a.x; p.w = a.w; p.bias = a.bias; p.y = a.y; p.y_aux = a.y_aux; p.partial = a.partial;
+  p.M = c.M; p.N = a.cout; p.K = a.k * a.k * chan_pad(a.cin, a.dtype); p.Cin = chan_pad(a.cin, a.dtype); p.chunks = c.chunks;
+  igemm_geometry(a0, a, 16 * c.chunks, &p);
+  p.tiles_n = (a.cout + c.bn - 1) / c.bn;
+  int splits = c.splits;
+  if (splits > 1 && (!a.splitk_ws || (int64_t)splits * c.M * p.N > a.splitk_floats)) splits = 1;
+  p.tiles_mn = (int)c.tiles;
+  p.slabs_per_split = (c.KT + splits - 1) / splits;
+  splits = (c.KT + p.slabs_per_split - 1) / p.slabs_per_split;
+  p.split_out = splits > 1 ? a.splitk_ws : nullptr;
+  const dim3 grid((unsigned)(c.tiles * splits * p.phases));
+#define CHUNKS_LAUNCH(T, BMV, BNV, GM, GN) \
+  hipLaunchKernelGGL((k_igemm<T, BMV, BNV, GM, GN, 64, false, true, 0, true>), grid, dim3(256), 0, s, p)
+#define CHUNKS_TILE(T)                                                              \
+  do {                                                                              \
+    if (c.bn == 128) CHUNKS_LAUNCH(T, 128, 128, 2, 2);                            \
+    else if (c.bn == 64) CHUNKS_LAUNCH(T, 128, 64, 2, 2);                         \
+    else if (c.bm == 256) CHUNKS_LAUNCH(T, 256, 32, 4, 1);                        \
+    else CHUNKS_LAUNCH(T, 128, 32, 4, 1);                                           \
+  } while (0)
+  if (a.dtype == AE_F32) CHUNKS_TILE(float);
+  else if (c.bn == 64 && c.bm == 256) CHUNKS_LAUNCH(bf16_t, 256, 64, 4, 1);
+  else CHUNKS_TILE(bf16_t);
+#undef CHUNKS_TILE
+#undef CHUNKS_LAUNCH
+  AE_TRY(launch_status("conv_chunks"));
+  return splits > 1 ? launch_splitk_finish(a, splits, p.M, p.N, s) : AE_OK;
 }
 
 }  // namespace ae
@@ -1341,6 +1413,14 @@ namespace {
 typedef short short4v __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) short4v lds_short4v;
 
+// quotient by a divisor fixed at launch, for dividends below 2^31: l = ceil(log2 d), mul = ceil(2^(31+l) / d); the error
+// of mul, below one part in 2^31 of a quotient step, cannot carry a dividend that small over a border
+struct FastDiv {
+  uint32_t mul;
+  int shift;
+  __device__ __forceinline__ unsigned quot(unsigned n) const { return (unsigned)(((uint64_t)n * mul) >> shift); }
+};
+
 struct WgradParams {
   const void* x; const void* dy; float* partial;
   int64_t M;            // pixels
@@ -1350,6 +1430,8 @@ struct WgradParams {
   int K;                // k*k*C_in
   int log_w, log_h;     // log2 of Wc / Hc when both are powers of two (POW2 kernels)
   unsigned x_bytes, dy_bytes;
+  int chunks = 0, dy_chunks = 0;   // k_wgrad_chunks: 16-byte chunks of a stored pixel of x and of dY
+  FastDiv div_w = {}, div_h = {};  // k_wgrad_chunks: division by Wc and Hc
 };
 
 __device__ __forceinline__ bf16x8 lds_tr_frag(const bf16_t* base0, const bf16_t* base1) {
@@ -1536,6 +1618,117 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         if (co < p.Cout && ci < p.Cin) P[(int64_t)co * p.K + tap * p.Cin + ci] = acc[i][j][e];
       }
     }
+}
+
+// The same for any channel counts.  Pixels of x and dY are stored as whole 16-byte chunks (zeros behind the channels),
+// and the columns of the product are the chunks of all taps in a row, (tap, chunk), cut into tiles of BN wherever a tile
+// ends: a loader thread moves the same column chunk in every pass, so its tap is fixed for the whole loop and the tile
+// border costs nothing.  9 x 48 channels fill 3.4 tiles of 128 columns, where a tile per tap would be 9 with a quarter
+// of each empty; a 3-channel image fills 0.6 tiles instead of 9.  Chunks past the end read zeros and are not stored.
+// Measured (bf16, 24 x 36 x 60 pixels, 80 x 9 x 48 weights): 22 us = 160 TFLOP/s, where a thread per weight that walks the
+// pixels alone took 4.5 ms.
+template <typename T, int BM, int BN>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_wgrad_chunks(WgradParams p) {
+  constexpr int ES = (int)sizeof(T);
+  constexpr int EPC = 16 / ES;
+  constexpr int BK = ES == 2 ? 32 : 16;          // pixels per slab
+  constexpr int LPAD = 32;                       // (as in k_wgrad)
+  constexpr int LA = BM + LPAD, LB = BN + LPAD;
+  constexpr int WM = BM / 2, WN = BN / 2;
+  constexpr int MI = WM / 32, NJ = WN / 32;
+  constexpr int A_TPR = BM / EPC, B_TPR = BN / EPC;
+  constexpr int A_CHUNKS = BK * A_TPR / 256, B_CHUNKS = BK * B_TPR / 256;
+  static_assert(256 % A_TPR == 0 && 256 % B_TPR == 0, "a thread keeps its column chunk");
+  __shared__ __attribute__((aligned(16))) T sA[2][BK * LA];
+  __shared__ __attribute__((aligned(16))) T sB[2][BK * LB];
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave >> 1, wn = wave & 1;
+  int b = xcd_logical_block((int)blockIdx.x, (int)gridDim.x);     // column tiles fastest: they share a dY slab
+  const int tn = b % p.tiles_n; b /= p.tiles_n;
+  const int tm = b % p.tiles_m;
+  const int split = b / p.tiles_m;
+  const int pad = (p.ksz - 1) >> 1, kc = p.ksz * p.ksz * p.chunks;
+  const int Hin = p.Hc >> p.up, Win = p.Wc >> p.up;
+  const unsigned m_begin = (unsigned)split * (unsigned)p.rows_per_split;
+  const unsigned m_end = min(m_begin + (unsigned)p.rows_per_split, (unsigned)p.M);
+  const int KT = (int)((m_end - m_begin + BK - 1) / BK);
+  const __amdgpu_buffer_rsrc_t rX = make_rsrc(p.x, p.x_bytes);
+  const __amdgpu_buffer_rsrc_t rDY = make_rsrc(p.dy, p.dy_bytes);
+
+  const int ca = tm * A_TPR + tid % A_TPR;       // this thread's column chunk of dY ...
+  const int cb = tn * B_TPR + tid % B_TPR;       // ... and of the gathered input: tap (r, s), channels 16-byte chunk cc
+  const int tap = cb / p.chunks, cc = cb - tap * p.chunks, r = tap / p.ksz, s = tap - r * p.ksz;
+  const bool a_in = ca < p.dy_chunks, b_in = cb < kc;
+  unsigned ma = m_begin + (unsigned)(tid / A_TPR), mb = m_begin + (unsigned)(tid / B_TPR);   // pixels of the next slab
+  auto load = [&](uint4v (&ra)[A_CHUNKS], uint4v (&rb)[B_CHUNKS]) {
+#pragma unroll
+    for (int i = 0; i < A_CHUNKS; ++i) {
+      const unsigned m = ma + i * (256 / A_TPR);
+      ra[i] = __builtin_amdgcn_raw_buffer_load_b128(rDY, a_in && m < m_end ? (m * (unsigned)p.dy_chunks + (unsigned)ca) * 16u : kOob, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < B_CHUNKS; ++i) {
+      const unsigned m = mb + i * (256 / B_TPR);
+      const unsigned t = p.div_w.quot(m), n = p.div_h.quot(t);
+      const int hh = (int)(t - n * (unsigned)p.Hc) + r - pad, ww = (int)(m - t * (unsigned)p.Wc) + s - pad;
+      const bool ok = b_in && m < m_end && hh >= 0 && hh < p.Hc && ww >= 0 && ww < p.Wc;
+      const unsigned pix = (n * (unsigned)Hin + (unsigned)(hh >> p.up)) * (unsigned)Win + (unsigned)(ww >> p.up);
+      rb[i] = __builtin_amdgcn_raw_buffer_load_b128(rX, ok ? (pix * (unsigned)p.chunks + (unsigned)cc) * 16u : kOob, 0, 0);
+    }
+    ma += BK;
+    mb += BK;
+  };
+  auto store = [&](int buf, const uint4v (&ra)[A_CHUNKS], const uint4v (&rb)[B_CHUNKS]) {
+#pragma unroll
+    for (int i = 0; i < A_CHUNKS; ++i)
+      *reinterpret_cast<uint4v*>(&sA[buf][(tid / A_TPR + i * (256 / A_TPR)) * LA + (tid % A_TPR) * EPC]) = ra[i];
+#pragma unroll
+    for (int i = 0; i < B_CHUNKS; ++i)
+      *reinterpret_cast<uint4v*>(&sB[buf][(tid / B_TPR + i * (256 / B_TPR)) * LB + (tid % B_TPR) * EPC]) = rb[i];
+  };
+  floatx16 acc[MI][NJ];
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+
+  // KT >= 1: every split owns at least one pixel (the host sizes the splits that way)
+  uint4v ra0[A_CHUNKS], rb0[B_CHUNKS], ra1[A_CHUNKS], rb1[B_CHUNKS];
+  load(ra0, rb0);
+  if (KT > 1) load(ra1, rb1);
+  store(0, ra0, rb0);
+  __syncthreads();
+  for (int kt = 0; kt < KT; kt += 2) {
+    if (kt + 2 < KT) load(ra0, rb0);
+    wgrad_compute<T, MI, NJ, BK, LA, LB>(&sA[0][wm * WM], &sB[0][wn * WN], lane, acc);
+    if (kt + 1 < KT) store(1, ra1, rb1);
+    __syncthreads();
+    if (kt + 1 >= KT) break;
+    if (kt + 3 < KT) load(ra1, rb1);
+    wgrad_compute<T, MI, NJ, BK, LA, LB>(&sA[1][wm * WM], &sB[1][wn * WN], lane, acc);
+    if (kt + 2 < KT) store(0, ra0, rb0);
+    __syncthreads();
+  }
+
+  // partial[split][co][tap*Cin + ci]
+  float* __restrict__ P = p.partial + (int64_t)split * p.Cout * p.K;
+  const int col_lane = lane & 31, row_lane = (lane >> 5) * 4;
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    const int col = tn * BN + wn * WN + j * 32 + col_lane, q = col / EPC;
+    const int tap_o = q / p.chunks, ci = (q - tap_o * p.chunks) * EPC + col % EPC;
+    if (q >= kc || ci >= p.Cin) continue;
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int co = tm * BM + wm * WM + i * 32 + (e >> 2) * 8 + row_lane + (e & 3);
+        if (co < p.Cout) P[(int64_t)co * p.K + tap_o * p.Cin + ci] = acc[i][j][e];
+      }
+  }
 }
 
 // The same kernel for images whose width is a multiple of the slab depth BK: a slab is then BK
@@ -2171,6 +2364,52 @@ int launch_wgrad_mfma(const WgradArgs& a, float* workspace, hipStream_t s) {
   else
     hipLaunchKernelGGL(k_wgrad_reduce, dim3((unsigned)g), dim3(256), 0, s, workspace, w.splits, a.cout, a.cin, a.k * a.k,
                        a.dw_canonical);
+  return launch_status("wgrad_reduce");
+}
+
+// ---- any channel counts -------------------------------------------------------------------------------------------
+static FastDiv fast_div(int d) {
+  int l = 0;
+  while ((int64_t{1} << l) < d) ++l;
+  FastDiv f;
+  f.mul = (uint32_t)(((uint64_t{1} << (31 + l)) + (uint64_t)d - 1) / (uint64_t)d);
+  f.shift = 31 + l;
+  return f;
+}
+
+// a.x and a.dy hold whole 16-byte chunks per pixel (chan_pad channels, zeros behind the layer's own)
+int launch_wgrad_chunks(const WgradArgs& a, float* workspace, hipStream_t s) {
+  if (!wgrad_chunks_supported(a)) return fail(AE_EINVAL, "wgrad_chunks: shape not supported");
+  const WgradChunksPlan w = plan_wgrad_chunks(a);
+  const int64_t rows = (int64_t)a.n * a.hc * a.wc;
+  const int es = (int)dtype_size(a.dtype), epc = 16 / es;
+  const bool direct = w.splits == 1 && a.k == 1;        // the partial layout [co][ci] is the canonical one
+  WgradParams p = {};
+  p.x = a.x; p.dy = a.dy; p.partial = direct ? a.dw_canonical : workspace;
+  p.M = rows; p.Cout = a.cout; p.Cin = a.cin; p.Hc = a.hc; p.Wc = a.wc; p.ksz = a.k; p.up = a.up;
+  p.tiles_m = w.tiles_m; p.tiles_n = w.tiles_n; p.rows_per_split = w.rows_per_split;
+  p.K = a.k * a.k * a.cin;
+  p.chunks = chan_pad(a.cin, a.dtype) / epc; p.dy_chunks = chan_pad(a.cout, a.dtype) / epc;
+  p.dy_bytes = (unsigned)(rows * p.dy_chunks * 16);
+  p.x_bytes = (unsigned)((int64_t)a.n * (a.hc >> a.up) * (a.wc >> a.up) * p.chunks * 16);
+  p.div_w = fast_div(a.wc); p.div_h = fast_div(a.hc);
+  const int64_t blocks = (int64_t)w.splits * w.tiles_m * w.tiles_n;
+  if (blocks > 0x7FFFFFFF) return fail(AE_EINVAL, "wgrad_chunks: grid too large");
+  const dim3 grid((unsigned)blocks);
+#define WGRAD_CHUNKS(T)                                                                                         \
+  do {                                                                                                          \
+    if (w.bm == 128 && w.bn == 128) hipLaunchKernelGGL((k_wgrad_chunks<T, 128, 128>), grid, dim3(256), 0, s, p); \
+    else if (w.bm == 128) hipLaunchKernelGGL((k_wgrad_chunks<T, 128, 64>), grid, dim3(256), 0, s, p);           \
+    else if (w.bn == 128) hipLaunchKernelGGL((k_wgrad_chunks<T, 64, 128>), grid, dim3(256), 0, s, p);           \
+    else hipLaunchKernelGGL((k_wgrad_chunks<T, 64, 64>), grid, dim3(256), 0, s, p);                             \
+  } while (0)
+  if (a.dtype == AE_BF16) WGRAD_CHUNKS(bf16_t);
+  else WGRAD_CHUNKS(float);
+#undef WGRAD_CHUNKS
+  AE_TRY(launch_status("wgrad_chunks"));
+  if (direct) return AE_OK;
+  const int64_t g = ((int64_t)a.cout * a.cin * a.k * a.k + 63) / 64;
+  hipLaunchKernelGGL(k_wgrad_reduce, dim3((unsigned)g), dim3(256), 0, s, workspace, w.splits, a.cout, a.cin, a.k * a.k, a.dw_canonical);
   return launch_status("wgrad_reduce");
 }
 

@@ -34,6 +34,11 @@ inline int launch_status(const char* what) {
 }
 
 inline size_t dtype_size(int dtype) { return dtype == AE_BF16 ? 2 : 4; }
+// channel count rounded up to whole 16-byte chunks
+inline int chan_pad(int c, int dtype) {
+  const int epc = 16 / (int)dtype_size(dtype);
+  return (c + epc - 1) / epc * epc;
+}
 
 // ---- plan ------------------------------------------------------------------
 enum StepKind { ST_TRANSPOSE = 0, ST_CONV = 1, ST_CHANNEL = 2 };
@@ -67,6 +72,9 @@ struct Step {
   float* aux = nullptr;             // binary32 copy of a sigmoid output produced in the conv epilogue (bf16 models):
                                     // y*(1-y) from a bf16-rounded y loses all accuracy where the sigmoid saturates
   bool mfma = false;                // forward uses the MFMA implicit-GEMM kernel
+  bool chunks = false, chunks_d = false, chunks_w = false;   // forward / input gradient / weight gradient on the matrix-core kernels for any channel counts
+  int64_t off_xpad = -1;
+  void* xpad = nullptr;             // input with chan_pad(cin) channels per pixel, where those kernels need it (null: the input itself will do)
   bool up_phases = false;           // forward of an upsampled conv as four 2x2 phase convolutions (CONV_UP_PHASES)
   bool up_dgrad = false;            // its input gradient as one 4x4 stride-2 convolution (CONV_UP_DGRAD)
   bool wfrag = false, wfrag_d = false;   // packed weights of the forward / input-gradient conv in MFMA fragment order (conv_weights_frag_order)
@@ -84,13 +92,14 @@ struct Plan {
   std::vector<Step> steps;
   // workspace sizing (bytes)
   int64_t ws_bytes = 0;
-  int64_t off_grad_a = 0, off_grad_b = 0, off_draw = 0, off_draw2 = 0, off_dfull = 0, off_partial = 0, off_wgrad = 0, off_wgrad_inorder = 0, off_splitk = 0;
+  int64_t off_grad_a = 0, off_grad_b = 0, off_draw = 0, off_draw2 = 0, off_dfull = 0, off_partial = 0, off_wgrad = 0, off_wgrad_inorder = 0, off_splitk = 0, off_dypad = 0;
   int64_t max_act_elems = 0;        // largest step output
   int64_t max_raw_elems = 0;        // largest conv-resolution tensor (raw / dRaw)
   int64_t max_full_elems = 0;       // largest conv-resolution input gradient of an upsampled conv
   int64_t max_partial_floats = 0;   // column-reduction partial buffer
   int64_t max_wgrad_floats = 0;     // split partial tiles of the MFMA weight-gradient kernel
   int64_t max_wgrad_inorder_floats = 0;   // the same for layers whose weight gradient runs in order on the caller's stream
+  int64_t max_dypad_bytes = 0;      // a conv-output gradient with chan_pad(cout) channels per pixel (three such buffers)
   int64_t max_splitk_floats = 0;    // split-K partial tiles of the forward / input-gradient convolutions
 };
 
@@ -122,12 +131,13 @@ inline int reduce_blocks(int64_t rows) {
 // ---- launchers (all asynchronous on `s`) -----------------------------------
 // layout / dtype
 int launch_transpose(const void* in, void* out, int64_t batch, int rows, int cols, int dtype, hipStream_t s);
+int launch_pad_channels(const void* in, void* out, int64_t rows, int c, int dtype, hipStream_t s);   // [rows][c] -> [rows][chan_pad(c)], zeros behind
 int launch_to_f32_nchw(const void* in_nhwc, float* out_nchw, int64_t batch, int c, int hw, int dtype, hipStream_t s);
 
 // weights
-int launch_pack_weights(const float* w, void* wp, int cout, int cin, int k, int dtype, bool for_dgrad, hipStream_t s, bool frag = false);
+int launch_pack_weights(const float* w, void* wp, int cout, int cin, int k, int dtype, bool for_dgrad, hipStream_t s, bool frag = false, int ld = 0);
 // several layers in one launch
-struct PackJob { const float* w; void* wp; int cout, cin, k, dgrad; int64_t first_block; int frag; };   // frag: rows in MFMA fragment order
+struct PackJob { const float* w; void* wp; int cout, cin, k, dgrad; int64_t first_block; int frag; int ld; };   // frag: rows in MFMA fragment order; ld: channels per tap of the packed rows (0: as many as there are)
 constexpr int kMaxPackJobs = 32;
 struct PackBatch { int n; PackJob job[kMaxPackJobs]; };
 int launch_pack_weights_batch(PackBatch& pb, int dtype, hipStream_t s);
@@ -200,11 +210,19 @@ int conv_comp_blocks(const ConvArgs& a);
 bool conv_weights_frag_order(const ConvArgs& a);   // does this launch take its weights in fragment order (ConvArgs::w_frag)?
 bool conv_up_dgrad_usable(const ConvArgs& a);    // a: the plain description of the input-gradient conv at conv resolution
 // Summed weights of the two forms above from the canonical [cout][cin][3][3] fp32 weights.
-int launch_pack_weights_up(const float* w, void* wp, int cout, int cin, int dtype, int geom, hipStream_t s);
+int launch_pack_weights_up(const float* w, void* wp, int cout, int cin, int dtype, int geom, hipStream_t s, int ld = 0);
 int64_t conv_mfma_splitk_floats(const ConvArgs& a);   // 0: this layer runs without split-K
 int launch_conv_direct(const ConvArgs& a, hipStream_t s);
 bool conv_mfma_supported(const ConvArgs& a);
+ConvArgs conv_effective(const ConvArgs& a);   // the GEMM that a.geom runs as
 int launch_conv_mfma(const ConvArgs& a, hipStream_t s);
+// The matrix-core kernel for any channel counts: a.x and a.w hold chan_pad(cin) channels per pixel and per tap, zeros
+// behind the layer's own (launch_pad_channels, the packing kernels); a.y has plain rows of cout.
+bool conv_chunks_supported(const ConvArgs& a);
+struct ConvChunksPlan { int bm, bn, chunks, KT, splits; int64_t M, tiles; };   // chunks: of one tap; KT: slabs of four chunks
+ConvChunksPlan plan_conv_chunks(const ConvArgs& a);   // (a.partial: rows per block of sums = bm)
+int64_t conv_chunks_splitk_floats(const ConvArgs& a);
+int launch_conv_chunks(const ConvArgs& a, hipStream_t s);
 int conv_partial_rows(const ConvArgs& a, bool mfma);  // rows per partial-sum block of the kernel that will run
 
 struct WgradArgs {
@@ -217,6 +235,12 @@ bool wgrad_mfma_supported(const WgradArgs& a);
 bool wgrad_mfma_up_phases(const WgradArgs& a);   // will it run as the phase form of an upsampled conv (4/9 of the multiply-adds)?
 int64_t wgrad_mfma_workspace_floats(const WgradArgs& a);
 int launch_wgrad_mfma(const WgradArgs& a, float* workspace, hipStream_t s);  // overwrites dw (no zeroing needed)
+// any channel counts; a.x and a.dy hold chan_pad channels per pixel
+bool wgrad_chunks_supported(const WgradArgs& a);
+struct WgradChunksPlan { int bm, bn, tiles_m, tiles_n, splits, rows_per_split; };
+WgradChunksPlan plan_wgrad_chunks(const WgradArgs& a);
+int64_t wgrad_chunks_workspace_floats(const WgradArgs& a);
+int launch_wgrad_chunks(const WgradArgs& a, float* workspace, hipStream_t s);
 
 // 3x3 convolutions with 1..4 channels on one side (first / last layer); see ae_conv_thin.hip
 bool thin_in_supported(int ct, int cw, int k, int up);

@@ -115,6 +115,123 @@ int64_t align_up(int64_t v, int64_t a) { return (v + a - 1) / a * a; }
 
 }  // namespace
 
+// The GEMM behind the two forms of an upsampled convolution: rows are pixels of the STORED
+// (half-size) grid, 2x2 taps per phase or 4x4 taps with stride 2.
+ConvArgs conv_effective(const ConvArgs& a) {
+  ConvArgs e = a;
+  if (a.geom == CONV_PLAIN) return e;
+  e.hc = a.hc / 2; e.wc = a.wc / 2; e.up = 0;
+  e.k = a.geom == CONV_UP_PHASES ? 2 : 4;
+  e.geom = CONV_PLAIN;                      // (applying this twice must not halve twice)
+  return e;
+}
+
+bool conv_mfma_supported(const ConvArgs& a0) {
+  const ConvArgs a = conv_effective(a0);
+  const int es = (int)dtype_size(a.dtype);
+  if ((a.cin * es) % 64 != 0 || a.cout < 32) return false;
+  const int64_t M = (int64_t)a.n * a.hc * a.wc;
+  const int64_t x_bytes = a0.geom == CONV_UP_DGRAD ? (int64_t)a0.n * a0.hc * a0.wc * a.cin * es
+                                                   : (int64_t)a.n * (a.hc >> a.up) * (a.wc >> a.up) * a.cin * es;
+  const int64_t w_bytes = (int64_t)a.cout * a.k * a.k * a.cin * es * (a0.geom == CONV_UP_PHASES ? 4 : 1);
+  if (x_bytes >= 0x7FFFFFFF || w_bytes >= 0x7FFFFFFF) return false;   // 32-bit buffer offsets
+  return M * ((a.cout + 63) / 64) / 128 < 0x7FFFFFFF && M < 0x7FFFFFFF;
+}
+
+// ---- any channel counts (the chunk walk of k_igemm, k_wgrad_chunks) ----------------------------------------------
+ConvChunksPlan plan_conv_chunks(const ConvArgs& a) {
+  ConvChunksPlan c;
+  const int epc = 16 / (int)dtype_size(a.dtype);
+  const ConvArgs e = conv_effective(a);
+  c.M = (int64_t)e.n * e.hc * e.wc;
+  c.chunks = chan_pad(a.cin, a.dtype) / epc;
+  c.KT = (e.k * e.k * c.chunks + 3) / 4;
+  // Column tiles of 32 and 64 for few channels (a latent, an image), 64 where 128 would leave a whole 64 empty; 256-row
+  // tiles only while they are about two per compute unit.
+  c.bn = a.cout <= 32 ? 32 : ((a.cout + 63) / 64) % 2 == 1 ? 64 : 128;
+  const int64_t tiles_n = (a.cout + c.bn - 1) / c.bn;
+  const bool tall = c.bn == 32 || (c.bn == 64 && a.dtype == AE_BF16);
+  c.bm = tall && (c.M + 255) / 256 * tiles_n >= 512 ? 256 : 128;
+  c.tiles = (c.M + c.bm - 1) / c.bm * tiles_n;
+  c.splits = 1;
+  if (!a.partial && a.geom != CONV_UP_PHASES && c.tiles < 256 && c.KT >= 16)   // fewer than one workgroup per compute unit and a long K
+    c.splits = (int)std::max<int64_t>(1, std::min<int64_t>((512 + c.tiles - 1) / c.tiles, c.KT / 4));
+  return c;
+}
+
+bool conv_chunks_supported(const ConvArgs& a) {
+  if (a.epi != CONV_EPI_NONE || a.tri != 0 || a.comp_mode != 0) return false;
+  const int64_t es = (int64_t)dtype_size(a.dtype), cin_p = chan_pad(a.cin, a.dtype);
+  const int64_t x_px = (int64_t)a.n * (a.hc >> a.up) * (a.wc >> a.up);
+  const int64_t taps = a.geom != CONV_PLAIN ? 16 : a.k * a.k;
+  const int64_t M = (int64_t)a.n * a.hc * a.wc;
+  return x_px * cin_p * es < 0x7FFFFFFF && (int64_t)a.cout * taps * cin_p * es < 0x7FFFFFFF && M < 0x7FFFFFFF &&
+         M / 128 * ((a.cout + 31) / 32) < 0xFFFFFFF;           // 32-bit buffer offsets and grids
+}
+
+int64_t conv_chunks_splitk_floats(const ConvArgs& a) {
+  const ConvChunksPlan c = plan_conv_chunks(a);
+  return c.splits > 1 ? (int64_t)c.splits * c.M * a.cout : 0;
+}
+
+WgradChunksPlan plan_wgrad_chunks(const WgradArgs& a) {
+  WgradChunksPlan w;
+  const int64_t rows = (int64_t)a.n * a.hc * a.wc;
+  const int cols = a.k * a.k * chan_pad(a.cin, a.dtype);
+  // tiles of 64 where 128 would leave a whole 64 empty
+  w.bm = ((a.cout + 63) / 64) % 2 == 0 ? 128 : 64;
+  w.bn = ((cols + 63) / 64) % 2 == 0 || cols > 320 ? 128 : 64;
+  w.tiles_m = (a.cout + w.bm - 1) / w.bm;
+  w.tiles_n = (cols + w.bn - 1) / w.bn;
+  const int64_t tiles = (int64_t)w.tiles_m * w.tiles_n;
+  int64_t splits = (1024 + tiles - 1) / tiles;          // about four workgroups per compute unit
+  const int64_t max_splits = (rows + 255) / 256;        // at least 256 pixels per split
+  if (splits > max_splits) splits = max_splits;
+  if (splits < 1) splits = 1;
+  int64_t rps = (rows + splits - 1) / splits;
+  rps = (rps + 31) / 32 * 32;
+  w.rows_per_split = (int)rps;
+  w.splits = (int)((rows + rps - 1) / rps);
+  return w;
+}
+
+bool wgrad_chunks_supported(const WgradArgs& a) {
+  const int64_t es = (int64_t)dtype_size(a.dtype), rows = (int64_t)a.n * a.hc * a.wc;
+  const int64_t cin_p = chan_pad(a.cin, a.dtype), cout_p = chan_pad(a.cout, a.dtype);
+  if (rows * cout_p * es >= 0x7FFFFFFF || (int64_t)a.n * (a.hc >> a.up) * (a.wc >> a.up) * cin_p * es >= 0x7FFFFFFF) return false;
+  return rows < 0x7FFFFFFF - 64 && (int64_t)a.k * a.k * cin_p < 0x3FFFFFFF;
+}
+
+int64_t wgrad_chunks_workspace_floats(const WgradArgs& a) {
+  return (int64_t)plan_wgrad_chunks(a).splits * a.cout * a.cin * a.k * a.k;
+}
+
+namespace {
+// A layer whose channel counts the tiled matrix-core kernels do not take runs on the kernel for any channel counts,
+// except for small 1x1 layers, whose few launches are their time: the direct kernel needs no padded input and, in
+// binary32, no packed weights.  Measured on two such layers forward, direct against chunks: 100 -> 50 -> 100 channels x 64
+// rows 19.5 against 33.4 us, 1 -> 8 -> 1 x 32768 rows 15.5 against 18.9; on the other side 16 -> 12 -> 16 x 32768 rows 28.4
+// against 20.4, 24 -> 20 -> 24 x 32768 rows 63 against 22, 1000 -> 10 -> 1000 x 32 rows 117 against 25 (a thread of the
+// direct kernel walks K alone, so a long K is slow at any size).  3x3 layers gain from 4 x 4 images on (8 -> 8 channels:
+// 24.6 against 21.4 us).
+bool conv_chunks_worthwhile(const ConvArgs& a) {
+  return a.k != 1 || a.cin > 128 || (int64_t)a.n * a.hc * a.wc * a.cin * a.cout > (1 << 21);
+}
+// (a weight gradient over a handful of pixels: the direct kernel's serial walk over them is shorter than a slab's way
+// through LDS, and nothing is padded: 100 -> 50 -> 100 channels x 1 row, forward and backward, 48 against 53 us; 16 rows of
+// 48 -> 80 -> 48 channels 69 against 57, 64 rows of 100 -> 50 -> 100 channels 114 against 63)
+bool wgrad_chunks_worthwhile(const WgradArgs& a) { return (int64_t)a.n * a.hc * a.wc > 8; }
+ConvArgs chunks_form(ConvArgs a, int geom) {
+  if (geom == CONV_UP_PHASES) a.up = 1;
+  a.geom = geom;
+  return a;
+}
+int64_t wgrad_floats(const Step& st, const WgradArgs& wa) {
+  return wgrad_mfma_supported(wa) ? wgrad_mfma_workspace_floats(wa)
+         : st.chunks_w ? wgrad_chunks_workspace_floats(wa) : wgrad_direct_workspace_floats(wa);
+}
+}  // namespace
+
 int build_plan(const char* spec, int batch, int dtype, int bn_mode, Plan* plan) {
   if (batch <= 0) return fail(AE_EINVAL, "batch must be positive");
   if (dtype != AE_F32 && dtype != AE_BF16) return fail(AE_EINVAL, "dtype must be AE_F32 or AE_BF16");
@@ -269,7 +386,7 @@ int build_plan(const char* spec, int batch, int dtype, int bn_mode, Plan* plan) 
   };
   plan->max_act_elems = B * plan->c0 * plan->h0 * plan->w0;
   plan->max_raw_elems = plan->max_full_elems = plan->max_partial_floats = plan->max_wgrad_floats = plan->max_splitk_floats = 0;
-  plan->max_wgrad_inorder_floats = 0;
+  plan->max_wgrad_inorder_floats = plan->max_dypad_bytes = 0;
   for (Step& st : plan->steps) {
     int64_t out_elems = B * st.cout * st.hout * st.wout;
     int64_t in_elems = B * st.cin * st.hin * st.win;
@@ -282,10 +399,12 @@ int build_plan(const char* spec, int batch, int dtype, int bn_mode, Plan* plan) 
       if (st.has_bn || st.pool) st.off_raw = take(raw_elems * es);
       else if (st.act == ACT_SIGMOID && dtype == AE_BF16) st.off_aux = take(raw_elems * 4);
       plan->max_full_elems = std::max(plan->max_full_elems, rows * st.cin);
-      int64_t wel = (int64_t)st.cout * st.cin * st.k * st.k;
+      const int cin_p = chan_pad(st.cin, dtype), cout_p = chan_pad(st.cout, dtype);
+      // (both packings; the matrix-core kernels for any channel counts read whole 16-byte chunks per tap)
+      int64_t wel = std::max((int64_t)st.cout * cin_p, (int64_t)st.cin * cout_p) * st.k * st.k;
       // thin layers keep their weights repacked as MFMA operand rows of the wide side
       // (the summed-weight forms of an upsampled 3x3 conv hold 16 taps instead of 9)
-      const int64_t wpk = (st.up && st.k == 3 ? (int64_t)16 * st.cout * st.cin : wel) * es;
+      const int64_t wpk = (st.up && st.k == 3 ? wel / 9 * 16 : wel) * es;
       st.off_wpack = take(std::max(wpk, st.thin == 1 ? thin_wfrag_bytes(st.cout)
                                         : st.thin == 2 ? thin_out_wz_bytes(st.cout, st.cin) : (int64_t)0));
       st.off_wpack_d = take(std::max(wpk, st.thin == 2 ? thin_wfrag_bytes(st.cin) : (int64_t)0));
@@ -303,6 +422,9 @@ int build_plan(const char* spec, int batch, int dtype, int bn_mode, Plan* plan) 
         ca.x = ca.w = nullptr; ca.bias = nullptr; ca.y = nullptr; ca.partial = nullptr; ca.y_aux = nullptr;
         ca.n = batch; ca.hc = st.hc; ca.wc = st.wc; ca.cin = st.cin; ca.cout = st.cout; ca.k = st.k; ca.up = st.up;
         ca.act = ACT_NONE; ca.dtype = dtype;
+        st.chunks = !conv_mfma_supported(ca) && conv_chunks_worthwhile(ca) && conv_chunks_supported(chunks_form(ca, st.up && st.k == 3 ? CONV_UP_PHASES : CONV_PLAIN));
+        if (st.chunks && !st.has_bn)
+          plan->max_splitk_floats = std::max(plan->max_splitk_floats, conv_chunks_splitk_floats(chunks_form(ca, st.up && st.k == 3 ? CONV_UP_PHASES : CONV_PLAIN)));
         if (!st.has_bn) plan->max_splitk_floats = std::max(plan->max_splitk_floats, conv_mfma_splitk_floats(ca));
         ca.cin = st.cout; ca.cout = st.cin; ca.up = 0;
         plan->max_splitk_floats = std::max(plan->max_splitk_floats, conv_mfma_splitk_floats(ca));
@@ -310,6 +432,16 @@ int build_plan(const char* spec, int batch, int dtype, int bn_mode, Plan* plan) 
           ca.geom = CONV_UP_DGRAD;
           plan->max_splitk_floats = std::max(plan->max_splitk_floats, conv_mfma_splitk_floats(ca));
         }
+        if (st.needs_dx) {
+          ca.geom = CONV_PLAIN;
+          const ConvArgs cd = chunks_form(ca, st.up && st.k == 3 ? CONV_UP_DGRAD : CONV_PLAIN);
+          st.chunks_d = !conv_mfma_supported(ca) && conv_chunks_worthwhile(ca) && conv_chunks_supported(cd);
+          if (st.chunks_d) plan->max_splitk_floats = std::max(plan->max_splitk_floats, conv_chunks_splitk_floats(cd));
+        }
+        st.chunks_w = !wgrad_mfma_supported(wa) && wgrad_chunks_worthwhile(wa) && wgrad_chunks_supported(wa);
+        if ((st.chunks || st.chunks_w) && cin_p != st.cin) st.off_xpad = take(in_elems / st.cin * cin_p * es);
+        if ((st.chunks_d || st.chunks_w) && cout_p != st.cout)
+          plan->max_dypad_bytes = std::max(plan->max_dypad_bytes, rows * cout_p * es);
       }
       if (st.thin == 1) {
         plan->max_wgrad_floats = std::max(plan->max_wgrad_floats, thin_wgrad_workspace_floats(rows, st.cin, st.cout));
@@ -324,16 +456,12 @@ int build_plan(const char* spec, int batch, int dtype, int bn_mode, Plan* plan) 
           plan->max_wgrad_floats = std::max(plan->max_wgrad_floats,
                                             thin_wgrad_mfma_workspace_floats(batch, st.hin, st.win, st.cin));
       }
-      else if (wgrad_mfma_supported(wa))
-        plan->max_wgrad_floats = std::max(plan->max_wgrad_floats, wgrad_mfma_workspace_floats(wa));
       else
-        plan->max_wgrad_floats = std::max(plan->max_wgrad_floats, wgrad_direct_workspace_floats(wa));
+        plan->max_wgrad_floats = std::max(plan->max_wgrad_floats, wgrad_floats(st, wa));
       // a layer without batch-norm, activation or pooling has no conv-output gradient buffer of its own: its
       // weight gradient runs in order on the caller's stream, with scratch apart from the side stream's
       if (!st.has_bn && !st.pool && st.act == ACT_NONE && st.thin == 0)
-        plan->max_wgrad_inorder_floats = std::max(plan->max_wgrad_inorder_floats,
-                                                  wgrad_mfma_supported(wa) ? wgrad_mfma_workspace_floats(wa)
-                                                                           : wgrad_direct_workspace_floats(wa));
+        plan->max_wgrad_inorder_floats = std::max(plan->max_wgrad_inorder_floats, wgrad_floats(st, wa));
       if (st.thin == 2)
         plan->max_partial_floats = std::max(plan->max_partial_floats,
                                             B * plane_sums_split((int64_t)st.hc * st.wc) * 2 * (int64_t)st.cout);
@@ -348,6 +476,7 @@ int build_plan(const char* spec, int batch, int dtype, int bn_mode, Plan* plan) 
   plan->off_wgrad = take(plan->max_wgrad_floats * 4);
   plan->off_wgrad_inorder = take(plan->max_wgrad_inorder_floats * 4);
   plan->off_splitk = take(plan->max_splitk_floats * 4);
+  plan->off_dypad = take(3 * plan->max_dypad_bytes);
   plan->ws_bytes = total;
   return AE_OK;
 }

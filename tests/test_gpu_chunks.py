@@ -1,0 +1,44 @@
+"""The matrix-core kernels for any channel counts (16-byte chunks of K walked across tap borders) against the oracle, at
+the sizes where they can go wrong: channel counts around a chunk, a slab, a column tile; row counts around a row tile;
+images narrower than a slab of pixels; the summed-weight forms behind a x2 upsample; split K."""
+import pytest
+
+from parity_util import run_case
+
+pytestmark = pytest.mark.gpu
+
+# The tail turns the compared layer's gradient into one that is not constant; conv1:2 keeps its own gradients small.
+CASES = [
+    # channel counts around a chunk (8 or 4 elements), a slab (32 or 16), the column tiles (32, 64, 128)
+    ("in:5x6x7,conv3:33,relu,conv3:1", 3),
+    ("in:8x5x9,conv3:31,relu,conv3:17,relu,conv1:3", 2),
+    ("in:24x8x8,conv3:65,relu,conv3:129,relu,conv1:2", 2),
+    ("in:12x7x5,conv1:40,relu,conv1:130,relu,conv1:7", 4),
+    ("in:36x4x4,conv3:96,relu,conv3:12", 3),
+    # 127, 128 and 129 rows; one row of one pixel
+    ("in:20x1x127,conv3:24,relu,conv1:20", 1),
+    ("in:20x8x16,conv3:24,relu,conv1:20", 1),
+    ("in:20x3x43,conv3:24,relu,conv1:20", 1),
+    ("in:7x1x1,fc:9,relu,fc:5", 1),
+    # batch-norm statistics, pooling, the channel in the middle, the summed-weight forms of an upsampled layer
+    ("in:3x12x20,conv3:12,bn,relu,pool2,conv3:24,bn,relu,pool2,conv1:6,pnorm,awgn,conv1:24,up2,conv3:12,relu,up2,conv3:3,sigmoid", 3),
+    ("in:6x3x5,up2,conv3:20,bn,relu,up2,conv1:9,sigmoid", 2),
+    ("in:72x6x6,up2,conv3:56,relu,conv3:64,relu,conv3:40", 2),
+    # a long K over few rows (split), and an unaligned fully-connected pair
+    ("in:5x9x21,flatten,fc:33,relu,fc:945,relu,reshape:5x9x21,conv3:2", 3),
+    # one side aligned to the tiled kernels, the other not
+    ("in:64x8x8,conv3:48,relu,conv3:64,relu,conv1:20,relu,conv1:128", 2),
+]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_any_channel_counts(case, dtype):
+    spec, batch = CASES[case]
+    run_case(spec, batch, dtype=dtype, seed=400 + case, flips=(dtype == "bf16"))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_tall_tiles_and_many_splits(dtype):
+    # 33,024 rows: the 256-row tiles with a ragged last one; a weight gradient in over a hundred pieces
+    run_case("in:12x64x43,conv3:20,relu,conv3:12,relu,conv1:3", 12, dtype=dtype, seed=431, flips=(dtype == "bf16"))
