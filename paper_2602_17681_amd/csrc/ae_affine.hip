@@ -646,6 +646,12 @@ int dense_product(const void* x, const void* w, void* y, int d, int dtype, int t
   a.x = x; a.w = w; a.bias = nullptr; a.y = y;
   a.n = d; a.hc = a.wc = 1; a.cin = a.cout = d; a.k = 1; a.up = 0; a.act = ACT_NONE; a.dtype = dtype;
   a.tri = tri;
+  // Products of matrices close to the identity (the exponential and its squarings, the only ones without a triangular
+  // operand) keep the binary32 MFMA up to d = 480: a bf16 dot of 16 products is rounded at its largest one, a bias of 1.6e-7 at the
+  // diagonal that five squarings carry along coherently, while the binary32 MFMA's error grows with d.  A after compose, 2-norm
+  // against float64: d = 256 4.0e-6 by parts against 3.6e-6, d = 1024 4.2e-6 against 1.4e-5, d = 2048 4.6e-6 against 3.7e-5;
+  // dG 3.5e-6 against 2.5e-6, 3.4e-6 against 1.1e-5, 3.5e-6 against 3.1e-5.
+  a.f32_mfma = tri == CONV_TRI_NONE && d < 512;
   if (!g_timing) return launch_conv_mfma(a, s);
   AE_HIP(hipEventRecord(g_ev0, s));
   AE_TRY(launch_conv_mfma(a, s));

@@ -503,6 +503,75 @@ struct SlabReads<KS, KS, MI, NJ, BKB> {
   static __device__ __forceinline__ void run(uint4v (&)[KS][MI], uint4v (&)[KS][NJ], unsigned, unsigned, const int (&)[KS]) {}
 };
 
+// Which tile a workgroup computes, in what order (ONE_SPLIT: the launch does not split K)
+struct IgemmTileId { int64_t m; int n, split, phase; };
+template <int BM, int BN, bool ONE_SPLIT>
+__device__ __forceinline__ IgemmTileId igemm_tile_id(const IgemmParams& p) {
+  IgemmTileId t;
+  int lb0 = xcd_logical_block((int)blockIdx.x, (int)gridDim.x);
+  // triangular products: tile rows differ in work by an order of magnitude, so neighbouring tiles go to different
+  // XCDs (the hardware's own round-robin) instead of one contiguous range per XCD, the longest K ranges first
+  if (p.tri != 0 && p.tri < 8) lb0 = p.tri == 1 ? (int)gridDim.x - 1 - (int)blockIdx.x : (int)blockIdx.x;
+  if (p.tri == 4 && (gridDim.x & 63) == 0) {    // runs of eight consecutive tiles per XCD (they share an operand panel in its L2), runs interleaved
+    const int i = (int)blockIdx.x >> 3, x = (int)blockIdx.x & 7;
+    lb0 = ((((i >> 3) << 3) + x) << 3) + (i & 7);
+  }
+  t.phase = 0;
+  if (p.phases == 4) { t.phase = lb0 & 3; lb0 >>= 2; }   // the four phases of a tile run side by side: they read the same input
+  t.split = ONE_SPLIT ? 0 : lb0 / p.tiles_mn;
+  const int lb = ONE_SPLIT ? lb0 : lb0 - t.split * p.tiles_mn;
+  // tile order: groups of kGroupM tile rows are walked column by column, so the workgroups in flight on an XCD
+  // cover a squarish patch of the output (few distinct operand rows per K slab in its L2) instead of a wide strip
+  constexpr int kGroupM = 4;
+  const int gsz = kGroupM * p.tiles_n, grp = lb / gsz, in_grp = lb - grp * gsz;
+  const int gm = min(p.tiles_mn / p.tiles_n - grp * kGroupM, kGroupM);
+  t.n = in_grp / gm;
+  t.m = grp * kGroupM + in_grp % gm;
+  if (p.tri == 3) {                             // K range [column, K): walk column by column, the longest first
+    const int tiles_m = p.tiles_mn / p.tiles_n;
+    t.n = lb / tiles_m;
+    t.m = lb - t.n * tiles_m;
+  }
+  if (p.tri == 4 && p.tiles_mn == p.tiles_n * p.tiles_n) {
+    // K range [max(row, column), K): on a square tile grid walk the L-shaped shells max(tile row, tile column) = 0, 1, ...
+    // so that the workgroups are dispatched longest first and the hardware's in-order dispatch balances the rest
+    int sh = (int)sqrtf((float)lb);
+    while (sh * sh > lb) --sh;
+    while ((sh + 1) * (sh + 1) <= lb) ++sh;
+    const int r = lb - sh * sh;                 // 0 .. 2 sh
+    t.m = r <= sh ? r : sh;
+    t.n = r <= sh ? sh : r - sh - 1;
+  }
+  if (p.tri >= 8) {                             // only the tiles of one off-diagonal block per pair are launched
+    const int tbm = p.tri_b / BM, tbn = p.tri_b / BN, per_pair = tbm * tbn;
+    const int pair = lb / per_pair, in_pair = lb - pair * per_pair;
+    const int tr = in_pair / tbn, tc = in_pair - tr * tbn;
+    t.m = (2 * pair + (p.tri == 9 ? 1 : 0)) * tbm + tr;
+    t.n = (2 * pair + (p.tri == 9 ? 0 : 1)) * tbn + tc;
+  }
+  return t;
+}
+// its K range (triangular operands: see IgemmParams::tri); false: no output of the tile is wanted
+template <int BM, int BN>
+__device__ __forceinline__ bool igemm_k_range(const IgemmParams& p, int64_t m0, int n0, int& k_lo, int& k_hi) {
+  k_lo = 0; k_hi = p.K;
+  if (p.tri == 1) k_hi = (int)min((int64_t)p.K, min(m0 + BM, (int64_t)n0 + BN));
+  else if (p.tri == 2) { if ((int64_t)n0 + BN <= m0) return false; k_lo = (int)m0; }
+  else if (p.tri == 3) { if ((int64_t)n0 >= m0 + BM) return false; k_lo = n0; }
+  else if (p.tri == 4) k_lo = (int)max(m0, (int64_t)n0);
+  else if (p.tri >= 8) {
+    const int rb = (int)(m0 / p.tri_b), cb = n0 / p.tri_b;
+    if (p.tri == 9 ? !((rb & 1) == 1 && cb == rb - 1) : !((rb & 1) == 0 && cb == rb + 1)) return false;
+    k_lo = rb * p.tri_b;
+    k_hi = k_lo + p.tri_b;
+    if (p.tri_d > 0) {
+      if ((p.tri == 9 ? m0 : (int64_t)n0) >= p.tri_d) return false;
+      if (p.tri == 9) k_hi = min(k_hi, p.tri_d);
+    }
+  }
+  return true;
+}
+
 // INTERIOR: the host guarantees M % BM == 0, N % BN == 0, 16-byte aligned rows, no sigmoid, no
 // auxiliary copy and no activation together with statistics, so the epilogue needs no checks.
 // DMA: the slabs go from global memory straight into LDS (buffer loads with the LDS
@@ -547,47 +616,10 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WGN, wn = wave % WGN;
-  int lb0 = xcd_logical_block((int)blockIdx.x, (int)gridDim.x);
-  // triangular products: tile rows differ in work by an order of magnitude, so neighbouring tiles go to different
-  // XCDs (the hardware's own round-robin) instead of one contiguous range per XCD, the longest K ranges first
-  if (p.tri != 0 && p.tri < 8) lb0 = p.tri == 1 ? (int)gridDim.x - 1 - (int)blockIdx.x : (int)blockIdx.x;
-  if (p.tri == 4 && (gridDim.x & 63) == 0) {    // runs of eight consecutive tiles per XCD (they share an operand panel in its L2), runs interleaved
-    const int i = (int)blockIdx.x >> 3, x = (int)blockIdx.x & 7;
-    lb0 = ((((i >> 3) << 3) + x) << 3) + (i & 7);
-  }
-  int phase = 0;
-  if (p.phases == 4) { phase = lb0 & 3; lb0 >>= 2; }   // the four phases of a tile run side by side: they read the same input
-  const int split = INTERIOR ? 0 : lb0 / p.tiles_mn;
-  const int lb = INTERIOR ? lb0 : lb0 - split * p.tiles_mn;
-  // tile order: groups of kGroupM tile rows are walked column by column, so the workgroups in flight on an XCD
-  // cover a squarish patch of the output (few distinct operand rows per K slab in its L2) instead of a wide strip
-  constexpr int kGroupM = 4;
-  const int gsz = kGroupM * p.tiles_n, grp = lb / gsz, in_grp = lb - grp * gsz;
-  const int gm = min(p.tiles_mn / p.tiles_n - grp * kGroupM, kGroupM);
-  int tile_n = in_grp / gm;
-  int64_t tile_m = grp * kGroupM + in_grp % gm;
-  if (p.tri == 3) {                             // K range [column, K): walk column by column, the longest first
-    const int tiles_m = p.tiles_mn / p.tiles_n;
-    tile_n = lb / tiles_m;
-    tile_m = lb - tile_n * tiles_m;
-  }
-  if (p.tri == 4 && p.tiles_mn == p.tiles_n * p.tiles_n) {
-    // K range [max(row, column), K): on a square tile grid walk the L-shaped shells max(tile row, tile column) = 0, 1, ...
-    // so that the workgroups are dispatched longest first and the hardware's in-order dispatch balances the rest
-    int sh = (int)sqrtf((float)lb);
-    while (sh * sh > lb) --sh;
-    while ((sh + 1) * (sh + 1) <= lb) ++sh;
-    const int r = lb - sh * sh;                 // 0 .. 2 sh
-    tile_m = r <= sh ? r : sh;
-    tile_n = r <= sh ? sh : r - sh - 1;
-  }
-  if (p.tri >= 8) {                             // only the tiles of one off-diagonal block per pair are launched
-    const int tbm = p.tri_b / BM, tbn = p.tri_b / BN, per_pair = tbm * tbn;
-    const int pair = lb / per_pair, in_pair = lb - pair * per_pair;
-    const int tr = in_pair / tbn, tc = in_pair - tr * tbn;
-    tile_m = (2 * pair + (p.tri == 9 ? 1 : 0)) * tbm + tr;
-    tile_n = (2 * pair + (p.tri == 9 ? 0 : 1)) * tbn + tc;
-  }
+  const IgemmTileId tile = igemm_tile_id<BM, BN, INTERIOR>(p);
+  const int phase = tile.phase, split = tile.split;
+  const int64_t tile_m = tile.m;
+  const int tile_n = tile.n;
   const int64_t m0 = tile_m * BM;
   const int n0 = tile_n * BN;
   const int pad_h = p.pad - (phase >> 1), pad_w = p.pad - (phase & 1);
@@ -620,21 +652,8 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
     b_off[i] = row < p.N && lrow + i * RSTEP < BN ? (unsigned)(phase * p.N + row) * (unsigned)p.K * (unsigned)ES + (unsigned)gchunk * 16u : kOob;
   }
 
-  int k_lo = 0, k_hi = p.K;                                             // triangular operands: see IgemmParams::tri
-  if (p.tri == 1) k_hi = (int)min((int64_t)p.K, min(m0 + BM, (int64_t)n0 + BN));
-  else if (p.tri == 2) { if ((int64_t)n0 + BN <= m0) return; k_lo = (int)m0; }
-  else if (p.tri == 3) { if ((int64_t)n0 >= m0 + BM) return; k_lo = n0; }
-  else if (p.tri == 4) k_lo = (int)max(m0, (int64_t)n0);
-  else if (p.tri >= 8) {
-    const int rb = (int)(m0 / p.tri_b), cb = n0 / p.tri_b;
-    if (p.tri == 9 ? !((rb & 1) == 1 && cb == rb - 1) : !((rb & 1) == 0 && cb == rb + 1)) return;
-    k_lo = rb * p.tri_b;
-    k_hi = k_lo + p.tri_b;
-    if (p.tri_d > 0) {
-      if ((p.tri == 9 ? m0 : (int64_t)n0) >= p.tri_d) return;
-      if (p.tri == 9) k_hi = min(k_hi, p.tri_d);
-    }
-  }
+  int k_lo, k_hi;
+  if (!igemm_k_range<BM, BN>(p, m0, n0, k_lo, k_hi)) return;
   const int kt_lo = k_lo / BK, kt_hi = (k_hi + BK - 1) / BK;
   const int kt0 = INTERIOR ? kt_lo : max(kt_lo, split * p.slabs_per_split);   // first K slab of this workgroup
   // CHUNKS: the tap and the chunk within it of this lane's next load (q = chunk index along K)
@@ -814,6 +833,219 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
     }
   }
   igemm_epilogue<T, BM, BN, WGM, WGN, INTERIOR, EPI, CHUNKS>(acc, p, smem, sRed, m0, n0, tile_m, phase);
+}
+
+// ---------------------------------------------------------------------------
+// Dense binary32 products (k = 1, one pixel per row) on the bf16 matrix cores.
+//
+// Every value is cut into three bfloat16 parts on its way into LDS, x = h + m + l (each rounded to nearest, the remainders
+// exact: |m| <= 2^-8 |x|, |l| <= 2^-16 |x|, h + m + l = x), and a product is the six MFMAs hh + hm + mh + mm + hl + lh; what
+// is dropped, ml + lm + ll, is of the size of one binary32 rounding of the product at worst.  hh goes to an accumulator of
+// its own, the five small ones to a second one whose roundings are their own size: a K of 16 rounds the sum once, where
+// eight binary32 MFMAs round it eight times.  Six bf16 MFMAs take 192 cycles for that K, the eight binary32 ones 512.
+// Measured at d = 4096: 0.63 ms = 218 TFLOP/s against 1.01 ms = 136 (87 % of the binary32 MFMA's rate), the matrix cores
+// busy two thirds of the cycles at the 1.8 GHz that the power limit leaves; errors at the rule in launch_conv_mfma.
+//
+// A workgroup is WGM x WGN wavefronts of 64 x 64 outputs.  Slabs of 16 k's are loaded into registers two slabs ahead, cut
+// into parts between the MFMAs of the slab before (the split is a third of the VALU issue slots that the MFMAs leave)
+// and stored to the other of two LDS stages; one barrier per slab.  LDS: [stage][part][32-row block] of 1 KiB in fragment
+// order, chunk c (8 of the 16 k's) of row r at 512 c + (16 r ^ 128 c): a fragment read is 1 KiB in lane order, and the 8-byte
+// stores of 8 rows x 4 quarters fall into 64 different banks.
+//
+// A part below 2^-126 may be flushed, and a value that rounds to infinity has no parts: a workgroup that meets an infinity
+// (or a value within half a bf16 step of it), or an operand row whose largest magnitude is nonzero and below 2^-96,
+// computes its tile again with the binary32 MFMA.
+// ---------------------------------------------------------------------------
+template <int BM, int BN, int WGM, int WGN, bool INTERIOR, int EPI = 0>
+__global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_split(IgemmParams p) {
+  constexpr int NT = WGM * WGN * 64;
+  constexpr int WM = BM / WGM, WN = BN / WGN, MI = WM / 32, NJ = WN / 32;
+  constexpr int RSTEP = NT / 4;                  // rows per loader pass: four lanes of 16 bytes share a row
+  constexpr int AC = BM / RSTEP, BC = BN / RSTEP;
+  constexpr int PA = BM * 32, PB = BN * 32, STAGE = 3 * (PA + PB);
+  constexpr int SW = WN + 4, STAGE_BYTES = (NT / 64) * 32 * SW * 4;
+  __shared__ __attribute__((aligned(16))) char smem[3 * STAGE > STAGE_BYTES ? 3 * STAGE : STAGE_BYTES];
+  __shared__ float sRed[WGM][2][BN];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave / WGN, wn = wave % WGN;
+  const IgemmTileId tile = igemm_tile_id<BM, BN, INTERIOR>(p);
+  const int64_t m0 = tile.m * BM;
+  const int n0 = tile.n * BN;
+  int k_lo, k_hi;
+  if (!igemm_k_range<BM, BN>(p, m0, n0, k_lo, k_hi)) return;
+  // slabs of 16 (K ranges start at multiples of 32)
+  const int kt0 = INTERIOR ? k_lo / 16 : max(k_lo / 16, tile.split * p.slabs_per_split);
+  const int KT = INTERIOR ? (k_hi + 15) / 16 - kt0 : min((k_hi + 15) / 16 - kt0, p.slabs_per_split);
+  const __amdgpu_buffer_rsrc_t rX = make_rsrc(p.x, p.x_bytes);
+  const __amdgpu_buffer_rsrc_t rW = make_rsrc(p.w, p.w_bytes);
+  const int lrow = tid >> 2, kq = tid & 3;
+  unsigned off[AC + BC];                         // byte offset of this lane's next 16 bytes of each row
+#pragma unroll
+  for (int i = 0; i < AC; ++i) {
+    const int64_t m = m0 + lrow + i * RSTEP;
+    off[i] = m < p.M ? (unsigned)m * (unsigned)p.K * 4u + (unsigned)(kt0 * 64 + kq * 16) : kOob;
+  }
+#pragma unroll
+  for (int i = 0; i < BC; ++i) {
+    const int n = n0 + lrow + i * RSTEP;
+    off[AC + i] = n < p.N ? (unsigned)n * (unsigned)p.K * 4u + (unsigned)(kt0 * 64 + kq * 16) : kOob;
+  }
+  uint4v r[AC + BC];
+  float mx[AC + BC];
+#pragma unroll
+  for (int i = 0; i < AC + BC; ++i) mx[i] = 0.0f;
+  auto load = [&](int i) {                       // (past the last slab: values that nobody uses)
+    r[i] = __builtin_amdgcn_raw_buffer_load_b128(i < AC ? rX : rW, off[i], 0, 0);
+    off[i] += 64;
+  };
+  const int sc = kq >> 1;
+  char* const st = smem + (lrow >> 5) * 1024 + sc * 512 + (((lrow & 31) * 16) ^ (sc * 128)) + (kq & 1) * 8;
+  auto split = [&](int stage, int i) {           // the four values of one load: three 8-byte stores
+    char* const dst = st + stage + (i < AC ? i * (RSTEP * 32) : 3 * PA + (i - AC) * (RSTEP * 32));
+    const float4v f = __builtin_bit_cast(float4v, r[i]);
+    mx[i] = fmaxf(fmaxf(mx[i], fabsf(f[0])), fabsf(f[1]));
+    mx[i] = fmaxf(fmaxf(mx[i], fabsf(f[2])), fabsf(f[3]));
+    float r0 = f[0], r1 = f[1], r2 = f[2], r3 = f[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const uint32_t w0 = pack_bf16(r0, r1), w1 = pack_bf16(r2, r3);
+      *reinterpret_cast<uint2*>(dst + q * (i < AC ? PA : PB)) = make_uint2(w0, w1);
+      r0 -= __uint_as_float(w0 << 16); r1 -= __uint_as_float(w0 & 0xFFFF0000u);
+      r2 -= __uint_as_float(w1 << 16); r3 -= __uint_as_float(w1 & 0xFFFF0000u);
+    }
+  };
+  floatx16 acc[MI][NJ], low[MI][NJ];             // the sum of the hh, of the five small products
+  auto clear = [&](floatx16 (&c)[MI][NJ]) {
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) c[i][j][e] = 0.0f;
+  };
+  clear(acc);
+  clear(low);
+  const int f_off = (lane >> 5) * 512 + (((lane & 31) * 16) ^ ((lane >> 5) * 128));
+  const char* const fa = smem + wm * WM * 32 + f_off;
+  const char* const fb = smem + 3 * PA + wn * WN * 32 + f_off;
+  uint4v a[3][MI], b[3][NJ];
+  auto read_a = [&](int stage, int q) {
+#pragma unroll
+    for (int i = 0; i < MI; ++i) a[q][i] = *reinterpret_cast<const uint4v*>(fa + stage + q * PA + i * 1024);
+  };
+  auto read_b = [&](int stage, int q) {
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) b[q][j] = *reinterpret_cast<const uint4v*>(fb + stage + q * PB + j * 1024);
+  };
+  auto mma = [&](int qa, int qb) {
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) mma_step<bf16_t>(a[qa][i], b[qb][j], qa + qb == 0 ? acc[i][j] : low[i][j]);
+  };
+#pragma unroll
+  for (int i = 0; i < AC + BC; ++i) load(i);
+#pragma unroll
+  for (int i = 0; i < AC + BC; ++i) { split(0, i); load(i); }
+  __syncthreads();
+  read_b(0, 0); read_a(0, 0);
+  int cur = 0, nxt = STAGE;
+  for (int kt = 1; kt < KT; ++kt) {
+    // A slab: its first fragments are in registers.  The next slab goes into the stage read two slabs ago (every wave has
+    // passed the barrier of the slab in between, so that stage is free) and its first fragments are fetched behind the
+    // last two products.
+    // (the scheduling barriers keep the reads ahead of the MFMAs they would otherwise be sunk to)
+    read_b(cur, 1); read_a(cur, 1); read_b(cur, 2); read_a(cur, 2);
+    __builtin_amdgcn_sched_barrier(0);
+    mma(0, 0); mma(0, 1); mma(1, 0); mma(1, 1);
+#pragma unroll
+    for (int i = 0; i < AC + BC; ++i) { split(nxt, i); load(i); }
+#pragma unroll
+    for (int g = 0; g < 4 * MI * NJ; ++g) {      // the split spread between the MFMAs
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x002, (AC + BC) * 26 / (4 * MI * NJ) + 1, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    __syncthreads();
+    uint4v a2[MI], b2[NJ];
+#pragma unroll
+    for (int i = 0; i < MI; ++i) a2[i] = a[0][i];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) b2[j] = b[0][j];
+    read_b(nxt, 0); read_a(nxt, 0);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) mma_step<bf16_t>(a2[i], b[2][j], low[i][j]);
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) mma_step<bf16_t>(a[2][i], b2[j], low[i][j]);
+    __builtin_amdgcn_sched_barrier(0);
+    cur = nxt;
+    nxt = nxt == 2 * STAGE ? 0 : nxt + STAGE;
+  }
+  read_b(cur, 1); read_a(cur, 1); read_b(cur, 2); read_a(cur, 2);
+  mma(0, 0); mma(0, 1); mma(1, 0); mma(1, 1); mma(0, 2); mma(2, 0);
+  // a row is loaded by four neighbouring lanes
+  bool odd = false;
+#pragma unroll
+  for (int i = 0; i < AC + BC; ++i) {
+    float v = mx[i];
+    v = fmaxf(v, __shfl_xor(v, 1, 64));
+    v = fmaxf(v, __shfl_xor(v, 2, 64));
+    odd = odd || v >= 0x1.FFp127f || (v > 0.0f && v < 0x1p-96f);
+  }
+  if (__syncthreads_or(odd) != 0) {
+    // fragments straight from global memory: lane l holds four k's of row l % 32, the same ones on both sides
+    unsigned fo[MI + NJ];
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+      const int64_t m = m0 + wm * WM + i * 32 + (lane & 31);
+      fo[i] = m < p.M ? (unsigned)m * (unsigned)p.K * 4u + (unsigned)(kt0 * 64 + (lane >> 5) * 16) : kOob;
+    }
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const int n = n0 + wn * WN + j * 32 + (lane & 31);
+      fo[MI + j] = n < p.N ? (unsigned)n * (unsigned)p.K * 4u + (unsigned)(kt0 * 64 + (lane >> 5) * 16) : kOob;
+    }
+    clear(acc);
+    clear(low);
+    for (int h = 0; h < 2 * KT; ++h) {
+      uint4v f[MI + NJ];
+#pragma unroll
+      for (int i = 0; i < MI + NJ; ++i) f[i] = __builtin_amdgcn_raw_buffer_load_b128(i < MI ? rX : rW, fo[i] + (unsigned)h * 32u, 0, 0);
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) mma_step<float>(f[i], f[MI + j], acc[i][j]);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] += low[i][j][e];
+  if constexpr (!INTERIOR) {
+    if (p.split_out) {
+      float* __restrict__ P = p.split_out + (int64_t)tile.split * p.M * p.N;
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          const int col = n0 + wn * WN + j * 32 + (lane & 31);
+#pragma unroll
+          for (int e = 0; e < 16; ++e) {
+            const int64_t m = m0 + wm * WM + i * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
+            if (m < p.M && col < p.N) P[m * p.N + col] = acc[i][j][e];
+          }
+        }
+      return;
+    }
+  }
+  igemm_epilogue<float, BM, BN, WGM, WGN, INTERIOR, EPI>(acc, p, smem, sRed, m0, n0, tile.m, 0);
 }
 
 // y = act(round(sum over splits of partial[split] + bias)) for split-K launches
@@ -1305,6 +1537,22 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
     if (interior) hipLaunchKernelGGL((k_igemm<T, BMV, BNV, GM, GN, KB, true, true>), grid, dim3(256), 0, s, p); \
     else hipLaunchKernelGGL((k_igemm<T, BMV, BNV, GM, GN, KB, false, true>), grid, dim3(256), 0, s, p); \
   } while (0)
+  // Dense binary32 products: three bf16 parts (k_gemm_split), unless the caller asks for the binary32 MFMA
+  const bool split_gemm = a.dtype == AE_F32 && !a0.f32_mfma && a.k == 1 && a.hc == 1 && a.wc == 1 && a.up == 0 && t.bn == 128;
+  if (split_gemm) {
+    // 256-row tiles, one workgroup per compute unit, where they fill the chip and K is long enough to outweigh their
+    // prologue and epilogue, which nothing runs beside (d = 4096: 0.63 against 0.71 ms; K = 512, 65536 x 512 outputs: no gain)
+    const int64_t tall = p.M % 256 == 0 && interior && a0.tri == 0 && a0.epi == CONV_EPI_NONE && p.K >= 1024 ? p.M / 256 * p.tiles_n : 0;
+    if (tall >= 256) {
+      p.tiles_mn = (int)tall;
+      hipLaunchKernelGGL((k_gemm_split<256, 128, 4, 2, true>), dim3((unsigned)tall), dim3(512), 0, s, p);
+    } else if (a0.epi == CONV_EPI_MXQ) hipLaunchKernelGGL((k_gemm_split<128, 128, 2, 2, true, 1>), grid, dim3(256), 0, s, p);   // (conv_epi_usable: interior)
+    else if (a0.epi == CONV_EPI_RESID) hipLaunchKernelGGL((k_gemm_split<128, 128, 2, 2, true, 2>), grid, dim3(256), 0, s, p);
+    else if (interior) hipLaunchKernelGGL((k_gemm_split<128, 128, 2, 2, true>), grid, dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((k_gemm_split<128, 128, 2, 2, false>), grid, dim3(256), 0, s, p);
+    AE_TRY(launch_status("gemm_split"));
+    return splits > 1 ? launch_splitk_finish(a, splits, p.M, p.N, s) : AE_OK;
+  }
 #define IGEMM_LAUNCH_T(T, BMV, BNV, GM, GN) IGEMM_LAUNCH_K(T, BMV, BNV, GM, GN, 64)   /* pick_tile: 64-byte slabs only */
 #define IGEMM_LAUNCH(BMV, BNV, GM, GN)                                         \
   do {                                                                         \

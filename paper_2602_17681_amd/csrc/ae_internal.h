@@ -199,6 +199,7 @@ struct ConvArgs {
   //                         tri_d; tiles and K ranges beyond it are skipped (outputs there are zero, left unwritten).
   int tri_pairs = 0;
   int tri_d = 0;
+  bool f32_mfma = false;           // dense binary32 products: not through bf16 parts
 };
 enum { CONV_TRI_NONE = 0, CONV_TRI_LOWER_UPPER = 1, CONV_TRI_UPPER_X = 2, CONV_TRI_UPPER_W = 3, CONV_TRI_UPPER_LOWER = 4,
        CONV_TRI_PAIR_UPPER_K0 = 8, CONV_TRI_PAIR_LOWER_K1 = 9 };
