@@ -354,10 +354,17 @@ __global__ __launch_bounds__(256) void k_tri_diag_inverse(LuSrc q, int dp, float
 
 // ---- many small matrices at once (the per-block transformations: one d x d parameter set per transformer block, d the
 // head dimension) --------------------------------------------------------------------------------------------------
-// For d <= 128 a matrix fits into LDS, and the full-size path above would be a dozen launch-bound kernels per matrix.
-// Here one workgroup of 256 threads owns one matrix and one launch covers `count` of them; the products are plain
-// binary32 multiply-adds out of LDS (2 d^3 operations per product: microseconds).  Thread (ty, tx) = (tid / 16,
-// tid % 16) owns the outputs (ty + 16 a, tx + 16 b), a, b = 0..7.
+// For d <= 128 a matrix fits into LDS, and the full-size path above would be a dozen launch-bound kernels per matrix; one
+// launch covers `count` of them.  A product of 128 x 128 matrices is microseconds of the binary32 MFMA, so what counts is
+// that a handful of matrices (32 blocks of a model) still spreads over the chip and that no thread waits for one load at a
+// time: a workgroup of four wavefronts owns 32 rows of one product (four workgroups per matrix composing, eight backward),
+// a wavefront one 32 x 32 tile of them, and the operands come into LDS eight loads of 16 bytes at a time.  Measured for
+// 32 matrices of 128 (bfloat16 in and out) against one workgroup per matrix with vector-ALU products and scalar loads:
+// compose 82 -> 13 us, backward 135 -> 14 us, inverse 106 -> 31 us.
+// LDS rows are 132 floats: the 16-byte fragment reads of 16 rows and the 4-byte ones of two rows fall into different banks.
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+constexpr int kSmallLd = 132;
+
 __device__ __forceinline__ LuSrc small_src(const float* lp, const float* up, const float* log_s, const float* sign_s, int d, int m) {
   const int64_t mo = (int64_t)m * d * d, vo = (int64_t)m * d;
   return LuSrc{lp + mo, up + mo, log_s + vo, sign_s + vo, nullptr, nullptr, d};
@@ -367,182 +374,341 @@ __device__ __forceinline__ int small_perm(const int* perm, int d, int i) {      
   return (unsigned)p < (unsigned)d ? p : i;
 }
 
-// out[r][j] = sum_k L[perm[r]][k] (U + diag s)[k][j]
+// four consecutive entries of row r (c0 % 4 == 0), zeros past column d; vec: the rows allow one wide load
+template <typename T>
+__device__ __forceinline__ float4 small_load4(const T* m, int d, int r, int c0, bool vec) {
+  const T* p = m + (int64_t)r * d + c0;
+  if (vec) {
+    if constexpr (sizeof(T) == 4) return *reinterpret_cast<const float4*>(p);
+    const uint2 w = *reinterpret_cast<const uint2*>(p);
+    return make_float4(__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xFFFF0000u), __uint_as_float(w.y << 16), __uint_as_float(w.y & 0xFFFF0000u));
+  }
+  return make_float4(Store<T>::ld(p), c0 + 1 < d ? Store<T>::ld(p + 1) : 0.0f, c0 + 2 < d ? Store<T>::ld(p + 2) : 0.0f, c0 + 3 < d ? Store<T>::ld(p + 3) : 0.0f);
+}
+template <typename T> __device__ __forceinline__ bool small_vec(const T* p, int d) { return d % 4 == 0 && ((uintptr_t)p % (4 * sizeof(T))) == 0; }
+
+// dst[i][c] for i < rows, c < cols (both multiples of 4), dst rows of kSmallLd: entry (src_row(i), c0 + c) of src, passed through
+// fix(value, i, c); a negative row, or one past the matrix, reads zeros.  All threads of the workgroup, eight loads in flight.
+template <typename T, typename ROW, typename FIX>
+__device__ __forceinline__ void small_stage(float* dst, int rows, int cols, const T* src, int d, int c0, bool vec, ROW src_row, FIX fix) {
+  const int q = cols >> 2, n = rows * q, nt = (int)blockDim.x;
+  for (int e0 = threadIdx.x; e0 < n; e0 += 8 * nt) {
+    float4 v[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      const int e = e0 + t * nt, i = e / q, c = (e - i * q) * 4;
+      const int r = e < n ? src_row(i) : -1;
+      v[t] = r >= 0 && r < d && c0 + c < d ? small_load4<T>(src, d, r, c0 + c, vec) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    }
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      const int e = e0 + t * nt, i = e / q, c = (e - i * q) * 4;
+      if (e < n)
+        *reinterpret_cast<float4*>(dst + i * kSmallLd + c) = make_float4(fix(v[t].x, i, c), fix(v[t].y, i, c + 1), fix(v[t].z, i, c + 2), fix(v[t].w, i, c + 3));
+    }
+  }
+}
+
+// c += the 32 x 32 product over k = k0 .. k1 - 1 (multiples of 8): a(h, k, t), b(h, k, t) give this lane's operand for the k's
+// k + 4 h + t, h = lane / 32 (the low lanes' k is paired with the high lanes' in one MFMA; both operands use the same pairing).
+// Two partial sums: half the roundings at the size of the whole, and two MFMA chains in flight.
+template <typename A, typename B>
+__device__ __forceinline__ void small_mma(floatx16& c, int k0, int k1, A a, B b) {
+  floatx16 c2 = {};
+#pragma unroll 2
+  for (int k = k0; k < k1; k += 8) {
+    float av[4], bv[4];
+    a(k, av);
+    b(k, bv);
+#pragma unroll
+    for (int t = 0; t < 4; t += 2) {
+      c = __builtin_amdgcn_mfma_f32_32x32x2f32(av[t], bv[t], c, 0, 0, 0);
+      c2 = __builtin_amdgcn_mfma_f32_32x32x2f32(av[t + 1], bv[t + 1], c2, 0, 0, 0);
+    }
+  }
+  c += c2;
+}
+// element e of a lane's accumulator: row 8 (e / 4) + 4 (lane / 32) + e % 4, column lane % 32
+__device__ __forceinline__ int small_row(int lane, int e) { return (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3); }
+// operands in LDS: four k's of one row, or one column of four rows
+__device__ __forceinline__ void small_row4(const float* p, float (&v)[4]) {
+  const float4 f = *reinterpret_cast<const float4*>(p);
+  v[0] = f.x; v[1] = f.y; v[2] = f.z; v[3] = f.w;
+}
+__device__ __forceinline__ void small_col4(const float* p, float (&v)[4]) {
+#pragma unroll
+  for (int t = 0; t < 4; ++t) v[t] = p[t * kSmallLd];
+}
+
+// out[r][j] = sum_k L[perm[r]][k] (U + diag s)[k][j]: workgroup (m, rb) has rows 32 rb .. of matrix m, wavefront j columns 32 j ..
 template <typename T>
 __global__ __launch_bounds__(256) void k_lu_small_compose(const float* __restrict__ lp, const float* __restrict__ up, const float* __restrict__ log_s,
                                                           const float* __restrict__ sign_s, const int* __restrict__ perm, int d, T* __restrict__ out) {
-  __shared__ float lm[128][129];
-  __shared__ float um[128][129];
-  const int m = blockIdx.x, tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
+  __shared__ __attribute__((aligned(16))) float lm[32 * kSmallLd];
+  __shared__ __attribute__((aligned(16))) float um[128 * kSmallLd];
+  __shared__ int pr[32];
+  __shared__ float dg[128];
+  const int nb = (d + 31) >> 5, dp = nb * 32, m = blockIdx.x / nb, rb = blockIdx.x - m * nb, tid = threadIdx.x;
   const LuSrc q = small_src(lp, up, log_s, sign_s, d, m);
-  for (int e = tid; e < d * d; e += 256) {
-    const int i = e / d, j = e - i * d;
-    lm[i][j] = tri_elem<0>(q, i, j);
-    um[j][i] = tri_elem<1>(q, i, j);                   // tri_elem<1> is (U + diag s)^T
-  }
+  if (tid < 32) pr[tid] = rb * 32 + tid < d ? small_perm(perm + (int64_t)m * d, d, rb * 32 + tid) : -1;
+  if (tid < d) dg[tid] = q.sign[tid] * expf(q.log_s[tid]);
   __syncthreads();
-  int pr[8];
+  small_stage<float>(lm, 32, dp, q.lp, d, 0, small_vec(q.lp, d), [&](int i) { return pr[i]; },
+                     [&](float v, int i, int c) { return c < pr[i] ? v : (c == pr[i] ? 1.0f : 0.0f); });
+  small_stage<float>(um, dp, dp, q.up, d, 0, small_vec(q.up, d), [](int i) { return i; },
+                     [&](float v, int i, int c) { return c > i ? v : (c == i && i < d ? dg[i] : 0.0f); });
+  __syncthreads();
+  const int j = tid >> 6, lane = tid & 63, col = j * 32 + (lane & 31), h = lane >> 5;
+  if (j >= nb) return;
+  floatx16 acc = {};
+  // (below 64 the few terms of a sum come out closer to float64 when they are added one by one with fused multiply-adds:
+  // 2-norm 3.9e-8 against 4.3e-8 at d = 24, but 6.1e-8 against 5.6e-8 at d = 128)
+  if (d < 64) {
+    for (int k = 0; k < 32 * (j + 1); ++k) {
+      const float b = um[k * kSmallLd + col];
 #pragma unroll
-  for (int a = 0; a < 8; ++a) pr[a] = ty + 16 * a < d ? small_perm(perm + (int64_t)m * d, d, ty + 16 * a) : 0;
-  float acc[8][8];
-#pragma unroll
-  for (int a = 0; a < 8; ++a)
-#pragma unroll
-    for (int b = 0; b < 8; ++b) acc[a][b] = 0.0f;
-  for (int k = 0; k < d; ++k) {
-    float av[8], bv[8];
-#pragma unroll
-    for (int a = 0; a < 8; ++a) av[a] = ty + 16 * a < d ? lm[pr[a]][k] : 0.0f;
-#pragma unroll
-    for (int b = 0; b < 8; ++b) bv[b] = tx + 16 * b < d ? um[k][tx + 16 * b] : 0.0f;
-#pragma unroll
-    for (int a = 0; a < 8; ++a)
-#pragma unroll
-      for (int b = 0; b < 8; ++b) acc[a][b] = fmaf(av[a], bv[b], acc[a][b]);
-  }
+      for (int e = 0; e < 16; ++e) acc[e] = fmaf(lm[small_row(lane, e) * kSmallLd + k], b, acc[e]);
+    }
+  } else
+    small_mma(acc, 0, 32 * (j + 1), [&](int k, float (&v)[4]) { small_row4(lm + (lane & 31) * kSmallLd + k + 4 * h, v); },
+            [&](int k, float (&v)[4]) { small_col4(um + (k + 4 * h) * kSmallLd + col, v); });
   T* o = out + (int64_t)m * d * d;
 #pragma unroll
-  for (int a = 0; a < 8; ++a)
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      const int r = ty + 16 * a, j = tx + 16 * b;
-      if (r < d && j < d) Store<T>::st(o + (int64_t)r * d + j, acc[a][b]);
-    }
+  for (int e = 0; e < 16; ++e) {
+    const int r = rb * 32 + small_row(lane, e);
+    if (r < d && col < d) Store<T>::st(o + (int64_t)r * d + col, acc[e]);
+  }
 }
 
-// B = P^T G (B[perm[i]] = G[i]);  d_up = strictly upper part of L^T B, d_log_s = its diagonal times s,
-// d_lp = strictly lower part of B (U + diag s)^T
+// B = P^T G (B[perm[i]] = G[i], zero rows where perm names none);  d_up = strictly upper part of L^T B, d_log_s = its diagonal
+// times s, d_lp = strictly lower part of B (U + diag s)^T.  Workgroup (m, w): w < nb rows 32 w .. of the first product, else rows
+// 32 (w - nb) .. of the second; wavefront j columns 32 j ..
 template <typename T>
 __global__ __launch_bounds__(256) void k_lu_small_backward(const T* __restrict__ g, const float* __restrict__ lp, const float* __restrict__ up,
                                                            const float* __restrict__ log_s, const float* __restrict__ sign_s, const int* __restrict__ perm,
                                                            int d, float* __restrict__ d_lp, float* __restrict__ d_up, float* __restrict__ d_log_s) {
-  __shared__ float bm[128][129];
-  __shared__ float fm[128][129];
-  const int m = blockIdx.x, tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
+  __shared__ __attribute__((aligned(16))) float thin[128 * kSmallLd];   // 32 columns of L, or 32 rows of B
+  __shared__ __attribute__((aligned(16))) float wide[128 * kSmallLd];   // B, or U + diag s
+  __shared__ int inv[128];
+  __shared__ float dg[128];
+  const int nb = (d + 31) >> 5, dp = nb * 32, m = blockIdx.x / (2 * nb), w = blockIdx.x - m * 2 * nb, tid = threadIdx.x;
   const int64_t mo = (int64_t)m * d * d, vo = (int64_t)m * d;
   const LuSrc q = small_src(lp, up, log_s, sign_s, d, m);
-  for (int e = tid; e < d * d; e += 256) {
-    const int i = e / d, j = e - i * d;
-    bm[i][j] = 0.0f;                                   // (rows that a perm with duplicates never names)
-    fm[i][j] = tri_elem<0>(q, i, j);
-  }
+  if (tid < 128) inv[tid] = -1;
+  if (tid < d) dg[tid] = q.sign[tid] * expf(q.log_s[tid]);
   __syncthreads();
-  for (int e = tid; e < d * d; e += 256) {
-    const int i = e / d, j = e - i * d;
-    bm[small_perm(perm + vo, d, i)][j] = Store<T>::ld(g + mo + e);
-  }
+  if (tid < d) inv[small_perm(perm + vo, d, tid)] = tid;
   __syncthreads();
-  float acc[8][8];
+  const int j = tid >> 6, lane = tid & 63, col = j * 32 + (lane & 31), h = lane >> 5;
+  floatx16 acc = {};
+  if (w < nb) {
+    const int r0 = w * 32;                               // (L^T B)[k][n] = sum over i >= k of L[i][k] B[i][n], n >= k
+    small_stage<float>(thin, dp - r0, 32, q.lp, d, r0, small_vec(q.lp, d), [&](int i) { return r0 + i; },
+                       [&](float v, int i, int c) { return c < i ? v : (c == i && r0 + i < d ? 1.0f : 0.0f); });
+    small_stage<T>(wide, dp - r0, dp - r0, g + mo, d, r0, small_vec(g + mo, d), [&](int i) { return inv[r0 + i]; }, [](float v, int, int) { return v; });
+    __syncthreads();
+    if (j >= nb) return;
+    if (j >= w)
+      small_mma(acc, 0, dp - r0, [&](int k, float (&v)[4]) { small_col4(thin + (k + 4 * h) * kSmallLd + (lane & 31), v); },
+                [&](int k, float (&v)[4]) { small_col4(wide + (k + 4 * h) * kSmallLd + col - r0, v); });
 #pragma unroll
-  for (int a = 0; a < 8; ++a)
-#pragma unroll
-    for (int b = 0; b < 8; ++b) acc[a][b] = 0.0f;
-  for (int i = 0; i < d; ++i) {                        // (L^T B)[k][n] = sum_i L[i][k] B[i][n]
-    float av[8], bv[8];
-#pragma unroll
-    for (int a = 0; a < 8; ++a) av[a] = ty + 16 * a < d ? fm[i][ty + 16 * a] : 0.0f;
-#pragma unroll
-    for (int b = 0; b < 8; ++b) bv[b] = tx + 16 * b < d ? bm[i][tx + 16 * b] : 0.0f;
-#pragma unroll
-    for (int a = 0; a < 8; ++a)
-#pragma unroll
-      for (int b = 0; b < 8; ++b) acc[a][b] = fmaf(av[a], bv[b], acc[a][b]);
-  }
-#pragma unroll
-  for (int a = 0; a < 8; ++a)
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      const int k = ty + 16 * a, n = tx + 16 * b;
-      if (k < d && n < d) {
-        d_up[mo + (int64_t)k * d + n] = n > k ? acc[a][b] : 0.0f;
-        if (n == k) d_log_s[vo + k] = acc[a][b] * (q.sign[k] * expf(q.log_s[k]));
+    for (int e = 0; e < 16; ++e) {
+      const int k = r0 + small_row(lane, e);
+      if (k < d && col < d) {
+        d_up[mo + (int64_t)k * d + col] = col > k ? acc[e] : 0.0f;
+        if (col == k) d_log_s[vo + k] = acc[e] * dg[k];
       }
-      acc[a][b] = 0.0f;
     }
-  __syncthreads();
-  for (int e = tid; e < d * d; e += 256) {
-    const int i = e / d, j = e - i * d;
-    fm[j][i] = tri_elem<1>(q, i, j);                   // fm = U + diag s
+    return;
   }
+  const int r0 = (w - nb) * 32;                          // (B (U + diag s)^T)[r][k] = sum over n >= k of B[r][n] (U + diag s)[k][n], k < r
+  small_stage<T>(thin, 32, dp, g + mo, d, 0, small_vec(g + mo, d), [&](int i) { return r0 + i < d ? inv[r0 + i] : -1; }, [](float v, int, int) { return v; });
+  small_stage<float>(wide, r0 + 32, dp, q.up, d, 0, small_vec(q.up, d), [](int i) { return i; },
+                     [&](float v, int i, int c) { return c > i ? v : (c == i && i < d ? dg[i] : 0.0f); });
   __syncthreads();
-  for (int n = 0; n < d; ++n) {                        // (B (U + diag s)^T)[r][k] = sum_n B[r][n] (U + diag s)[k][n]
-    float av[8], bv[8];
+  if (j >= nb) return;
+  if (col - (lane & 31) <= r0)
+    small_mma(acc, j * 32, dp, [&](int k, float (&v)[4]) { small_row4(thin + (lane & 31) * kSmallLd + k + 4 * h, v); },
+              [&](int k, float (&v)[4]) { small_row4(wide + col * kSmallLd + k + 4 * h, v); });
 #pragma unroll
-    for (int a = 0; a < 8; ++a) av[a] = ty + 16 * a < d ? bm[ty + 16 * a][n] : 0.0f;
-#pragma unroll
-    for (int b = 0; b < 8; ++b) bv[b] = tx + 16 * b < d ? fm[tx + 16 * b][n] : 0.0f;
-#pragma unroll
-    for (int a = 0; a < 8; ++a)
-#pragma unroll
-      for (int b = 0; b < 8; ++b) acc[a][b] = fmaf(av[a], bv[b], acc[a][b]);
+  for (int e = 0; e < 16; ++e) {
+    const int r = r0 + small_row(lane, e);
+    if (r < d && col < d) d_lp[mo + (int64_t)r * d + col] = col < r ? acc[e] : 0.0f;
   }
-#pragma unroll
-  for (int a = 0; a < 8; ++a)
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      const int r = ty + 16 * a, k = tx + 16 * b;
-      if (r < d && k < d) d_lp[mo + (int64_t)r * d + k] = k < r ? acc[a][b] : 0.0f;
-    }
 }
 
-// out[i][c] = ((U + diag s)^-1 L^-1)[i][perm[c]]: both factors inverted by the in-LDS recursion (padded to 128 with an
-// identity block), L^-1 parked in registers while (U + diag s)^T is inverted
+// Both triangular factors of one matrix in LDS at once, inverted in place by four wavefronts each: entry (i, j), j <= i, of L is
+// p[129 i + j], of (U + diag s)^T p[129 j + i + 1] — U as it lies in memory, one column to the right.
+struct SmallTri {
+  float* p;
+  int si, sj;                     // strides of i and j
+  __device__ __forceinline__ float& at(int i, int j) const { return p[i * si + j * sj]; }
+};
+
+// one merge level (as tri128_merge) of one factor in place: X21 = -X22 (M21 X11) over M21; 256 threads (tid), tb: 64 * 68
+// floats.  Blocks of 16 on the vector ALUs; blocks of 32 and 64 on the matrix cores, a wavefront per 32 x 32 tile.
+__device__ __forceinline__ void small_tri_merge16(const SmallTri& x, float* tb, int tid) {
+  const int pr = tid >> 6, t = tid & 63, tr = t >> 3, tc = t & 7, o0 = 32 * pr, o1 = o0 + 16;
+  float* tp = tb + pr * 256;
+  float acc[2][2] = {};
+#pragma unroll
+  for (int k = 0; k < 16; ++k)                         // T = M21 X11:  X11[k][c] = 0 for k < c
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const float v = k >= tc + 8 * j ? x.at(o0 + k, o0 + tc + 8 * j) : 0.0f;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) acc[i][j] = fmaf(x.at(o1 + tr + 8 * i, o0 + k), v, acc[i][j]);
+    }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      tp[(tr + 8 * i) * 16 + tc + 8 * j] = acc[i][j];
+      acc[i][j] = 0.0f;
+    }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 16; ++k)                         // X21 = -X22 T:  X22[r][k] = 0 for k > r
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const float a = k <= tr + 8 * i ? x.at(o1 + tr + 8 * i, o1 + k) : 0.0f;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[i][j] = fmaf(a, tp[k * 16 + tc + 8 * j], acc[i][j]);
+    }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) x.at(o1 + tr + 8 * i, o0 + tc + 8 * j) = -acc[i][j];   // (M21 was last read before the barrier)
+  __syncthreads();
+}
+template <int B>
+__device__ __forceinline__ void small_tri_merge(const SmallTri& x, float* tb, int tid) {
+  constexpr int N = B / 32, LT = B + 4;                // tiles per side; row length of T
+  const int w = tid >> 6, lane = tid & 63, h = lane >> 5, pr = w / (N * N), ti = (w / N) % N, tj = w % N;
+  const int o0 = 2 * pr * B, o1 = o0 + B, r = ti * 32 + (lane & 31), c = tj * 32 + (lane & 31);
+  float* tp = tb + (pr & 1) * (B * LT);
+  const bool on = o1 < 128;
+  floatx16 acc = {};
+  if (on) {
+    small_mma(acc, tj * 32, B,                         // T = M21 X11:  X11[k][c] = 0 for k < c
+              [&](int k, float (&v)[4]) {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) v[t] = x.at(o1 + r, o0 + k + 4 * h + t);
+              },
+              [&](int k, float (&v)[4]) {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) { const int kk = k + 4 * h + t; const float u = x.at(o0 + kk, o0 + c); v[t] = kk >= c ? u : 0.0f; }
+              });
+#pragma unroll
+    for (int e = 0; e < 16; ++e) tp[(ti * 32 + small_row(lane, e)) * LT + c] = acc[e];
+  }
+  __syncthreads();
+  if (on) {
+    acc = floatx16{};
+    small_mma(acc, 0, ti * 32 + 32,                    // X21 = -X22 T:  X22[r][k] = 0 for k > r
+              [&](int k, float (&v)[4]) {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) { const int kk = k + 4 * h + t; const float u = x.at(o1 + r, o1 + kk); v[t] = kk <= r ? u : 0.0f; }
+              },
+              [&](int k, float (&v)[4]) {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) v[t] = tp[(k + 4 * h + t) * LT + c];
+              });
+#pragma unroll
+    for (int e = 0; e < 16; ++e) x.at(o1 + ti * 32 + small_row(lane, e), o0 + c) = -acc[e];   // (M21 was last read before the barrier)
+  }
+  __syncthreads();
+}
+
+// out[i][c] = ((U + diag s)^-1 L^-1)[i][perm[c]]: one workgroup of eight wavefronts per matrix, both factors inverted side by side
+// (16 x 16 diagonal blocks by substitution, a column per thread in registers, then merges), padded to 128 with an identity
+// block; the product on the matrix cores, a wavefront has the tiles (h, j) and (3 - h, j) of equal total K.
 template <typename T>
-__global__ __launch_bounds__(256) void k_lu_small_inverse(const float* __restrict__ lp, const float* __restrict__ up, const float* __restrict__ log_s,
+__global__ __launch_bounds__(512) void k_lu_small_inverse(const float* __restrict__ lp, const float* __restrict__ up, const float* __restrict__ log_s,
                                                           const float* __restrict__ sign_s, const int* __restrict__ perm, int d, T* __restrict__ out) {
-  __shared__ float mb[128][129];
-  __shared__ float xb[128][129];
-  __shared__ float tb[64 * 64];
-  const int m = blockIdx.x, tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
+  __shared__ float pk[128 * 129];
+  __shared__ float tb[2][64 * 68];
+  __shared__ int pc[128];
+  const int m = blockIdx.x, tid = threadIdx.x;
   const LuSrc q = small_src(lp, up, log_s, sign_s, d, m);
-  for (int e = tid; e < 128 * 128; e += 256) {
-    const int i = e >> 7, j = e & 127;
-    mb[i][j] = tri_elem<0>(q, i, j);
-    xb[i][j] = 0.0f;
+  if (tid < 128) pc[tid] = tid < d ? small_perm(perm + (int64_t)m * d, d, tid) : tid;
+  const bool vl = small_vec(q.lp, d), vu = small_vec(q.up, d);
+#pragma unroll
+  for (int b0 = 0; b0 < 8; b0 += 4) {                    // 128 x 32 chunks of four columns: eight per thread, four of each factor in flight
+    float4 l[4], u[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int e = tid + (b0 + t) * 512, i = e >> 5, c = (e & 31) * 4;
+      const bool in = i < d && c < d;
+      l[t] = in && c < i ? small_load4<float>(q.lp, d, i, c, vl) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      u[t] = in && c + 3 > i ? small_load4<float>(q.up, d, i, c, vu) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int e = tid + (b0 + t) * 512, i = e >> 5, c = (e & 31) * 4;
+      const float lv[4] = {l[t].x, l[t].y, l[t].z, l[t].w}, uv[4] = {u[t].x, u[t].y, u[t].z, u[t].w};
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        if (c + s < i) pk[i * 129 + c + s] = lv[s];
+        else if (c + s > i) pk[i * 129 + c + s + 1] = uv[s];
+      }
+    }
+  }
+  if (tid < 128) {
+    pk[tid * 129 + tid] = 1.0f;
+    pk[tid * 129 + tid + 1] = tid < d ? q.sign[tid] * expf(q.log_s[tid]) : 1.0f;
   }
   __syncthreads();
-  tri128_inverse_lds(mb, xb, tb, tid);
-  float keep[64];                                      // L^-1, element tid + 256 e
+  const int f = tid >> 8, ft = tid & 255;
+  const SmallTri x = f == 0 ? SmallTri{pk, 129, 1} : SmallTri{pk + 1, 1, 129};
+  float col[16];
+  const int b0 = ft & ~15, jj = ft & 15;
+  if (ft < 128) {                                        // column jj of the 16 x 16 diagonal block at b0
 #pragma unroll
-  for (int e = 0; e < 64; ++e) keep[e] = xb[(tid + 256 * e) >> 7][(tid + 256 * e) & 127];
-  __syncthreads();
-  for (int e = tid; e < 128 * 128; e += 256) {
-    const int i = e >> 7, j = e & 127;
-    mb[i][j] = tri_elem<1>(q, i, j);
-    xb[i][j] = 0.0f;
+    for (int i = 0; i < 16; ++i) {
+      float acc = 0.0f;
+#pragma unroll
+      for (int k = 0; k < i; ++k) acc = fmaf(x.at(b0 + i, b0 + k), col[k], acc);
+      const float dv = x.at(b0 + i, b0 + i);
+      col[i] = i < jj ? 0.0f : (i == jj ? 1.0f / dv : -acc / dv);
+    }
   }
   __syncthreads();
-  tri128_inverse_lds(mb, xb, tb, tid);                 // xb = ((U + diag s)^T)^-1 = ((U + diag s)^-1)^T
+  if (ft < 128) {
 #pragma unroll
-  for (int e = 0; e < 64; ++e) mb[(tid + 256 * e) >> 7][(tid + 256 * e) & 127] = keep[e];
-  __syncthreads();
-  int pc[8];
-#pragma unroll
-  for (int b = 0; b < 8; ++b) pc[b] = tx + 16 * b < d ? small_perm(perm + (int64_t)m * d, d, tx + 16 * b) : 0;
-  float acc[8][8];
-#pragma unroll
-  for (int a = 0; a < 8; ++a)
-#pragma unroll
-    for (int b = 0; b < 8; ++b) acc[a][b] = 0.0f;
-  for (int k = 0; k < d; ++k) {                        // sum_k (U + diag s)^-1[i][k] L^-1[k][j]
-    float av[8], bv[8];
-#pragma unroll
-    for (int a = 0; a < 8; ++a) av[a] = xb[k][ty + 16 * a];
-#pragma unroll
-    for (int b = 0; b < 8; ++b) bv[b] = mb[k][pc[b]];
-#pragma unroll
-    for (int a = 0; a < 8; ++a)
-#pragma unroll
-      for (int b = 0; b < 8; ++b) acc[a][b] = fmaf(av[a], bv[b], acc[a][b]);
+    for (int i = 0; i < 16; ++i)
+      if (i >= jj) x.at(b0 + i, b0 + jj) = col[i];
   }
+  __syncthreads();
+  // (a level whose lower blocks are all padding leaves zeros as they are)
+  if (d > 16) small_tri_merge16(x, tb[f], ft);
+  if (d > 32) small_tri_merge<32>(x, tb[f], ft);
+  if (d > 64) small_tri_merge<64>(x, tb[f], ft);
+  const int nb = (d + 31) >> 5, dp = nb * 32, wave = tid >> 6, lane = tid & 63, h = lane >> 5, j = wave & 3;
+  const int c = j * 32 + (lane & 31), src = pc[c];
+  if (j >= nb) return;
   T* o = out + (int64_t)m * d * d;
 #pragma unroll
-  for (int a = 0; a < 8; ++a)
+  for (int half = 0; half < 2; ++half) {
+    const int ti = half == 0 ? wave >> 2 : 3 - (wave >> 2);
+    if (ti >= nb) continue;
+    const int i = ti * 32 + (lane & 31);
+    floatx16 acc = {};
+    small_mma(acc, ti * 32, dp,                          // sum over k >= i, k >= perm[c]
+              [&](int k, float (&v)[4]) {
 #pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      const int i = ty + 16 * a, c = tx + 16 * b;
-      if (i < d && c < d) Store<T>::st(o + (int64_t)i * d + c, acc[a][b]);
+                for (int t = 0; t < 4; ++t) { const int kk = k + 4 * h + t; const float w = pk[i * 129 + kk + 1]; v[t] = kk >= i ? w : 0.0f; }
+              },
+              [&](int k, float (&v)[4]) {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) { const int kk = k + 4 * h + t; const float w = pk[kk * 129 + src]; v[t] = kk >= src ? w : 0.0f; }
+              });
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int r = ti * 32 + small_row(lane, e);
+      if (r < d && c < d) Store<T>::st(o + (int64_t)r * d + c, acc[e]);
     }
+  }
 }
 
 // out[r][c] = z[r][perm[c]] in the storage type (z P^T); z has rows of dp entries, out is d x d
@@ -856,8 +1022,9 @@ extern "C" int model_lu_compose_batch(const float* lp, const float* up, const fl
   if (!lp || !up || !log_s || !sign_s || !perm || !a_out) return fail(AE_EINVAL, "model_lu_compose_batch: null argument");
   AE_TRY(check_small_batch("model_lu_compose_batch", count, d, dtype));
   hipStream_t s = (hipStream_t)stream;
-  if (dtype == AE_BF16) hipLaunchKernelGGL((k_lu_small_compose<bf16_t>), dim3((unsigned)count), dim3(256), 0, s, lp, up, log_s, sign_s, perm, (int)d, (bf16_t*)a_out);
-  else hipLaunchKernelGGL((k_lu_small_compose<float>), dim3((unsigned)count), dim3(256), 0, s, lp, up, log_s, sign_s, perm, (int)d, (float*)a_out);
+  const dim3 grid((unsigned)(count * ((d + 31) / 32)));
+  if (dtype == AE_BF16) hipLaunchKernelGGL((k_lu_small_compose<bf16_t>), grid, dim3(256), 0, s, lp, up, log_s, sign_s, perm, (int)d, (bf16_t*)a_out);
+  else hipLaunchKernelGGL((k_lu_small_compose<float>), grid, dim3(256), 0, s, lp, up, log_s, sign_s, perm, (int)d, (float*)a_out);
   return launch_status("lu_small_compose");
 }
 
@@ -868,8 +1035,9 @@ extern "C" int model_lu_backward_batch(const void* g, const float* lp, const flo
   if (!g || !lp || !up || !log_s || !sign_s || !perm || !d_lp || !d_up || !d_log_s) return fail(AE_EINVAL, "model_lu_backward_batch: null argument");
   AE_TRY(check_small_batch("model_lu_backward_batch", count, d, dtype));
   hipStream_t s = (hipStream_t)stream;
-  if (dtype == AE_BF16) hipLaunchKernelGGL((k_lu_small_backward<bf16_t>), dim3((unsigned)count), dim3(256), 0, s, (const bf16_t*)g, lp, up, log_s, sign_s, perm, (int)d, d_lp, d_up, d_log_s);
-  else hipLaunchKernelGGL((k_lu_small_backward<float>), dim3((unsigned)count), dim3(256), 0, s, (const float*)g, lp, up, log_s, sign_s, perm, (int)d, d_lp, d_up, d_log_s);
+  const dim3 grid((unsigned)(count * 2 * ((d + 31) / 32)));
+  if (dtype == AE_BF16) hipLaunchKernelGGL((k_lu_small_backward<bf16_t>), grid, dim3(256), 0, s, (const bf16_t*)g, lp, up, log_s, sign_s, perm, (int)d, d_lp, d_up, d_log_s);
+  else hipLaunchKernelGGL((k_lu_small_backward<float>), grid, dim3(256), 0, s, (const float*)g, lp, up, log_s, sign_s, perm, (int)d, d_lp, d_up, d_log_s);
   return launch_status("lu_small_backward");
 }
 
@@ -879,8 +1047,8 @@ extern "C" int model_lu_inverse_batch(const float* lp, const float* up, const fl
   if (!lp || !up || !log_s || !sign_s || !perm || !a_inv_out) return fail(AE_EINVAL, "model_lu_inverse_batch: null argument");
   AE_TRY(check_small_batch("model_lu_inverse_batch", count, d, dtype));
   hipStream_t s = (hipStream_t)stream;
-  if (dtype == AE_BF16) hipLaunchKernelGGL((k_lu_small_inverse<bf16_t>), dim3((unsigned)count), dim3(256), 0, s, lp, up, log_s, sign_s, perm, (int)d, (bf16_t*)a_inv_out);
-  else hipLaunchKernelGGL((k_lu_small_inverse<float>), dim3((unsigned)count), dim3(256), 0, s, lp, up, log_s, sign_s, perm, (int)d, (float*)a_inv_out);
+  if (dtype == AE_BF16) hipLaunchKernelGGL((k_lu_small_inverse<bf16_t>), dim3((unsigned)count), dim3(512), 0, s, lp, up, log_s, sign_s, perm, (int)d, (bf16_t*)a_inv_out);
+  else hipLaunchKernelGGL((k_lu_small_inverse<float>), dim3((unsigned)count), dim3(512), 0, s, lp, up, log_s, sign_s, perm, (int)d, (float*)a_inv_out);
   return launch_status("lu_small_inverse");
 }
 

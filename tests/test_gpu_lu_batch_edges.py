@@ -1,0 +1,50 @@
+"""The batched small-matrix calls at sizes around a 32-wide tile, a 16-wide block of the inversion and the wide loads (d no
+multiple of four, matrices that start off a 16-byte border), with a permutation that names a row twice and one out of range."""
+import pytest
+import torch
+
+from paper_2602_17681_amd import binding as ae
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("count,d", [(1, 1), (3, 2), (2, 15), (2, 17), (3, 31), (2, 33), (2, 47), (5, 63), (2, 65), (3, 96), (2, 97), (300, 128)])
+def test_sizes(count, d, dtype):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    rnd = lambda *s: torch.randn(*s, device="cuda", generator=g)      # noqa: E731
+    td = {"f32": torch.float32, "bf16": torch.bfloat16}[dtype]
+    lp, up, ls = rnd(count, d, d) * d ** -0.5, rnd(count, d, d) * d ** -0.5, 0.3 * rnd(count, d)
+    sign = torch.where(rnd(count, d) < 0, -1.0, 1.0)
+    perm = torch.argsort(torch.rand(count, d, device="cuda", generator=g), dim=1).to(torch.int32)
+    if d > 4:
+        perm[-1, 3] = d                       # out of range: read as 3, which another entry names too
+    gr = rnd(count, d, d).to(td)
+    a, ai = torch.empty(count, d, d, device="cuda", dtype=td), torch.empty(count, d, d, device="cuda", dtype=td)
+    dlp, dup, dls = torch.empty(count, d, d, device="cuda"), torch.empty(count, d, d, device="cuda"), torch.empty(count, d, device="cuda")
+    ae.model_lu_compose_batch(lp, up, ls, sign, perm, count, d, a)
+    ae.model_lu_backward_batch(gr, lp, up, ls, sign, perm, count, d, dlp, dup, dls)
+    ae.model_lu_inverse_batch(lp, up, ls, sign, perm, count, d, ai)
+    p = perm.long()
+    p = torch.where(p < d, p, torch.arange(d, device="cuda"))
+    s = sign.double() * ls.double().exp()
+    L = torch.tril(lp.double(), -1) + torch.eye(d, device="cuda", dtype=torch.float64)
+    U = torch.triu(up.double(), 1) + torch.diag_embed(s)
+    A = torch.stack([(L[i] @ U[i])[p[i]] for i in range(count)])
+    inv = torch.linalg.inv(L @ U)
+    Ai = torch.stack([inv[i][:, p[i]] for i in range(count)])
+    # K <= 128 terms in binary32, once rounded to the storage type; the inverse goes through the growth of two triangles
+    tol = 3e-7 if dtype == "f32" else 3e-3
+    rel = lambda x, r: ((x.double() - r).norm() / r.norm().clamp_min(1e-300)).item()      # noqa: E731
+    assert rel(a, A) <= tol and rel(ai, Ai) <= 4 * tol, (rel(a, A), rel(ai, Ai))
+    ok = count if d <= 4 else count - 1       # (which of two rows with the same name wins is not defined)
+    B = torch.zeros_like(L)
+    for i in range(ok):
+        B[i][p[i]] = gr[i].double()
+    dU, dL = L.transpose(1, 2).contiguous() @ B, B @ U.transpose(1, 2).contiguous()
+    if ok:
+        assert rel(dls[:ok], torch.diagonal(dU, dim1=1, dim2=2)[:ok] * s[:ok]) <= 5e-7
+    if ok and d > 1:
+        assert rel(dup[:ok], torch.triu(dU, 1)[:ok]) <= 5e-7 and rel(dlp[:ok], torch.tril(dL, -1)[:ok]) <= 5e-7
+    assert torch.equal(dup, torch.triu(dup, 1)) and torch.equal(dlp, torch.tril(dlp, -1))
