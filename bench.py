@@ -107,7 +107,8 @@ def kernel_table(st, steps):
 
 
 FAMILY = {"conv_mfma": "k_igemm", "dgrad_mfma": "k_igemm", "conv_mfma_phases": "k_igemm", "dgrad_mfma_stride2": "k_igemm",
-          "wgrad_mfma": "k_wgrad", "wgrad_mfma_phases": "k_wgrad",
+          "wgrad_mfma": "k_wgrad", "wgrad_mfma_phases": "k_wgrad", "wgrad_chunks": "k_wgrad", "conv_chunks": "k_igemm",
+          "conv_chunks_phases": "k_igemm", "dgrad_chunks": "k_igemm", "dgrad_chunks_stride2": "k_igemm",
           "conv_thin_in_mfma": "k_thin_in_mfma", "dgrad_thin_mfma": "k_thin_in_mfma"}
 
 
@@ -115,7 +116,8 @@ FAMILY = {"conv_mfma": "k_igemm", "dgrad_mfma": "k_igemm", "conv_mfma_phases": "
 # convolution (input gradient) or sixteen phase-tap correlations (weight gradient): 4/9 of the multiply-adds of the
 # definition.  The library's slots carry the algorithmic FLOPs of the definition (2*M*N*K); the share below turns
 # them into the multiply-adds the kernels really perform (per-kernel `tflops` in the line are executed rates).
-EXECUTED_SHARE = {"conv_mfma_phases": 4.0 / 9.0, "dgrad_mfma_stride2": 4.0 / 9.0, "wgrad_mfma_phases": 4.0 / 9.0}
+EXECUTED_SHARE = {"conv_mfma_phases": 4.0 / 9.0, "dgrad_mfma_stride2": 4.0 / 9.0, "wgrad_mfma_phases": 4.0 / 9.0,
+                  "conv_chunks_phases": 4.0 / 9.0, "dgrad_chunks_stride2": 4.0 / 9.0}
 
 
 _MEASURED = {}

@@ -233,6 +233,8 @@ int pack_all_beside(ae_model* m, const float* params, bool dgrad, hipStream_t s)
   m->pack_fc_pending = true;
   return AE_OK;
 }
+// must rows of c channels at p be copied before a kernel that reads whole aligned 16-byte chunks?
+bool chunk_copy(const Plan& P, const void* p, int c) { return chan_pad(c, P.dtype) != c || ((uintptr_t)p & 15) != 0; }
 // before the first kernel that reads a packed copy (big_fc: that of a big fully-connected layer)
 int join_pack(ae_model* m, hipStream_t s, bool big_fc = false) {
   if (m->pack_pending) {
@@ -281,7 +283,8 @@ int forward_conv(ae_model* m, int si, Step& st, const float* params, const void*
     }
     w = st.wpack;
   }
-  if (st.xpad && (st.chunks || !m->inference))     // kept until the weight gradient has read it
+  const bool pad_x = st.xpad && chunk_copy(P, in, st.cin);
+  if (pad_x && (st.chunks || !m->inference))     // kept until the weight gradient has read it
     TIMED(si, "fwd.pad_channels", 0.0, 2.0 * in_el * es,
           launch_pad_channels(in, st.xpad, (int64_t)P.batch * st.hin * st.win, st.cin, P.dtype, s));
   const bool second_pass = st.has_bn || st.pool;
@@ -347,7 +350,7 @@ int forward_conv(ae_model* m, int si, Step& st, const float* params, const void*
     // named apart, executes 4/9 of them)
     TIMED(si, st.up_phases ? "fwd.conv_mfma_phases" : "fwd.conv_mfma", conv_flops, conv_bytes, launch_conv_mfma(a, s));
   } else if (st.chunks) {
-    if (st.xpad) a.x = st.xpad;
+    if (pad_x) a.x = st.xpad;
     if (st.has_bn && P.bn_mode == 0 && !st.up_phases) {
       a.partial = m->partial;
       const int pr = plan_conv_chunks(a).bm;
@@ -471,11 +474,15 @@ int backward_conv(ae_model* m, int si, Step& st, const float* params, const void
   }
   // the conv-output gradient in whole chunks, where the kernels below want it; its buffer is guarded like the draw buffer beside it
   const void* dr_p = dr;
-  if ((st.chunks_d || st.chunks_w) && chan_pad(st.cout, P.dtype) != st.cout) {
+  if ((st.chunks_d || st.chunks_w) && chunk_copy(P, dr, st.cout)) {
     char* const buf = m->dypad[dr == m->draw ? m->draw_sel : 2];
     TIMED(si, "bwd.pad_channels", 0.0, 2.0 * raw_el * es, launch_pad_channels(dr, buf, rows, st.cout, P.dtype, s));
     dr_p = buf;
   }
+  const bool pad_x = st.chunks_w && st.xpad && chunk_copy(P, in, st.cin);
+  if (pad_x && si == 0)                          // (the caller's x of this call need not be where the forward pass found it)
+    TIMED(si, "bwd.pad_channels", 0.0, 2.0 * in_el * es,
+          launch_pad_channels(in, st.xpad, (int64_t)P.batch * st.hin * st.win, st.cin, P.dtype, s));
   // Fork: the weight gradient reads dr and the saved input.  When dr is one of the two
   // alternating buffers it may run beside the rest of the pass; a dr that is the incoming
   // gradient itself is overwritten by the very next layer, so that case stays in order.
@@ -574,7 +581,7 @@ int backward_conv(ae_model* m, int si, Step& st, const float* params, const void
   }
   // weight gradient
   WgradArgs wa;
-  wa.x = st.chunks_w && st.xpad ? st.xpad : in; wa.dy = st.chunks_w ? dr_p : dr; wa.dw_canonical = grads + st.w_off;
+  wa.x = pad_x ? st.xpad : in; wa.dy = st.chunks_w ? dr_p : dr; wa.dw_canonical = grads + st.w_off;
   wa.n = P.batch; wa.hc = st.hc; wa.wc = st.wc; wa.cin = st.cin; wa.cout = st.cout; wa.k = st.k; wa.up = st.up;
   wa.dtype = P.dtype;
   if (wgrad_mfma_supported(wa)) {

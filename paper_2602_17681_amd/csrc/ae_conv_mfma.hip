@@ -19,8 +19,9 @@
 //                  convolution for the input gradient; see IgemmParams)
 //                  and, with CHUNKS, any channel counts (a 16-byte chunk of K belongs to one tap; see there)
 //   k_wgrad_row3   weight gradient, three taps per workgroup from one input patch (bf16)
-//   k_wgrad_rows, k_wgrad   weight gradient, one tap per workgroup (fp32, 1x1, odd shapes)
-//   k_wgrad_chunks          weight gradient of any channel counts, columns (tap, ci) walked across tap borders
+//   k_wgrad_rows, k_wgrad   weight gradient, one tap per workgroup (1x1, odd shapes)
+//   k_wgrad_chunks          weight gradient of any channel counts, columns (tap, ci) walked across tap borders; binary32: k_wgrad_split
+//   k_gemm_split            binary32 products and convolutions by bf16 parts
 // The shared epilogue adds the bias, rounds to the storage type, optionally reduces per-channel
 // sum / sum of squares of the tile (batch-norm statistics), applies the activation and stores [M][N].
 #include "ae_device.h"
@@ -836,7 +837,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
 }
 
 // ---------------------------------------------------------------------------
-// Dense binary32 products (k = 1, one pixel per row) on the bf16 matrix cores.
+// Binary32 products and convolutions (CONV: the gather of k_igemm) on the bf16 matrix cores.
 //
 // Every value is cut into three bfloat16 parts on its way into LDS, x = h + m + l (each rounded to nearest, the remainders
 // exact: |m| <= 2^-8 |x|, |l| <= 2^-16 |x|, h + m + l = x), and a product is the six MFMAs hh + hm + mh + mm + hl + lh; what
@@ -846,7 +847,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
 // Measured at d = 4096: 0.63 ms = 218 TFLOP/s against 1.01 ms = 136 (87 % of the binary32 MFMA's rate), the matrix cores
 // busy two thirds of the cycles at the 1.8 GHz that the power limit leaves; errors at the rule in launch_conv_mfma.
 //
-// A workgroup is WGM x WGN wavefronts of 64 x 64 outputs.  Slabs of 16 k's are loaded into registers two slabs ahead, cut
+// A workgroup is WGM x WGN wavefronts of 64 x 64 outputs (32 x 64 where there are only 64 columns).  Slabs of 16 k's are loaded into registers two slabs ahead, cut
 // into parts between the MFMAs of the slab before (the split is a third of the VALU issue slots that the MFMAs leave)
 // and stored to the other of two LDS stages; one barrier per slab.  LDS: [stage][part][32-row block] of 1 KiB in fragment
 // order, chunk c (8 of the 16 k's) of row r at 512 c + (16 r ^ 128 c): a fragment read is 1 KiB in lane order, and the 8-byte
@@ -856,7 +857,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
 // (or a value within half a bf16 step of it), or an operand row whose largest magnitude is nonzero and below 2^-96,
 // computes its tile again with the binary32 MFMA.
 // ---------------------------------------------------------------------------
-template <int BM, int BN, int WGM, int WGN, bool INTERIOR, int EPI = 0>
+template <int BM, int BN, int WGM, int WGN, bool INTERIOR, int EPI = 0, bool CONV = false>
 __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_split(IgemmParams p) {
   constexpr int NT = WGM * WGN * 64;
   constexpr int WM = BM / WGM, WN = BN / WGN, MI = WM / 32, NJ = WN / 32;
@@ -879,17 +880,54 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
   const __amdgpu_buffer_rsrc_t rX = make_rsrc(p.x, p.x_bytes);
   const __amdgpu_buffer_rsrc_t rW = make_rsrc(p.w, p.w_bytes);
   const int lrow = tid >> 2, kq = tid & 3;
+  // GEMM row m of A: where its K-bytes start (dense), or its pixel (CONV: grid position, image; a slab lies in one tap)
+  struct Row { int h, w; unsigned img; };
+  const int pad_h = p.pad - (tile.phase >> 1), pad_w = p.pad - (tile.phase & 1);
+  auto row_of = [&](int64_t m) {
+    Row x = {0, 0, kOob};
+    if (m < p.M) {
+      if constexpr (CONV) {
+        const unsigned mu = (unsigned)m, t = mu / (unsigned)p.Wc, n = t / (unsigned)p.Hc;
+        x.w = (int)(mu - t * (unsigned)p.Wc);
+        x.h = (int)(t - n * (unsigned)p.Hc);
+        x.img = n * (unsigned)((p.Hv >> p.up) * (p.Wv >> p.up)) * (unsigned)p.Cin * 4u;
+      } else {
+        x.img = (unsigned)m * (unsigned)p.K * 4u;
+      }
+    }
+    return x;
+  };
+  auto tap_off = [&](const Row& x, int tap) {    // byte offset of the row's pixel under a tap (CONV)
+    const int r_ = tap / p.ksz, s_ = tap - r_ * p.ksz;
+    const int hh = x.h * p.stride + r_ - pad_h, ww = x.w * p.stride + s_ - pad_w;
+    const bool ok = x.img != kOob && hh >= 0 && hh < p.Hv && ww >= 0 && ww < p.Wv;
+    return ok ? x.img + (unsigned)((hh >> p.up) * (p.Wv >> p.up) + (ww >> p.up)) * (unsigned)p.Cin * 4u : kOob;
+  };
+  int tap = CONV ? kt0 * 16 / p.Cin : 0, ci = CONV ? kt0 * 16 - tap * p.Cin : kt0 * 16;   // of the next slab to load
   unsigned off[AC + BC];                         // byte offset of this lane's next 16 bytes of each row
+  Row ar[CONV ? AC : 1];
 #pragma unroll
   for (int i = 0; i < AC; ++i) {
-    const int64_t m = m0 + lrow + i * RSTEP;
-    off[i] = m < p.M ? (unsigned)m * (unsigned)p.K * 4u + (unsigned)(kt0 * 64 + kq * 16) : kOob;
+    const Row x = row_of(m0 + lrow + i * RSTEP);
+    if constexpr (CONV) ar[i] = x;
+    off[i] = (CONV ? tap_off(x, tap) : x.img) + (unsigned)(ci * 4 + kq * 16);      // (kOob plus a row's bytes stays out of range)
   }
 #pragma unroll
   for (int i = 0; i < BC; ++i) {
     const int n = n0 + lrow + i * RSTEP;
-    off[AC + i] = n < p.N ? (unsigned)n * (unsigned)p.K * 4u + (unsigned)(kt0 * 64 + kq * 16) : kOob;
+    off[AC + i] = n < p.N ? (unsigned)(tile.phase * p.N + n) * (unsigned)p.K * 4u + (unsigned)(kt0 * 64 + kq * 16) : kOob;
   }
+  auto next_slab = [&]() {                       // CONV: behind the loads of a slab
+    if constexpr (CONV) {
+      ci += 16;
+      if (ci == p.Cin) {
+        ci = 0;
+        ++tap;
+#pragma unroll
+        for (int i = 0; i < AC; ++i) off[i] = tap_off(ar[i], tap) + (unsigned)(kq * 16);
+      }
+    }
+  };
   uint4v r[AC + BC];
   float mx[AC + BC];
 #pragma unroll
@@ -945,8 +983,10 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
   };
 #pragma unroll
   for (int i = 0; i < AC + BC; ++i) load(i);
+  next_slab();
 #pragma unroll
   for (int i = 0; i < AC + BC; ++i) { split(0, i); load(i); }
+  next_slab();
   __syncthreads();
   read_b(0, 0); read_a(0, 0);
   int cur = 0, nxt = STAGE;
@@ -983,6 +1023,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
       for (int j = 0; j < NJ; ++j) mma_step<bf16_t>(a[2][i], b2[j], low[i][j]);
     __builtin_amdgcn_sched_barrier(0);
+    next_slab();
     cur = nxt;
     nxt = nxt == 2 * STAGE ? 0 : nxt + STAGE;
   }
@@ -999,23 +1040,23 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
   }
   if (__syncthreads_or(odd) != 0) {
     // fragments straight from global memory: lane l holds four k's of row l % 32, the same ones on both sides
-    unsigned fo[MI + NJ];
-#pragma unroll
-    for (int i = 0; i < MI; ++i) {
-      const int64_t m = m0 + wm * WM + i * 32 + (lane & 31);
-      fo[i] = m < p.M ? (unsigned)m * (unsigned)p.K * 4u + (unsigned)(kt0 * 64 + (lane >> 5) * 16) : kOob;
-    }
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      const int n = n0 + wn * WN + j * 32 + (lane & 31);
-      fo[MI + j] = n < p.N ? (unsigned)n * (unsigned)p.K * 4u + (unsigned)(kt0 * 64 + (lane >> 5) * 16) : kOob;
-    }
     clear(acc);
     clear(low);
-    for (int h = 0; h < 2 * KT; ++h) {
+    for (int h = 0; h < 2 * KT; ++h) {           // eight k's
+      const int k = (kt0 * 2 + h) * 8, tap_x = CONV ? k / p.Cin : 0;
       uint4v f[MI + NJ];
 #pragma unroll
-      for (int i = 0; i < MI + NJ; ++i) f[i] = __builtin_amdgcn_raw_buffer_load_b128(i < MI ? rX : rW, fo[i] + (unsigned)h * 32u, 0, 0);
+      for (int i = 0; i < MI; ++i) {
+        const Row x = row_of(m0 + wm * WM + i * 32 + (lane & 31));
+        const unsigned o = (CONV ? tap_off(x, tap_x) : x.img) + (unsigned)((k - tap_x * p.Cin) * 4 + (lane >> 5) * 16);
+        f[i] = __builtin_amdgcn_raw_buffer_load_b128(rX, o, 0, 0);
+      }
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const int n = n0 + wn * WN + j * 32 + (lane & 31);
+        const unsigned o = n < p.N ? (unsigned)(tile.phase * p.N + n) * (unsigned)p.K * 4u + (unsigned)(k * 4 + (lane >> 5) * 16) : kOob;
+        f[MI + j] = __builtin_amdgcn_raw_buffer_load_b128(rW, o, 0, 0);
+      }
 #pragma unroll
       for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -1045,7 +1086,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
       return;
     }
   }
-  igemm_epilogue<float, BM, BN, WGM, WGN, INTERIOR, EPI>(acc, p, smem, sRed, m0, n0, tile.m, 0);
+  igemm_epilogue<float, BM, BN, WGM, WGN, INTERIOR, EPI>(acc, p, smem, sRed, m0, n0, tile.m, tile.phase);
 }
 
 // y = act(round(sum over splits of partial[split] + bias)) for split-K launches
@@ -1317,7 +1358,7 @@ IgemmTile pick_tile(int64_t M, int cout, int cin, int es, bool wide = true, int 
 // column width of the patch kernel's tiles
 static int conv3_patch_bn(const ConvArgs& a) { return a.cout % 128 == 0 ? 128 : 64; }
 static bool conv3_patch_usable(const ConvArgs& a) {
-  if (a.geom != CONV_PLAIN || a.k != 3 || !conv_mfma_supported(a)) return false;
+  if (a.geom != CONV_PLAIN || a.k != 3 || a.dtype != AE_BF16 || !conv_mfma_supported(a)) return false;   // (binary32: k_gemm_split)
   // (a 128-pixel-wide tile would need 96 KB of LDS, one workgroup per compute unit: wider images are cut into column
   // strips of 64 pixels instead, whose halo columns come from the neighbouring strip)
   if (a.wc != 16 && a.wc != 32 && a.wc != 64 && a.wc != 128 && a.wc != 256) return false;
@@ -1491,22 +1532,14 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
     if (bn == 128) hipLaunchKernelGGL((k_conv3_patch<T, 128, 2, 2, WV, true, E>), pgrid, dim3(256), 0, s, p); \
     else hipLaunchKernelGGL((k_conv3_patch<T, 64, 4, 1, WV, true, E>), pgrid, dim3(256), 0, s, p);           \
   } while (0)
-#define PATCH_LAUNCH_W(T, WV) PATCH_LAUNCH_E(T, WV, 0)
     if (a0.comp_mode != 0) {            // (conv_comp_blocks: bfloat16 only)
       if (a0.comp_mode == 1) { if (a.wc == 16) PATCH_LAUNCH_E(bf16_t, 16, 3); else if (a.wc == 32) PATCH_LAUNCH_E(bf16_t, 32, 3); else PATCH_LAUNCH_E(bf16_t, 64, 3); }
       else { if (a.wc == 16) PATCH_LAUNCH_E(bf16_t, 16, 4); else if (a.wc == 32) PATCH_LAUNCH_E(bf16_t, 32, 4); else PATCH_LAUNCH_E(bf16_t, 64, 4); }
       return launch_status("conv3_patch");
     }
-#define PATCH_LAUNCH(T)                                     \
-  do {                                                      \
-    if (a.wc == 16) PATCH_LAUNCH_W(T, 16);                  \
-    else if (a.wc == 32) PATCH_LAUNCH_W(T, 32);             \
-    else PATCH_LAUNCH_W(T, 64);                             \
-  } while (0)
-    if (a.dtype == AE_BF16) PATCH_LAUNCH(bf16_t);
-    else PATCH_LAUNCH(float);
-#undef PATCH_LAUNCH
-#undef PATCH_LAUNCH_W
+    if (a.wc == 16) PATCH_LAUNCH_E(bf16_t, 16, 0);
+    else if (a.wc == 32) PATCH_LAUNCH_E(bf16_t, 32, 0);
+    else PATCH_LAUNCH_E(bf16_t, 64, 0);
 #undef PATCH_LAUNCH_E
     return launch_status("conv3_patch");
   }
@@ -1537,19 +1570,30 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
     if (interior) hipLaunchKernelGGL((k_igemm<T, BMV, BNV, GM, GN, KB, true, true>), grid, dim3(256), 0, s, p); \
     else hipLaunchKernelGGL((k_igemm<T, BMV, BNV, GM, GN, KB, false, true>), grid, dim3(256), 0, s, p); \
   } while (0)
-  // Dense binary32 products: three bf16 parts (k_gemm_split), unless the caller asks for the binary32 MFMA
-  const bool split_gemm = a.dtype == AE_F32 && !a0.f32_mfma && a.k == 1 && a.hc == 1 && a.wc == 1 && a.up == 0 && t.bn == 128;
+  // Binary32: three bf16 parts (k_gemm_split), unless the caller asks for the binary32 MFMA or there are few columns and a
+  // short K, where both only move the operands (65,536 rows, 64 -> 64 channels: 13.6 and 12.8 us; 131,072 rows, 48 -> 64 -> 48: 18.7
+  // and 18.6, 22.4 and 22.9; from there on the parts win: 64 -> 512 -> 64 channels 60.5 against 45.6 and 45.0 against 37.4)
+  const bool split_gemm = a.dtype == AE_F32 && !a0.f32_mfma && !(p.N <= 64 && p.K < 128);
+  const bool dense = a.k == 1 && a.up == 0 && p.phases == 1 && p.stride == 1;
   if (split_gemm) {
     // 256-row tiles, one workgroup per compute unit, where they fill the chip and K is long enough to outweigh their
     // prologue and epilogue, which nothing runs beside (d = 4096: 0.63 against 0.71 ms; K = 512, 65536 x 512 outputs: no gain)
-    const int64_t tall = p.M % 256 == 0 && interior && a0.tri == 0 && a0.epi == CONV_EPI_NONE && p.K >= 1024 ? p.M / 256 * p.tiles_n : 0;
+    const int64_t tall = dense && t.bn == 128 && p.M % 256 == 0 && interior && a0.tri == 0 && a0.epi == CONV_EPI_NONE && p.K >= 1024 ? p.M / 256 * p.tiles_n : 0;
     if (tall >= 256) {
       p.tiles_mn = (int)tall;
       hipLaunchKernelGGL((k_gemm_split<256, 128, 4, 2, true>), dim3((unsigned)tall), dim3(512), 0, s, p);
     } else if (a0.epi == CONV_EPI_MXQ) hipLaunchKernelGGL((k_gemm_split<128, 128, 2, 2, true, 1>), grid, dim3(256), 0, s, p);   // (conv_epi_usable: interior)
     else if (a0.epi == CONV_EPI_RESID) hipLaunchKernelGGL((k_gemm_split<128, 128, 2, 2, true, 2>), grid, dim3(256), 0, s, p);
-    else if (interior) hipLaunchKernelGGL((k_gemm_split<128, 128, 2, 2, true>), grid, dim3(256), 0, s, p);
-    else hipLaunchKernelGGL((k_gemm_split<128, 128, 2, 2, false>), grid, dim3(256), 0, s, p);
+#define SPLIT_LAUNCH(BNV, GM, GN, IN, CV) hipLaunchKernelGGL((k_gemm_split<128, BNV, GM, GN, IN, 0, CV>), grid, dim3(256), 0, s, p)
+#define SPLIT_LAUNCH_T(BNV, GM, GN)                                                                                    \
+  do {                                                                                                                 \
+    if (dense) { if (interior) SPLIT_LAUNCH(BNV, GM, GN, true, false); else SPLIT_LAUNCH(BNV, GM, GN, false, false); } \
+    else { if (interior) SPLIT_LAUNCH(BNV, GM, GN, true, true); else SPLIT_LAUNCH(BNV, GM, GN, false, true); }         \
+  } while (0)
+    else if (t.bn == 128) SPLIT_LAUNCH_T(128, 2, 2);
+    else SPLIT_LAUNCH_T(64, 4, 1);
+#undef SPLIT_LAUNCH_T
+#undef SPLIT_LAUNCH
     AE_TRY(launch_status("gemm_split"));
     return splits > 1 ? launch_splitk_finish(a, splits, p.M, p.N, s) : AE_OK;
   }
@@ -1868,6 +1912,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     }
 }
 
+// partial[split][co][tap*Cin + ci] of a tile whose columns are the chunks of all taps in a row
+template <int EPC, int BM, int BN>
+__device__ __forceinline__ void wgrad_store_chunks(const WgradParams& p, const floatx16 (&acc)[BM / 64][BN / 64], int split, int tm, int tn,
+                                                   int wm, int wn, int lane) {
+  constexpr int WM = BM / 2, WN = BN / 2, MI = WM / 32, NJ = WN / 32;
+  const int kc = p.ksz * p.ksz * p.chunks;
+  float* __restrict__ P = p.partial + (int64_t)split * p.Cout * p.K;
+  const int col_lane = lane & 31, row_lane = (lane >> 5) * 4;
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    const int col = tn * BN + wn * WN + j * 32 + col_lane, q = col / EPC;
+    const int tap_o = q / p.chunks, ci = (q - tap_o * p.chunks) * EPC + col % EPC;
+    if (q >= kc || ci >= p.Cin) continue;
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int co = tm * BM + wm * WM + i * 32 + (e >> 2) * 8 + row_lane + (e & 3);
+        if (co < p.Cout) P[(int64_t)co * p.K + tap_o * p.Cin + ci] = acc[i][j][e];
+      }
+  }
+}
+
 // The same for any channel counts.  Pixels of x and dY are stored as whole 16-byte chunks (zeros behind the channels),
 // and the columns of the product are the chunks of all taps in a row, (tap, chunk), cut into tiles of BN wherever a tile
 // ends: a loader thread moves the same column chunk in every pass, so its tap is fixed for the whole loop and the tile
@@ -1961,22 +2028,190 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     __syncthreads();
   }
 
-  // partial[split][co][tap*Cin + ci]
-  float* __restrict__ P = p.partial + (int64_t)split * p.Cout * p.K;
-  const int col_lane = lane & 31, row_lane = (lane >> 5) * 4;
+  wgrad_store_chunks<EPC, BM, BN>(p, acc, split, tm, tn, wm, wn, lane);
+}
+
+// The same for binary32: the three bfloat16 parts of k_gemm_split, cut on the way into LDS ([part][pixel][channel], read back
+// with the transposing loads), the six part products in two accumulators.  Slabs of 16 pixels, two LDS stages, one
+// barrier per slab, the split of the next slab between the MFMAs of this one.  128 x 9 x 128 weights over 65,536 pixels: 106 us
+// where the binary32 MFMA took 143 (both beside the input gradients on the other stream).  A workgroup that meets an infinity (or a
+// value within half a bf16 step of it), or a channel of its tile whose largest magnitude over its pixels is nonzero and
+// below 2^-96, computes its tile again with the binary32 MFMA.
+template <int BM, int BN>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_wgrad_split(WgradParams p) {
+  constexpr int BK = 16;                         // pixels per slab
+  constexpr int LA = BM + 32, LB = BN + 32;      // (as in k_wgrad, for both element sizes)
+  constexpr int WM = BM / 2, WN = BN / 2, MI = WM / 32, NJ = WN / 32;
+  constexpr int A_TPR = BM / 4, B_TPR = BN / 4;
+  constexpr int AC = BK * A_TPR / 256, BC = BK * B_TPR / 256;
+  constexpr int PA = BK * LA * 2, PB = BK * LB * 2, STAGE = 3 * (PA + PB);
+  static_assert(2 * STAGE >= 2 * BK * (LA + LB) * 4, "the binary32 loop fits into the same memory");
+  __shared__ __attribute__((aligned(16))) char smem[2 * STAGE];
+  __shared__ unsigned s_max[BM + BN];
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave >> 1, wn = wave & 1;
+  int b = xcd_logical_block((int)blockIdx.x, (int)gridDim.x);
+  const int tn = b % p.tiles_n; b /= p.tiles_n;
+  const int tm = b % p.tiles_m;
+  const int split_id = b / p.tiles_m;
+  const int pad = (p.ksz - 1) >> 1, kc = p.ksz * p.ksz * p.chunks;
+  const int Hin = p.Hc >> p.up, Win = p.Wc >> p.up;
+  const unsigned m_begin = (unsigned)split_id * (unsigned)p.rows_per_split;
+  const unsigned m_end = min(m_begin + (unsigned)p.rows_per_split, (unsigned)p.M);
+  const int KT = (int)((m_end - m_begin + BK - 1) / BK);
+  const __amdgpu_buffer_rsrc_t rX = make_rsrc(p.x, p.x_bytes);
+  const __amdgpu_buffer_rsrc_t rDY = make_rsrc(p.dy, p.dy_bytes);
+  const int ca = tm * A_TPR + tid % A_TPR, cb = tn * B_TPR + tid % B_TPR;
+  const int tap = cb / p.chunks, cc = cb - tap * p.chunks, r = tap / p.ksz, s = tap - r * p.ksz;
+  const bool a_in = ca < p.dy_chunks, b_in = cb < kc;
+  unsigned ma = m_begin + (unsigned)(tid / A_TPR), mb = m_begin + (unsigned)(tid / B_TPR);   // pixels of the next slab
+  auto load_a = [&](uint4v& v, int i) {
+    const unsigned m = ma + i * (256 / A_TPR);
+    v = __builtin_amdgcn_raw_buffer_load_b128(rDY, a_in && m < m_end ? (m * (unsigned)p.dy_chunks + (unsigned)ca) * 16u : kOob, 0, 0);
+  };
+  auto load_b = [&](uint4v& v, int i) {
+    const unsigned m = mb + i * (256 / B_TPR);
+    const unsigned t = p.div_w.quot(m), n = p.div_h.quot(t);
+    const int hh = (int)(t - n * (unsigned)p.Hc) + r - pad, ww = (int)(m - t * (unsigned)p.Wc) + s - pad;
+    const bool ok = b_in && m < m_end && hh >= 0 && hh < p.Hc && ww >= 0 && ww < p.Wc;
+    const unsigned pix = (n * (unsigned)Hin + (unsigned)(hh >> p.up)) * (unsigned)Win + (unsigned)(ww >> p.up);
+    v = __builtin_amdgcn_raw_buffer_load_b128(rX, ok ? (pix * (unsigned)p.chunks + (unsigned)cc) * 16u : kOob, 0, 0);
+  };
+  uint4v ra[AC], rb[BC];
+  float mxa[4] = {}, mxb[4] = {};                // this thread's four channels of either side
+  auto split = [&](char* dst, int plane, const uint4v& v, float (&mx)[4]) {
+    const float4v f = __builtin_bit_cast(float4v, v);
+    float x[4];
 #pragma unroll
-  for (int j = 0; j < NJ; ++j) {
-    const int col = tn * BN + wn * WN + j * 32 + col_lane, q = col / EPC;
-    const int tap_o = q / p.chunks, ci = (q - tap_o * p.chunks) * EPC + col % EPC;
-    if (q >= kc || ci >= p.Cin) continue;
+    for (int t = 0; t < 4; ++t) {
+      mx[t] = fmaxf(mx[t], fabsf(f[t]));
+      x[t] = f[t];
+    }
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const uint32_t w0 = pack_bf16(x[0], x[1]), w1 = pack_bf16(x[2], x[3]);
+      *reinterpret_cast<uint2*>(dst + q * plane) = make_uint2(w0, w1);
+      x[0] -= __uint_as_float(w0 << 16); x[1] -= __uint_as_float(w0 & 0xFFFF0000u);
+      x[2] -= __uint_as_float(w1 << 16); x[3] -= __uint_as_float(w1 & 0xFFFF0000u);
+    }
+  };
+  char* const sta = smem + ((tid / A_TPR) * LA + (tid % A_TPR) * 4) * 2;
+  char* const stb = smem + 3 * PA + ((tid / B_TPR) * LB + (tid % B_TPR) * 4) * 2;
+  auto refill = [&](int buf) {                   // registers into a stage, then the slab after that into the registers
+#pragma unroll
+    for (int i = 0; i < AC; ++i) { split(sta + buf * STAGE + i * (256 / A_TPR) * LA * 2, PA, ra[i], mxa); load_a(ra[i], i); }
+#pragma unroll
+    for (int i = 0; i < BC; ++i) { split(stb + buf * STAGE + i * (256 / B_TPR) * LB * 2, PB, rb[i], mxb); load_b(rb[i], i); }
+    ma += BK;
+    mb += BK;
+  };
+  floatx16 acc[MI][NJ], low[MI][NJ];             // the leading products, the five small ones
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = low[i][j][e] = 0.0f;
+  // transposing-load geometry: as in wgrad_compute
+  const int grp = lane >> 4, sl = lane & 15;
+  const int t_pix = 8 * (grp >> 1) + (sl >> 2), t_ch = 16 * (grp & 1) + 4 * (sl & 3);
+  bf16x8 fa[3][MI], fb[3][NJ];
+  auto read = [&](int buf) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+#pragma unroll
+      for (int i = 0; i < MI; ++i) {
+        const bf16_t* a = reinterpret_cast<const bf16_t*>(smem + buf * STAGE + q * PA) + t_pix * LA + wm * WM + i * 32 + t_ch;
+        fa[q][i] = lds_tr_frag(a, a + 4 * LA);
+      }
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const bf16_t* x = reinterpret_cast<const bf16_t*>(smem + buf * STAGE + 3 * PA + q * PB) + t_pix * LB + wn * WN + j * 32 + t_ch;
+        fb[q][j] = lds_tr_frag(x, x + 4 * LB);
+      }
+    }
+  };
+  auto products = [&]() {
+    constexpr int QA[6] = {0, 0, 1, 1, 0, 2}, QB[6] = {0, 1, 0, 1, 2, 0};
+#pragma unroll
+    for (int t = 0; t < 6; ++t)
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          floatx16& c = t == 0 ? acc[i][j] : low[i][j];
+          c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[QA[t]][i], fb[QB[t]][j], c, 0, 0, 0);
+        }
+  };
+#pragma unroll
+  for (int i = 0; i < AC; ++i) load_a(ra[i], i);
+#pragma unroll
+  for (int i = 0; i < BC; ++i) load_b(rb[i], i);
+  ma += BK;
+  mb += BK;
+  refill(0);
+  __syncthreads();
+  for (int kt = 1; kt < KT; ++kt) {              // (KT >= 1: every split owns at least one pixel)
+    const int buf = (kt & 1) ^ 1;
+    read(buf);
+    __builtin_amdgcn_sched_barrier(0);           // (the reads stay ahead of the MFMAs they would otherwise be sunk to)
+    products();
+    refill(buf ^ 1);
+#pragma unroll
+    for (int g = 0; g < 6 * MI * NJ; ++g) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x002, (AC * 36 + BC * 56) / (6 * MI * NJ) + 1, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    __syncthreads();
+  }
+  read((KT & 1) ^ 1);
+  products();
+  // the largest magnitude of every channel of the tile
+  for (int i = tid; i < BM + BN; i += 256) s_max[i] = 0u;
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    atomicMax(&s_max[(tid % A_TPR) * 4 + t], __float_as_uint(mxa[t]));
+    atomicMax(&s_max[BM + (tid % B_TPR) * 4 + t], __float_as_uint(mxb[t]));
+  }
+  __syncthreads();
+  bool odd = false;
+  for (int i = tid; i < BM + BN; i += 256) {
+    const float v = __uint_as_float(s_max[i]);
+    odd = odd || v >= 0x1.FFp127f || (v > 0.0f && v < 0x1p-96f);
+  }
+  if (__syncthreads_or(odd) != 0) {
+    float* const sA = reinterpret_cast<float*>(smem);
+    float* const sB = sA + BK * LA;
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int co = tm * BM + wm * WM + i * 32 + (e >> 2) * 8 + row_lane + (e & 3);
-        if (co < p.Cout) P[(int64_t)co * p.K + tap_o * p.Cin + ci] = acc[i][j][e];
-      }
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[i][j][e] = low[i][j][e] = 0.0f;
+    ma = m_begin + (unsigned)(tid / A_TPR);
+    mb = m_begin + (unsigned)(tid / B_TPR);
+    for (int kt = 0; kt < KT; ++kt) {
+#pragma unroll
+      for (int i = 0; i < AC; ++i) { load_a(ra[i], i); *reinterpret_cast<uint4v*>(&sA[(tid / A_TPR + i * (256 / A_TPR)) * LA + (tid % A_TPR) * 4]) = ra[i]; }
+#pragma unroll
+      for (int i = 0; i < BC; ++i) { load_b(rb[i], i); *reinterpret_cast<uint4v*>(&sB[(tid / B_TPR + i * (256 / B_TPR)) * LB + (tid % B_TPR) * 4]) = rb[i]; }
+      ma += BK;
+      mb += BK;
+      __syncthreads();
+      wgrad_compute<float, MI, NJ, BK, LA, LB>(&sA[wm * WM], &sB[wn * WN], lane, acc);
+      __syncthreads();
+    }
   }
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] += low[i][j][e];
+  wgrad_store_chunks<4, BM, BN>(p, acc, split_id, tm, tn, wm, wn, lane);
 }
 
 // The same kernel for images whose width is a multiple of the slab depth BK: a slab is then BK
@@ -2515,7 +2750,7 @@ WgradPlan plan_wgrad(int cout, int cin, int k, int64_t rows, int wc, int es, int
 }  // namespace
 
 bool wgrad_mfma_supported(const WgradArgs& a) {
-  if (a.cin % 64 != 0 || a.cout % 64 != 0) return false;
+  if (a.dtype != AE_BF16 || a.cin % 64 != 0 || a.cout % 64 != 0) return false;   // (binary32: launch_wgrad_chunks)
   const int64_t es = (int64_t)dtype_size(a.dtype);
   if ((int64_t)a.n * a.hc * a.wc * a.cout * es >= 0x7FFFFFFF) return false;                    // 32-bit buffer offsets
   if ((int64_t)a.n * (a.hc >> a.up) * (a.wc >> a.up) * a.cin * es >= 0x7FFFFFFF) return false;
@@ -2596,10 +2831,8 @@ int launch_wgrad_mfma(const WgradArgs& a, float* workspace, hipStream_t s) {
     else { if (w.bm == 128) WGRAD_ROW3(128, false); else WGRAD_ROW3(64, false); }
 #undef WGRAD_ROW3
   }
-  else if (w.bk && a.dtype == AE_BF16) { if (w.bk == 64) WGRAD_ROWS(bf16_t, 64); else WGRAD_ROWS(bf16_t, 32); }
-  else if (w.bk) { if (w.bk == 32) WGRAD_ROWS(float, 32); else WGRAD_ROWS(float, 16); }
-  else if (a.dtype == AE_BF16) WGRAD_LAUNCH(bf16_t);
-  else WGRAD_LAUNCH(float);
+  else if (w.bk) { if (w.bk == 64) WGRAD_ROWS(bf16_t, 64); else WGRAD_ROWS(bf16_t, 32); }
+  else WGRAD_LAUNCH(bf16_t);
 #undef WGRAD_ROWS
 #undef WGRAD_LAUNCH_P
 #undef WGRAD_LAUNCH
@@ -2651,8 +2884,13 @@ int launch_wgrad_chunks(const WgradArgs& a, float* workspace, hipStream_t s) {
     else if (w.bn == 128) hipLaunchKernelGGL((k_wgrad_chunks<T, 64, 128>), grid, dim3(256), 0, s, p);           \
     else hipLaunchKernelGGL((k_wgrad_chunks<T, 64, 64>), grid, dim3(256), 0, s, p);                             \
   } while (0)
+#define WGRAD_SPLIT(BMV, BNV) hipLaunchKernelGGL((k_wgrad_split<BMV, BNV>), grid, dim3(256), 0, s, p)
   if (a.dtype == AE_BF16) WGRAD_CHUNKS(bf16_t);
-  else WGRAD_CHUNKS(float);
+  else if (w.bm == 128 && w.bn == 128) WGRAD_SPLIT(128, 128);
+  else if (w.bm == 128) WGRAD_SPLIT(128, 64);
+  else if (w.bn == 128) WGRAD_SPLIT(64, 128);
+  else WGRAD_SPLIT(64, 64);
+#undef WGRAD_SPLIT
 #undef WGRAD_CHUNKS
   AE_TRY(launch_status("wgrad_chunks"));
   if (direct) return AE_OK;

@@ -184,7 +184,7 @@ WgradChunksPlan plan_wgrad_chunks(const WgradArgs& a) {
   w.tiles_m = (a.cout + w.bm - 1) / w.bm;
   w.tiles_n = (cols + w.bn - 1) / w.bn;
   const int64_t tiles = (int64_t)w.tiles_m * w.tiles_n;
-  int64_t splits = (1024 + tiles - 1) / tiles;          // about four workgroups per compute unit
+  int64_t splits = 512 / tiles;                         // two workgroups per compute unit fit: one full round and none behind it
   const int64_t max_splits = (rows + 255) / 256;        // at least 256 pixels per split
   if (splits > max_splits) splits = max_splits;
   if (splits < 1) splits = 1;
@@ -439,8 +439,10 @@ int build_plan(const char* spec, int batch, int dtype, int bn_mode, Plan* plan) 
           if (st.chunks_d) plan->max_splitk_floats = std::max(plan->max_splitk_floats, conv_chunks_splitk_floats(cd));
         }
         st.chunks_w = !wgrad_mfma_supported(wa) && wgrad_chunks_worthwhile(wa) && wgrad_chunks_supported(wa);
-        if ((st.chunks || st.chunks_w) && cin_p != st.cin) st.off_xpad = take(in_elems / st.cin * cin_p * es);
-        if ((st.chunks_d || st.chunks_w) && cout_p != st.cout)
+        // (the caller's own x and dy may lie anywhere: copied into whole aligned chunks if need be, see chunk_rows)
+        const bool reads_x = &st == &plan->steps[0], reads_dy = &st == &plan->steps.back() && !st.has_bn && !st.pool && st.act == ACT_NONE;
+        if ((st.chunks || st.chunks_w) && (cin_p != st.cin || reads_x)) st.off_xpad = take(in_elems / st.cin * cin_p * es);
+        if ((st.chunks_d || st.chunks_w) && (cout_p != st.cout || reads_dy))
           plan->max_dypad_bytes = std::max(plan->max_dypad_bytes, rows * cout_p * es);
       }
       if (st.thin == 1) {

@@ -42,3 +42,51 @@ def test_any_channel_counts(case, dtype):
 def test_tall_tiles_and_many_splits(dtype):
     # 33,024 rows: the 256-row tiles with a ragged last one; a weight gradient in over a hundred pieces
     run_case("in:12x64x43,conv3:20,relu,conv3:12,relu,conv1:3", 12, dtype=dtype, seed=431, flips=(dtype == "bf16"))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_tensors_of_the_caller_off_a_16_byte_border(dtype):
+    """x and dy one element into a buffer: the same results, bit for bit, as from aligned copies."""
+    import torch
+    from paper_2602_17681_amd import binding as ae
+    td = {"f32": torch.float32, "bf16": torch.bfloat16}[dtype]
+    torch.manual_seed(7)
+    B = 200
+    m = ae.Model("in:24x1x1,fc:144,relu,fc:40", B, ae.DTYPES[dtype])
+    p = torch.randn(m.n_params, device="cuda") * 0.1
+    out = []
+    for off in (0, 1):
+        x, dy = (torch.empty(B * c + 1, device="cuda", dtype=td)[off:off + B * c] for c in (24, 40))
+        torch.manual_seed(8)
+        x.copy_(torch.randn(B * 24, device="cuda"))
+        dy.copy_(torch.randn(B * 40, device="cuda"))
+        y, g = torch.empty(B, 40, device="cuda", dtype=td), torch.empty(m.n_params, device="cuda")
+        m.model_forward(p, x, 10.0, 1, y)
+        m.model_backward(p, x, dy, g)
+        out.append((y.clone(), g.clone()))
+    assert all(torch.equal(a, b) for a, b in zip(*out))
+
+
+def test_gradients_by_parts_of_extreme_size():
+    """Binary32: a channel whose gradients are all tiny, and an infinity among the activations."""
+    import torch
+    from paper_2602_17681_amd import binding as ae
+    torch.manual_seed(9)
+    B, cin, cout = 600, 64, 96
+    m = ae.Model("in:%dx1x1,fc:%d" % (cin, cout), B, ae.DTYPES["f32"])
+    p = torch.randn(m.n_params, device="cuda") * 0.1
+    x, dy = torch.randn(B, cin, device="cuda"), torch.randn(B, cout, device="cuda")
+    dy[:, 70] *= 2.0 ** -110
+    y, g = torch.empty(B, cout, device="cuda"), torch.empty(m.n_params, device="cuda")
+    for bad in (False, True):
+        if bad:
+            x[5, 3] = float("inf")
+            dy[:, 4] = 0.0
+        m.model_forward(p, x, 10.0, 1, y)
+        m.model_backward(p, x, dy, g)
+        got, ref = g[:cin * cout].view(cout, cin).double(), dy.double().t() @ x.double()
+        assert torch.equal(got.isnan(), ref.isnan()) and torch.equal(got.isinf(), ref.isinf())
+        ok = ref.isfinite()
+        err = torch.where(ok, got - ref, 0.0).norm(dim=1) / torch.where(ok, ref, 0.0).norm(dim=1).clamp_min(1e-300)
+        # 600 terms in binary32: about sqrt(600 / 16) roundings of 2^-24
+        assert err.max().item() <= 1e-6, err.max()
