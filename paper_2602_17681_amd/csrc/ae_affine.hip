@@ -223,132 +223,31 @@ void launch_build(const LuSrc& q, void* out, hipStream_t s) {
 // matrix M (L itself; (U + diag s)^T for the upper factor): 128 x 128 diagonal blocks are inverted by substitution,
 // then neighbouring inverses X11, X22 of blocks of size b merge into the inverse of the 2b x 2b block,
 //     [[X11, 0], [-X22 M21 X11, X22]].
-// X and X^T live as full d x d binary32 matrices that start block diagonal and fill level by level; one level is
+// X and X^T live as full d x d binary32 matrices whose diagonal blocks come first and which fill level by level (the other
+// triangle is never written and never read: every product starts or ends its K range at the tile's own rows); one level is
 // two launches of the matrix-core kernel over ALL pairs at once (K-range modes CONV_TRI_PAIR_*) and a transposing copy:
 //     T' = -(M21 X11)^T  into the upper blocks of a scratch matrix,   X21 = X22 T'^T  in place into X,
 //     X21^T  into X^T.
 
-// entry (r, c) of the lower triangular matrix: WHICH 0: L; 1: (U + diag s)^T.  Rows and columns past d belong to
-// the identity block that pads the matrix to the working size of the recursion.
+// mneg = -M in the 32 x 32 tiles below the 128 x 128 diagonal blocks, the only ones the merges read.  Of M = L (WHICH 0) or
+// (U + diag s)^T (1, through LDS: both sides of the transpose move whole rows) these tiles hold nothing but parameters, and
+// zeros beyond row d, where an identity block pads the matrix to the working size of the recursion.
 template <int WHICH>
-__device__ __forceinline__ float tri_elem(const LuSrc& q, int r, int c) {
-  if (c > r) return 0.0f;
-  if (r >= q.d) return r == c ? 1.0f : 0.0f;
-  if (WHICH == 0) return c < r ? q.lp[(int64_t)r * q.d + c] : 1.0f;
-  return c < r ? q.up[(int64_t)c * q.d + r] : q.sign[c] * expf(q.log_s[c]);
-}
-
-// mneg = -M (full dp x dp), x = xt = 0: 32 x 32 tiles
-template <int WHICH>
-__global__ __launch_bounds__(256) void k_tri_prepare(LuSrc q, int dp, float* __restrict__ mneg, float* __restrict__ x, float* __restrict__ xt) {
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+__global__ __launch_bounds__(256) void k_tri_prepare(LuSrc q, int dp, float* __restrict__ mneg) {
+  __shared__ float tile[32][33];
   const int r0 = blockIdx.y * 32, c0 = blockIdx.x * 32;
+  if ((c0 >> 7) >= (r0 >> 7)) return;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  if (WHICH == 1) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) tile[ty + 8 * j][tx] = r0 + tx < q.d ? q.up[(int64_t)(c0 + ty + 8 * j) * q.d + r0 + tx] : 0.0f;
+    __syncthreads();
+  }
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int r = r0 + ty + 8 * j, c = c0 + tx;
-    const int64_t i = (int64_t)r * dp + c;
-    // (U + diag s)^T is read along its columns: the tile is small enough for the cache to absorb the stride
-    mneg[i] = -tri_elem<WHICH>(q, r, c);
-    x[i] = 0.0f;
-    xt[i] = 0.0f;
-  }
-}
-
-// One merge level of the in-LDS recursion: for every pair p of neighbouring B x B diagonal blocks of the 128 x 128
-// matrix, X21 = -X22 (M21 X11) into xb below the diagonal blocks.  64 / B pairs, 256 threads, each a TR x TC register
-// tile of outputs (rows tr + (B/TR) i, columns tc + (B/TC) j: neighbouring threads read neighbouring LDS columns).
-// X11 and X22 are lower triangular inside xb, whose other entries are zero, so the K ranges are cut per thread only:
-// the first product starts at the thread's first column, the second ends at its last row.  Ends on a barrier.
-template <int B, int TR, int TC>
-__device__ __forceinline__ void tri128_merge(float (*mb)[129], float (*xb)[129], float* tb, int tid) {
-  constexpr int PAIRS = 64 / B, TPP = 256 / PAIRS, TCN = B / TC, TRN = B / TR;
-  static_assert(TRN * TCN == TPP, "one register tile per thread");
-  const int p = tid / TPP, t = tid % TPP, tr = t / TCN, tc = t % TCN;
-  const int o0 = 2 * p * B, o1 = o0 + B;             // first row / column of the pair's two diagonal blocks
-  float* tp = tb + p * B * B;
-  float acc[TR][TC];
-#pragma unroll
-  for (int i = 0; i < TR; ++i)
-#pragma unroll
-    for (int j = 0; j < TC; ++j) acc[i][j] = 0.0f;
-#pragma unroll 4
-  for (int k = tc; k < B; ++k) {                       // T = M21 X11:  X11[k][c] = 0 for k < c, and c >= tc
-    float a[TR], x[TC];
-#pragma unroll
-    for (int i = 0; i < TR; ++i) a[i] = mb[o1 + tr + TRN * i][o0 + k];
-#pragma unroll
-    for (int j = 0; j < TC; ++j) x[j] = xb[o0 + k][o0 + tc + TCN * j];
-#pragma unroll
-    for (int i = 0; i < TR; ++i)
-#pragma unroll
-      for (int j = 0; j < TC; ++j) acc[i][j] = fmaf(a[i], x[j], acc[i][j]);
-  }
-#pragma unroll
-  for (int i = 0; i < TR; ++i)
-#pragma unroll
-    for (int j = 0; j < TC; ++j) {
-      tp[(tr + TRN * i) * B + tc + TCN * j] = acc[i][j];
-      acc[i][j] = 0.0f;
-    }
-  __syncthreads();
-  const int kend = tr + TRN * (TR - 1);                // X21 = -X22 T:  X22[r][k] = 0 for k > r, and r <= kend
-#pragma unroll 4
-  for (int k = 0; k <= kend; ++k) {
-    float a[TR], x[TC];
-#pragma unroll
-    for (int i = 0; i < TR; ++i) a[i] = xb[o1 + tr + TRN * i][o1 + k];
-#pragma unroll
-    for (int j = 0; j < TC; ++j) x[j] = tp[k * B + tc + TCN * j];
-#pragma unroll
-    for (int i = 0; i < TR; ++i)
-#pragma unroll
-      for (int j = 0; j < TC; ++j) acc[i][j] = fmaf(a[i], x[j], acc[i][j]);
-  }
-#pragma unroll
-  for (int i = 0; i < TR; ++i)
-#pragma unroll
-    for (int j = 0; j < TC; ++j) xb[o1 + tr + TRN * i][o0 + tc + TCN * j] = -acc[i][j];   // (below the diagonal blocks: nobody reads it in this pass)
-  __syncthreads();
-}
-
-// xb = mb^-1 for a lower triangular 128 x 128 matrix in LDS (all 256 threads of the workgroup; xb must be zero on
-// entry and both arrays visible to every thread; ends on a barrier): 16 x 16 diagonal blocks by forward substitution
-// (thread j solves column j of its block), then three levels of merges [[X11, 0], [-X22 M21 X11, X22]] (tri128_merge).
-// tb: 64 * 64 values of scratch.
-__device__ __forceinline__ void tri128_inverse_lds(float (*mb)[129], float (*xb)[129], float* tb, int tid) {
-  if (tid < 128) {                                     // column tid of its 16 x 16 diagonal block
-    const int j = tid, b0 = j & ~15;
-    for (int i = j; i < b0 + 16; ++i) {
-      float acc = 0.0f;
-      for (int k = j; k < i; ++k) acc = fmaf(mb[i][k], xb[k][j], acc);
-      xb[i][j] = i == j ? 1.0f / mb[j][j] : -acc / mb[i][i];
-    }
-  }
-  __syncthreads();
-  tri128_merge<16, 2, 2>(mb, xb, tb, tid);
-  tri128_merge<32, 2, 4>(mb, xb, tb, tid);
-  tri128_merge<64, 4, 4>(mb, xb, tb, tid);
-}
-
-// X_bb = M_bb^-1 for every 128 x 128 diagonal block b (one workgroup of 256 threads each) by the recursion above;
-// the block and its transpose are written into the full matrices x and xt.
-template <int WHICH>
-__global__ __launch_bounds__(256) void k_tri_diag_inverse(LuSrc q, int dp, float* __restrict__ x, float* __restrict__ xt) {
-  __shared__ float mb[128][129];
-  __shared__ float xb[128][129];
-  __shared__ float tb[64 * 64];
-  const int blk = blockIdx.x, tid = threadIdx.x, o = blk * 128;
-  for (int e = tid; e < 128 * 128; e += 256) {
-    const int i = e >> 7, j = e & 127;
-    mb[i][j] = tri_elem<WHICH>(q, o + i, o + j);
-    xb[i][j] = 0.0f;
-  }
-  __syncthreads();
-  tri128_inverse_lds(mb, xb, tb, tid);
-  for (int e = tid; e < 128 * 128; e += 256) {
-    const int i = e >> 7, j = e & 127;
-    x[(int64_t)(o + i) * dp + o + j] = xb[i][j];
-    xt[(int64_t)(o + i) * dp + o + j] = xb[j][i];
+    const float v = WHICH == 0 ? (r < q.d ? q.lp[(int64_t)r * q.d + c] : 0.0f) : tile[tx][ty + 8 * j];
+    mneg[(int64_t)r * dp + c] = -v;
   }
 }
 
@@ -545,8 +444,31 @@ struct SmallTri {
   __device__ __forceinline__ float& at(int i, int j) const { return p[i * si + j * sj]; }
 };
 
-// one merge level (as tri128_merge) of one factor in place: X21 = -X22 (M21 X11) over M21; 256 threads (tid), tb: 64 * 68
-// floats.  Blocks of 16 on the vector ALUs; blocks of 32 and 64 on the matrix cores, a wavefront per 32 x 32 tile.
+// the 16 x 16 diagonal blocks by substitution: thread tid < 128 has column tid, in registers; all 256 threads of the factor call
+__device__ __forceinline__ void small_tri_diag(const SmallTri& x, int tid) {
+  float col[16];
+  const int b0 = tid & ~15, jj = tid & 15;
+  if (tid < 128) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      float acc = 0.0f;
+#pragma unroll
+      for (int k = 0; k < i; ++k) acc = fmaf(x.at(b0 + i, b0 + k), col[k], acc);
+      const float dv = x.at(b0 + i, b0 + i);
+      col[i] = i < jj ? 0.0f : (i == jj ? 1.0f / dv : -acc / dv);
+    }
+  }
+  __syncthreads();
+  if (tid < 128) {
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      if (i >= jj) x.at(b0 + i, b0 + jj) = col[i];
+  }
+  __syncthreads();
+}
+
+// one merge level of one factor in place, all pairs of neighbouring B x B diagonal blocks: X21 = -X22 (M21 X11) over M21; 256
+// threads (tid), tb: 64 * 68 floats.  Blocks of 16 on the vector ALUs; blocks of 32 and 64 on the matrix cores, a wavefront per 32 x 32 tile.
 __device__ __forceinline__ void small_tri_merge16(const SmallTri& x, float* tb, int tid) {
   const int pr = tid >> 6, t = tid & 63, tr = t >> 3, tc = t & 7, o0 = 32 * pr, o1 = o0 + 16;
   float* tp = tb + pr * 256;
@@ -661,25 +583,7 @@ __global__ __launch_bounds__(512) void k_lu_small_inverse(const float* __restric
   __syncthreads();
   const int f = tid >> 8, ft = tid & 255;
   const SmallTri x = f == 0 ? SmallTri{pk, 129, 1} : SmallTri{pk + 1, 1, 129};
-  float col[16];
-  const int b0 = ft & ~15, jj = ft & 15;
-  if (ft < 128) {                                        // column jj of the 16 x 16 diagonal block at b0
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      float acc = 0.0f;
-#pragma unroll
-      for (int k = 0; k < i; ++k) acc = fmaf(x.at(b0 + i, b0 + k), col[k], acc);
-      const float dv = x.at(b0 + i, b0 + i);
-      col[i] = i < jj ? 0.0f : (i == jj ? 1.0f / dv : -acc / dv);
-    }
-  }
-  __syncthreads();
-  if (ft < 128) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i)
-      if (i >= jj) x.at(b0 + i, b0 + jj) = col[i];
-  }
-  __syncthreads();
+  small_tri_diag(x, ft);
   // (a level whose lower blocks are all padding leaves zeros as they are)
   if (d > 16) small_tri_merge16(x, tb[f], ft);
   if (d > 32) small_tri_merge<32>(x, tb[f], ft);
@@ -711,15 +615,66 @@ __global__ __launch_bounds__(512) void k_lu_small_inverse(const float* __restric
   }
 }
 
-// out[r][c] = z[r][perm[c]] in the storage type (z P^T); z has rows of dp entries, out is d x d
+// X_bb = M_bb^-1 for every 128 x 128 diagonal block b of M = L (WHICH 0) or (U + diag s)^T (1) (one workgroup of 256 threads
+// each), inverted in place in LDS as above; the block and its transpose are written into the full matrices x and xt.
+template <int WHICH>
+__global__ __launch_bounds__(256) void k_tri_diag_inverse(LuSrc q, int dp, float* __restrict__ x, float* __restrict__ xt) {
+  __shared__ float pk[128 * 129];
+  __shared__ float tb[64 * 68];
+  const int tid = threadIdx.x, o = blockIdx.x * 128;
+  const float* src = WHICH == 0 ? q.lp : q.up;
+#pragma unroll
+  for (int b0 = 0; b0 < 16; b0 += 8) {                   // 128 x 32 chunks of four columns, eight per thread in flight
+    float4 v[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      const int e = tid + (b0 + t) * 256, i = e >> 5, c = (e & 31) * 4;
+      const bool in = o + i < q.d && o + c < q.d && (WHICH == 0 ? c < i : c + 3 > i);
+      v[t] = in ? small_load4<float>(src, q.d, o + i, o + c, true) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    }
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      const int e = tid + (b0 + t) * 256, i = e >> 5, c = (e & 31) * 4;
+      const float w[4] = {v[t].x, v[t].y, v[t].z, v[t].w};
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+        if (c + s != i) pk[i * 129 + c + s] = w[s];
+    }
+  }
+  if (tid < 128) pk[tid * 129 + tid] = WHICH == 0 || o + tid >= q.d ? 1.0f : q.sign[o + tid] * expf(q.log_s[o + tid]);
+  __syncthreads();
+  const SmallTri m = WHICH == 0 ? SmallTri{pk, 129, 1} : SmallTri{pk, 1, 129};
+  small_tri_diag(m, tid);
+  small_tri_merge16(m, tb, tid);
+  small_tri_merge<32>(m, tb, tid);
+  small_tri_merge<64>(m, tb, tid);
+  for (int e = tid; e < 128 * 128; e += 256) {
+    const int i = e >> 7, j = e & 127;
+    x[(int64_t)(o + i) * dp + o + j] = j <= i ? m.at(i, j) : 0.0f;
+    xt[(int64_t)(o + i) * dp + o + j] = i <= j ? m.at(j, i) : 0.0f;
+  }
+}
+
+// out[r][c] = z[r][perm[c]] in the storage type (z P^T); z is d x d, d % 8 == 0.  A row goes through LDS, so that global memory sees
+// whole rows on both sides (gathered straight from memory, d = 4096 took 81 us; this way 18).
 template <typename T>
-__global__ __launch_bounds__(256) void k_lu_inverse_out(const float* __restrict__ z, const int* __restrict__ perm, int d, int dp, T* __restrict__ out) {
-  const int64_t n = (int64_t)d * d;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-    const int r = (int)(i / d), c = (int)(i - (int64_t)r * d);
-    int src = perm[c];
-    if ((unsigned)src >= (unsigned)d) src = c;                         // not a permutation: stay inside the arrays
-    Store<T>::st(out + i, z[(int64_t)r * dp + src]);
+__global__ __launch_bounds__(256) void k_lu_inverse_out(const float* __restrict__ z, const int* __restrict__ perm, int d, T* __restrict__ out) {
+  extern __shared__ __attribute__((aligned(16))) float row[];
+  for (int r = blockIdx.x; r < d; r += gridDim.x) {
+    for (int c = 4 * threadIdx.x; c < d; c += 1024) *reinterpret_cast<float4*>(row + c) = *reinterpret_cast<const float4*>(z + (int64_t)r * d + c);
+    __syncthreads();
+    for (int c0 = 8 * threadIdx.x; c0 < d; c0 += 2048) {
+      float v[8];
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        const int src = perm[c0 + t];
+        v[t] = row[(unsigned)src < (unsigned)d ? src : c0 + t];      // not a permutation: stay inside the row
+      }
+      T* o = out + (int64_t)r * d + c0;
+#pragma unroll
+      for (int t = 0; t < 8; ++t) Store<T>::st(o + t, v[t]);
+    }
+    __syncthreads();
   }
 }
 
@@ -862,7 +817,7 @@ int64_t tri_padded_size(int64_t d) {
 template <int WHICH>
 int tri_inverse(const LuSrc& q, int dp, float* mneg, float* tt, float* x, float* xt, hipStream_t s) {
   const int d = dp;
-  hipLaunchKernelGGL((k_tri_prepare<WHICH>), dim3(d / 32, d / 32), dim3(256), 0, s, q, d, mneg, x, xt);
+  hipLaunchKernelGGL((k_tri_prepare<WHICH>), dim3(d / 32, d / 32), dim3(256), 0, s, q, d, mneg);
   hipLaunchKernelGGL((k_tri_diag_inverse<WHICH>), dim3(d / 128), dim3(256), 0, s, q, d, x, xt);
   AE_TRY(launch_status("tri_diag_inverse"));
   for (int b = 128; b < d; b *= 2) {
@@ -1304,9 +1259,9 @@ extern "C" int model_qr_inverse(const float* rp, const float* log_s, const float
     AE_TRY(launch_status("tri_compact"));
     rdinv = mneg;
   }
-  // A^-1 = (R + diag s)^-1 Q^T = x w^T with w = Q
-  if (dtype == AE_F32) return dense_product(rdinv, w.q(squarings), a_inv_out, (int)d, AE_F32, CONV_TRI_NONE, s);
-  AE_TRY(dense_product(rdinv, w.q(squarings), z, (int)d, AE_F32, CONV_TRI_NONE, s));
+  // A^-1 = (R + diag s)^-1 Q^T = x w^T with w = Q, x upper triangular (its lower triangle is not written)
+  if (dtype == AE_F32) return dense_product(rdinv, w.q(squarings), a_inv_out, (int)d, AE_F32, CONV_TRI_UPPER_X_FULL, s);
+  AE_TRY(dense_product(rdinv, w.q(squarings), z, (int)d, AE_F32, CONV_TRI_UPPER_X_FULL, s));
   hipLaunchKernelGGL((k_from_f32<bf16_t>), dim3(lu_grid(dd)), dim3(256), 0, s, (const float*)z, (bf16_t*)a_inv_out, dd);
   return launch_status("qr_inverse");
 }
@@ -1354,8 +1309,9 @@ extern "C" int model_lu_inverse(const float* lp, const float* up, const float* l
   }
   float* z = linv;
   AE_TRY(dense_product(udinv, linv_t, z, (int)d, AE_F32, CONV_TRI_UPPER_LOWER, s));
-  if (dtype == AE_BF16) hipLaunchKernelGGL((k_lu_inverse_out<bf16_t>), dim3(lu_grid(dd)), dim3(256), 0, s, (const float*)z, perm, (int)d, (int)d, (bf16_t*)a_inv_out);
-  else hipLaunchKernelGGL((k_lu_inverse_out<float>), dim3(lu_grid(dd)), dim3(256), 0, s, (const float*)z, perm, (int)d, (int)d, (float*)a_inv_out);
+  const dim3 og((unsigned)(d < 2048 ? d : 2048));
+  if (dtype == AE_BF16) hipLaunchKernelGGL((k_lu_inverse_out<bf16_t>), og, dim3(256), (size_t)d * 4, s, (const float*)z, perm, (int)d, (bf16_t*)a_inv_out);
+  else hipLaunchKernelGGL((k_lu_inverse_out<float>), og, dim3(256), (size_t)d * 4, s, (const float*)z, perm, (int)d, (float*)a_inv_out);
   return launch_status("lu_inverse_out");
 }
 

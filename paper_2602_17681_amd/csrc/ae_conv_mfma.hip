@@ -67,10 +67,11 @@ struct IgemmParams {
   //   2: x[m][k] = 0 for k < m, wanted outputs n >= m: K starts at the tile's first row; tiles below the diagonal return
   //   3: w[n][k] = 0 for k < n, wanted outputs n < m: K starts at the tile's first column; tiles above the diagonal return
   //   4: x[m][k] = 0 for k < m and w[n][k] = 0 for k < n (upper times lower): K starts at max(first row, first column)
+  //   5: x[m][k] = 0 for k < m: K starts at the tile's first row
   // Blocked triangular inverse, all pairs of neighbouring tri_b x tri_b diagonal blocks in one launch (tile sizes divide
   // tri_b): only the tiles of one off-diagonal block per pair are computed, over the K range of one block:
-  //   8: tile rows in an even block r, columns in block r+1, K = block r;
-  //   9: tile rows in an odd block r, columns in block r-1, K = block r
+  //   8: tile rows in an even block r, columns in block r+1, K = block r, x upper triangular: from the tile's first row on;
+  //   9: tile rows in an odd block r, columns in block r-1, K = block r, x lower triangular: up to the tile's last row
   // tri_d > 0 (modes 8, 9): the matrices are an identity block beyond row and column tri_d; tiles of the odd block that
   // lie wholly beyond it return (their outputs are zero and stay unwritten) and K ranges over the odd block end at tri_d.
   int tri, tri_b, tri_d;
@@ -560,11 +561,12 @@ __device__ __forceinline__ bool igemm_k_range(const IgemmParams& p, int64_t m0, 
   else if (p.tri == 2) { if ((int64_t)n0 + BN <= m0) return false; k_lo = (int)m0; }
   else if (p.tri == 3) { if ((int64_t)n0 >= m0 + BM) return false; k_lo = n0; }
   else if (p.tri == 4) k_lo = (int)max(m0, (int64_t)n0);
+  else if (p.tri == 5) k_lo = (int)m0;
   else if (p.tri >= 8) {
     const int rb = (int)(m0 / p.tri_b), cb = n0 / p.tri_b;
     if (p.tri == 9 ? !((rb & 1) == 1 && cb == rb - 1) : !((rb & 1) == 0 && cb == rb + 1)) return false;
-    k_lo = rb * p.tri_b;
-    k_hi = k_lo + p.tri_b;
+    k_lo = p.tri == 8 ? (int)m0 : rb * p.tri_b;
+    k_hi = p.tri == 8 ? (rb + 1) * p.tri_b : (int)m0 + BM;
     if (p.tri_d > 0) {
       if ((p.tri == 9 ? m0 : (int64_t)n0) >= p.tri_d) return false;
       if (p.tri == 9) k_hi = min(k_hi, p.tri_d);
@@ -1518,7 +1520,7 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
   if (a0.tri >= 8 && (a0.tri > 9 || a.dtype != AE_F32 || a0.tri_b < 128 || a0.tri_b % 128 != 0 || a.n % (2 * a0.tri_b) != 0 ||
                       a0.tri_d < 0 || a0.tri_d > a.n || a0.tri_d % 128 != 0))
     return fail(AE_EINVAL, "conv_mfma: bad block size for the blocked triangular inverse");
-  if (a0.tri != 0 && (a0.tri < 0 || (a0.tri > 4 && a0.tri < 8) || a0.tri > 9 || a.k != 1 || a.hc != 1 || a.wc != 1 || a.up != 0 || a.n != a.cout || a.cin != a.cout ||
+  if (a0.tri != 0 && (a0.tri < 0 || (a0.tri > 5 && a0.tri < 8) || a0.tri > 9 || a.k != 1 || a.hc != 1 || a.wc != 1 || a.up != 0 || a.n != a.cout || a.cin != a.cout ||
                       a0.epi != CONV_EPI_NONE || a.partial))
     return fail(AE_EINVAL, "conv_mfma: triangular K ranges are for square dense products only");
   if (conv3_patch_usable(a0)) {

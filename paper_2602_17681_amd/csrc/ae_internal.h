@@ -187,11 +187,12 @@ struct ConvArgs {
   //   CONV_TRI_UPPER_X      x upper triangular; wanted: the outputs on and above the diagonal;
   //   CONV_TRI_UPPER_W      w upper triangular (w[n][k] = 0 for k < n); wanted: the outputs below the diagonal.
   //   CONV_TRI_UPPER_LOWER  x upper triangular, w^T lower triangular (w[n][k] = 0 for k < n): every output wanted;
+  //   CONV_TRI_UPPER_X_FULL x upper triangular; every output wanted;
   //   CONV_TRI_PAIR_*       one level of a blocked triangular inverse: all pairs of neighbouring tri_b x tri_b diagonal
   //                         blocks (r even, r+1) in one launch; only the tiles of the named off-diagonal block of
   //                         each pair are computed, over the K range of the named block:
-  //                           UPPER_K0: rows in block r, columns in block r+1, K = block r;
-  //                           LOWER_K1: rows in block r+1, columns in block r, K = block r+1.
+  //                           UPPER_K0: rows in block r, columns in block r+1, K = block r (x upper triangular: from the row on);
+  //                           LOWER_K1: rows in block r+1, columns in block r, K = block r+1 (x lower triangular: up to the row).
   //                         tri_pairs > 0 limits the launch to the first tri_pairs pairs (the rest keep their contents).
   int tri = 0;
   int tri_b = 0;
@@ -201,7 +202,7 @@ struct ConvArgs {
   int tri_d = 0;
   bool f32_mfma = false;           // dense binary32 products: not through bf16 parts
 };
-enum { CONV_TRI_NONE = 0, CONV_TRI_LOWER_UPPER = 1, CONV_TRI_UPPER_X = 2, CONV_TRI_UPPER_W = 3, CONV_TRI_UPPER_LOWER = 4,
+enum { CONV_TRI_NONE = 0, CONV_TRI_LOWER_UPPER = 1, CONV_TRI_UPPER_X = 2, CONV_TRI_UPPER_W = 3, CONV_TRI_UPPER_LOWER = 4, CONV_TRI_UPPER_X_FULL = 5,
        CONV_TRI_PAIR_UPPER_K0 = 8, CONV_TRI_PAIR_LOWER_K1 = 9 };
 enum { CONV_PLAIN = 0, CONV_UP_PHASES = 1, CONV_UP_DGRAD = 2 };
 enum { CONV_EPI_NONE = 0, CONV_EPI_MXQ = 1, CONV_EPI_RESID = 2 };
