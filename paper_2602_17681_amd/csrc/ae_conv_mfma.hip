@@ -1578,12 +1578,28 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
   const bool split_gemm = a.dtype == AE_F32 && !a0.f32_mfma && !(p.N <= 64 && p.K < 128);
   const bool dense = a.k == 1 && a.up == 0 && p.phases == 1 && p.stride == 1;
   if (split_gemm) {
-    // 256-row tiles, one workgroup per compute unit, where they fill the chip and K is long enough to outweigh their
-    // prologue and epilogue, which nothing runs beside (d = 4096: 0.63 against 0.71 ms; K = 512, 65536 x 512 outputs: no gain)
-    const int64_t tall = dense && t.bn == 128 && p.M % 256 == 0 && interior && a0.tri == 0 && a0.epi == CONV_EPI_NONE && p.K >= 1024 ? p.M / 256 * p.tiles_n : 0;
-    if (tall >= 256) {
-      p.tiles_mn = (int)tall;
-      hipLaunchKernelGGL((k_gemm_split<256, 128, 4, 2, true>), dim3((unsigned)tall), dim3(512), 0, s, p);
+    // Dense products whose tiles all lie inside the output: 128 x 128 tiles (two workgroups per compute unit), halves of them
+    // where those would leave compute units idle, or 256 x 128 (one workgroup, the cheapest per output) where K is long
+    // enough to outweigh their prologue and epilogue, which nothing runs beside.  The costs are rounds of workgroups, in
+    // units of a full round of 512 of the first kind: 256 of them 0.63, 512 halves 0.69, 256 halves 0.45, 256 tall ones 0.89.
+    // Measured (QR step, 30 products): d = 512, 768, 1024 0.71, 0.97, 1.21 ms with halves, 0.94, 1.29, 1.63 without; d = 1536 the same;
+    // d = 2048 3.66 with, 3.34 without; d = 4096 19.9 ms with tall tiles, 22.7 without.  Triangular K ranges gain from halves
+    // up to 256 tiles (d = 2048, LU step: 0.56 against 0.71 ms).
+    auto rounds = [](int64_t n, int64_t slots, double half, double full) {
+      const int64_t rem = n % slots;
+      return (double)(n / slots) * full + (rem == 0 ? 0.0 : rem <= slots / 2 ? half : full);
+    };
+    const int64_t n128 = grid.x;
+    const bool choice = dense && interior && t.bn == 128 && a0.epi == CONV_EPI_NONE;
+    const double c128 = rounds(n128, 512, 0.63, 1.0), c64 = rounds(2 * n128, 512, 0.45, 0.69);
+    const double tall = a0.tri == 0 && p.M % 256 == 0 && p.K >= 1024 ? rounds(n128 / 2, 256, 0.89, 0.89) : 1e30;
+    if (choice && tall < c128 && tall < c64) {
+      p.tiles_mn /= 2;
+      hipLaunchKernelGGL((k_gemm_split<256, 128, 4, 2, true>), dim3(grid.x / 2), dim3(512), 0, s, p);
+    } else if (choice && (a0.tri != 0 ? n128 <= 256 : c64 < c128)) {
+      p.tiles_n *= 2;
+      p.tiles_mn *= 2;
+      hipLaunchKernelGGL((k_gemm_split<128, 64, 4, 1, true>), dim3(grid.x * 2), dim3(256), 0, s, p);
     } else if (a0.epi == CONV_EPI_MXQ) hipLaunchKernelGGL((k_gemm_split<128, 128, 2, 2, true, 1>), grid, dim3(256), 0, s, p);   // (conv_epi_usable: interior)
     else if (a0.epi == CONV_EPI_RESID) hipLaunchKernelGGL((k_gemm_split<128, 128, 2, 2, true, 2>), grid, dim3(256), 0, s, p);
 #define SPLIT_LAUNCH(BNV, GM, GN, IN, CV) hipLaunchKernelGGL((k_gemm_split<128, BNV, GM, GN, IN, 0, CV>), grid, dim3(256), 0, s, p)
