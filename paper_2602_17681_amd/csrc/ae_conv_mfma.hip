@@ -1592,7 +1592,8 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
     const int64_t n128 = grid.x;
     const bool choice = dense && interior && t.bn == 128 && a0.epi == CONV_EPI_NONE;
     const double c128 = rounds(n128, 512, 0.63, 1.0), c64 = rounds(2 * n128, 512, 0.45, 0.69);
-    const double tall = a0.tri == 0 && p.M % 256 == 0 && p.K >= 1024 ? rounds(n128 / 2, 256, 0.89, 0.89) : 1e30;
+    // (not with column sums: the caller counts one block of them per 128 rows)
+    const double tall = a0.tri == 0 && !p.partial && p.M % 256 == 0 && p.K >= 1024 ? rounds(n128 / 2, 256, 0.89, 0.89) : 1e30;
     if (choice && tall < c128 && tall < c64) {
       p.tiles_mn /= 2;
       hipLaunchKernelGGL((k_gemm_split<256, 128, 4, 2, true>), dim3(grid.x / 2), dim3(512), 0, s, p);

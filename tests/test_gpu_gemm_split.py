@@ -3,6 +3,7 @@ import pytest
 import torch
 
 from paper_2602_17681_amd import binding as ae
+from parity_util import run_case
 
 pytestmark = pytest.mark.gpu
 
@@ -52,3 +53,8 @@ def test_infinities_nan_and_the_largest_values():
     ok = ref.isfinite()
     assert (got.double() - ref)[ok].abs().max() <= 1e-6 * ref[ok].abs().max()
     assert (got.double() - ref)[300][ok[300]].abs().max() <= 1e-6 * 1.7e38
+
+
+def test_column_sums_of_a_launch_of_many_tiles():
+    """Batch statistics behind a dense product large enough for the 256-row tiles: the sums stay one block per 128 rows."""
+    run_case("in:1024x16x16,conv1:512,bn,relu,conv1:2", 33, dtype="f32", seed=440, flips=True, backward=False)
