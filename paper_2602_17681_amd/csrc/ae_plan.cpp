@@ -440,7 +440,8 @@ int build_plan(const char* spec, int batch, int dtype, int bn_mode, Plan* plan) 
         }
         st.chunks_w = !wgrad_mfma_supported(wa) && wgrad_chunks_worthwhile(wa) && wgrad_chunks_supported(wa);
         // (the caller's own x and dy may lie anywhere: copied into whole aligned chunks if need be, see chunk_rows)
-        const bool reads_x = &st == &plan->steps[0], reads_dy = &st == &plan->steps.back() && !st.has_bn && !st.pool && st.act == ACT_NONE;
+        // (noise alone hands its incoming gradient on: dy may reach a layer that is not the last)
+        const bool reads_x = &st == &plan->steps[0], reads_dy = !st.has_bn && !st.pool && st.act == ACT_NONE;
         if ((st.chunks || st.chunks_w) && (cin_p != st.cin || reads_x)) st.off_xpad = take(in_elems / st.cin * cin_p * es);
         if ((st.chunks_d || st.chunks_w) && (cout_p != st.cout || reads_dy))
           plan->max_dypad_bytes = std::max(plan->max_dypad_bytes, rows * cout_p * es);

@@ -44,15 +44,16 @@ def test_tall_tiles_and_many_splits(dtype):
     run_case("in:12x64x43,conv3:20,relu,conv3:12,relu,conv1:3", 12, dtype=dtype, seed=431, flips=(dtype == "bf16"))
 
 
+@pytest.mark.parametrize("tail", ["", ",awgn"])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-def test_tensors_of_the_caller_off_a_16_byte_border(dtype):
+def test_tensors_of_the_caller_off_a_16_byte_border(dtype, tail):
     """x and dy one element into a buffer: the same results, bit for bit, as from aligned copies."""
     import torch
     from paper_2602_17681_amd import binding as ae
     td = {"f32": torch.float32, "bf16": torch.bfloat16}[dtype]
     torch.manual_seed(7)
     B = 200
-    m = ae.Model("in:24x1x1,fc:144,relu,fc:40", B, ae.DTYPES[dtype])
+    m = ae.Model("in:24x1x1,fc:144,relu,fc:40" + tail, B, ae.DTYPES[dtype])
     p = torch.randn(m.n_params, device="cuda") * 0.1
     out = []
     for off in (0, 1):
