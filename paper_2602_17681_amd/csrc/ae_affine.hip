@@ -623,6 +623,7 @@ __global__ __launch_bounds__(256) void k_tri_diag_inverse(LuSrc q, int dp, float
   __shared__ float tb[64 * 68];
   const int tid = threadIdx.x, o = blockIdx.x * 128;
   const float* src = WHICH == 0 ? q.lp : q.up;
+  const bool vec = small_vec(src, q.d);
 #pragma unroll
   for (int b0 = 0; b0 < 16; b0 += 8) {                   // 128 x 32 chunks of four columns, eight per thread in flight
     float4 v[8];
@@ -630,7 +631,7 @@ __global__ __launch_bounds__(256) void k_tri_diag_inverse(LuSrc q, int dp, float
     for (int t = 0; t < 8; ++t) {
       const int e = tid + (b0 + t) * 256, i = e >> 5, c = (e & 31) * 4;
       const bool in = o + i < q.d && o + c < q.d && (WHICH == 0 ? c < i : c + 3 > i);
-      v[t] = in ? small_load4<float>(src, q.d, o + i, o + c, true) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      v[t] = in ? small_load4<float>(src, q.d, o + i, o + c, vec) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     }
 #pragma unroll
     for (int t = 0; t < 8; ++t) {

@@ -48,3 +48,18 @@ def test_sizes(count, d, dtype):
     if ok and d > 1:
         assert rel(dup[:ok], torch.triu(dU, 1)[:ok]) <= 5e-7 and rel(dlp[:ok], torch.tril(dL, -1)[:ok]) <= 5e-7
     assert torch.equal(dup, torch.triu(dup, 1)) and torch.equal(dlp, torch.tril(dlp, -1))
+
+
+def test_full_size_inverse_takes_parameters_off_a_16_byte_border():
+    d = 256
+    torch.manual_seed(5)
+    par = [torch.randn(d, d, device="cuda") * d ** -0.5, torch.randn(d, d, device="cuda") * d ** -0.5, 0.3 * torch.randn(d, device="cuda")]
+    sign, perm = torch.ones(d, device="cuda"), torch.randperm(d, device="cuda").to(torch.int32)
+    ws = torch.empty(ae.model_lu_inverse_workspace(d), dtype=torch.uint8, device="cuda")
+    out = []
+    for off in (0, 1):
+        lp, up = (torch.empty(d * d + 1, device="cuda")[off:off + d * d].view(d, d).copy_(p) for p in par[:2])
+        ai = torch.empty(d, d, device="cuda")
+        ae.model_lu_inverse(lp, up, par[2], sign, perm, d, ai, ws)
+        out.append(ai)
+    assert torch.equal(*out)
