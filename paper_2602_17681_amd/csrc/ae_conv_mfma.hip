@@ -167,6 +167,22 @@ template <> __device__ __forceinline__ void mma_step<float>(const uint4v& a, con
   c = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[3], fb[3], c, 0, 0, 0);
 }
 
+// acc += low; true if a sum is then no finite number
+template <int MI, int NJ>
+__device__ __forceinline__ bool add_not_finite(floatx16 (&acc)[MI][NJ], const floatx16 (&low)[MI][NJ]) {
+  float z = 0.0f;
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        acc[i][j][e] += low[i][j][e];
+        z = fmaf(acc[i][j][e], 0.0f, z);         // NaN from the first infinity or NaN on
+      }
+  return z != 0.0f;
+}
+
 // Epilogue of a tile that lies wholly inside the output (no bounds checks): bias, rounding to the
 // storage type, optional column statistics of the stored value, optional ReLU, then 16-byte
 // row stores staged through this wave's LDS area.
@@ -855,9 +871,10 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
 // order, chunk c (8 of the 16 k's) of row r at 512 c + (16 r ^ 128 c): a fragment read is 1 KiB in lane order, and the 8-byte
 // stores of 8 rows x 4 quarters fall into 64 different banks.
 //
-// A part below 2^-126 may be flushed, and a value that rounds to infinity has no parts: a workgroup that meets an infinity
-// (or a value within half a bf16 step of it), or an operand row whose largest magnitude is nonzero and below 2^-96,
-// computes its tile again with the binary32 MFMA.
+// A part below 2^-126 may be flushed: a workgroup that meets an operand row whose largest magnitude is nonzero and below 2^-96
+// computes its tile again with the binary32 MFMA.  So does one with a sum that is no finite number: a value that rounds
+// to infinity has no parts, the product of two parts rounded up may lie beyond the range where the product of the values does
+// not, and where both accumulators leave it with different signs their sum would be NaN for an infinity.
 // ---------------------------------------------------------------------------
 template <int BM, int BN, int WGM, int WGN, bool INTERIOR, int EPI = 0, bool CONV = false>
 __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_split(IgemmParams p) {
@@ -1038,12 +1055,12 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
     float v = mx[i];
     v = fmaxf(v, __shfl_xor(v, 1, 64));
     v = fmaxf(v, __shfl_xor(v, 2, 64));
-    odd = odd || v >= 0x1.FFp127f || (v > 0.0f && v < 0x1p-96f);
+    odd = odd || (v > 0.0f && v < 0x1p-96f);
   }
+  odd = add_not_finite(acc, low) || odd;
   if (__syncthreads_or(odd) != 0) {
     // fragments straight from global memory: lane l holds four k's of row l % 32, the same ones on both sides
     clear(acc);
-    clear(low);
     for (int h = 0; h < 2 * KT; ++h) {           // eight k's
       const int k = (kt0 * 2 + h) * 8, tap_x = CONV ? k / p.Cin : 0;
       uint4v f[MI + NJ];
@@ -1065,12 +1082,6 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
         for (int j = 0; j < NJ; ++j) mma_step<float>(f[i], f[MI + j], acc[i][j]);
     }
   }
-#pragma unroll
-  for (int i = 0; i < MI; ++i)
-#pragma unroll
-    for (int j = 0; j < NJ; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] += low[i][j][e];
   if constexpr (!INTERIOR) {
     if (p.split_out) {
       float* __restrict__ P = p.split_out + (int64_t)tile.split * p.M * p.N;
@@ -2053,9 +2064,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 // The same for binary32: the three bfloat16 parts of k_gemm_split, cut on the way into LDS ([part][pixel][channel], read back
 // with the transposing loads), the six part products in two accumulators.  Slabs of 16 pixels, two LDS stages, one
 // barrier per slab, the split of the next slab between the MFMAs of this one.  128 x 9 x 128 weights over 65,536 pixels: 106 us
-// where the binary32 MFMA took 143 (both beside the input gradients on the other stream).  A workgroup that meets an infinity (or a
-// value within half a bf16 step of it), or a channel of its tile whose largest magnitude over its pixels is nonzero and
-// below 2^-96, computes its tile again with the binary32 MFMA.
+// where the binary32 MFMA took 143 (both beside the input gradients on the other stream).  A workgroup that meets a channel
+// of its tile whose largest magnitude over its pixels is nonzero and below 2^-96, or has a sum that is no finite number, computes its
+// tile again with the binary32 MFMA (the reasons as there).
 template <int BM, int BN>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_wgrad_split(WgradParams p) {
   constexpr int BK = 16;                         // pixels per slab
@@ -2199,8 +2210,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   bool odd = false;
   for (int i = tid; i < BM + BN; i += 256) {
     const float v = __uint_as_float(s_max[i]);
-    odd = odd || v >= 0x1.FFp127f || (v > 0.0f && v < 0x1p-96f);
+    odd = odd || (v > 0.0f && v < 0x1p-96f);
   }
+  odd = add_not_finite(acc, low) || odd;
   if (__syncthreads_or(odd) != 0) {
     float* const sA = reinterpret_cast<float*>(smem);
     float* const sB = sA + BK * LA;
@@ -2209,7 +2221,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 #pragma unroll
       for (int j = 0; j < NJ; ++j)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc[i][j][e] = low[i][j][e] = 0.0f;
+        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
     ma = m_begin + (unsigned)(tid / A_TPR);
     mb = m_begin + (unsigned)(tid / B_TPR);
     for (int kt = 0; kt < KT; ++kt) {
@@ -2224,12 +2236,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
       __syncthreads();
     }
   }
-#pragma unroll
-  for (int i = 0; i < MI; ++i)
-#pragma unroll
-    for (int j = 0; j < NJ; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] += low[i][j][e];
   wgrad_store_chunks<4, BM, BN>(p, acc, split_id, tm, tn, wm, wn, lane);
 }
 

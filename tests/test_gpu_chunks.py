@@ -91,3 +91,22 @@ def test_gradients_by_parts_of_extreme_size():
         err = torch.where(ok, got - ref, 0.0).norm(dim=1) / torch.where(ok, ref, 0.0).norm(dim=1).clamp_min(1e-300)
         # 600 terms in binary32: about sqrt(600 / 16) roundings of 2^-24
         assert err.max().item() <= 1e-6, err.max()
+
+
+def test_weight_gradients_beyond_the_range():
+    import torch
+    from paper_2602_17681_amd import binding as ae
+    B, cin, cout = 600, 64, 96
+    m = ae.Model("in:%dx1x1,fc:%d" % (cin, cout), B, ae.DTYPES["f32"])
+    p, y, g = torch.zeros(m.n_params, device="cuda"), torch.empty(B, cout, device="cuda"), torch.empty(m.n_params, device="cuda")
+    torch.manual_seed(10)
+    x, dy = torch.randn(B, cin, device="cuda").abs() * 2.0 ** 70, torch.randn(B, cout, device="cuda").abs() * 2.0 ** 70
+    for one in (False, True):
+        if one:
+            dy.zero_()
+            # 1.996 x 2^127; the leading parts of both round up, to 2.008 x 2^127
+            x[9], dy[9] = (1 + 2.0 ** -8 + 2.0 ** -20) * 2.0 ** 63, 1.98829 * 2.0 ** 64
+        m.model_forward(p, x, 10.0, 1, y)
+        m.model_backward(p, x, dy, g)
+        got, ref = g[:cin * cout].view(cout, cin).double(), dy.double().t() @ x.double()
+        assert ((got - ref).abs() <= 2.0 ** -23 * ref).all() if one else got.isposinf().all()

@@ -55,6 +55,15 @@ def test_infinities_nan_and_the_largest_values():
     assert (got.double() - ref)[300][ok[300]].abs().max() <= 1e-6 * 1.7e38
 
 
+def test_sums_beyond_the_range():
+    e, a = rand(130, 512, seed=8).abs() * 2.0 ** 70, rand(512, 512, seed=9).abs() * 2.0 ** 70
+    assert product(e, a).isposinf().all()
+    e.zero_()
+    e[:, 9], a[:, 9] = (1 + 2.0 ** -8 + 2.0 ** -20) * 2.0 ** 63, 1.98829 * 2.0 ** 64       # 1.996 x 2^127; both round up to 2.008 x 2^127
+    ref = e.double() @ a.double().t()
+    assert ((product(e, a).double() - ref).abs() <= 2.0 ** -23 * ref).all()
+
+
 def test_column_sums_of_a_launch_of_many_tiles():
     """Batch statistics behind a dense product large enough for the 256-row tiles: the sums stay one block per 128 rows."""
     run_case("in:1024x16x16,conv1:512,bn,relu,conv1:2", 33, dtype="f32", seed=440, flips=True, backward=False)
