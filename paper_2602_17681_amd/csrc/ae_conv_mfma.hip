@@ -167,6 +167,14 @@ template <> __device__ __forceinline__ void mma_step<float>(const uint4v& a, con
   c = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[3], fb[3], c, 0, 0, 0);
 }
 
+// Smallest magnitude seen, zeros aside, as twice its bits less one (a zero wraps to the largest number).  The parts of a
+// binary32 value are exact while its last place is one of a bfloat16 denormal, 2^-133: from 2^-110 on.
+__device__ __forceinline__ void track_smallest(unsigned& lo, const uint4v& v) {
+  lo = min(min(lo, v[0] * 2u - 1u), v[1] * 2u - 1u);
+  lo = min(min(lo, v[2] * 2u - 1u), v[3] * 2u - 1u);
+}
+__device__ __forceinline__ bool parts_inexact(unsigned lo) { return lo < 2u * ((127u - 110u) << 23) - 1u; }
+
 // acc += low; true if a sum is then no finite number
 template <int MI, int NJ>
 __device__ __forceinline__ bool add_not_finite(floatx16 (&acc)[MI][NJ], const floatx16 (&low)[MI][NJ]) {
@@ -871,8 +879,11 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
 // order, chunk c (8 of the 16 k's) of row r at 512 c + (16 r ^ 128 c): a fragment read is 1 KiB in lane order, and the 8-byte
 // stores of 8 rows x 4 quarters fall into 64 different banks.
 //
-// A part below 2^-126 may be flushed: a workgroup that meets an operand row whose largest magnitude is nonzero and below 2^-96
-// computes its tile again with the binary32 MFMA.  So does one with a sum that is no finite number: a value that rounds
+// A workgroup that meets an operand below 2^-110 other than zero, whose last part would end below the smallest bfloat16
+// denormal, computes its tile again with the binary32 MFMA: such a value may be all there is of an output, whatever else its row
+// holds.  (The bf16 MFMA flushes no denormals: 256-term sums of 2^-63 x 2^-63 products come out to 1.2 x 2^-24 of the sum of
+// magnitudes, as at any size.  The check is 6 VALU instructions per 16 bytes:
+// 1.4 % of a QR step of d = 4096, 20.7 -> 21.0 ms, nothing seen elsewhere.)  So does one with a sum that is no finite number: a value that rounds
 // to infinity has no parts, the product of two parts rounded up may lie beyond the range where the product of the values does
 // not, and where both accumulators leave it with different signs their sum would be NaN for an infinity.
 // ---------------------------------------------------------------------------
@@ -948,9 +959,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
     }
   };
   uint4v r[AC + BC];
-  float mx[AC + BC];
-#pragma unroll
-  for (int i = 0; i < AC + BC; ++i) mx[i] = 0.0f;
+  unsigned lo = ~0u;
   auto load = [&](int i) {                       // (past the last slab: values that nobody uses)
     r[i] = __builtin_amdgcn_raw_buffer_load_b128(i < AC ? rX : rW, off[i], 0, 0);
     off[i] += 64;
@@ -960,8 +969,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
   auto split = [&](int stage, int i) {           // the four values of one load: three 8-byte stores
     char* const dst = st + stage + (i < AC ? i * (RSTEP * 32) : 3 * PA + (i - AC) * (RSTEP * 32));
     const float4v f = __builtin_bit_cast(float4v, r[i]);
-    mx[i] = fmaxf(fmaxf(mx[i], fabsf(f[0])), fabsf(f[1]));
-    mx[i] = fmaxf(fmaxf(mx[i], fabsf(f[2])), fabsf(f[3]));
+    track_smallest(lo, r[i]);
     float r0 = f[0], r1 = f[1], r2 = f[2], r3 = f[3];
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
@@ -1048,16 +1056,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
   }
   read_b(cur, 1); read_a(cur, 1); read_b(cur, 2); read_a(cur, 2);
   mma(0, 0); mma(0, 1); mma(1, 0); mma(1, 1); mma(0, 2); mma(2, 0);
-  // a row is loaded by four neighbouring lanes
-  bool odd = false;
-#pragma unroll
-  for (int i = 0; i < AC + BC; ++i) {
-    float v = mx[i];
-    v = fmaxf(v, __shfl_xor(v, 1, 64));
-    v = fmaxf(v, __shfl_xor(v, 2, 64));
-    odd = odd || (v > 0.0f && v < 0x1p-96f);
-  }
-  odd = add_not_finite(acc, low) || odd;
+  const bool odd = add_not_finite(acc, low) || parts_inexact(lo);
   if (__syncthreads_or(odd) != 0) {
     // fragments straight from global memory: lane l holds four k's of row l % 32, the same ones on both sides
     clear(acc);
@@ -2064,9 +2063,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 // The same for binary32: the three bfloat16 parts of k_gemm_split, cut on the way into LDS ([part][pixel][channel], read back
 // with the transposing loads), the six part products in two accumulators.  Slabs of 16 pixels, two LDS stages, one
 // barrier per slab, the split of the next slab between the MFMAs of this one.  128 x 9 x 128 weights over 65,536 pixels: 106 us
-// where the binary32 MFMA took 143 (both beside the input gradients on the other stream).  A workgroup that meets a channel
-// of its tile whose largest magnitude over its pixels is nonzero and below 2^-96, or has a sum that is no finite number, computes its
-// tile again with the binary32 MFMA (the reasons as there).
+// where the binary32 MFMA took 143 (both beside the input gradients on the other stream).  A workgroup that meets an operand
+// below 2^-110 other than zero, or has a sum that is no finite number, computes its tile again with the binary32 MFMA (the reasons
+// as there).
 template <int BM, int BN>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_wgrad_split(WgradParams p) {
   constexpr int BK = 16;                         // pixels per slab
@@ -2077,7 +2076,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   constexpr int PA = BK * LA * 2, PB = BK * LB * 2, STAGE = 3 * (PA + PB);
   static_assert(2 * STAGE >= 2 * BK * (LA + LB) * 4, "the binary32 loop fits into the same memory");
   __shared__ __attribute__((aligned(16))) char smem[2 * STAGE];
-  __shared__ unsigned s_max[BM + BN];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
@@ -2109,15 +2107,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     v = __builtin_amdgcn_raw_buffer_load_b128(rX, ok ? (pix * (unsigned)p.chunks + (unsigned)cc) * 16u : kOob, 0, 0);
   };
   uint4v ra[AC], rb[BC];
-  float mxa[4] = {}, mxb[4] = {};                // this thread's four channels of either side
-  auto split = [&](char* dst, int plane, const uint4v& v, float (&mx)[4]) {
-    const float4v f = __builtin_bit_cast(float4v, v);
-    float x[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      mx[t] = fmaxf(mx[t], fabsf(f[t]));
-      x[t] = f[t];
-    }
+  unsigned lo = ~0u;
+  auto split = [&](char* dst, int plane, const uint4v& v) {
+    track_smallest(lo, v);
+    float4v x = __builtin_bit_cast(float4v, v);
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
       const uint32_t w0 = pack_bf16(x[0], x[1]), w1 = pack_bf16(x[2], x[3]);
@@ -2130,9 +2123,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   char* const stb = smem + 3 * PA + ((tid / B_TPR) * LB + (tid % B_TPR) * 4) * 2;
   auto refill = [&](int buf) {                   // registers into a stage, then the slab after that into the registers
 #pragma unroll
-    for (int i = 0; i < AC; ++i) { split(sta + buf * STAGE + i * (256 / A_TPR) * LA * 2, PA, ra[i], mxa); load_a(ra[i], i); }
+    for (int i = 0; i < AC; ++i) { split(sta + buf * STAGE + i * (256 / A_TPR) * LA * 2, PA, ra[i]); load_a(ra[i], i); }
 #pragma unroll
-    for (int i = 0; i < BC; ++i) { split(stb + buf * STAGE + i * (256 / B_TPR) * LB * 2, PB, rb[i], mxb); load_b(rb[i], i); }
+    for (int i = 0; i < BC; ++i) { split(stb + buf * STAGE + i * (256 / B_TPR) * LB * 2, PB, rb[i]); load_b(rb[i], i); }
     ma += BK;
     mb += BK;
   };
@@ -2198,21 +2191,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   }
   read((KT & 1) ^ 1);
   products();
-  // the largest magnitude of every channel of the tile
-  for (int i = tid; i < BM + BN; i += 256) s_max[i] = 0u;
-  __syncthreads();
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    atomicMax(&s_max[(tid % A_TPR) * 4 + t], __float_as_uint(mxa[t]));
-    atomicMax(&s_max[BM + (tid % B_TPR) * 4 + t], __float_as_uint(mxb[t]));
-  }
-  __syncthreads();
-  bool odd = false;
-  for (int i = tid; i < BM + BN; i += 256) {
-    const float v = __uint_as_float(s_max[i]);
-    odd = odd || (v > 0.0f && v < 0x1p-96f);
-  }
-  odd = add_not_finite(acc, low) || odd;
+  const bool odd = add_not_finite(acc, low) || parts_inexact(lo);
   if (__syncthreads_or(odd) != 0) {
     float* const sA = reinterpret_cast<float*>(smem);
     float* const sB = sA + BK * LA;

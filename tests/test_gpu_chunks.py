@@ -93,6 +93,24 @@ def test_gradients_by_parts_of_extreme_size():
         assert err.max().item() <= 1e-6, err.max()
 
 
+@pytest.mark.parametrize("rest", [-109, -112, -130])
+def test_every_weight_gradient_to_its_own_terms(rest):
+    """Binary32: a large output gradient meets zero inputs; all there is of a weight's are products of its tiny ones."""
+    import torch
+    from paper_2602_17681_amd import binding as ae
+    B, cin, cout = 256, 64, 96
+    m = ae.Model("in:%dx1x1,fc:%d" % (cin, cout), B, ae.DTYPES["f32"])
+    p, y, g = torch.zeros(m.n_params, device="cuda"), torch.empty(B, cout, device="cuda"), torch.empty(m.n_params, device="cuda")
+    torch.manual_seed(11)
+    x, dy = torch.randn(B, cin, device="cuda") * 2.0 ** 60, torch.randn(B, cout, device="cuda")
+    dy[1:] *= 2.0 ** rest
+    x[0] = 0.0
+    m.model_forward(p, x, 10.0, 1, y)
+    m.model_backward(p, x, dy, g)
+    err = (g[:cin * cout].view(cout, cin).double() - dy.double().t() @ x.double()).abs() / (dy.double().abs().t() @ x.double().abs())
+    assert err.max().item() <= 16 * 2.0 ** -24, err.max()          # 256 terms in binary32: sqrt(256) roundings of 2^-24
+
+
 def test_weight_gradients_beyond_the_range():
     import torch
     from paper_2602_17681_amd import binding as ae

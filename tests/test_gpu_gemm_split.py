@@ -41,6 +41,18 @@ def test_rows_of_extreme_size(scale):
     assert err <= 1e-6, err
 
 
+@pytest.mark.parametrize("first,rest,w", [(0, -109, 60), (0, -112, 60), (0, -126, 60), (0, -140, 60), (-100, -130, 60), (-63, -63, -63)])
+def test_every_output_to_its_own_terms(first, rest, w):
+    """Rows whose large first element meets zeros: all there is of an output are products of their tiny elements."""
+    e, a = rand(130, 256, seed=10), rand(256, 256, seed=11) * 2.0 ** w
+    e[:, :1] *= 2.0 ** first
+    e[:, 1:] *= 2.0 ** rest
+    a[:, 0] = 0.0
+    err = (product(e, a).double() - e.double() @ a.double().t()).abs() / (e.double().abs() @ a.double().abs().t())
+    # 256 terms in binary32: sqrt(256) roundings of 2^-24
+    assert err.max().item() <= 16 * 2.0 ** -24, err.max()
+
+
 def test_infinities_nan_and_the_largest_values():
     e, a = rand(384, 512, seed=6).round() + 0.5, rand(512, 512, seed=7).round() + 0.5      # bf16 values: their lower parts are zero
     e[5, 17] = float("inf")
