@@ -217,10 +217,15 @@ namespace {
 bool conv_chunks_worthwhile(const ConvArgs& a) {
   return a.k != 1 || a.cin > 128 || (int64_t)a.n * a.hc * a.wc * a.cin * a.cout > (1 << 21);
 }
-// (a weight gradient over a handful of pixels: the direct kernel's serial walk over them is shorter than a slab's way
+// (a small weight gradient over a handful of pixels: the direct kernel's serial walk over them is shorter than a slab's way
 // through LDS, and nothing is padded: 100 -> 50 -> 100 channels x 1 row, forward and backward, 48 against 53 us; 16 rows of
-// 48 -> 80 -> 48 channels 69 against 57, 64 rows of 100 -> 50 -> 100 channels 114 against 63)
-bool wgrad_chunks_worthwhile(const WgradArgs& a) { return (int64_t)a.n * a.hc * a.wc > 8; }
+// 48 -> 80 -> 48 channels 69 against 57, 64 rows of 100 -> 50 -> 100 channels 114 against 63.  Its threads divide 64-bit indices
+// for every product, so a large one is slow at any number of rows; backward pass of c -> c -> c channels in binary32, direct
+// against chunks: 1024 x 1 row 91 and 94 us, 2048 x 1 row 111 and 97, 1024 x 8 105 and 92, 4096 x 8 673 and 160)
+bool wgrad_chunks_worthwhile(const WgradArgs& a) {
+  const int64_t rows = (int64_t)a.n * a.hc * a.wc;
+  return rows > 8 || rows * a.cout * a.cin * a.k * a.k > (1 << 20);
+}
 ConvArgs chunks_form(ConvArgs a, int geom) {
   if (geom == CONV_UP_PHASES) a.up = 1;
   a.geom = geom;

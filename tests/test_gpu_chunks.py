@@ -68,6 +68,22 @@ def test_tensors_of_the_caller_off_a_16_byte_border(dtype, tail):
     assert all(torch.equal(a, b) for a, b in zip(*out))
 
 
+@pytest.mark.parametrize("c,batch,kernel", [(256, 8, "direct"), (1024, 1, "direct"), (1024, 2, "chunks"), (2048, 8, "chunks"), (192, 9, "chunks")])
+def test_weight_gradient_over_a_few_rows(c, batch, kernel):
+    import torch
+    from paper_2602_17681_amd import binding as ae
+    torch.manual_seed(12)
+    m = ae.Model("in:%dx1x1,fc:%d" % (c, c), batch, ae.DTYPES["f32"])
+    p, x, dy = torch.zeros(m.n_params, device="cuda"), torch.randn(batch, c, device="cuda"), torch.randn(batch, c, device="cuda")
+    y, g = torch.empty(batch, c, device="cuda"), torch.empty(m.n_params, device="cuda")
+    m.model_timing_enable(True)
+    m.model_forward(p, x, 10.0, 1, y)
+    m.model_backward(p, x, dy, g)
+    assert any(r["name"].endswith("bwd.wgrad_" + kernel) for r in m.model_timing_read())
+    ref = dy.double().t() @ x.double()
+    assert ((g[:c * c].view(c, c).double() - ref).norm() / ref.norm()).item() <= 2e-7      # at most nine terms in binary32
+
+
 def test_gradients_by_parts_of_extreme_size():
     """Binary32: a channel whose gradients are all tiny, and an infinity among the activations."""
     import torch
