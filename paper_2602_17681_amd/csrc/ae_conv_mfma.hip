@@ -599,6 +599,45 @@ __device__ __forceinline__ bool igemm_k_range(const IgemmParams& p, int64_t m0, 
   return true;
 }
 
+// Accumulators that are NaN, as bits (element e of tile (i, j): bit 16 (i NJ + j) + e); 0 after one fused multiply-add per
+// accumulator where all are finite.
+template <int MI, int NJ>
+__device__ __forceinline__ uint64_t nan_bits(const floatx16 (&acc)[MI][NJ]) {
+  static_assert(MI * NJ <= 4, "64 bits");
+  float z = 0.0f;
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) z = fmaf(acc[i][j][e], 0.0f, z);
+  uint64_t bits = 0;
+  if (z != 0.0f) {
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) bits |= (uint64_t)(acc[i][j][e] != acc[i][j][e]) << (16 * (i * NJ + j) + e);
+  }
+  return bits;
+}
+// those accumulators replaced by value(i, j, e)
+template <int MI, int NJ, typename VALUE>
+__device__ __forceinline__ void replace_bits(floatx16 (&acc)[MI][NJ], uint64_t bits, VALUE value) {
+  while (bits != 0) {
+    const int t = __ffsll((unsigned long long)bits) - 1;
+    bits &= bits - 1;
+    const float v = value(t / (16 * NJ), (t >> 4) % NJ, t & 15);
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[i][j][e] = 16 * (i * NJ + j) + e == t ? v : acc[i][j][e];
+  }
+}
+
 // INTERIOR: the host guarantees M % BM == 0, N % BN == 0, 16-byte aligned rows, no sigmoid, no
 // auxiliary copy and no activation together with statistics, so the epilogue needs no checks.
 // DMA: the slabs go from global memory straight into LDS (buffer loads with the LDS
@@ -1964,6 +2003,33 @@ __device__ __forceinline__ void wgrad_store_chunks(const WgradParams& p, const f
   }
 }
 
+// Gradients that are NaN summed again over the pixels whose tap lies inside the image: outside it the kernels multiply by zero,
+// NaN for an infinite dY (at the pace of one thread per weight; nothing but infinities and NaN gets here)
+template <typename T, int BM, int BN>
+__device__ __forceinline__ void wgrad_resum_nan(const WgradParams& p, floatx16 (&acc)[BM / 64][BN / 64], unsigned m_begin, unsigned m_end,
+                                                int tm, int tn, int wm, int wn, int lane) {
+  constexpr int EPC = 16 / (int)sizeof(T), MI = BM / 64, NJ = BN / 64;
+  const uint64_t bits = p.ksz > 1 ? nan_bits(acc) : 0;
+  replace_bits<MI, NJ>(acc, bits, [&](int i, int j, int e) {
+    const int co = tm * BM + wm * (BM / 2) + i * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
+    const int col = tn * BN + wn * (BN / 2) + j * 32 + (lane & 31), q = col / EPC;
+    const int tap = q / p.chunks, ci = (q - tap * p.chunks) * EPC + col % EPC, pad = (p.ksz - 1) >> 1;
+    const int dh = tap / p.ksz - pad, dw = tap % p.ksz - pad, Hin = p.Hc >> p.up, Win = p.Wc >> p.up;
+    if (co >= p.Cout || tap >= p.ksz * p.ksz || ci >= p.Cin || (dh == 0 && dw == 0)) return __builtin_nanf("");
+    const T* const x = reinterpret_cast<const T*>(p.x) + ci;
+    const T* const dy = reinterpret_cast<const T*>(p.dy) + co;
+    float v = 0.0f;
+    for (unsigned m = m_begin; m < m_end; ++m) {
+      const unsigned t = m / (unsigned)p.Wc, n = t / (unsigned)p.Hc;
+      const int hh = (int)(t - n * (unsigned)p.Hc) + dh, ww = (int)(m - t * (unsigned)p.Wc) + dw;
+      if (hh < 0 || hh >= p.Hc || ww < 0 || ww >= p.Wc) continue;
+      const int64_t pix = ((int64_t)n * Hin + (hh >> p.up)) * Win + (ww >> p.up);
+      v = fmaf(Store<T>::ld(dy + (int64_t)m * p.dy_chunks * EPC), Store<T>::ld(x + pix * p.chunks * EPC), v);
+    }
+    return v;
+  });
+}
+
 // The same for any channel counts.  Pixels of x and dY are stored as whole 16-byte chunks (zeros behind the channels),
 // and the columns of the product are the chunks of all taps in a row, (tap, chunk), cut into tiles of BN wherever a tile
 // ends: a loader thread moves the same column chunk in every pass, so its tap is fixed for the whole loop and the tile
@@ -2057,6 +2123,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     __syncthreads();
   }
 
+  wgrad_resum_nan<T, BM, BN>(p, acc, m_begin, m_end, tm, tn, wm, wn, lane);
   wgrad_store_chunks<EPC, BM, BN>(p, acc, split, tm, tn, wm, wn, lane);
 }
 
@@ -2214,6 +2281,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
       wgrad_compute<float, MI, NJ, BK, LA, LB>(&sA[wm * WM], &sB[wn * WN], lane, acc);
       __syncthreads();
     }
+    wgrad_resum_nan<float, BM, BN>(p, acc, m_begin, m_end, tm, tn, wm, wn, lane);
   }
   wgrad_store_chunks<4, BM, BN>(p, acc, split_id, tm, tn, wm, wn, lane);
 }

@@ -144,3 +144,31 @@ def test_weight_gradients_beyond_the_range():
         m.model_backward(p, x, dy, g)
         got, ref = g[:cin * cout].view(cout, cin).double(), dy.double().t() @ x.double()
         assert ((got - ref).abs() <= 2.0 ** -23 * ref).all() if one else got.isposinf().all()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("where", ["dy", "x"])
+@pytest.mark.parametrize("spec", ["in:12x5x9,conv3:20,conv3:7", "in:12x1x70,conv3:36,conv3:150", "in:20x3x4,up2,conv3:24,up2,conv3:9", "in:168x4x3,conv3:40,conv3:10", "in:60x5x6,conv3:100,conv3:68"])
+def test_infinities_at_the_border(spec, where, dtype):
+    """Nothing but positive numbers and one infinity: no sum is NaN, and the ones that are infinite are those in which 1e30
+    in its place makes itself felt.  The infinite values lie in an image's corner."""
+    import torch
+    from paper_2602_17681_amd import binding as ae
+    td, B = {"f32": torch.float32, "bf16": torch.bfloat16}[dtype], 2
+    m = ae.Model(spec, B, ae.DTYPES[dtype])
+    torch.manual_seed(14)
+    p = 0.1 * torch.rand(m.n_params, device="cuda") + 0.01
+    x, dy = (torch.rand(B, *c, device="cuda") + 0.5 for c in (m.in_shape, m.out_shape))
+    out = []
+    for big in (float("inf"), 1e30):
+        v = dict(p=p.clone(), x=x.to(td), dy=dy.to(td))
+        v[where].view(-1)[0] = big
+        y, g = torch.empty(B, *m.out_shape, device="cuda", dtype=td), torch.empty(m.n_params, device="cuda")
+        m.model_forward(v["p"], v["x"], 10.0, 1, y)
+        m.model_backward(v["p"], v["x"], v["dy"], g)
+        out.append((y.double(), g.double()))
+    for got, ref in zip(*out):
+        assert not got.isnan().any() and torch.equal(got.isinf(), ref > 1e20), (int(got.isnan().sum()), int(got.isinf().sum()), int((ref > 1e20).sum()))
+        ok = got.isfinite()
+        # the re-summed outputs add their terms one by one: at most 1512 in binary32, then a rounding to the format per layer
+        assert ((got - ref)[ok].abs() <= (1e-4 if dtype == "f32" else 2.0 ** -6) * ref[ok]).all()
