@@ -881,6 +881,30 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
 #undef IGEMM_STORE
 #undef IGEMM_COMPUTE
 
+  if constexpr (CHUNKS) {
+    // A tap outside the image is a product with zero, NaN for an infinite weight: such an output of a row at the border is
+    // summed again over the taps inside (at the pace of one thread per output; nothing but infinities and NaN gets here).
+    const uint64_t bits = p.ksz > 1 ? nan_bits(acc) : 0;
+    constexpr int EPC = 16 / ES;
+    replace_bits(acc, bits, [&](int i, int j, int e) {
+      const int64_t m = m0 + wm * WM + i * 32 + (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3);
+      const int n = n0 + wn * WN + j * 32 + (lane & 31);
+      const unsigned mu = (unsigned)m, t = mu / (unsigned)p.Wc, img = t / (unsigned)p.Hc;
+      const int h0 = (int)(t - img * (unsigned)p.Hc) * p.stride - pad_h, w0 = (int)(mu - t * (unsigned)p.Wc) * p.stride - pad_w;
+      if (m >= p.M || n >= p.N || (h0 >= 0 && w0 >= 0 && h0 + p.ksz <= p.Hv && w0 + p.ksz <= p.Wv)) return __builtin_nanf("");
+      const T* const x = reinterpret_cast<const T*>(p.x) + (int64_t)img * Hin * Win * p.Cin;
+      const T* const wr = reinterpret_cast<const T*>(p.w) + ((int64_t)phase * p.N + n) * p.K;
+      const int k_end = min((kt0 + KT) * BK, p.K);
+      float v = 0.0f;
+      for (int k = kt0 * BK; k < k_end; k += EPC) {            // (a chunk lies in one tap)
+        const int tap = k / p.Cin, ci = k - tap * p.Cin, r = tap / p.ksz, hh = h0 + r, ww = w0 + tap - r * p.ksz;
+        if (hh < 0 || hh >= p.Hv || ww < 0 || ww >= p.Wv) continue;
+        const T* const px = x + ((int64_t)(hh >> p.up) * Win + (ww >> p.up)) * p.Cin + ci;
+        for (int c = 0; c < EPC; ++c) v = fmaf(Store<T>::ld(px + c), Store<T>::ld(wr + k + c), v);
+      }
+      return v;
+    });
+  }
   if constexpr (!INTERIOR) {
     if (p.split_out) {
       float* __restrict__ P = p.split_out + (int64_t)split * p.M * p.N;

@@ -147,22 +147,27 @@ def test_weight_gradients_beyond_the_range():
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("where", ["dy", "x"])
+@pytest.mark.parametrize("where", ["first weight", "second weight", "dy", "x"])
 @pytest.mark.parametrize("spec", ["in:12x5x9,conv3:20,conv3:7", "in:12x1x70,conv3:36,conv3:150", "in:20x3x4,up2,conv3:24,up2,conv3:9", "in:168x4x3,conv3:40,conv3:10", "in:60x5x6,conv3:100,conv3:68"])
 def test_infinities_at_the_border(spec, where, dtype):
     """Nothing but positive numbers and one infinity: no sum is NaN, and the ones that are infinite are those in which 1e30
-    in its place makes itself felt.  The infinite values lie in an image's corner."""
+    in its place makes itself felt.  The infinite weights are corner taps, the infinite values lie in an image's corner."""
     import torch
     from paper_2602_17681_amd import binding as ae
+    import workloads as wl
     td, B = {"f32": torch.float32, "bf16": torch.bfloat16}[dtype], 2
     m = ae.Model(spec, B, ae.DTYPES[dtype])
+    weights = [e for e in wl.param_layout(spec)[0] if e["kind"] == "w"]
     torch.manual_seed(14)
     p = 0.1 * torch.rand(m.n_params, device="cuda") + 0.01
     x, dy = (torch.rand(B, *c, device="cuda") + 0.5 for c in (m.in_shape, m.out_shape))
     out = []
     for big in (float("inf"), 1e30):
         v = dict(p=p.clone(), x=x.to(td), dy=dy.to(td))
-        v[where].view(-1)[0] = big
+        if "weight" in where:
+            v["p"][weights[where == "second weight"]["offset"]] = big          # channels 0 -> 0, tap (0, 0)
+        else:
+            v[where].view(-1)[0] = big
         y, g = torch.empty(B, *m.out_shape, device="cuda", dtype=td), torch.empty(m.n_params, device="cuda")
         m.model_forward(v["p"], v["x"], 10.0, 1, y)
         m.model_backward(v["p"], v["x"], v["dy"], g)
