@@ -329,6 +329,25 @@ __device__ __forceinline__ void small_mma(floatx16& c, int k0, int k1, A a, B b)
 }
 // element e of a lane's accumulator: row 8 (e / 4) + 4 (lane / 32) + e % 4, column lane % 32
 __device__ __forceinline__ int small_row(int lane, int e) { return (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3); }
+// sums that are NaN replaced by value(e): a zero of a triangle meets an infinity in a tile's K range, where the sum over the
+// triangle alone need not be NaN (nothing but infinities and NaN gets there; one fused multiply-add per sum otherwise)
+template <typename VALUE>
+__device__ __forceinline__ void small_resum_nan(floatx16& c, VALUE value) {
+  float z = 0.0f;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) z = fmaf(c[e], 0.0f, z);
+  if (z == 0.0f) return;
+  unsigned bits = 0;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) bits |= (unsigned)(c[e] != c[e]) << e;
+  while (bits != 0) {
+    const int t = __ffs(bits) - 1;
+    bits &= bits - 1;
+    const float v = value(t);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) c[e] = e == t ? v : c[e];
+  }
+}
 // operands in LDS: four k's of one row, or one column of four rows
 __device__ __forceinline__ void small_row4(const float* p, float (&v)[4]) {
   const float4 f = *reinterpret_cast<const float4*>(p);
@@ -449,6 +468,7 @@ __device__ __forceinline__ void small_tri_diag(const SmallTri& x, int tid) {
   float col[16];
   const int b0 = tid & ~15, jj = tid & 15;
   if (tid < 128) {
+    float z = 0.0f;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       float acc = 0.0f;
@@ -456,6 +476,17 @@ __device__ __forceinline__ void small_tri_diag(const SmallTri& x, int tid) {
       for (int k = 0; k < i; ++k) acc = fmaf(x.at(b0 + i, b0 + k), col[k], acc);
       const float dv = x.at(b0 + i, b0 + i);
       col[i] = i < jj ? 0.0f : (i == jj ? 1.0f / dv : -acc / dv);
+      z = fmaf(acc, 0.0f, z);
+    }
+    if (z != 0.0f) {                                   // again from row jj on: a zero above it may have met an infinity
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        float acc = 0.0f;
+#pragma unroll
+        for (int k = 0; k < i; ++k) acc = k >= jj ? fmaf(x.at(b0 + i, b0 + k), col[k], acc) : acc;
+        const float dv = x.at(b0 + i, b0 + i);
+        col[i] = i < jj ? 0.0f : (i == jj ? 1.0f / dv : -acc / dv);
+      }
     }
   }
   __syncthreads();
@@ -481,6 +512,17 @@ __device__ __forceinline__ void small_tri_merge16(const SmallTri& x, float* tb, 
 #pragma unroll
       for (int i = 0; i < 2; ++i) acc[i][j] = fmaf(x.at(o1 + tr + 8 * i, o0 + k), v, acc[i][j]);
     }
+  // (as small_resum_nan: a zero of a triangle may have met an infinity)
+  auto odd = [&]() { return fmaf(acc[0][0], 0.0f, fmaf(acc[0][1], 0.0f, fmaf(acc[1][0], 0.0f, acc[1][1] * 0.0f))) != 0.0f; };
+  if (odd()) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        acc[i][j] = 0.0f;
+        for (int k = tc + 8 * j; k < 16; ++k) acc[i][j] = fmaf(x.at(o1 + tr + 8 * i, o0 + k), x.at(o0 + k, o0 + tc + 8 * j), acc[i][j]);
+      }
+  }
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -497,6 +539,15 @@ __device__ __forceinline__ void small_tri_merge16(const SmallTri& x, float* tb, 
 #pragma unroll
       for (int j = 0; j < 2; ++j) acc[i][j] = fmaf(a, tp[k * 16 + tc + 8 * j], acc[i][j]);
     }
+  if (odd()) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        acc[i][j] = 0.0f;
+        for (int k = 0; k <= tr + 8 * i; ++k) acc[i][j] = fmaf(x.at(o1 + tr + 8 * i, o1 + k), tp[k * 16 + tc + 8 * j], acc[i][j]);
+      }
+  }
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -521,6 +572,11 @@ __device__ __forceinline__ void small_tri_merge(const SmallTri& x, float* tb, in
 #pragma unroll
                 for (int t = 0; t < 4; ++t) { const int kk = k + 4 * h + t; const float u = x.at(o0 + kk, o0 + c); v[t] = kk >= c ? u : 0.0f; }
               });
+    small_resum_nan(acc, [&](int e) {
+      float v = 0.0f;
+      for (int k = c; k < B; ++k) v = fmaf(x.at(o1 + ti * 32 + small_row(lane, e), o0 + k), x.at(o0 + k, o0 + c), v);
+      return v;
+    });
 #pragma unroll
     for (int e = 0; e < 16; ++e) tp[(ti * 32 + small_row(lane, e)) * LT + c] = acc[e];
   }
@@ -536,6 +592,12 @@ __device__ __forceinline__ void small_tri_merge(const SmallTri& x, float* tb, in
 #pragma unroll
                 for (int t = 0; t < 4; ++t) v[t] = tp[(k + 4 * h + t) * LT + c];
               });
+    small_resum_nan(acc, [&](int e) {
+      const int row = ti * 32 + small_row(lane, e);
+      float v = 0.0f;
+      for (int k = 0; k <= row; ++k) v = fmaf(x.at(o1 + row, o1 + k), tp[k * LT + c], v);
+      return v;
+    });
 #pragma unroll
     for (int e = 0; e < 16; ++e) x.at(o1 + ti * 32 + small_row(lane, e), o0 + c) = -acc[e];   // (M21 was last read before the barrier)
   }

@@ -63,3 +63,25 @@ def test_full_size_inverse_takes_parameters_off_a_16_byte_border():
         ae.model_lu_inverse(lp, up, par[2], sign, perm, d, ai, ws)
         out.append(ai)
     assert torch.equal(*out)
+
+
+@pytest.mark.parametrize("which", ["L", "U"])
+@pytest.mark.parametrize("d,i,j", [(2, 1, 0), (16, 15, 8), (24, 20, 3), (40, 39, 1), (64, 63, 32), (100, 99, 50), (128, 5, 2), (128, 127, 64), (128, 70, 20), (256, 5, 2), (256, 127, 64), (256, 250, 130)])
+def test_an_infinity_stays_in_its_columns_and_rows(d, i, j, which):
+    """An infinite entry (i, j) of L enters columns up to j of its inverse, one (j, i) of U rows up to j: the others are what
+    they are with a zero in its place."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    rnd = lambda *s: torch.randn(*s, device="cuda", generator=g)      # noqa: E731
+    lp, up, ls = rnd(d, d) * d ** -0.5, rnd(d, d) * d ** -0.5, 0.3 * rnd(d)
+    sign, perm = torch.ones(d, device="cuda"), torch.randperm(d, device="cuda", generator=g).to(torch.int32)
+    out = []
+    for value in (float("inf"), 0.0):
+        (lp if which == "L" else up.t())[i, j] = value
+        ai = torch.empty(d, d, device="cuda")
+        if d <= 128:
+            ae.model_lu_inverse_batch(lp, up, ls, sign, perm, 1, d, ai)
+        else:
+            ae.model_lu_inverse(lp, up, ls, sign, perm, d, ai, torch.empty(ae.model_lu_inverse_workspace(d), dtype=torch.uint8, device="cuda"))
+        out.append(ai[:, perm.long() > j] if which == "L" else ai[j + 1:])
+    assert torch.equal(*out) or ((out[0] - out[1]).norm() <= 1e-6 * out[1].norm()).item()
