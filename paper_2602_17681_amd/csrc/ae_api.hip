@@ -284,7 +284,8 @@ int forward_conv(ae_model* m, int si, Step& st, const float* params, const void*
     w = st.wpack;
   }
   const bool pad_x = st.xpad && chunk_copy(P, in, st.cin);
-  if (pad_x && (st.chunks || !m->inference))     // kept until the weight gradient has read it
+  // kept until the weight gradient has read it (the backward pass copies the caller's x of its own call)
+  if (pad_x && (st.chunks || (!m->inference && si > 0)))
     TIMED(si, "fwd.pad_channels", 0.0, 2.0 * in_el * es,
           launch_pad_channels(in, st.xpad, (int64_t)P.batch * st.hin * st.win, st.cin, P.dtype, s));
   const bool second_pass = st.has_bn || st.pool;

@@ -68,6 +68,23 @@ def test_tensors_of_the_caller_off_a_16_byte_border(dtype, tail):
     assert all(torch.equal(a, b) for a, b in zip(*out))
 
 
+@pytest.mark.parametrize("spec,pads", [("in:10x1x1,fc:12", 0), ("in:10x1x1,fc:1200", 1), ("in:8x1x1,fc:10,relu,fc:12", 1)])
+def test_no_copy_that_nothing_reads(spec, pads):
+    """Inputs with rows that are no whole chunks: copied in the forward pass where its kernel or, for a layer behind the first, the weight gradient reads the copy."""
+    import torch
+    from paper_2602_17681_amd import binding as ae
+    m = ae.Model(spec, 200, ae.DTYPES["f32"])
+    p, x, dy = torch.rand(m.n_params, device="cuda"), torch.rand(200, *m.in_shape, device="cuda"), torch.rand(200, *m.out_shape, device="cuda")
+    y, g = torch.empty_like(dy), torch.empty(m.n_params, device="cuda")
+    m.model_timing_enable(True)
+    m.model_forward(p, x, 10.0, 1, y)
+    assert sum(r["launches"] for r in m.model_timing_read() if r["name"].endswith("fwd.pad_channels")) == pads
+    m.model_backward(p, x, dy, g)
+    if ",relu" not in spec:
+        ref = dy.flatten(1).double().t() @ x.flatten(1).double()
+        assert ((g[:ref.numel()].view_as(ref).double() - ref).norm() / ref.norm()).item() <= 1e-6      # 200 terms in binary32
+
+
 @pytest.mark.parametrize("c,batch,kernel", [(256, 8, "direct"), (1024, 1, "direct"), (1024, 2, "chunks"), (2048, 8, "chunks"), (192, 9, "chunks")])
 def test_weight_gradient_over_a_few_rows(c, batch, kernel):
     import torch
