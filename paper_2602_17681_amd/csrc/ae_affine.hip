@@ -369,12 +369,12 @@ __global__ __launch_bounds__(256) void k_lu_small_compose(const float* __restric
   const int nb = (d + 31) >> 5, dp = nb * 32, m = blockIdx.x / nb, rb = blockIdx.x - m * nb, tid = threadIdx.x;
   const LuSrc q = small_src(lp, up, log_s, sign_s, d, m);
   if (tid < 32) pr[tid] = rb * 32 + tid < d ? small_perm(perm + (int64_t)m * d, d, rb * 32 + tid) : -1;
-  if (tid < d) dg[tid] = q.sign[tid] * expf(q.log_s[tid]);
+  if (tid < 128) dg[tid] = tid < d ? q.sign[tid] * expf(q.log_s[tid]) : 0.0f;
   __syncthreads();
   small_stage<float>(lm, 32, dp, q.lp, d, 0, small_vec(q.lp, d), [&](int i) { return pr[i]; },
                      [&](float v, int i, int c) { return c < pr[i] ? v : (c == pr[i] ? 1.0f : 0.0f); });
   small_stage<float>(um, dp, dp, q.up, d, 0, small_vec(q.up, d), [](int i) { return i; },
-                     [&](float v, int i, int c) { return c > i ? v : (c == i && i < d ? dg[i] : 0.0f); });
+                     [](float v, int i, int c) { return c > i ? v : 0.0f; });
   __syncthreads();
   const int j = tid >> 6, lane = tid & 63, col = j * 32 + (lane & 31), h = lane >> 5;
   if (j >= nb) return;
@@ -390,6 +390,17 @@ __global__ __launch_bounds__(256) void k_lu_small_compose(const float* __restric
   } else
     small_mma(acc, 0, 32 * (j + 1), [&](int k, float (&v)[4]) { small_row4(lm + (lane & 31) * kSmallLd + k + 4 * h, v); },
             [&](int k, float (&v)[4]) { small_col4(um + (k + 4 * h) * kSmallLd + col, v); });
+  // The term with the diagonal of U + diag s, by far the largest of a result of which it is one, last and in a fused multiply-add: the
+  // binary32 MFMA rounds at twice the last place (largest deviation over 24 matrices of 128: 1.6e-6 of the root mean square with it
+  // in the product, 0.8e-6 this way, 1.0e-6 one by one; 2-norm 5.3e-8, 4.7e-8, 5.7e-8)
+#pragma unroll
+  for (int e = 0; e < 16; ++e) acc[e] = fmaf(lm[small_row(lane, e) * kSmallLd + col], dg[col], acc[e]);
+  small_resum_nan(acc, [&](int e) {
+    const float* const l = lm + small_row(lane, e) * kSmallLd;
+    float v = 0.0f;
+    for (int t = 0; t < col; ++t) v = fmaf(l[t], um[t * kSmallLd + col], v);
+    return fmaf(l[col], dg[col], v);
+  });
   T* o = out + (int64_t)m * d * d;
 #pragma unroll
   for (int e = 0; e < 16; ++e) {

@@ -65,6 +65,21 @@ def test_full_size_inverse_takes_parameters_off_a_16_byte_border():
     assert torch.equal(*out)
 
 
+@pytest.mark.parametrize("d", [33, 64, 97, 128])
+def test_the_large_term_is_rounded_once(d):
+    """Small off-diagonal entries beside a diagonal of ones: the results with the diagonal in them are off by their own rounding."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    n, eye = 64, torch.eye(d, device="cuda", dtype=torch.float64)
+    lp, up = (0.02 * torch.randn(n, d, d, device="cuda", generator=g) for _ in range(2))
+    perm = torch.arange(d, device="cuda", dtype=torch.int32).repeat(n, 1)
+    a = torch.empty(n, d, d, device="cuda")
+    ae.model_lu_compose_batch(lp, up, torch.zeros(n, d, device="cuda"), torch.ones(n, d, device="cuda"), perm, n, d, a)
+    ref = torch.diagonal((torch.tril(lp.double(), -1) + eye) @ (torch.triu(up.double(), 1) + eye).contiguous(), dim1=1, dim2=2)
+    err = ((torch.diagonal(a, dim1=1, dim2=2).double() - ref).abs() / ref.abs()).max().item()
+    assert err <= 1.1 * 2.0 ** -24, err * 2 ** 24        # half a last place; the other terms add up to 1e-2 of the result
+
+
 @pytest.mark.parametrize("which", ["L", "U"])
 @pytest.mark.parametrize("d,i,j", [(2, 1, 0), (16, 15, 8), (24, 20, 3), (40, 39, 1), (64, 63, 32), (100, 99, 50), (128, 5, 2), (128, 127, 64), (128, 70, 20), (256, 5, 2), (256, 127, 64), (256, 250, 130)])
 def test_an_infinity_stays_in_its_columns_and_rows(d, i, j, which):
