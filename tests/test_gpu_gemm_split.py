@@ -76,6 +76,58 @@ def test_sums_beyond_the_range():
     assert ((product(e, a).double() - ref).abs() <= 2.0 ** -23 * ref).all()
 
 
+# few tiles and a long K (split K, ragged tiles); tiles that all lie inside; behind an upsample as four phases and with the
+# stride-2 input gradient; behind an upsample with few tiles (no phases)
+@pytest.mark.parametrize("wide,hw,up,cout", [(64, (6, 10), 0, 96), (32, (32, 64), 0, 128), (32, (64, 32), 1, 64), (48, (3, 5), 1, 64)])
+def test_convolutions_of_operands_that_the_parts_cannot_hold(wide, hw, up, cout):
+    """A sample of tiny inputs and one of tiny output gradients, then infinities: every sample's outputs and input gradients and
+    the tiny sample's own weight gradients to their size.  The first layer's weight gradients of input channel n are those
+    of sample n, the only one with something in that channel."""
+    B, (h, w) = 4, hw
+    m = ae.Model("in:%dx%dx%d,conv1:%d,%sconv3:%d" % (B, h, w, wide, "up2," if up else "", cout), B, ae.DTYPES["f32"])
+    torch.manual_seed(13)
+    w1, w2 = torch.randn(wide, B, 1, 1), torch.randn(cout, wide, 3, 3)
+    p = torch.cat([w1.flatten(), torch.zeros(wide), w2.flatten(), torch.zeros(cout)]).cuda()
+    x = torch.eye(B).view(B, B, 1, 1) * torch.rand(B, B, h, w)
+    dy = torch.randn(B, cout, h << up, w << up)
+    x[1] *= 2.0 ** -120
+    dy[2] *= 2.0 ** -120
+    dy[[0, 2, 3], 5] = 0.0
+    rel = lambda a, r: ((a - r).norm() / r.norm()).item()      # noqa: E731
+    # sums of at most 32,768 terms in binary32: sqrt(32768 / 16) roundings of 2^-24 of the growing sum, 2.7e-6
+    tol = 3e-6
+    for infinite in ("", "x", "dy"):
+        xi, dyi = x.clone(), dy.clone()
+        if infinite == "x":
+            xi[3, 3, 0, 0] = float("inf")
+        if infinite == "dy":
+            dyi[0, 7, 0, 0] = float("inf")
+        r1, r2 = w1.double().requires_grad_(), w2.double().requires_grad_()
+        z = torch.nn.functional.conv2d(xi.double(), r1)
+        ry = torch.nn.functional.conv2d(torch.nn.functional.interpolate(z, scale_factor=2) if up else z, r2, padding=1)
+        ry.backward(dyi.double())
+        y, g = torch.empty(dy.shape, device="cuda"), torch.empty(m.n_params, device="cuda")
+        m.model_timing_enable(True)
+        m.model_forward(p, xi.cuda(), 10.0, 1, y)
+        m.model_backward(p, xi.cuda(), dyi.cuda(), g)
+        names = [r["name"] for r in m.model_timing_read()]
+        y, g1, g2 = y.cpu().double(), g[:w1.numel()].view(w1.shape).cpu().double(), g[w1.numel() + wide:-cout].view(w2.shape).cpu().double()
+        sound = [n for n in range(B) if infinite != "x" or n != 3]
+        err = [rel(y[n], ry[n]) for n in sound]
+        if infinite != "dy":
+            err += [rel(g1[:, n], r1.grad[:, n]) for n in sound]
+        if infinite == "":
+            err += [rel(g2[5], r2.grad[5]), rel(g2, r2.grad)]
+        if infinite == "x":
+            assert torch.equal(y[3].isfinite(), ry[3].isfinite()) and torch.equal(g1[:, 3].isfinite(), r1.grad[:, 3].isfinite())
+        if infinite == "dy":
+            rows = [c for c in range(cout) if c != 7]
+            err += [rel(g2[rows], r2.grad[rows]), rel(g2[5], r2.grad[5])]
+            assert not g2[7].isfinite().all()
+        assert max(err) <= tol and all(e == e for e in err), (infinite, err)
+    assert any("fwd.conv_mfma" in n for n in names) and any("bwd.dgrad_mfma" in n for n in names) and any("bwd.wgrad_chunks" in n for n in names)
+
+
 def test_column_sums_of_a_launch_of_many_tiles():
     """Batch statistics behind a dense product large enough for the 256-row tiles: the sums stay one block per 128 rows."""
     run_case("in:1024x16x16,conv1:512,bn,relu,conv1:2", 33, dtype="f32", seed=440, flips=True, backward=False)
