@@ -1246,10 +1246,10 @@ constexpr int passes_before(int passes, int tap) {
 }
 constexpr int vm_imm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0F70; }   // s_waitcnt vmcnt(n) only
 
-template <typename T, int BN, int WGM, int WGN, int W, bool INTERIOR, int EPI = 0>
+template <int BN, int WGM, int WGN, int W, bool INTERIOR, int EPI = 0>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_conv3_patch(IgemmParams p) {
   static_assert(WGM * WGN == 4, "four wavefronts per workgroup");
-  constexpr int ES = (int)sizeof(T);
+  constexpr int ES = 2;
   constexpr int BM = 256, BKB = 64;
   constexpr int TH = BM / W, PW = W + 2, PC = (TH + 2) * PW;
   constexpr int PASSES = patch_passes(W);
@@ -1369,7 +1369,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
       Conv3Reads<0, MI>::run(f1a, aa, 32u);                                                                  \
     }                                                                                                        \
     lds_wait_tie_a<MI, MI>(f0a);                                                                             \
-    mma_group<T, MI, NJ>(f0a, bq[(TAP) % 3][0], acc);                                                        \
+    mma_group<bf16_t, MI, NJ>(f0a, bq[(TAP) % 3][0], acc);                                                   \
     __builtin_amdgcn_sched_barrier(0);                                                                       \
     lds_wait_tie_a<0, MI>(f1a);                                                                              \
     if (!(last && (TAP) == 8)) {                                                                             \
@@ -1378,7 +1378,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
       Conv3Reads<0, MI>::run(f0a, aa, 0u);                                                                   \
     }                                                                                                        \
     __builtin_amdgcn_sched_barrier(0);                                                                       \
-    mma_group<T, MI, NJ>(f1a, bq[(TAP) % 3][1], acc);                                                        \
+    mma_group<bf16_t, MI, NJ>(f1a, bq[(TAP) % 3][1], acc);                                                   \
     __builtin_amdgcn_sched_barrier(0);                                                                       \
   }
   // (the last slab is a copy of its own with `last` a constant: where one body served both, the compiler's wait
@@ -1406,7 +1406,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 #undef WFRAG_LOAD
 #undef PATCH_DMA
   __syncthreads();                               // every wave is done with the operands: the epilogue reuses the memory
-  igemm_epilogue<T, BM, BN, WGM, WGN, INTERIOR, EPI>(acc, p, smem, sRed, m0, n0, (int64_t)tile_m);
+  igemm_epilogue<bf16_t, BM, BN, WGM, WGN, INTERIOR, EPI>(acc, p, smem, sRed, m0, n0, (int64_t)tile_m);
 }
 
 struct IgemmTile { int bm, bn, bkb; };
@@ -1602,19 +1602,19 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
     p.strips = a.wc > 64 ? a.wc / 64 : 1;
     p.log_wt = 6;                                // strips of 64 pixels
     dim3 pgrid((unsigned)((p.M / 256) * p.tiles_n));
-#define PATCH_LAUNCH_E(T, WV, E)                                                                             \
+#define PATCH_LAUNCH_E(WV, E)                                                                                \
   do {                                                                                                      \
-    if (bn == 128) hipLaunchKernelGGL((k_conv3_patch<T, 128, 2, 2, WV, true, E>), pgrid, dim3(256), 0, s, p); \
-    else hipLaunchKernelGGL((k_conv3_patch<T, 64, 4, 1, WV, true, E>), pgrid, dim3(256), 0, s, p);           \
+    if (bn == 128) hipLaunchKernelGGL((k_conv3_patch<128, 2, 2, WV, true, E>), pgrid, dim3(256), 0, s, p);    \
+    else hipLaunchKernelGGL((k_conv3_patch<64, 4, 1, WV, true, E>), pgrid, dim3(256), 0, s, p);              \
   } while (0)
     if (a0.comp_mode != 0) {            // (conv_comp_blocks: bfloat16 only)
-      if (a0.comp_mode == 1) { if (a.wc == 16) PATCH_LAUNCH_E(bf16_t, 16, 3); else if (a.wc == 32) PATCH_LAUNCH_E(bf16_t, 32, 3); else PATCH_LAUNCH_E(bf16_t, 64, 3); }
-      else { if (a.wc == 16) PATCH_LAUNCH_E(bf16_t, 16, 4); else if (a.wc == 32) PATCH_LAUNCH_E(bf16_t, 32, 4); else PATCH_LAUNCH_E(bf16_t, 64, 4); }
+      if (a0.comp_mode == 1) { if (a.wc == 16) PATCH_LAUNCH_E(16, 3); else if (a.wc == 32) PATCH_LAUNCH_E(32, 3); else PATCH_LAUNCH_E(64, 3); }
+      else { if (a.wc == 16) PATCH_LAUNCH_E(16, 4); else if (a.wc == 32) PATCH_LAUNCH_E(32, 4); else PATCH_LAUNCH_E(64, 4); }
       return launch_status("conv3_patch");
     }
-    if (a.wc == 16) PATCH_LAUNCH_E(bf16_t, 16, 0);
-    else if (a.wc == 32) PATCH_LAUNCH_E(bf16_t, 32, 0);
-    else PATCH_LAUNCH_E(bf16_t, 64, 0);
+    if (a.wc == 16) PATCH_LAUNCH_E(16, 0);
+    else if (a.wc == 32) PATCH_LAUNCH_E(32, 0);
+    else PATCH_LAUNCH_E(64, 0);
 #undef PATCH_LAUNCH_E
     return launch_status("conv3_patch");
   }
@@ -1710,16 +1710,15 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
     return launch_status("conv_mfma_comp");
   }
   if (a0.epi != CONV_EPI_NONE) {
-    // (conv_epi_usable: interior tiles, BN = 128, no split)
-#define IGEMM_LAUNCH_EPI(T, BMV, E) hipLaunchKernelGGL((k_igemm<T, BMV, 128, 2, 2, 64, true, true, E>), grid, dim3(256), 0, s, p)
+    // (conv_epi_usable: interior tiles, BN = 128, no split; binary32 went to k_gemm_split above: a dense product of 128 columns or more)
+    if (a.dtype != AE_BF16) return fail(AE_EINVAL, "conv_mfma: no such epilogue on the binary32 MFMA");
+#define IGEMM_LAUNCH_EPI(BMV, E) hipLaunchKernelGGL((k_igemm<bf16_t, BMV, 128, 2, 2, 64, true, true, E>), grid, dim3(256), 0, s, p)
     if (t.bn == 256) {
       if (a0.epi == CONV_EPI_MXQ) hipLaunchKernelGGL((k_igemm<bf16_t, 256, 256, 2, 4, 64, true, true, 1>), grid, dim3(512), 0, s, p);
       else hipLaunchKernelGGL((k_igemm<bf16_t, 256, 256, 2, 4, 64, true, true, 2>), grid, dim3(512), 0, s, p);
-    } else if (a.dtype == AE_BF16) {
-      if (t.bm == 256) { if (a0.epi == CONV_EPI_MXQ) IGEMM_LAUNCH_EPI(bf16_t, 256, 1); else IGEMM_LAUNCH_EPI(bf16_t, 256, 2); }
-      else { if (a0.epi == CONV_EPI_MXQ) IGEMM_LAUNCH_EPI(bf16_t, 128, 1); else IGEMM_LAUNCH_EPI(bf16_t, 128, 2); }
     } else {
-      if (a0.epi == CONV_EPI_MXQ) IGEMM_LAUNCH_EPI(float, 128, 1); else IGEMM_LAUNCH_EPI(float, 128, 2);
+      if (t.bm == 256) { if (a0.epi == CONV_EPI_MXQ) IGEMM_LAUNCH_EPI(256, 1); else IGEMM_LAUNCH_EPI(256, 2); }
+      else { if (a0.epi == CONV_EPI_MXQ) IGEMM_LAUNCH_EPI(128, 1); else IGEMM_LAUNCH_EPI(128, 2); }
     }
 #undef IGEMM_LAUNCH_EPI
     return launch_status("conv_mfma_epi");
@@ -1875,22 +1874,21 @@ __device__ __forceinline__ void wgrad_compute(const T* sa, const T* sb, int lane
   }
 }
 
-template <typename T, int BM, int BN, bool POW2>
+template <int BM, int BN, bool POW2>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_wgrad(WgradParams p) {
-  constexpr int ES = (int)sizeof(T);
-  constexpr int EPC = 16 / ES;                   // elements per 16-byte chunk
-  constexpr int BK = ES == 2 ? 32 : 16;          // pixels per slab
-  // LDS row strides in elements (64 banks).  bf16: +64 bytes: 32 lanes of a transposing
-  // load touch 4 pixel rows x 64 bytes, which then tile the 256-byte bank space; fp32:
-  // +128 bytes, so that the two pixel rows a 64-lane 4-byte read touches are 32 banks apart.
+  constexpr int ES = 2;
+  constexpr int EPC = 8;                         // elements per 16-byte chunk
+  constexpr int BK = 32;                         // pixels per slab
+  // LDS row strides in elements (64 banks): +64 bytes, so that the 4 pixel rows x 64 bytes that 32 lanes of a
+  // transposing load touch tile the 256-byte bank space.
   constexpr int LPAD = 32;
   constexpr int LA = BM + LPAD, LB = BN + LPAD;
   constexpr int WM = BM / 2, WN = BN / 2;
   constexpr int MI = WM / 32, NJ = WN / 32;
   constexpr int A_TPR = BM / EPC, B_TPR = BN / EPC;  // 16-byte chunks per pixel row
   constexpr int A_CHUNKS = BK * A_TPR / 256, B_CHUNKS = BK * B_TPR / 256;
-  __shared__ __attribute__((aligned(16))) T sA[2][BK * LA];
-  __shared__ __attribute__((aligned(16))) T sB[2][BK * LB];
+  __shared__ __attribute__((aligned(16))) bf16_t sA[2][BK * LA];
+  __shared__ __attribute__((aligned(16))) bf16_t sB[2][BK * LB];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
@@ -1957,7 +1955,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
       *reinterpret_cast<uint4v*>(&sB[BUF][(id / B_TPR) * LB + (id % B_TPR) * EPC]) = RB[i];                  \
     }                                                                                                        \
   }
-#define WGRAD_COMPUTE(BUF) wgrad_compute<T, MI, NJ, BK, LA, LB>(&sA[BUF][wm * WM], &sB[BUF][wn * WN], lane, acc)
+#define WGRAD_COMPUTE(BUF) wgrad_compute<bf16_t, MI, NJ, BK, LA, LB>(&sA[BUF][wm * WM], &sB[BUF][wn * WN], lane, acc)
 
   floatx16 acc[MI][NJ];
 #pragma unroll
@@ -2061,11 +2059,11 @@ __device__ __forceinline__ void wgrad_resum_nan(const WgradParams& p, floatx16 (
 // of each empty; a 3-channel image fills 0.6 tiles instead of 9.  Chunks past the end read zeros and are not stored.
 // Measured (bf16, 24 x 36 x 60 pixels, 80 x 9 x 48 weights): 22 us = 160 TFLOP/s, where a thread per weight that walks the
 // pixels alone took 4.5 ms.
-template <typename T, int BM, int BN>
+template <int BM, int BN>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_wgrad_chunks(WgradParams p) {
-  constexpr int ES = (int)sizeof(T);
-  constexpr int EPC = 16 / ES;
-  constexpr int BK = ES == 2 ? 32 : 16;          // pixels per slab
+  constexpr int ES = 2;
+  constexpr int EPC = 8;
+  constexpr int BK = 32;                         // pixels per slab
   constexpr int LPAD = 32;                       // (as in k_wgrad)
   constexpr int LA = BM + LPAD, LB = BN + LPAD;
   constexpr int WM = BM / 2, WN = BN / 2;
@@ -2073,8 +2071,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   constexpr int A_TPR = BM / EPC, B_TPR = BN / EPC;
   constexpr int A_CHUNKS = BK * A_TPR / 256, B_CHUNKS = BK * B_TPR / 256;
   static_assert(256 % A_TPR == 0 && 256 % B_TPR == 0, "a thread keeps its column chunk");
-  __shared__ __attribute__((aligned(16))) T sA[2][BK * LA];
-  __shared__ __attribute__((aligned(16))) T sB[2][BK * LB];
+  __shared__ __attribute__((aligned(16))) bf16_t sA[2][BK * LA];
+  __shared__ __attribute__((aligned(16))) bf16_t sB[2][BK * LB];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
@@ -2137,17 +2135,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   __syncthreads();
   for (int kt = 0; kt < KT; kt += 2) {
     if (kt + 2 < KT) load(ra0, rb0);
-    wgrad_compute<T, MI, NJ, BK, LA, LB>(&sA[0][wm * WM], &sB[0][wn * WN], lane, acc);
+    wgrad_compute<bf16_t, MI, NJ, BK, LA, LB>(&sA[0][wm * WM], &sB[0][wn * WN], lane, acc);
     if (kt + 1 < KT) store(1, ra1, rb1);
     __syncthreads();
     if (kt + 1 >= KT) break;
     if (kt + 3 < KT) load(ra1, rb1);
-    wgrad_compute<T, MI, NJ, BK, LA, LB>(&sA[1][wm * WM], &sB[1][wn * WN], lane, acc);
+    wgrad_compute<bf16_t, MI, NJ, BK, LA, LB>(&sA[1][wm * WM], &sB[1][wn * WN], lane, acc);
     if (kt + 2 < KT) store(0, ra0, rb0);
     __syncthreads();
   }
 
-  wgrad_resum_nan<T, BM, BN>(p, acc, m_begin, m_end, tm, tn, wm, wn, lane);
+  wgrad_resum_nan<bf16_t, BM, BN>(p, acc, m_begin, m_end, tm, tn, wm, wn, lane);
   wgrad_store_chunks<EPC, BM, BN>(p, acc, split, tm, tn, wm, wn, lane);
 }
 
@@ -2160,7 +2158,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 template <int BM, int BN>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_wgrad_split(WgradParams p) {
   constexpr int BK = 16;                         // pixels per slab
-  constexpr int LA = BM + 32, LB = BN + 32;      // (as in k_wgrad, for both element sizes)
+  constexpr int LA = BM + 32, LB = BN + 32;      // (parts: as in k_wgrad; binary32: +128 bytes, the two pixel rows of a 64-lane 4-byte read are 32 banks apart)
   constexpr int WM = BM / 2, WN = BN / 2, MI = WM / 32, NJ = WN / 32;
   constexpr int A_TPR = BM / 4, B_TPR = BN / 4;
   constexpr int AC = BK * A_TPR / 256, BC = BK * B_TPR / 256;
@@ -2316,10 +2314,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 // address arithmetic is one add, one compare and one select per 16-byte load.  The output
 // gradient advances through the scalar offset of the buffer load.  Every slab is full (the
 // host makes the splits multiples of BK).
-template <typename T, int BM, int BN, int BK>
+template <int BM, int BN, int BK>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_wgrad_rows(WgradParams p) {
-  constexpr int ES = (int)sizeof(T);
-  constexpr int EPC = 16 / ES;
+  constexpr int ES = 2;
+  constexpr int EPC = 8;
   constexpr int LPAD = 32;
   constexpr int LA = BM + LPAD, LB = BN + LPAD;
   constexpr int WM = BM / 2, WN = BN / 2;
@@ -2327,8 +2325,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   constexpr int A_TPR = BM / EPC, B_TPR = BN / EPC;
   constexpr int A_CHUNKS = BK * A_TPR / 256, B_CHUNKS = BK * B_TPR / 256;
   static_assert(A_CHUNKS >= 1 && B_CHUNKS >= 1, "slab too small for 256 loader threads");
-  __shared__ __attribute__((aligned(16))) T sA[2][BK * LA];
-  __shared__ __attribute__((aligned(16))) T sB[2][BK * LB];
+  __shared__ __attribute__((aligned(16))) bf16_t sA[2][BK * LA];
+  __shared__ __attribute__((aligned(16))) bf16_t sB[2][BK * LB];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
@@ -2395,7 +2393,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
       *reinterpret_cast<uint4v*>(&sB[BUF][(id / B_TPR) * LB + (id % B_TPR) * EPC]) = RB[i];                  \
     }                                                                                                        \
   }
-#define WGRAD_COMPUTE(BUF) wgrad_compute<T, MI, NJ, BK, LA, LB>(&sA[BUF][wm * WM], &sB[BUF][wn * WN], lane, acc)
+#define WGRAD_COMPUTE(BUF) wgrad_compute<bf16_t, MI, NJ, BK, LA, LB>(&sA[BUF][wm * WM], &sB[BUF][wn * WN], lane, acc)
 
   floatx16 acc[MI][NJ];
 #pragma unroll
@@ -2779,12 +2777,12 @@ __global__ __launch_bounds__(256) void k_wgrad_reduce(const float* __restrict__ 
 
 struct WgradPlan { int bm, bn, bk, tiles_m, tiles_n, splits, rows_per_split, row3; };   // bk = 0: generic kernel; row3: three taps per workgroup
 
-WgradPlan plan_wgrad(int cout, int cin, int k, int64_t rows, int wc, int es, int hc = 0, int up = 0) {
+WgradPlan plan_wgrad(int cout, int cin, int k, int64_t rows, int wc, int hc = 0, int up = 0) {
   WgradPlan w;
   w.row3 = 0;
   // an upsampled 3x3 layer in its phase form (row3 = 2): eight groups (a, b, u) of two taps over the stored image
   const int hs = hc >> 1, ws = wc >> 1;
-  if (es == 2 && k == 3 && up == 1 && hc > 0 && !(hc & 1) && !(wc & 1) && (ws % 64 == 0 || (ws >= 8 && 64 % ws == 0)) &&
+  if (k == 3 && up == 1 && hc > 0 && !(hc & 1) && !(wc & 1) && (ws % 64 == 0 || (ws >= 8 && 64 % ws == 0)) &&
       ((int64_t)hs * ws) % 64 == 0) {
     w.row3 = 2;
     w.bm = cout % 128 == 0 ? 128 : 64;
@@ -2804,7 +2802,7 @@ WgradPlan plan_wgrad(int cout, int cin, int k, int64_t rows, int wc, int es, int
     w.splits = (int)((prow + rps - 1) / rps);
     return w;
   }
-  if (es == 2 && k == 3 && hc > 0 && (wc % 64 == 0 || (wc >= 16 && 64 % wc == 0)) && ((int64_t)hc * wc) % 64 == 0) {
+  if (k == 3 && hc > 0 && (wc % 64 == 0 || (wc >= 16 && 64 % wc == 0)) && ((int64_t)hc * wc) % 64 == 0) {
     w.row3 = 1;
     w.bm = cout % 128 == 0 ? 128 : 64;
     w.bn = 64;
@@ -2833,8 +2831,7 @@ WgradPlan plan_wgrad(int cout, int cin, int k, int64_t rows, int wc, int es, int
   if (splits > max_splits) splits = max_splits;
   if (splits < 1) splits = 1;
   // row-slab kernel: slabs of bk pixels that never straddle an image row
-  const int bk_big = es == 2 ? 64 : 32;
-  w.bk = wc % bk_big == 0 ? bk_big : (wc % (bk_big / 2) == 0 ? bk_big / 2 : 0);
+  w.bk = wc % 64 == 0 ? 64 : wc % 32 == 0 ? 32 : 0;
   const int gran = w.bk ? w.bk : 32;
   int64_t rps = (rows + splits - 1) / splits;
   rps = (rps + gran - 1) / gran * gran;
@@ -2847,7 +2844,7 @@ WgradPlan plan_wgrad(int cout, int cin, int k, int64_t rows, int wc, int es, int
 
 bool wgrad_mfma_supported(const WgradArgs& a) {
   if (a.dtype != AE_BF16 || a.cin % 64 != 0 || a.cout % 64 != 0) return false;   // (binary32: launch_wgrad_chunks)
-  const int64_t es = (int64_t)dtype_size(a.dtype);
+  const int64_t es = 2;
   if ((int64_t)a.n * a.hc * a.wc * a.cout * es >= 0x7FFFFFFF) return false;                    // 32-bit buffer offsets
   if ((int64_t)a.n * (a.hc >> a.up) * (a.wc >> a.up) * a.cin * es >= 0x7FFFFFFF) return false;
   const int64_t rows = (int64_t)a.n * a.hc * a.wc;
@@ -2857,19 +2854,19 @@ bool wgrad_mfma_supported(const WgradArgs& a) {
 // does launch_wgrad_mfma run this layer in the phase form of an upsampled convolution (4/9 of the multiply-adds)?
 bool wgrad_mfma_up_phases(const WgradArgs& a) {
   if (!wgrad_mfma_supported(a)) return false;
-  return plan_wgrad(a.cout, a.cin, a.k, (int64_t)a.n * a.hc * a.wc, a.wc, (int)dtype_size(a.dtype), a.hc, a.up).row3 == 2;
+  return plan_wgrad(a.cout, a.cin, a.k, (int64_t)a.n * a.hc * a.wc, a.wc, a.hc, a.up).row3 == 2;
 }
 
 int64_t wgrad_mfma_workspace_floats(const WgradArgs& a) {
   const int64_t rows = (int64_t)a.n * a.hc * a.wc;
-  const WgradPlan w = plan_wgrad(a.cout, a.cin, a.k, rows, a.wc, (int)dtype_size(a.dtype), a.hc, a.up);
+  const WgradPlan w = plan_wgrad(a.cout, a.cin, a.k, rows, a.wc, a.hc, a.up);
   return (int64_t)w.splits * a.cout * a.cin * (w.row3 == 2 ? 16 : a.k * a.k);
 }
 
 int launch_wgrad_mfma(const WgradArgs& a, float* workspace, hipStream_t s) {
   if (!wgrad_mfma_supported(a)) return fail(AE_EINVAL, "wgrad_mfma: shape not supported");
   const int64_t rows = (int64_t)a.n * a.hc * a.wc;
-  const WgradPlan w = plan_wgrad(a.cout, a.cin, a.k, rows, a.wc, (int)dtype_size(a.dtype), a.hc, a.up);
+  const WgradPlan w = plan_wgrad(a.cout, a.cin, a.k, rows, a.wc, a.hc, a.up);
   WgradParams p;
   // a 1x1 layer that needs no split: the partial layout [co][ci] is the canonical one
   const bool direct = w.splits == 1 && a.k == 1;
@@ -2892,24 +2889,19 @@ int launch_wgrad_mfma(const WgradArgs& a, float* workspace, hipStream_t s) {
   const int64_t blocks = (int64_t)w.splits * w.tiles_m * w.tiles_n * (w.row3 == 2 ? 8 : w.row3 ? 3 : a.k * a.k);
   if (blocks > 0x7FFFFFFF) return fail(AE_EINVAL, "wgrad_mfma: grid too large");
   dim3 grid((unsigned)blocks);
-#define WGRAD_LAUNCH_P(T, P2)                                                                           \
-  do {                                                                                                  \
-    if (w.bm == 128 && w.bn == 128) hipLaunchKernelGGL((k_wgrad<T, 128, 128, P2>), grid, dim3(256), 0, s, p); \
-    else if (w.bm == 128) hipLaunchKernelGGL((k_wgrad<T, 128, 64, P2>), grid, dim3(256), 0, s, p);      \
-    else if (w.bn == 128) hipLaunchKernelGGL((k_wgrad<T, 64, 128, P2>), grid, dim3(256), 0, s, p);      \
-    else hipLaunchKernelGGL((k_wgrad<T, 64, 64, P2>), grid, dim3(256), 0, s, p);                        \
+#define WGRAD_LAUNCH(P2)                                                                             \
+  do {                                                                                               \
+    if (w.bm == 128 && w.bn == 128) hipLaunchKernelGGL((k_wgrad<128, 128, P2>), grid, dim3(256), 0, s, p); \
+    else if (w.bm == 128) hipLaunchKernelGGL((k_wgrad<128, 64, P2>), grid, dim3(256), 0, s, p);      \
+    else if (w.bn == 128) hipLaunchKernelGGL((k_wgrad<64, 128, P2>), grid, dim3(256), 0, s, p);      \
+    else hipLaunchKernelGGL((k_wgrad<64, 64, P2>), grid, dim3(256), 0, s, p);                        \
   } while (0)
-#define WGRAD_LAUNCH(T)                      \
-  do {                                       \
-    if (pow2) WGRAD_LAUNCH_P(T, true);       \
-    else WGRAD_LAUNCH_P(T, false);           \
-  } while (0)
-#define WGRAD_ROWS(T, BKV)                                                                              \
-  do {                                                                                                  \
-    if (w.bm == 128 && w.bn == 128) hipLaunchKernelGGL((k_wgrad_rows<T, 128, 128, BKV>), grid, dim3(256), 0, s, p); \
-    else if (w.bm == 128) hipLaunchKernelGGL((k_wgrad_rows<T, 128, 64, BKV>), grid, dim3(256), 0, s, p); \
-    else if (w.bn == 128) hipLaunchKernelGGL((k_wgrad_rows<T, 64, 128, BKV>), grid, dim3(256), 0, s, p); \
-    else hipLaunchKernelGGL((k_wgrad_rows<T, 64, 64, BKV>), grid, dim3(256), 0, s, p);                  \
+#define WGRAD_ROWS(BKV)                                                                              \
+  do {                                                                                               \
+    if (w.bm == 128 && w.bn == 128) hipLaunchKernelGGL((k_wgrad_rows<128, 128, BKV>), grid, dim3(256), 0, s, p); \
+    else if (w.bm == 128) hipLaunchKernelGGL((k_wgrad_rows<128, 64, BKV>), grid, dim3(256), 0, s, p); \
+    else if (w.bn == 128) hipLaunchKernelGGL((k_wgrad_rows<64, 128, BKV>), grid, dim3(256), 0, s, p); \
+    else hipLaunchKernelGGL((k_wgrad_rows<64, 64, BKV>), grid, dim3(256), 0, s, p);                  \
   } while (0)
   if (w.row3) {
     const int sw = p.Wc < 64 ? p.Wc : 64;
@@ -2927,10 +2919,9 @@ int launch_wgrad_mfma(const WgradArgs& a, float* workspace, hipStream_t s) {
     else { if (w.bm == 128) WGRAD_ROW3(128, false); else WGRAD_ROW3(64, false); }
 #undef WGRAD_ROW3
   }
-  else if (w.bk) { if (w.bk == 64) WGRAD_ROWS(bf16_t, 64); else WGRAD_ROWS(bf16_t, 32); }
-  else WGRAD_LAUNCH(bf16_t);
+  else if (w.bk) { if (w.bk == 64) WGRAD_ROWS(64); else WGRAD_ROWS(32); }
+  else { if (pow2) WGRAD_LAUNCH(true); else WGRAD_LAUNCH(false); }
 #undef WGRAD_ROWS
-#undef WGRAD_LAUNCH_P
 #undef WGRAD_LAUNCH
   AE_TRY(launch_status("wgrad_mfma"));
   if (direct) return AE_OK;
@@ -2973,20 +2964,16 @@ int launch_wgrad_chunks(const WgradArgs& a, float* workspace, hipStream_t s) {
   const int64_t blocks = (int64_t)w.splits * w.tiles_m * w.tiles_n;
   if (blocks > 0x7FFFFFFF) return fail(AE_EINVAL, "wgrad_chunks: grid too large");
   const dim3 grid((unsigned)blocks);
-#define WGRAD_CHUNKS(T)                                                                                         \
-  do {                                                                                                          \
-    if (w.bm == 128 && w.bn == 128) hipLaunchKernelGGL((k_wgrad_chunks<T, 128, 128>), grid, dim3(256), 0, s, p); \
-    else if (w.bm == 128) hipLaunchKernelGGL((k_wgrad_chunks<T, 128, 64>), grid, dim3(256), 0, s, p);           \
-    else if (w.bn == 128) hipLaunchKernelGGL((k_wgrad_chunks<T, 64, 128>), grid, dim3(256), 0, s, p);           \
-    else hipLaunchKernelGGL((k_wgrad_chunks<T, 64, 64>), grid, dim3(256), 0, s, p);                             \
+  // (bfloat16: k_wgrad_chunks; binary32: k_wgrad_split)
+#define WGRAD_CHUNKS(BMV, BNV)                                                                                     \
+  do {                                                                                                             \
+    if (a.dtype == AE_BF16) hipLaunchKernelGGL((k_wgrad_chunks<BMV, BNV>), grid, dim3(256), 0, s, p);              \
+    else hipLaunchKernelGGL((k_wgrad_split<BMV, BNV>), grid, dim3(256), 0, s, p);                                  \
   } while (0)
-#define WGRAD_SPLIT(BMV, BNV) hipLaunchKernelGGL((k_wgrad_split<BMV, BNV>), grid, dim3(256), 0, s, p)
-  if (a.dtype == AE_BF16) WGRAD_CHUNKS(bf16_t);
-  else if (w.bm == 128 && w.bn == 128) WGRAD_SPLIT(128, 128);
-  else if (w.bm == 128) WGRAD_SPLIT(128, 64);
-  else if (w.bn == 128) WGRAD_SPLIT(64, 128);
-  else WGRAD_SPLIT(64, 64);
-#undef WGRAD_SPLIT
+  if (w.bm == 128 && w.bn == 128) WGRAD_CHUNKS(128, 128);
+  else if (w.bm == 128) WGRAD_CHUNKS(128, 64);
+  else if (w.bn == 128) WGRAD_CHUNKS(64, 128);
+  else WGRAD_CHUNKS(64, 64);
 #undef WGRAD_CHUNKS
   AE_TRY(launch_status("wgrad_chunks"));
   if (direct) return AE_OK;
