@@ -178,9 +178,17 @@ WgradChunksPlan plan_wgrad_chunks(const WgradArgs& a) {
   WgradChunksPlan w;
   const int64_t rows = (int64_t)a.n * a.hc * a.wc;
   const int cols = a.k * a.k * chan_pad(a.cin, a.dtype);
-  // tiles of 64 where 128 would leave a whole 64 empty
+  // Tiles of 64 where 128 would leave a whole 64 empty, of the columns only up to five 64s: beyond, the empty half is a sixth of the
+  // tiles at most and the wider tile reads dY half as often.  3x3 weights, wide tiles against tiles of 64: 72 -> 160 channels over
+  // 32,768 pixels 36 and 44 us, 120 -> 160 50 and 62; with few pixels, where the compute units are not full, 48 -> 80 over 18,432
+  // 20.4 and 18.2, 48 -> 40 over 2,304 12.2 and 11; binary32 16 -> 80 over 18,432 28 and 22, 64 -> 160 over 32,768 79 and 84.
   w.bm = ((a.cout + 63) / 64) % 2 == 0 ? 128 : 64;
   w.bn = ((cols + 63) / 64) % 2 == 0 || cols > 320 ? 128 : 64;
+  // Where even the most splits leave compute units without a workgroup, tiles of 64: a workgroup's time is then the launch's.
+  // Binary32, 3x3, 64 -> 64 over 256 pixels 19.8 -> 15.5 us (14.7 with a tile per tap and the binary32 MFMA), 64 -> 256 26.7 -> 16.9
+  // (21.0), 128 -> 128 over 1,024 27 -> 17 (53), 1x1 256 -> 256 over 4,096 28 -> 18 (50); bfloat16 80 -> 40 over 2,304 12.5 -> 11.1;
+  // no difference from 256 workgroups on (256 -> 256 over 4,096 53 and 52).
+  if ((int64_t)((a.cout + w.bm - 1) / w.bm) * ((cols + w.bn - 1) / w.bn) * ((rows + 255) / 256) < 256) w.bm = w.bn = 64;
   w.tiles_m = (a.cout + w.bm - 1) / w.bm;
   w.tiles_n = (cols + w.bn - 1) / w.bn;
   const int64_t tiles = (int64_t)w.tiles_m * w.tiles_n;
@@ -444,7 +452,7 @@ int build_plan(const char* spec, int batch, int dtype, int bn_mode, Plan* plan) 
           if (st.chunks_d) plan->max_splitk_floats = std::max(plan->max_splitk_floats, conv_chunks_splitk_floats(cd));
         }
         st.chunks_w = !wgrad_mfma_supported(wa) && wgrad_chunks_worthwhile(wa) && wgrad_chunks_supported(wa);
-        // (the caller's own x and dy may lie anywhere: copied into whole aligned chunks if need be, see chunk_rows)
+        // (the caller's own x and dy may lie anywhere: copied into whole aligned chunks if need be, see chunk_copy)
         // (noise alone hands its incoming gradient on: dy may reach a layer that is not the last)
         const bool reads_x = &st == &plan->steps[0], reads_dy = !st.has_bn && !st.pool && st.act == ACT_NONE;
         if ((st.chunks || st.chunks_w) && (cin_p != st.cin || reads_x)) st.off_xpad = take(in_elems / st.cin * cin_p * es);

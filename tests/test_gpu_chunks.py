@@ -68,6 +68,22 @@ def test_tensors_of_the_caller_off_a_16_byte_border(dtype, tail):
     assert all(torch.equal(a, b) for a, b in zip(*out))
 
 
+@pytest.mark.parametrize("cin,cout,batch,side", [(64, 64, 4, 8), (68, 132, 3, 7), (128, 96, 28, 16), (128, 96, 29, 16), (256, 256, 16, 16)])
+def test_weight_gradient_tiles(cin, cout, batch, side):
+    """Binary32 weight gradients of 3x3 layers on tiles of 64 (fewer than 256 workgroups: up to 28 x 16 x 16 pixels of 128 -> 96) and 128."""
+    import torch
+    from paper_2602_17681_amd import binding as ae
+    torch.manual_seed(15)
+    m = ae.Model("in:%dx%dx%d,conv3:%d" % (cin, side, side, cout), batch, ae.DTYPES["f32"])
+    p, x, dy = torch.zeros(m.n_params, device="cuda"), torch.randn(batch, cin, side, side), torch.randn(batch, cout, side, side)
+    y, g = torch.empty(dy.shape, device="cuda"), torch.empty(m.n_params, device="cuda")
+    m.model_forward(p, x.cuda(), 10.0, 1, y)
+    m.model_backward(p, x.cuda(), dy.cuda(), g)
+    ref = torch.nn.grad.conv2d_weight(x.double(), (cout, cin, 3, 3), dy.double(), padding=1)
+    # at most 7,424 terms in binary32: sqrt(7424 / 16) roundings of 2^-24 of the growing sum
+    assert ((g[:ref.numel()].cpu().double().view_as(ref) - ref).norm() / ref.norm()).item() <= 1.3e-6
+
+
 @pytest.mark.parametrize("spec,pads", [("in:10x1x1,fc:12", 0), ("in:10x1x1,fc:1200", 1), ("in:8x1x1,fc:10,relu,fc:12", 1)])
 def test_no_copy_that_nothing_reads(spec, pads):
     """Inputs with rows that are no whole chunks: copied in the forward pass where its kernel or, for a layer behind the first, the weight gradient reads the copy."""
