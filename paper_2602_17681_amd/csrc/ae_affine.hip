@@ -259,7 +259,7 @@ __global__ __launch_bounds__(256) void k_tri_prepare(LuSrc q, int dp, float* __r
 // time: a workgroup of four wavefronts owns 32 rows of one product (four workgroups per matrix composing, eight backward),
 // a wavefront one 32 x 32 tile of them, and the operands come into LDS eight loads of 16 bytes at a time.  Measured for
 // 32 matrices of 128 (bfloat16 in and out) against one workgroup per matrix with vector-ALU products and scalar loads:
-// compose 82 -> 13 us, backward 135 -> 14 us, inverse 106 -> 31 us.
+// compose 82 -> 11 us, backward 135 -> 14 us, inverse 106 -> 31 us.
 // LDS rows are 132 floats: the 16-byte fragment reads of 16 rows and the 4-byte ones of two rows fall into different banks.
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 constexpr int kSmallLd = 132;

@@ -896,7 +896,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
       const T* const wr = reinterpret_cast<const T*>(p.w) + ((int64_t)phase * p.N + n) * p.K;
       const int k_end = min((kt0 + KT) * BK, p.K);
       float v = 0.0f;
-      for (int k = kt0 * BK; k < k_end; k += EPC) {            // (a chunk lies in one tap)
+      for (int k = kt0 * BK; k < k_end && v == v; k += EPC) {  // (a chunk lies in one tap; NaN stays NaN)
         const int tap = k / p.Cin, ci = k - tap * p.Cin, r = tap / p.ksz, hh = h0 + r, ww = w0 + tap - r * p.ksz;
         if (hh < 0 || hh >= p.Hv || ww < 0 || ww >= p.Wv) continue;
         const T* const px = x + ((int64_t)(hh >> p.up) * Win + (ww >> p.up)) * p.Cin + ci;
@@ -933,22 +933,23 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
 // is dropped, ml + lm + ll, is of the size of one binary32 rounding of the product at worst.  hh goes to an accumulator of
 // its own, the five small ones to a second one whose roundings are their own size: a K of 16 rounds the sum once, where
 // eight binary32 MFMAs round it eight times.  Six bf16 MFMAs take 192 cycles for that K, the eight binary32 ones 512.
-// Measured at d = 4096: 0.63 ms = 218 TFLOP/s against 1.01 ms = 136 (87 % of the binary32 MFMA's rate), the matrix cores
-// busy two thirds of the cycles at the 1.8 GHz that the power limit leaves; errors at the rule in launch_conv_mfma.
+// Measured at d = 4096: 0.65 ms = 211 TFLOP/s against 1.01 ms = 136 (87 % of the binary32 MFMA's rate), the matrix cores
+// busy 75 % of the cycles at the 1.6 GHz that the power limit leaves; errors at the rule in launch_conv_mfma.
 //
-// A workgroup is WGM x WGN wavefronts of 64 x 64 outputs (32 x 64 where there are only 64 columns).  Slabs of 16 k's are loaded into registers two slabs ahead, cut
-// into parts between the MFMAs of the slab before (the split is a third of the VALU issue slots that the MFMAs leave)
-// and stored to the other of two LDS stages; one barrier per slab.  LDS: [stage][part][32-row block] of 1 KiB in fragment
-// order, chunk c (8 of the 16 k's) of row r at 512 c + (16 r ^ 128 c): a fragment read is 1 KiB in lane order, and the 8-byte
-// stores of 8 rows x 4 quarters fall into 64 different banks.
+// A workgroup is WGM x WGN wavefronts of 64 x 64 outputs (32 x 64 where there are only 64 columns).  Slabs of 16 k's are
+// loaded into registers two slabs ahead, cut into parts between the MFMAs of the slab before (the split is a third of the VALU
+// issue slots that the MFMAs leave) and stored to the next of three LDS stages, with one barrier per slab: a stage's last
+// read lies before the barrier of the slab, its next store behind that of the slab after.  LDS: [stage][part][32-row block] of
+// 1 KiB in fragment order, chunk c (8 of the 16 k's) of row r at 512 c + (16 r ^ 128 c): a fragment read is 1 KiB in lane
+// order, and the 8-byte stores of 8 rows x 4 quarters fall into 64 different banks.
 //
 // A workgroup that meets an operand below 2^-110 other than zero, whose last part would end below the smallest bfloat16
-// denormal, computes its tile again with the binary32 MFMA: such a value may be all there is of an output, whatever else its row
-// holds.  (The bf16 MFMA flushes no denormals: 256-term sums of 2^-63 x 2^-63 products come out to 1.2 x 2^-24 of the sum of
-// magnitudes, as at any size.  The check is 6 VALU instructions per 16 bytes:
-// 1.4 % of a QR step of d = 4096, 20.7 -> 21.0 ms, nothing seen elsewhere.)  So does one with a sum that is no finite number: a value that rounds
-// to infinity has no parts, the product of two parts rounded up may lie beyond the range where the product of the values does
-// not, and where both accumulators leave it with different signs their sum would be NaN for an infinity.
+// denormal, computes its tile again with the binary32 MFMA: such a value may be all there is of an output, whatever else its
+// row holds.  (The bf16 MFMA flushes no denormals: 256-term sums of 2^-63 x 2^-63 products come out to 1.2 x 2^-24 of the sum
+// of magnitudes, as at any size.  The check is 6 VALU instructions per 16 bytes, 1.4 % of a QR step of d = 4096.)  So does one
+// with a sum that is no finite number: a value that rounds to infinity has no parts, the product of two parts rounded up may
+// lie beyond the range where the product of the values does not, and where both accumulators leave it with different signs
+// their sum would be NaN for an infinity.
 // ---------------------------------------------------------------------------
 template <int BM, int BN, int WGM, int WGN, bool INTERIOR, int EPI = 0, bool CONV = false>
 __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_split(IgemmParams p) {
@@ -2041,7 +2042,7 @@ __device__ __forceinline__ void wgrad_resum_nan(const WgradParams& p, floatx16 (
     const T* const x = reinterpret_cast<const T*>(p.x) + ci;
     const T* const dy = reinterpret_cast<const T*>(p.dy) + co;
     float v = 0.0f;
-    for (unsigned m = m_begin; m < m_end; ++m) {
+    for (unsigned m = m_begin; m < m_end && v == v; ++m) {      // (NaN stays NaN)
       const unsigned t = m / (unsigned)p.Wc, n = t / (unsigned)p.Hc;
       const int hh = (int)(t - n * (unsigned)p.Hc) + dh, ww = (int)(m - t * (unsigned)p.Wc) + dw;
       if (hh < 0 || hh >= p.Hc || ww < 0 || ww >= p.Wc) continue;
