@@ -26,13 +26,14 @@ struct LuSrc {
   const float* lp; const float* up; const float* log_s; const float* sign; const int* inv_perm; const void* g;
   int d;
 };
-enum { LU_L = 0, LU_UD = 1, LU_B = 2 };
+enum { LU_L = 0, LU_UD = 1, LU_B = 2, LU_U = 3 };
 
-// entry (r, c) of L, of U + diag(s), or of B = P^T G (row r of B is row inv_perm[r] of G)
+// entry (r, c) of L, of U + diag(s), of B = P^T G (row r of B is row inv_perm[r] of G), or of U alone
 template <typename T, int SRC>
 __device__ __forceinline__ float lu_elem(const LuSrc& q, int r, int c) {
   if (SRC == LU_L) return c < r ? q.lp[(int64_t)r * q.d + c] : (c == r ? 1.0f : 0.0f);
   if (SRC == LU_UD) return r < c ? q.up[(int64_t)r * q.d + c] : (r == c ? q.sign[c] * expf(q.log_s[c]) : 0.0f);
+  if (SRC == LU_U) return r < c ? q.up[(int64_t)r * q.d + c] : 0.0f;
   return Store<T>::ld(reinterpret_cast<const T*>(q.g) + (int64_t)q.inv_perm[r] * q.d + c);
 }
 
@@ -151,6 +152,41 @@ __global__ __launch_bounds__(256) void k_lu_permute_rows(const uint4* __restrict
     int src = perm[r];
     if ((unsigned)src >= (unsigned)d) src = r;                        // not a permutation: stay inside the arrays
     a[i] = y[(int64_t)src * chunks_per_row + c];
+  }
+}
+
+// The same in binary32 with the diagonal's term of every entry: A[i][c] = Y[p][c] + L[p][c] s[c], p = perm[i], Y = L U.  That term is by
+// far the largest of the results it enters, and the matrix cores round it at twice their last place: the largest deviation of
+// A from float64 was 2.0e-6 of the root mean square at d = 256, 5.6e-6 at d = 1024 with it in the product (1.5e-6, 5.0e-6
+// with the binary32 MFMA), 0.7e-6 and 2.2e-6 this way; the call took 52 and 368 us at d = 1024 and 4096, now 54 and 365.  Grid: 256 chunks of four columns by 16 rows.
+// An entry that comes out as NaN is summed again over the triangles alone, up to the first NaN.
+__global__ __launch_bounds__(256) void k_lu_permute_rows_diag(const float* __restrict__ y, const float* __restrict__ l, LuSrc q,
+                                                              const int* __restrict__ perm, float* __restrict__ a) {
+  const int c0 = ((int)blockIdx.x * 256 + (int)threadIdx.x) * 4, r0 = (int)blockIdx.y * 16, d = q.d;
+  if (c0 >= d) return;
+  float sv[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) sv[t] = q.sign[c0 + t] * expf(q.log_s[c0 + t]);
+  for (int i = r0; i < min(r0 + 16, d); ++i) {
+    int src = perm[i];
+    if ((unsigned)src >= (unsigned)d) src = i;                        // not a permutation: stay inside the arrays
+    const float4 w = *reinterpret_cast<const float4*>(y + (int64_t)src * d + c0);
+    float v[4] = {w.x, w.y, w.z, w.w};
+    if (c0 <= src) {                                                  // (L's zeros need not be read)
+      const float4 x = *reinterpret_cast<const float4*>(l + (int64_t)src * d + c0);
+      const float lv[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+      for (int t = 0; t < 4; ++t) v[t] = c0 + t <= src ? fmaf(lv[t], sv[t], v[t]) : v[t];
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+      if (v[t] != v[t]) {
+        const int c = c0 + t;
+        v[t] = 0.0f;
+        for (int k = 0; k < min(src + 1, c) && v[t] == v[t]; ++k) v[t] = fmaf(l[(int64_t)src * d + k], q.up[(int64_t)k * d + c], v[t]);
+        if (c <= src) v[t] = fmaf(l[(int64_t)src * d + c], sv[t], v[t]);
+      }
+    *reinterpret_cast<float4*>(a + (int64_t)i * d + c0) = make_float4(v[0], v[1], v[2], v[3]);
   }
 }
 
@@ -397,9 +433,10 @@ __global__ __launch_bounds__(256) void k_lu_small_compose(const float* __restric
   for (int e = 0; e < 16; ++e) acc[e] = fmaf(lm[small_row(lane, e) * kSmallLd + col], dg[col], acc[e]);
   small_resum_nan(acc, [&](int e) {
     const float* const l = lm + small_row(lane, e) * kSmallLd;
+    const int p = pr[small_row(lane, e)];
     float v = 0.0f;
-    for (int t = 0; t < col; ++t) v = fmaf(l[t], um[t * kSmallLd + col], v);
-    return fmaf(l[col], dg[col], v);
+    for (int t = 0; t <= p && t < col; ++t) v = fmaf(l[t], um[t * kSmallLd + col], v);
+    return col <= p ? fmaf(l[col], dg[col], v) : v;
   });
   T* o = out + (int64_t)m * d * d;
 #pragma unroll
@@ -1101,13 +1138,18 @@ extern "C" int model_lu_compose(const float* lp, const float* up, const float* l
   const int64_t mat = lu_mat_bytes(d, dtype);
   char* ws = reinterpret_cast<char*>(workspace);
   void* l = ws;                 // L                 [i][k]
-  void* udt = ws + mat;         // (U + diag s)^T    [n][k]
+  void* udt = ws + mat;         // (U + diag s)^T    [n][k]   (binary32: U^T, the diagonal follows in k_lu_permute_rows_diag)
   void* y = ws + 2 * mat;       // L (U + diag s)    [i][n]
   LuSrc q{lp, up, log_s, sign_s, nullptr, nullptr, (int)d};
   if (dtype == AE_BF16) { launch_build_rows<bf16_t, LU_L>(q, l, s); launch_build_transposed<bf16_t, LU_UD>(q, udt, s); }
-  else { launch_build_rows<float, LU_L>(q, l, s); launch_build_transposed<float, LU_UD>(q, udt, s); }
+  else { launch_build_rows<float, LU_L>(q, l, s); launch_build_transposed<float, LU_U>(q, udt, s); }
   AE_TRY(launch_status("lu_build"));
   AE_TRY(dense_product(l, udt, y, (int)d, dtype, CONV_TRI_LOWER_UPPER, s));
+  if (dtype == AE_F32) {
+    const dim3 grid((unsigned)((d + 1023) / 1024), (unsigned)((d + 15) / 16));
+    hipLaunchKernelGGL(k_lu_permute_rows_diag, grid, dim3(256), 0, s, (const float*)y, (const float*)l, q, perm, (float*)a_out);
+    return launch_status("lu_permute_rows_diag");
+  }
   const int cpr = (int)(d * (int64_t)dtype_size(dtype) / 16);
   hipLaunchKernelGGL(k_lu_permute_rows, dim3(lu_grid(d * cpr)), dim3(256), 0, s, (const uint4*)y, perm, (int)d, cpr, (uint4*)a_out);
   return launch_status("lu_permute_rows");

@@ -65,19 +65,51 @@ def test_full_size_inverse_takes_parameters_off_a_16_byte_border():
     assert torch.equal(*out)
 
 
-@pytest.mark.parametrize("d", [33, 64, 97, 128])
+def compose(lp, up, ls, sign, perm):
+    """All matrices in one call, or each in a call of its own where they are too large for that."""
+    n, d = ls.shape
+    a = torch.empty(n, d, d, device="cuda")
+    if d <= 128:
+        ae.model_lu_compose_batch(lp, up, ls, sign, perm, n, d, a)
+    else:
+        ws = torch.empty(ae.model_lu_workspace(d, ae.DTYPES["f32"]), dtype=torch.uint8, device="cuda")
+        for i in range(n):
+            ae.model_lu_compose(lp[i], up[i], ls[i], sign[i], perm[i], d, a[i], ws)
+    return a
+
+
+@pytest.mark.parametrize("d", [33, 64, 97, 128, 160, 256, 1056])
 def test_the_large_term_is_rounded_once(d):
     """Small off-diagonal entries beside a diagonal of ones: the results with the diagonal in them are off by their own rounding."""
     g = torch.Generator(device="cuda")
     g.manual_seed(d)
-    n, eye = 64, torch.eye(d, device="cuda", dtype=torch.float64)
-    lp, up = (0.02 * torch.randn(n, d, d, device="cuda", generator=g) for _ in range(2))
+    n, eye = 64 if d <= 128 else 4, torch.eye(d, device="cuda", dtype=torch.float64)
+    lp, up = (0.2 / d ** 0.5 * torch.randn(n, d, d, device="cuda", generator=g) for _ in range(2))
     perm = torch.arange(d, device="cuda", dtype=torch.int32).repeat(n, 1)
-    a = torch.empty(n, d, d, device="cuda")
-    ae.model_lu_compose_batch(lp, up, torch.zeros(n, d, device="cuda"), torch.ones(n, d, device="cuda"), perm, n, d, a)
+    a = compose(lp, up, torch.zeros(n, d, device="cuda"), torch.ones(n, d, device="cuda"), perm)
     ref = torch.diagonal((torch.tril(lp.double(), -1) + eye) @ (torch.triu(up.double(), 1) + eye).contiguous(), dim1=1, dim2=2)
     err = ((torch.diagonal(a, dim1=1, dim2=2).double() - ref).abs() / ref.abs()).max().item()
     assert err <= 1.1 * 2.0 ** -24, err * 2 ** 24        # half a last place; the other terms add up to 1e-2 of the result
+
+
+@pytest.mark.parametrize("d,i,j", [(2, 1, 0), (40, 39, 20), (128, 70, 69), (160, 150, 3), (256, 255, 0), (256, 130, 129)])
+@pytest.mark.parametrize("which", ["L", "U"])
+def test_an_infinity_enters_one_row_or_column_of_the_product(d, i, j, which):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    rnd = lambda *s: torch.randn(1, *s, device="cuda", generator=g)      # noqa: E731
+    lp, up, ls = rnd(d, d) * d ** -0.5, rnd(d, d) * d ** -0.5, 0.3 * rnd(d)
+    perm = torch.randperm(d, device="cuda", generator=g).to(torch.int32)[None]
+    out = []
+    for value in (float("inf"), 0.0):
+        (lp[0] if which == "L" else up[0].t())[i, j] = value
+        a = torch.empty(d, d, device="cuda")
+        a[perm[0].long()] = compose(lp, up, ls, torch.ones(1, d, device="cuda"), perm)[0]         # rows as in L U
+        bad = a[i, j:] if which == "L" else a[j:, i]       # L[i, j] U[j, j:], L[j:, j] U[j, i]
+        out.append((bad.clone(), a))
+        bad.zero_()
+    assert not out[0][0].isfinite().any() and out[1][0].isfinite().all()
+    assert (out[0][1] - out[1][1]).norm() <= 1e-6 * out[1][1].norm()
 
 
 @pytest.mark.parametrize("which", ["L", "U"])
