@@ -24,6 +24,8 @@
 //   k_gemm_split            binary32 products and convolutions by bf16 parts
 // The shared epilogue adds the bias, rounds to the storage type, optionally reduces per-channel
 // sum / sum of squares of the tile (batch-norm statistics), applies the activation and stores [M][N].
+#include <type_traits>
+
 #include "ae_device.h"
 #include "ae_internal.h"
 
@@ -55,7 +57,7 @@ struct IgemmParams {
   // stored input (one per output parity (a, b) = (phase>>1, phase&1), pads 1-a and 1-b, weights
   // w + phase*N*K); row (n, i, j) of phase (a, b) is output pixel (2i+a, 2j+b) of a 2Hc x 2Wc image
   int phases;
-  // epilogue variants of the dense-GEMM use (EPI template parameter of k_igemm):
+  // epilogue variants of the dense-GEMM use (EPI template parameter of k_dense and k_gemm_split):
   //   1: the stored output is MX block-quantised (blocks of mx_block output columns: a power of two from one 16-byte
   //      chunk up to the 64 columns of a wave tile; FP4 E2M1 elements);
   //   2: nothing is stored; the epilogue forms resid[m][n] - (acc + bias) and leaves per-tile column sums of it
@@ -191,6 +193,20 @@ __device__ __forceinline__ bool add_not_finite(floatx16 (&acc)[MI][NJ], const fl
   return z != 0.0f;
 }
 
+typedef __attribute__((address_space(3))) char lds_char;
+typedef __attribute__((address_space(3))) void lds_void_t;
+// 16 bytes per lane from a buffer straight into LDS: lane l writes lds_wave_base + 16*l
+// (offsets past the buffer's range deliver zeros like any buffer load)
+__device__ __forceinline__ void dma_load16(__amdgpu_buffer_rsrc_t rsrc, char* lds_wave_base, unsigned voffset) {
+  typedef __attribute__((address_space(3))) void lds_void;
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)lds_wave_base, 16, voffset, 0, 0, 0);
+}
+// the same with a scalar (uniform) byte offset added to every lane's offset
+__device__ __forceinline__ void dma_load16s(__amdgpu_buffer_rsrc_t rsrc, char* lds_wave_base, unsigned voffset, unsigned soffset) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_t*)lds_wave_base, 16, voffset, soffset, 0, 0);
+}
+constexpr int vm_imm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0F70; }   // s_waitcnt vmcnt(n) only
+
 // Epilogue of a tile that lies wholly inside the output (no bounds checks): bias, rounding to the
 // storage type, optional column statistics of the stored value, optional ReLU, then 16-byte
 // row stores staged through this wave's LDS area.
@@ -212,7 +228,7 @@ template <> __device__ __forceinline__ void unpack_chunk<float>(const uint4v& w,
 // every row it handles, so it keeps that chunk's column sums (and the two coefficients of xhat per column).
 template <int EPC> struct CompSums { float s1[EPC], s2[EPC], p1[EPC], p0[EPC]; };
 
-template <typename T, int MI, int NJ, int WN, int SW, bool STATS, bool RELU, bool MXQ = false, int COMP = 0>
+template <typename T, int MI, int NJ, int WN, int SW, bool STATS, bool RELU, int MXF = -1, int COMP = 0>   // MXF: element format of the quantising epilogue, or -1
 __device__ __forceinline__ void igemm_store_interior(const floatx16 (&acc)[MI][NJ], const float (&bias)[NJ], T* stage,
                                                      T* yrow, int N, int lane, float (&s1)[NJ], float (&s2)[NJ],
                                                      const IgemmParams& p, int64_t mrow0, int phase, T* ycol,
@@ -262,7 +278,7 @@ __device__ __forceinline__ void igemm_store_interior(const floatx16 (&acc)[MI][N
       const int lr = idx / CPRO, ch = idx % CPRO;
       T* dst = (p.phases == 1 && p.strips == 1) ? yrow + (int64_t)(i * 32 + lr) * N + ch * EPC
                                                 : ycol + igemm_out_row(p, mrow0 + i * 32 + lr, phase, sbase) * N + ch * EPC;
-      if constexpr (MXQ) {
+      if constexpr (MXF >= 0) {
         // MX block quantisation of the stored row: a block of mx_block columns is mx_block/EPC neighbouring lanes of this
         // pass (a staged row is CPRO >= mx_block/EPC consecutive lanes, blocks do not straddle rows)
         float f[EPC];
@@ -272,12 +288,10 @@ __device__ __forceinline__ void igemm_store_interior(const floatx16 (&acc)[MI][N
         for (int t = 0; t < EPC; ++t) amax = fmaxf(amax, fabsf(f[t]));
         for (int off = 1; off < p.mx_block / EPC; off <<= 1) amax = fmaxf(amax, __shfl_xor(amax, off, 64));
         if (amax > 0.0f) {
-          const int k = mx_scale_exp(amax, p.mx_elem == MX_FP8 ? 8 : (p.mx_elem == MX_INT4 ? 0 : 2));
-          const float sc = ldexpf(1.0f, k), inv_sc = ldexpf(1.0f, -k);
+          const int k = mx_scale_exp(amax, MxFormat<MXF>::r_max);
+          const float sc = mx_pow2(k), inv_sc = mx_pow2(-k);
 #pragma unroll
-          for (int t = 0; t < EPC; ++t)
-            f[t] = p.mx_elem == MX_FP8 ? MxFormat<MX_FP8>::quant(f[t], inv_sc, sc)
-                                       : (p.mx_elem == MX_INT4 ? MxFormat<MX_INT4>::quant(f[t], inv_sc, sc) : mx_quant_e2m1(f[t], inv_sc, sc));
+          for (int t = 0; t < EPC; ++t) f[t] = MxFormat<MXF>::quant(f[t], inv_sc, sc);
         }
         Store<T>::stv(dst, f);
       } else if constexpr (COMP != 0) {
@@ -324,7 +338,8 @@ __device__ __forceinline__ void igemm_resid_stats(const floatx16 (&acc)[MI][NJ],
 // ended on a barrier) so that global stores are 16 bytes wide and each instruction covers
 // whole row segments.  smem: at least 4*32*(WN + 16/sizeof(T))*sizeof(T) bytes; sRed: [WGM][2][BN].
 // PHASED: a checked tile may belong to an output parity of an upsampled convolution (interior tiles always may).
-template <typename T, int BM, int BN, int WGM, int WGN, bool INTERIOR, int EPI = 0, bool PHASED = false>
+// RESID_LDS: smem holds the whole tile in the storage type.
+template <typename T, int BM, int BN, int WGM, int WGN, bool INTERIOR, int EPI = 0, bool PHASED = false, bool RESID_LDS = false>
 __device__ __forceinline__ void igemm_epilogue(floatx16 (&acc)[BM / WGM / 32][BN / WGN / 32], const IgemmParams& p,
                                                char* smem, float (*sRed)[2][BN], int64_t m0, int n0, int64_t tile_m,
                                                int phase = 0) {
@@ -349,9 +364,30 @@ __device__ __forceinline__ void igemm_epilogue(floatx16 (&acc)[BM / WGM / 32][BN
     T* ycol = Y + n0 + wn * WN;
     const int64_t mrow0 = m0 + wm * WM;
     if constexpr (EPI == 1)
-      igemm_store_interior<T, MI, NJ, WN, SW, false, false, true>(acc, bias, stage, yrow, p.N, lane, s1, s2, p, mrow0, phase, ycol);
-    else if constexpr (EPI == 2)
-      igemm_resid_stats<T, MI, NJ>(acc, bias, (const T*)p.resid + (m0 + wm * WM) * p.N + n0 + wn * WN, p.N, lane, s1, s2);
+      // (one copy per format: with the format looked up per value the compiler evaluates all three and selects)
+      switch (p.mx_elem) {
+        case MX_FP8: igemm_store_interior<T, MI, NJ, WN, SW, false, false, MX_FP8>(acc, bias, stage, yrow, p.N, lane, s1, s2, p, mrow0, phase, ycol); break;
+        case MX_INT4: igemm_store_interior<T, MI, NJ, WN, SW, false, false, MX_INT4>(acc, bias, stage, yrow, p.N, lane, s1, s2, p, mrow0, phase, ycol); break;
+        default: igemm_store_interior<T, MI, NJ, WN, SW, false, false, MX_FP4>(acc, bias, stage, yrow, p.N, lane, s1, s2, p, mrow0, phase, ycol); break;
+      }
+    else if constexpr (EPI == 2) {
+      const T* const resid = (const T*)p.resid + (m0 + wm * WM) * p.N + n0 + wn * WN;
+      if constexpr (RESID_LDS) {
+        // the wave's part of resid comes through the operand buffers, 16 bytes a lane at once (rows of WN values, lane order)
+        constexpr int CPRO = WN * ES / 16, ROWS = 64 / CPRO;
+        static_assert(WM % ROWS == 0, "whole passes");
+        char* const area = smem + __builtin_amdgcn_readfirstlane(wave) * (WM * WN * ES);
+        const unsigned row_bytes = (unsigned)p.N * (unsigned)ES;
+        const __amdgpu_buffer_rsrc_t rR = make_rsrc(resid, (WM - 1) * row_bytes + WN * ES);
+        const unsigned off = (unsigned)(lane / CPRO) * row_bytes + (unsigned)(lane % CPRO) * 16u;
+#pragma unroll
+        for (int r = 0; r < WM / ROWS; ++r) dma_load16s(rR, area + r * 1024, off, (unsigned)(r * ROWS) * row_bytes);
+        __builtin_amdgcn_s_waitcnt(vm_imm(0));
+        igemm_resid_stats<T, MI, NJ>(acc, bias, reinterpret_cast<const T*>(area), WN, lane, s1, s2);
+      } else {
+        igemm_resid_stats<T, MI, NJ>(acc, bias, resid, p.N, lane, s1, s2);
+      }
+    }
     else if constexpr (EPI == 3 || EPI == 4) {
       // companion-tensor sums (EPI 3: IgemmParams::comp_mode 1, EPI 4: comp_mode 2): this lane's chunk of columns is the same in every row it stores (CPRO divides 64)
       constexpr int EPC = 16 / ES, CPRO = WN / EPC;
@@ -371,7 +407,7 @@ __device__ __forceinline__ void igemm_epilogue(floatx16 (&acc)[BM / WGM / 32][BN
           }
         }
       }
-      igemm_store_interior<T, MI, NJ, WN, SW, false, false, false, EPI - 2>(acc, bias, stage, yrow, p.N, lane, s1, s2, p, mrow0, phase, ycol, &cs);
+      igemm_store_interior<T, MI, NJ, WN, SW, false, false, -1, EPI - 2>(acc, bias, stage, yrow, p.N, lane, s1, s2, p, mrow0, phase, ycol, &cs);
 #pragma unroll
       for (int t = 0; t < EPC; ++t) {
         for (int off = CPRO; off < 64; off <<= 1) {
@@ -455,31 +491,29 @@ __device__ __forceinline__ void igemm_epilogue(floatx16 (&acc)[BM / WGM / 32][BN
 // inline assembly, and the waits on them (lgkmcnt) are placed by hand: LDS reads of a wave
 // return in order, so "at most n outstanding" identifies which fragments have arrived.  An
 // empty asm with the fragment as in/out operand keeps the MFMAs after the wait.
-typedef __attribute__((address_space(3))) char lds_char;
-typedef __attribute__((address_space(3))) void lds_void_t;
-// 16 bytes per lane from a buffer straight into LDS: lane l writes lds_wave_base + 16*l
-// (offsets past the buffer's range deliver zeros like any buffer load)
-__device__ __forceinline__ void dma_load16(__amdgpu_buffer_rsrc_t rsrc, char* lds_wave_base, unsigned voffset) {
-  typedef __attribute__((address_space(3))) void lds_void;
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void*)lds_wave_base, 16, voffset, 0, 0, 0);
-}
-// the same with a scalar (uniform) byte offset added to every lane's offset
-__device__ __forceinline__ void dma_load16s(__amdgpu_buffer_rsrc_t rsrc, char* lds_wave_base, unsigned voffset, unsigned soffset) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_t*)lds_wave_base, 16, voffset, soffset, 0, 0);
-}
-template <int I, int N, int STRIDE>
+template <int I, int E, int STRIDE>              // fragments I .. E - 1
 struct LdsReadFrags {
+  template <int N>
   static __device__ __forceinline__ void run(uint4v (&f)[N], unsigned addr) {
 #if defined(__HIP_DEVICE_COMPILE__)             // the host pass only needs the kernel's stub
     asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(f[I]) : "v"(addr), "n"(I * STRIDE));
 #endif
-    LdsReadFrags<I + 1, N, STRIDE>::run(f, addr);
+    LdsReadFrags<I + 1, E, STRIDE>::run(f, addr);
   }
 };
-template <int N, int STRIDE>
-struct LdsReadFrags<N, N, STRIDE> {
+template <int E, int STRIDE>
+struct LdsReadFrags<E, E, STRIDE> {
+  template <int N>
   static __device__ __forceinline__ void run(uint4v (&)[N], unsigned) {}
 };
+// f(0), f(1), ... f(N - 1) with the index as a constant
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void unroll(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    unroll<N, I + 1>(f);
+  }
+}
 template <int I, int N>
 struct TieFrags {
   static __device__ __forceinline__ void run(uint4v (&f)[N]) {
@@ -493,6 +527,14 @@ template <int N>
 struct TieFrags<N, N> {
   static __device__ __forceinline__ void run(uint4v (&)[N]) {}
 };
+// wait until at most N LDS reads are outstanding, then hand the fragments to the compiler
+template <int N, int MI>
+__device__ __forceinline__ void lds_wait_tie_a(uint4v (&a)[MI]) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N));
+#endif
+  TieFrags<0, MI>::run(a);
+}
 // MFMAs of K-steps K .. KS-1 of one slab; fragments of step k arrived once at most
 // (KS-1-k)*(MI+NJ) reads are outstanding
 template <typename T, int KS, int K, int MI, int NJ>
@@ -926,6 +968,133 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
 }
 
 // ---------------------------------------------------------------------------
+// Dense bf16 products, check-free tiles: y[m][n] = x[m][:] w[n][:]^T, without the taps of k_igemm.
+//
+// The slabs are k_igemm's (64 bytes of K, straight from global memory into a ring of NSTAGE LDS stages, the same swizzle),
+// the schedule is not: a K-step's MFMAs run on fragments that are already in registers while the next K-step's are read
+// and the slab after the next two is asked for, one instruction between two MFMAs.  The workgroup barrier (slab kt + 1 has
+// landed everywhere; the stage of slab kt - 1 is free) stands between the two K-steps of slab kt, so neither an LDS latency
+// nor a burst of loads at the vector memory's issue port lies between a barrier and the next MFMA.
+// What bounds it is power: at 16 384 x 4 096 x 4 096 the matrix cores are busy 78 % of the cycles at 1.46 GHz, and the
+// loads alone cost 0.3 GHz (without them: 89 % at 1.78 GHz, 1.68 PFLOP/s); their place between the MFMAs, s_setprio, and
+// tile orders of 4 to 8 rows made no difference of 2 %, orders of 2 or 16 rows cost 4 %.
+// Measured against k_igemm's schedule with the same tiles (which read a slab's fragments behind the barrier that the slab's
+// MFMAs wait for): 4 096^3 143 -> 126 us, the quantising product of 16 384 x 4 096 x 4 096 683 -> 594 us, the one that only sums
+// its deviations 586 -> 537 us.  1 us a slab of 256 x 256 outputs, 0.55 us of it MFMAs at the full clock.
+// ---------------------------------------------------------------------------
+template <int BM, int BN, int WGM, int WGN, int EPI = 0>
+__global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(2))) void k_dense(IgemmParams p) {
+  constexpr int NT = WGM * WGN * 64, BKB = 64, BK = 32;
+  constexpr int WM = BM / WGM, WN = BN / WGN, MI = WM / 32, NJ = WN / 32;
+  constexpr int RSTEP = NT / 4, AC = BM / RSTEP, BC = BN / RSTEP, L = AC + BC;   // loads per thread and slab
+  constexpr int NSTAGE = (BM + BN) * BKB * 8 <= 160 * 1024 || NT == 512 ? 4 : 3;   // (four wavefronts: two workgroups share a compute unit's LDS)
+  constexpr int SA = BM * BKB, SB = BN * BKB, SW = WN + 8;
+  constexpr int SLAB_BYTES = NSTAGE * (SA + SB), STAGE_BYTES = (NT / 64) * 32 * SW * 2;
+  __shared__ __attribute__((aligned(16))) char smem[SLAB_BYTES > STAGE_BYTES ? SLAB_BYTES : STAGE_BYTES];
+  __shared__ float sRed[WGM][2][BN];
+  char* const sB = smem + NSTAGE * SA;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WGN, wn = wave % WGN;
+  const IgemmTileId tile = igemm_tile_id<BM, BN, true>(p);
+  const int64_t m0 = tile.m * BM;
+  const int n0 = tile.n * BN;
+  int k_lo, k_hi;
+  if (!igemm_k_range<BM, BN>(p, m0, n0, k_lo, k_hi)) return;
+  const int kt0 = k_lo / BK, KT = (k_hi + BK - 1) / BK - kt0;
+  const unsigned row_bytes = (unsigned)p.K * 2u;
+  const __amdgpu_buffer_rsrc_t rX = make_rsrc((const char*)p.x + m0 * row_bytes, BM * row_bytes);
+  const __amdgpu_buffer_rsrc_t rW = make_rsrc((const char*)p.w + (int64_t)n0 * row_bytes, BN * row_bytes);
+  const int lrow = tid >> 2;
+  const unsigned off0 = (unsigned)lrow * row_bytes + (unsigned)(((tid & 3) ^ ((lrow >> 2) & 3)) * 16);   // rows lrow + i RSTEP: the same swizzle
+  unsigned kbyte = (unsigned)kt0 * BKB;          // of the next slab to load
+  auto load = [&](auto c_, int stg) {            // load c of a slab into stage stg
+    constexpr int c = decltype(c_)::value;
+    if constexpr (c < AC) dma_load16s(rX, smem + stg * SA + c * (NT * 16) + wave * 1024, off0 + (unsigned)(c * RSTEP) * row_bytes, kbyte);
+    else dma_load16s(rW, sB + stg * SB + (c - AC) * (NT * 16) + wave * 1024, off0 + (unsigned)((c - AC) * RSTEP) * row_bytes, kbyte);
+    if constexpr (c == L - 1) kbyte += BKB;
+  };
+  const int fr = lane & 31, fsw = (fr >> 2) & 3;
+  unsigned fa_addr[2], fb_addr[2];               // of this lane's fragments of either K-step, stage 0
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) {
+    const unsigned o = (unsigned)(fr * BKB + (((ks * 2 + (lane >> 5)) ^ fsw) * 16));
+    fa_addr[ks] = (unsigned)(size_t)(lds_char*)smem + (unsigned)(wm * WM * BKB) + o;
+    fb_addr[ks] = (unsigned)(size_t)(lds_char*)sB + (unsigned)(wn * WN * BKB) + o;
+  }
+  floatx16 acc[MI][NJ];
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+  uint4v fa[2][MI], fb[2][NJ];
+  // K-step ks: between its MFMAs the fragment reads of the other K-step (stage rstg; waited for behind the last MFMA, so
+  // that nothing is in flight where the loop turns) and its half of a slab's loads (stage lstg; none if negative)
+  auto step = [&](auto ks_, auto read_, int rstg, int lstg) {
+    constexpr int ks = decltype(ks_)::value;
+    constexpr bool read = decltype(read_)::value;
+    constexpr int MM = MI * NJ, H = NSTAGE == 3 ? L : (L + 1) / 2, C0 = ks == 1 ? 0 : H, NL = ks == 1 ? H : L - H;
+    const unsigned ra = fa_addr[ks ^ 1] + (unsigned)(rstg * SA), rb = fb_addr[ks ^ 1] + (unsigned)(rstg * SB);
+    __builtin_amdgcn_sched_barrier(0);
+    unroll<MM>([&](auto q_) {
+      constexpr int q = decltype(q_)::value;
+      mma_step<bf16_t>(fa[ks][q / NJ], fb[ks][q % NJ], acc[q / NJ][q % NJ]);
+      if constexpr (read) {                      // two reads behind each of the first MFMAs
+        constexpr int r0 = 2 * q, r1 = 2 * q + 2;
+        constexpr int b0 = r0 < NJ ? r0 : NJ, b1 = r1 < NJ ? r1 : NJ;
+        constexpr int a0 = r0 < NJ ? 0 : (r0 - NJ < MI ? r0 - NJ : MI), a1 = r1 < NJ ? 0 : (r1 - NJ < MI ? r1 - NJ : MI);
+        LdsReadFrags<b0, b1, 32 * BKB>::run(fb[ks ^ 1], rb);
+        LdsReadFrags<a0, a1, 32 * BKB>::run(fa[ks ^ 1], ra);
+      }
+      if constexpr (NL > 0) {
+        if (lstg >= 0)
+          unroll<NL>([&](auto c_) {
+            constexpr int c = decltype(c_)::value;
+            if constexpr ((2 * c + 1) * MM / (2 * NL) == q) load(std::integral_constant<int, C0 + c>{}, lstg);
+          });
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    if constexpr (read) { lds_wait_tie_a<0, MI>(fa[ks ^ 1]); lds_wait_tie_a<0, NJ>(fb[ks ^ 1]); }
+  };
+  constexpr std::integral_constant<int, 0> k0{};
+  constexpr std::integral_constant<int, 1> k1{};
+  constexpr std::true_type yes{};
+  constexpr std::false_type no{};
+  unroll<NSTAGE - 1>([&](auto g_) {
+    constexpr int g = decltype(g_)::value;
+    if (g < KT) unroll<L>([&](auto c_) { load(c_, g); });
+  });
+  // vmcnt(n): at most n of this wave's loads outstanding (they complete in order)
+  if (NSTAGE == 4 && KT > 2) __builtin_amdgcn_s_waitcnt(vm_imm(2 * L));
+  else if (KT > 1) __builtin_amdgcn_s_waitcnt(vm_imm(L));
+  else __builtin_amdgcn_s_waitcnt(vm_imm(0));
+  __builtin_amdgcn_s_barrier();
+  LdsReadFrags<0, NJ, 32 * BKB>::run(fb[0], fb_addr[0]);
+  LdsReadFrags<0, MI, 32 * BKB>::run(fa[0], fa_addr[0]);
+  lds_wait_tie_a<0, MI>(fa[0]);
+  lds_wait_tie_a<0, NJ>(fb[0]);
+  int cur = 0, pend = -1;                        // stage of slab kt; stage whose loads are half issued
+  for (int kt = 0; kt + 1 < KT; ++kt) {
+    step(k0, yes, cur, pend);
+    // issued so far: the slabs up to kt + NSTAGE - 2; slab kt + 1 has to be there
+    if (NSTAGE == 4 && kt + 2 < KT) __builtin_amdgcn_s_waitcnt(vm_imm(L));
+    else __builtin_amdgcn_s_waitcnt(vm_imm(0));
+    __builtin_amdgcn_s_barrier();                // (every wave has its last fragments of slab kt: the stage of slab kt - 1 is free)
+    const int prev = cur == 0 ? NSTAGE - 1 : cur - 1;
+    pend = kt + NSTAGE - 1 < KT ? prev : -1;
+    cur = cur == NSTAGE - 1 ? 0 : cur + 1;
+    step(k1, yes, cur, pend);
+  }
+  step(k0, yes, cur, -1);
+  step(k1, no, 0, -1);
+  __syncthreads();                               // every wave is done with the slabs: the epilogue reuses the memory
+  static_assert(EPI != 2 || BM * BN * 2 <= SLAB_BYTES, "resid");
+  igemm_epilogue<bf16_t, BM, BN, WGM, WGN, true, EPI, false, true>(acc, p, smem, sRed, m0, n0, tile.m);
+}
+
+// ---------------------------------------------------------------------------
 // Binary32 products and convolutions (CONV: the gather of k_igemm) on the bf16 matrix cores.
 //
 // Every value is cut into three bfloat16 parts on its way into LDS, x = h + m + l (each rounded to nearest, the remainders
@@ -1181,14 +1350,6 @@ __global__ void k_splitk_finish(const float* __restrict__ partial, int splits, i
   }
 }
 
-// wait until at most N LDS reads are outstanding, then hand the fragments to the compiler
-template <int N, int MI>
-__device__ __forceinline__ void lds_wait_tie_a(uint4v (&a)[MI]) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N));
-#endif
-  TieFrags<0, MI>::run(a);
-}
 template <typename T, int MI, int NJ>
 __device__ __forceinline__ void mma_group(const uint4v (&a)[MI], const uint4v (&b)[NJ], floatx16 (&acc)[MI][NJ]) {
 #pragma unroll
@@ -1245,8 +1406,6 @@ constexpr int passes_before(int passes, int tap) {
   for (int t = 0; t < tap; ++t) n += passes_at(passes, t);
   return n;
 }
-constexpr int vm_imm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0F70; }   // s_waitcnt vmcnt(n) only
-
 template <int BN, int WGM, int WGN, int W, bool INTERIOR, int EPI = 0>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_conv3_patch(IgemmParams p) {
   static_assert(WGM * WGN == 4, "four wavefronts per workgroup");
@@ -1696,6 +1855,7 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
     if (a.dtype == AE_BF16) IGEMM_LAUNCH_T(bf16_t, BMV, BNV, GM, GN);          \
     else IGEMM_LAUNCH_T(float, BMV, BNV, GM, GN);                              \
   } while (0)
+  const bool dense_bf16 = a.dtype == AE_BF16 && dense && interior;
   if (a0.comp_mode != 0) {
     // (conv_comp_blocks: bfloat16, interior tiles, no split, not the eight-wavefront tile)
 #define IGEMM_LAUNCH_COMP(BMV, BNV, GM, GN)                                                                           \
@@ -1713,10 +1873,10 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
   if (a0.epi != CONV_EPI_NONE) {
     // (conv_epi_usable: interior tiles, BN = 128, no split; binary32 went to k_gemm_split above: a dense product of 128 columns or more)
     if (a.dtype != AE_BF16) return fail(AE_EINVAL, "conv_mfma: no such epilogue on the binary32 MFMA");
-#define IGEMM_LAUNCH_EPI(BMV, E) hipLaunchKernelGGL((k_igemm<bf16_t, BMV, 128, 2, 2, 64, true, true, E>), grid, dim3(256), 0, s, p)
+#define IGEMM_LAUNCH_EPI(BMV, E) hipLaunchKernelGGL((k_dense<BMV, 128, 2, 2, E>), grid, dim3(256), 0, s, p)
     if (t.bn == 256) {
-      if (a0.epi == CONV_EPI_MXQ) hipLaunchKernelGGL((k_igemm<bf16_t, 256, 256, 2, 4, 64, true, true, 1>), grid, dim3(512), 0, s, p);
-      else hipLaunchKernelGGL((k_igemm<bf16_t, 256, 256, 2, 4, 64, true, true, 2>), grid, dim3(512), 0, s, p);
+      if (a0.epi == CONV_EPI_MXQ) hipLaunchKernelGGL((k_dense<256, 256, 2, 4, 1>), grid, dim3(512), 0, s, p);
+      else hipLaunchKernelGGL((k_dense<256, 256, 2, 4, 2>), grid, dim3(512), 0, s, p);
     } else {
       if (t.bm == 256) { if (a0.epi == CONV_EPI_MXQ) IGEMM_LAUNCH_EPI(256, 1); else IGEMM_LAUNCH_EPI(256, 2); }
       else { if (a0.epi == CONV_EPI_MXQ) IGEMM_LAUNCH_EPI(128, 1); else IGEMM_LAUNCH_EPI(128, 2); }
@@ -1724,7 +1884,10 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
 #undef IGEMM_LAUNCH_EPI
     return launch_status("conv_mfma_epi");
   }
-  if (t.bn == 256) hipLaunchKernelGGL((k_igemm<bf16_t, 256, 256, 2, 4, 64, true, true>), grid, dim3(512), 0, s, p);   // (pick_tile: interior only)
+  if (dense_bf16 && t.bn == 256) hipLaunchKernelGGL((k_dense<256, 256, 2, 4>), grid, dim3(512), 0, s, p);
+  else if (dense_bf16 && t.bm == 256 && t.bn == 128) hipLaunchKernelGGL((k_dense<256, 128, 2, 2>), grid, dim3(256), 0, s, p);
+  else if (dense_bf16 && t.bm == 128 && t.bn == 128) hipLaunchKernelGGL((k_dense<128, 128, 2, 2>), grid, dim3(256), 0, s, p);
+  else if (t.bn == 256) hipLaunchKernelGGL((k_igemm<bf16_t, 256, 256, 2, 4, 64, true, true>), grid, dim3(512), 0, s, p);   // (pick_tile: interior only)
   else if (t.bm == 256 && t.bn == 128) IGEMM_LAUNCH_K(bf16_t, 256, 128, 2, 2, 64);
   else if (t.bm == 256) IGEMM_LAUNCH_K(bf16_t, 256, 64, 4, 1, 64);
   else if (t.bn == 128) IGEMM_LAUNCH(128, 128, 2, 2);

@@ -105,10 +105,13 @@ __device__ __forceinline__ float apply_act(float v, int act) {
 // scale exponent of a block from its largest magnitude (> 0): floor(log2 amax) - r_max (r_max = 2 for FP4 E2M1),
 // clamped to the E8M0 range
 __device__ __forceinline__ int mx_scale_exp(float amax, int r_max = 2) {
-  int k = ilogbf(amax) - r_max;                  // subnormal maxima included
-  k = k < -127 ? -127 : k;
-  return k > 127 ? 127 : k;
+  const int e = (int)(__float_as_uint(amax) >> 23);           // biased; 0: a subnormal maximum, clamped below whatever its value
+  if (e == 255) return 127;
+  const int k = e - 127 - r_max;
+  return k < -127 ? -127 : k;
 }
+// 2^k, -127 <= k <= 127 (2^-127 is subnormal)
+__device__ __forceinline__ float mx_pow2(int k) { return __uint_as_float(k == -127 ? 0x00400000u : (uint32_t)(k + 127) << 23); }
 // s * Q_e(v / s) for s = 2^k: nearest E2M1 magnitude, ties to even, saturating at 6
 __device__ __forceinline__ float mx_quant_e2m1(float v, float inv_s, float s) {
   const float y = v * inv_s;                     // exact (power of two), |y| < 8
