@@ -167,6 +167,8 @@ bool needs_dgrad_pack(const Step& st) { return st.kind == ST_CONV && st.thin == 
 // holds: the per-layer launches remain).
 // (channel counts that are whole 16-byte chunks in either type: plain conversion and transpose are the packed forms)
 bool is_big_fc(const Step& st) { return st.k == 1 && (int64_t)st.cout * st.cin >= (1 << 20) && st.cin % 8 == 0 && st.cout % 8 == 0; }
+// Does this pass of a fully-connected layer read the parameters themselves?  (Static parameters are packed once: half the bytes.)
+bool reads_params(const ae_model* m, const Step& st, bool dgrad) { return (dgrad ? st.fc_d : st.fc) && !m->params_static; }
 // channels per tap of the packed weights (0: as many as there are)
 int pack_ld(const Plan& P, const Step& st, bool dgrad) {
   return dgrad ? (st.chunks_d ? chan_pad(st.cout, P.dtype) : 0) : (st.chunks ? chan_pad(st.cin, P.dtype) : 0);
@@ -182,7 +184,7 @@ int pack_all(ae_model* m, const float* params, bool dgrad, hipStream_t s, int pa
   if (part == 0) m->packed_in_batch = false;
   for (const Step& st : P.steps) {
     const bool want = dgrad ? needs_dgrad_pack(st) : needs_fwd_pack(P, st);
-    if (!want) continue;
+    if (!want || reads_params(m, st, dgrad)) continue;
     if ((part == 1) != (is_big_fc(st) && !(dgrad ? st.up_dgrad : st.up_phases))) continue;
     if (dgrad ? st.up_dgrad : st.up_phases) {
       // upsampled conv in its cheaper form: summed weights, a kernel of their own
@@ -250,7 +252,7 @@ int join_pack(ae_model* m, hipStream_t s, bool big_fc = false) {
 
 int forward_conv(ae_model* m, int si, Step& st, const float* params, const void* in, hipStream_t s) {
   const Plan& P = m->plan;
-  if (st.thin == 0) AE_TRY(join_pack(m, s, is_big_fc(st)));
+  if (st.thin == 0 && !reads_params(m, st, false)) AE_TRY(join_pack(m, s, is_big_fc(st)));
   const double es = (double)dtype_size(P.dtype);
   const int64_t rows = (int64_t)P.batch * st.hc * st.wc;
   const double wel = (double)st.cout * st.cin * st.k * st.k;
@@ -265,6 +267,11 @@ int forward_conv(ae_model* m, int si, Step& st, const float* params, const void*
       TIMED(si, "fwd.conv_thin_out", 2.0 * raw_el * st.cin * st.k * st.k, (in_el + raw_el) * es,
             launch_thin_out_conv(in, params + st.w_off, params + st.b_off, st.out, st.aux, P.batch, st.hc, st.wc, st.cout,
                                  st.cin, st.up, st.act, P.dtype, s));
+    return AE_OK;
+  }
+  if (reads_params(m, st, false)) {
+    FcArgs f{in, params + st.w_off, params + st.b_off, st.out, P.batch, st.cout, st.cin, false, st.act, m->splitk_ws, P.max_splitk_floats};
+    TIMED(si, "fwd.fc", 2.0 * raw_el * st.cin, (in_el + raw_el) * es + wel * 4.0, launch_fc_direct(f, s));
     return AE_OK;
   }
   const void* w = nullptr;
@@ -596,6 +603,11 @@ int backward_conv(ae_model* m, int si, Step& st, const float* params, const void
              launch_wgrad_direct(wa, wws, wws == m->wgrad_ws ? P.max_wgrad_floats : P.max_wgrad_inorder_floats, ws));
   }
   AE_TRY(wgrad_enqueued());
+  if (st.needs_dx && reads_params(m, st, true)) {
+    FcArgs f{dr, params + st.w_off, nullptr, gnext, P.batch, st.cin, st.cout, true, ACT_NONE, m->splitk_ws, P.max_splitk_floats};
+    TIMED(si, "bwd.fc_dgrad", conv_flops, (in_el + raw_el) * es + wel * 4.0, launch_fc_direct(f, s));
+    return AE_OK;
+  }
   // input gradient: convolution of dr with the flipped, transposed weights at conv resolution
   if (st.needs_dx) {
     AE_TRY(join_pack(m, s, is_big_fc(st)));
@@ -720,6 +732,12 @@ int model_create(const char* layer_spec, int batch, int dtype, int bn_mode, ae_m
         // the kernel for any channel counts takes the cheaper forms always
         if (st.chunks) st.up_phases = true;
         if (st.chunks_d) st.up_dgrad = true;
+      }
+      if (st.mfma && st.k == 1 && !st.up && st.hc == 1 && st.wc == 1 && P.dtype == AE_BF16 && fc_direct_supported(P.batch, st.cin, st.cout)) {
+        st.fc = !st.has_bn && !st.pool && !st.aux;
+        // (a layer below whose ReLU or batch-norm backward rides in this launch's epilogue keeps the packed form)
+        const bool below = &st != &P.steps[0] && (&st - 1)->kind == ST_CONV;
+        st.fc_d = st.needs_dx && !below;
       }
       if (st.mfma && st.thin == 0) {
         // likewise the order of the packed weights

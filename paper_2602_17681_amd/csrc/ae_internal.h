@@ -80,6 +80,7 @@ struct Step {
   bool wfrag = false, wfrag_d = false;   // packed weights of the forward / input-gradient conv in MFMA fragment order (conv_weights_frag_order)
   int thin = 0;                     // 1: thin-in kernels (input is the planar boundary tensor); 2: thin-out kernels
   bool recompute = false;           // thin-in + bn + relu + pool2: the conv output is recomputed by every pass that needs it, never stored
+  bool fc = false, fc_d = false;    // forward / input gradient straight from the binary32 parameters (fc_direct_supported), unless the caller keeps them static
   bool out_planar = false;          // `out` is stored planar [n][C][H][W] (thin-out step)
 };
 
@@ -226,6 +227,16 @@ ConvChunksPlan plan_conv_chunks(const ConvArgs& a);   // (a.partial: rows per bl
 int64_t conv_chunks_splitk_floats(const ConvArgs& a);
 int launch_conv_chunks(const ConvArgs& a, hipStream_t s);
 int conv_partial_rows(const ConvArgs& a, bool mfma);  // rows per partial-sum block of the kernel that will run
+
+// Fully-connected layers of bf16 models straight from the binary32 parameters (ae_fc.hip): y[m][n] = act(a[m][:] w + bias),
+// w = [n][k] or, trans, [k][n].
+struct FcArgs {
+  const void* a; const float* w; const float* bias; void* y;
+  int m, n, k; bool trans; int act;
+  float* splitk_ws; int64_t splitk_floats;
+};
+bool fc_direct_supported(int m, int cin, int cout);   // both directions
+int launch_fc_direct(const FcArgs& a, hipStream_t s);
 
 struct WgradArgs {
   const void* x; const void* dy; float* dw_canonical;  // dw is accumulated with atomics: must be zeroed first
