@@ -11,8 +11,13 @@
 //                   ReLU + max-pool into LDS, conv 2, its output and partial statistics;
 //   k_small_tail    statistics of layer 2, batch-norm + ReLU + max-pool, flatten, fc, power normalisation, noise,
 //                   fc, reshape, both upsampled convolutions, sigmoid — all in LDS, y written once.
-// Arithmetic is plain binary32 FMA on the vector ALUs (these layers are far too small for the matrix cores);
-// definitions as in aemodel.h.  No activation is kept for a backward pass: the executor takes this path only for a
+// Arithmetic is binary32: the first three convolutions on the binary32 matrix instruction (16 pixels x 16 channels x 4 input
+// channels, one wavefront per 16 pixels), whose accumulators hold one channel per lane so that the batch statistics are
+// a few adds, the rest as fused multiply-adds on the vector ALUs.  Sixteen wavefronts per sample: a batch of 64 samples
+// occupies 64 of 256 compute units, so what counts is the length of one sample's chain of loads and LDS reads.  (Four
+// wavefronts and vector ALUs throughout: 10 + 18 + 50 us for the three launches at 64 samples of 28 x 28.  Now
+// 6 + 11 + 33; of the 33: statistics and pooling 4, fc 4.5, channel 1.5, fc 7.6, convolutions 9.5 and 4.3.)
+// Definitions as in aemodel.h.  No activation is kept for a backward pass: the executor takes this path only for a
 // model in inference mode.
 #include <hip/hip_runtime.h>
 
@@ -23,10 +28,18 @@
 namespace ae {
 namespace {
 
-constexpr int NT_MAX = 256;     // threads per workgroup (more wavefronts per sample were measured slower)
-constexpr int NT_CONV2 = 256;
-constexpr int COB = 16;        // output channels per accumulator block
+constexpr int NT_MAX = 1024;   // threads per workgroup (launch_fused_small chooses 1024 or 512)
 #define NT ((int)blockDim.x)
+constexpr int COB = 16;        // output channels per accumulator block
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
+// v of the lane that a DPP control selects
+template <int CTRL> __device__ __forceinline__ float dpp(float v) {
+  return __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), CTRL, 0xF, 0xF, false));
+}
+// sum over the 4 lanes of a quad / the 16 lanes of a row, in every lane of it
+__device__ __forceinline__ float quad_sum(float v) { v += dpp<0xB1>(v); return v + dpp<0x4E>(v); }
+__device__ __forceinline__ float row_sum(float v) { v += dpp<0x128>(v); v += dpp<0x124>(v); v += dpp<0x122>(v); return v + dpp<0x121>(v); }
 
 // sum over the workgroup of `v` (every thread contributes), result in thread 0 only; red: NT/64 floats of LDS
 __device__ __forceinline__ float block_sum_to0(float v, float* red) {
@@ -78,88 +91,82 @@ __device__ __forceinline__ void bn_vectors(const float* __restrict__ partial, in
   }
 }
 
-// One 3x3 convolution (zero padding) of a planar LDS image src[cin][hs*ws], read through an optional x2
-// nearest-neighbour upsample (UP: the convolution runs at 2hs x 2ws), for the output channels [co0, co0 + NCO):
-// weights wl[(ci*9 + tap)*NCO + k] in LDS (every lane reads the same address: a broadcast; scalar loads of the
-// weights straight from global memory were measured slower).  Thread-per-pixel; acc holds the NCO results of (y, x).
-template <int NCO, bool UP>
-__device__ __forceinline__ void conv3_pixel(const float* src, const float* wl, int cin, int hs, int ws, int y, int x,
-                                            float (&acc)[NCO]) {
-  const int hc = UP ? 2 * hs : hs, wc = UP ? 2 * ws : ws;
-  int off[9];
-  bool ok[9];
+// 16 output pixels x 16 channels of a 3x3 convolution (zero padding) of a planar LDS image src[cin][hs x ws] (planes `plane`
+// floats apart), UP: read through a x2 nearest-neighbour upsample.  Lane l multiplies input channel c + l/16 of pixel
+// `m0 + l % 16` (v_mfma_f32_16x16x4); results: channel l % 16 of pixels m0 + 4 (l/16) + 0..3.  Pixels past n_px are those of
+// pixel 0 (nobody stores them).  wl: [tap][cin rounded up to 4][16].
+template <bool UP>
+__device__ __forceinline__ floatx4 conv3_tile(const float* src, int plane, int cin, int hs, int ws, const float* wl, int m0, int n_px) {
+  const int lane = threadIdx.x & 63, g = lane >> 4;
+  const int hc = UP ? 2 * hs : hs, wc = UP ? 2 * ws : ws, cin4 = (cin + 3) & ~3;
+  const int px = m0 + (lane & 15) < n_px ? m0 + (lane & 15) : 0;
+  const int y = px / wc, x = px - y * wc;
+  floatx4 even = {0.f, 0.f, 0.f, 0.f}, odd = {0.f, 0.f, 0.f, 0.f};   // two chains: an MFMA waits for the one before the last
 #pragma unroll
-  for (int r = 0; r < 3; ++r)
+  for (int t = 0; t < 9; ++t) {
+    const int yy = y + t / 3 - 1, xx = x + t % 3 - 1;
+    const bool ok = yy >= 0 && yy < hc && xx >= 0 && xx < wc;
+    const float* sp = src + g * plane + (ok ? (UP ? (yy >> 1) * ws + (xx >> 1) : yy * ws + xx) : 0);
+    const float* wp = wl + (t * cin4 + g) * COB + (lane & 15);
+    const int c_end = ok ? cin - g : 0;          // this lane's channels g, g + 4, ... below cin
+    int c = 0;
+    for (; c + 32 <= cin4; c += 32) {            // all reads of 32 channels ahead of their MFMAs
+      float v[8], w[8];
 #pragma unroll
-    for (int s = 0; s < 3; ++s) {
-      const int yy = y + r - 1, xx = x + s - 1;
-      ok[r * 3 + s] = yy >= 0 && yy < hc && xx >= 0 && xx < wc;
-      const int ys = UP ? (yy >> 1) : yy, xs = UP ? (xx >> 1) : xx;
-      off[r * 3 + s] = ok[r * 3 + s] ? ys * ws + xs : 0;
+      for (int u = 0; u < 8; ++u) { v[u] = sp[(c + 4 * u) * plane]; w[u] = wp[(c + 4 * u) * COB]; }
+#pragma unroll
+      for (int u = 0; u < 8; u += 2) {
+        even = __builtin_amdgcn_mfma_f32_16x16x4f32(c + 4 * u < c_end ? v[u] : 0.0f, w[u], even, 0, 0, 0);
+        odd = __builtin_amdgcn_mfma_f32_16x16x4f32(c + 4 * u + 4 < c_end ? v[u + 1] : 0.0f, w[u + 1], odd, 0, 0, 0);
+      }
     }
-  const int plane = hs * ws;
-  for (int ci = 0; ci < cin; ++ci) {
-    const float* sp = src + ci * plane;
-    const float* wp = wl + ci * 9 * NCO;
-#pragma unroll
-    for (int t = 0; t < 9; ++t) {
-      const float v = ok[t] ? sp[off[t]] : 0.0f;
-#pragma unroll
-      for (int k = 0; k < NCO; ++k) acc[k] = fmaf(v, wp[t * NCO + k], acc[k]);
+    for (; c + 8 <= cin4; c += 8) {
+      const float v0 = c < c_end ? sp[c * plane] : 0.0f, v1 = c + 4 < c_end ? sp[(c + 4) * plane] : 0.0f;
+      even = __builtin_amdgcn_mfma_f32_16x16x4f32(v0, wp[c * COB], even, 0, 0, 0);
+      odd = __builtin_amdgcn_mfma_f32_16x16x4f32(v1, wp[(c + 4) * COB], odd, 0, 0, 0);
     }
+    if (c < cin4) even = __builtin_amdgcn_mfma_f32_16x16x4f32(c < c_end ? sp[c * plane] : 0.0f, wp[c * COB], even, 0, 0, 0);
   }
+  return even + odd;
 }
-
-// The 2x2 block of output pixels (rows 2*by, 2*by + 1, columns 2*bx, 2*bx + 1) of a plain 3x3 convolution of
-// src[cin][hs][ws] (hs, ws even): the block's 36 taps read the 4x4 source window around it, loaded once per input
-// channel; a weight serves four pixels.  Each output adds its taps in the order (ci, r, s) as conv3_pixel does.
-// wl: [ci*9 + tap][wstride], this thread's NCO channels first.  acc[2*a + b] is pixel (2*by + a, 2*bx + b).
-template <int NCO>
-__device__ __forceinline__ void conv3_block(const float* src, const float* wl, int wstride, int cin, int hs, int ws,
-                                            int by, int bx, float (&acc)[4][NCO]) {
-  int off[16];
-  bool ok[16];
-#pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    const int yy = 2 * by + q / 4 - 1, xx = 2 * bx + q % 4 - 1;
-    ok[q] = yy >= 0 && yy < hs && xx >= 0 && xx < ws;
-    off[q] = ok[q] ? yy * ws + xx : 0;
+// canonical conv weights W[co][ci][3][3], channels co0 .. co0 + 15 -> wl[tap][cin rounded up to 4][16] (zero beyond cin)
+__device__ __forceinline__ void stage_tile_weights(const float* __restrict__ w, int cin, int co0, float* wl) {
+  const int cin4 = (cin + 3) & ~3, row = cin * 9;
+  const float* src = w + (int64_t)co0 * row;
+  for (int i = threadIdx.x; i < COB * row; i += NT) {
+    const int co = i / row, r = i - co * row, ci = r / 9, t = r - ci * 9;
+    wl[(t * cin4 + ci) * COB + co] = src[i];
   }
-  const int plane = hs * ws;
-  for (int ci = 0; ci < cin; ++ci) {
-    const float* sp = src + ci * plane;
-    const float* wp = wl + ci * 9 * wstride;
-    float sv[16];
-#pragma unroll
-    for (int q = 0; q < 16; ++q) sv[q] = ok[q] ? sp[off[q]] : 0.0f;
-#pragma unroll
-    for (int t = 0; t < 9; ++t) {
-      float w[NCO];
-      if constexpr (NCO == 4) {
-        const float4 w4 = *reinterpret_cast<const float4*>(wp + t * wstride);
-        w[0] = w4.x; w[1] = w4.y; w[2] = w4.z; w[3] = w4.w;
-      } else {
-#pragma unroll
-        for (int k = 0; k < NCO; ++k) w[k] = wp[t * wstride + k];
-      }
-#pragma unroll
-      for (int ab = 0; ab < 4; ++ab) {
-        const float v = sv[((ab >> 1) + t / 3) * 4 + (ab & 1) + t % 3];
-#pragma unroll
-        for (int k = 0; k < NCO; ++k) acc[ab][k] = fmaf(v, w[k], acc[ab][k]);
-      }
+  if (cin4 != cin)
+    for (int i = threadIdx.x; i < 9 * (cin4 - cin) * COB; i += NT) {
+      const int co = i % COB, t = i / COB;
+      wl[((t % 9) * cin4 + cin + t / 9) * COB + co] = 0.0f;
     }
+}
+// Sum and sum of squares of a channel over the workgroup's tiles, lane l holding channel l % 16: over the four lane groups,
+// then the wavefronts in order.  red: [NT / 64][2][COB]; the first 2 COB threads store.
+__device__ __forceinline__ void store_channel_sums(float s1, float s2, float* red, float* __restrict__ part, int C, int co0) {
+  s1 += __shfl_xor(s1, 16, 64); s1 += __shfl_xor(s1, 32, 64);
+  s2 += __shfl_xor(s2, 16, 64); s2 += __shfl_xor(s2, 32, 64);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if (lane < COB) { red[(wave * 2) * COB + lane] = s1; red[(wave * 2 + 1) * COB + lane] = s2; }
+  __syncthreads();
+  if ((int)threadIdx.x < 2 * COB) {
+    float t = 0.0f;
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) t += red[w * 2 * COB + threadIdx.x];
+    part[(threadIdx.x / COB) * C + co0 + threadIdx.x % COB] = t;
   }
 }
 
 // The 2x2 block of output pixels (rows 2*by, 2*by + 1, columns 2*bx, 2*bx + 1) of a 3x3 convolution behind a x2
 // nearest upsample of src[cin][hs][ws]: the block's 36 taps read only the 3x3 source cells around (by, bx), which
-// are loaded once per input channel, and a weight serves four pixels.  (One pixel per thread, conv3_pixel, is bound
+// are loaded once per input channel, and a weight serves four pixels.  (One pixel per thread is bound
 // by the LDS reads: a value and NCO weights per NCO multiply-adds.)  Each output adds its taps in the order
-// (ci, r, s): the sums are those of conv3_pixel<NCO, true> bit for bit.
-// wl: [ci*9 + tap][wstride], this thread's NCO channels first.  acc[2*a + b] is pixel (2*by + a, 2*bx + b).
+// (ci, r, s); this call adds the input channels ci0, ci0 + 4, ...
+// wl: [ci*9 + tap][NCO].  acc[2*a + b] is pixel (2*by + a, 2*bx + b).
 template <int NCO>
-__device__ __forceinline__ void conv3_up_block(const float* src, const float* wl, int wstride, int cin, int hs, int ws,
+__device__ __forceinline__ void conv3_up_block(const float* src, int plane, const float* wl, int ci0, int cin, int hs, int ws,
                                                int by, int bx, float (&acc)[4][NCO]) {
   int off[9];
   bool ok[9];
@@ -169,10 +176,9 @@ __device__ __forceinline__ void conv3_up_block(const float* src, const float* wl
     ok[q] = yy >= 0 && yy < hs && xx >= 0 && xx < ws;
     off[q] = ok[q] ? yy * ws + xx : 0;
   }
-  const int plane = hs * ws;
-  for (int ci = 0; ci < cin; ++ci) {
+  for (int ci = ci0; ci < cin; ci += 4) {
     const float* sp = src + ci * plane;
-    const float* wp = wl + ci * 9 * wstride;
+    const float* wp = wl + ci * 9 * NCO;
     float sv[9];
 #pragma unroll
     for (int q = 0; q < 9; ++q) sv[q] = ok[q] ? sp[off[q]] : 0.0f;
@@ -180,11 +186,11 @@ __device__ __forceinline__ void conv3_up_block(const float* src, const float* wl
     for (int t = 0; t < 9; ++t) {
       float w[NCO];
       if constexpr (NCO == 4) {
-        const float4 w4 = *reinterpret_cast<const float4*>(wp + t * wstride);
+        const float4 w4 = *reinterpret_cast<const float4*>(wp + t * NCO);
         w[0] = w4.x; w[1] = w4.y; w[2] = w4.z; w[3] = w4.w;
       } else {
 #pragma unroll
-        for (int k = 0; k < NCO; ++k) w[k] = wp[t * wstride + k];
+        for (int k = 0; k < NCO; ++k) w[k] = wp[t * NCO + k];
       }
 #pragma unroll
       for (int ab = 0; ab < 4; ++ab) {
@@ -214,66 +220,53 @@ struct SmallArgs {
   int B, c0, h, w, c1, c2, n, cr, c3, c4;       // cr: channels after the reshape (input of the first decoder conv)
   int64_t w1, b1, bn1, w2, b2, bn2, wf1, bf1, wf2, bf2, w3, b3, w4, b4;   // offsets into params
   float sigma; uint64_t seed, first_sample;
+  int plane2, plane_d, plane3;                    // plane strides in LDS of conv 2's input, the decoder fc's output, the last conv's input
 };
 
 // ---- launch 1: conv 1 (planar input, c0 <= 4 channels) ------------------------------------------------------------
+// K = (ci, tap), four of them per MFMA
 __global__ __launch_bounds__(NT_MAX) void k_small_conv1(SmallArgs a) {
   extern __shared__ float lds[];
+  const int hw = a.h * a.w, K = a.c0 * 9, K4 = (K + 3) & ~3;
   float* img = lds;                               // [c0][h*w]
-  float* wl = img + a.c0 * a.h * a.w;             // [c0*9][COB]
-  float* red = wl + a.c0 * 9 * COB;               // [NT][2*COB + 1]: per-thread statistics (odd stride: no bank conflicts)
-  const int b = blockIdx.x, hw = a.h * a.w;
+  float* red = img + a.c0 * hw;                   // [NT/64][2][COB]
+  const int b = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4;
   const float* xb = a.x + (int64_t)b * a.c0 * hw;
   for (int i = threadIdx.x; i < a.c0 * hw; i += NT) img[i] = xb[i];
-  const float* bias = a.params + a.b1;
   for (int co0 = 0; co0 < a.c1; co0 += COB) {
-    __syncthreads();
-    stage_weights(a.params + a.w1, a.c1, a.c0, co0, COB, wl);
-    __syncthreads();
-    float s1[COB], s2[COB];
+    const int co = co0 + (lane & 15);
+    const float bias = a.params[a.b1 + co];
+    float wk[9];                                  // this lane's weights: k = 4 s + g
 #pragma unroll
-    for (int k = 0; k < COB; ++k) { s1[k] = 0.0f; s2[k] = 0.0f; }
-    for (int p = threadIdx.x; p < hw; p += NT) {
-      float acc[COB];
+    for (int s = 0; s < 9; ++s) wk[s] = 4 * s + g < K ? a.params[a.w1 + (int64_t)co * K + 4 * s + g] : 0.0f;
+    __syncthreads();                              // the image is there; the sums of the block before have been read
+    float s1 = 0.0f, s2 = 0.0f;
+    for (int m0 = wave * 16; m0 < hw; m0 += NT / 64 * 16) {       // (hw is a multiple of 16)
+      const int px = m0 + (lane & 15), y = px / a.w, x = px - y * a.w;
+      floatx4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int k = 0; k < COB; ++k) acc[k] = bias[co0 + k];
-      conv3_pixel<COB, false>(img, wl, a.c0, a.h, a.w, p / a.w, p % a.w, acc);
-      float* dst = a.raw1 + ((int64_t)b * hw + p) * a.c1 + co0;    // (c1 and co0 are multiples of COB: 16-byte pieces)
+      for (int s = 0; s < 9; ++s) {
+        if (4 * s >= K4) break;
+        const int k = 4 * s + g, ci = k / 9, t = k - 9 * ci, yy = y + t / 3 - 1, xx = x + t % 3 - 1;
+        const bool ok = k < K && yy >= 0 && yy < a.h && xx >= 0 && xx < a.w;
+        const float v = img[ok ? ci * hw + yy * a.w + xx : 0];
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(ok ? v : 0.0f, wk[s], acc, 0, 0, 0);
+      }
+      float* dst = a.raw1 + ((int64_t)b * hw + m0 + 4 * g) * a.c1 + co;
 #pragma unroll
-      for (int k = 0; k < COB; k += 4) *reinterpret_cast<float4*>(dst + k) = make_float4(acc[k], acc[k + 1], acc[k + 2], acc[k + 3]);
-#pragma unroll
-      for (int k = 0; k < COB; ++k) {
-        const float d = acc[k] - bias[co0 + k];
-        s1[k] += d;
-        s2[k] = fmaf(d, d, s2[k]);
+      for (int r = 0; r < 4; ++r) {
+        dst[r * a.c1] = acc[r] + bias;
+        s1 += acc[r];
+        s2 = fmaf(acc[r], acc[r], s2);
       }
     }
-    // channel sums over the threads in a fixed order, through LDS: groups of 32 threads, then the groups
-    constexpr int SR = 2 * COB + 1;
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < COB; ++k) { red[threadIdx.x * SR + k] = s1[k]; red[threadIdx.x * SR + COB + k] = s2[k]; }
-    __syncthreads();
-    {
-      const int c = threadIdx.x % (2 * COB), g = threadIdx.x / (2 * COB);      // NT / 32 groups of 32 threads
-      float t = 0.0f;
-      for (int th = g * 32; th < g * 32 + 32; ++th) t += red[th * SR + c];
-      __syncthreads();
-      red[g * SR + c] = t;
-      __syncthreads();
-      if (g == 0) {
-        float u = 0.0f;
-        for (int gg = 0; gg < NT / 32; ++gg) u += red[gg * SR + c];
-        const int q = c / COB, k = c % COB;
-        if (co0 + k < a.c1) a.part1[((int64_t)b * 2 + q) * a.c1 + co0 + k] = u;
-      }
-    }
+    store_channel_sums(s1, s2, red, a.part1 + (int64_t)b * 2 * a.c1, a.c1, co0);
   }
 }
 
 // batch-norm + ReLU + 2x2 max-pool of a [pixels][C] conv output of one sample into a planar LDS image dst[C][hp*wp]
 __device__ __forceinline__ void bn_relu_pool_to_lds(const float* __restrict__ raw, int hc, int wc, int C, const float* scale,
-                                                    const float* shift, float* dst) {
+                                                    const float* shift, float* dst, int plane) {
   const int hp = hc / 2, wp = wc / 2;
   for (int i = threadIdx.x; i < hp * wp * C; i += NT) {
     const int c = i % C, q = i / C;
@@ -282,65 +275,66 @@ __device__ __forceinline__ void bn_relu_pool_to_lds(const float* __restrict__ ra
     const float* r0 = raw + ((int64_t)(2 * yy) * wc + 2 * xx) * C + c;
     const float v0 = fmaf(r0[0], sc, sh), v1 = fmaf(r0[C], sc, sh);
     const float v2 = fmaf(r0[(int64_t)wc * C], sc, sh), v3 = fmaf(r0[(int64_t)wc * C + C], sc, sh);
-    dst[c * (hp * wp) + q] = fmaxf(fmaxf(fmaxf(v0, v1), fmaxf(v2, v3)), 0.0f);
+    dst[c * plane + q] = fmaxf(fmaxf(fmaxf(v0, v1), fmaxf(v2, v3)), 0.0f);
   }
 }
 
 // ---- launch 2: layer-1 statistics, bn + relu + pool, conv 2 (one workgroup per sample and block of COB channels) ----
-__global__ __launch_bounds__(NT_CONV2) void k_small_conv2(SmallArgs a) {
+__global__ __launch_bounds__(NT_MAX) void k_small_conv2(SmallArgs a) {
   extern __shared__ float lds[];
   const int h2 = a.h / 2, w2 = a.w / 2, hw2 = h2 * w2;
   double* tmp = reinterpret_cast<double*>(lds);   // [2*256] scratch of the statistics
-  float* a1 = lds + 1024;                         // [c1][hw2]
-  float* wl = a1 + a.c1 * hw2;                    // [c1*9][COB]
+  float* a1 = lds + 1024;                         // [c1][plane2]
+  float* wl = a1 + a.c1 * a.plane2;               // [9][c1][COB]
   float* scale = wl + a.c1 * 9 * COB;             // [c1]
   float* shift = scale + a.c1;                    // [c1]
-  float* red = shift + a.c1;
-  const int b = blockIdx.x, co0 = blockIdx.y * COB;
+  float* red = shift + a.c1;                      // [NT/64][2][COB]
+  const int b = blockIdx.x, co0 = blockIdx.y * COB, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  stage_tile_weights(a.params + a.w2, a.c1, co0, wl);
   bn_vectors(a.part1, a.B, a.c1, 1.0 / ((double)a.B * a.h * a.w), a.params + a.b1, a.params + a.bn1, scale, shift, tmp);
-  stage_weights(a.params + a.w2, a.c2, a.c1, co0, COB, wl);
   __syncthreads();
-  bn_relu_pool_to_lds(a.raw1 + (int64_t)b * a.h * a.w * a.c1, a.h, a.w, a.c1, scale, shift, a1);
+  bn_relu_pool_to_lds(a.raw1 + (int64_t)b * a.h * a.w * a.c1, a.h, a.w, a.c1, scale, shift, a1, a.plane2);
   __syncthreads();
-  const float* bias = a.params + a.b2;
-  // a thread owns a 2x2 block of output pixels and four of the workgroup's COB channels; the threads of a wavefront
-  // share the channels (their weight reads are broadcasts)
-  const int h4 = h2 / 2, w4 = w2 / 2, nblk = h4 * w4;
-  float* part = red + NT / 64 * 2 * COB;          // [item][sum | sum sq][4]: statistics of each item's 16 outputs
-  for (int item = threadIdx.x; item < nblk * (COB / 4); item += NT) {
-    const int blk = item % nblk, g4 = item / nblk;
-    const int by = blk / w4, bx = blk % w4;
-    float acc[4][4], bk[4];
+  const int co = co0 + (lane & 15);
+  const float bias = a.params[a.b2 + co];
+  float s1 = 0.0f, s2 = 0.0f;
+  for (int m0 = wave * 16; m0 < hw2; m0 += NT / 64 * 16) {
+    const floatx4 acc = conv3_tile<false>(a1, a.plane2, a.c1, h2, w2, wl, m0, hw2);
+    const int px = m0 + (lane >> 4) * 4;
+    if (px < hw2) {                               // (hw2 is a multiple of 4)
+      float* dst = a.raw2 + ((int64_t)b * hw2 + px) * a.c2 + co;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      bk[k] = bias[co0 + 4 * g4 + k];
-#pragma unroll
-      for (int ab = 0; ab < 4; ++ab) acc[ab][k] = bk[k];
-    }
-    conv3_block<4>(a1, wl + 4 * g4, COB, a.c1, h2, w2, by, bx, acc);
-    float s1[4] = {0.f, 0.f, 0.f, 0.f}, s2[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int ab = 0; ab < 4; ++ab) {
-      const int pix = (2 * by + (ab >> 1)) * w2 + 2 * bx + (ab & 1);
-      *reinterpret_cast<float4*>(a.raw2 + ((int64_t)b * hw2 + pix) * a.c2 + co0 + 4 * g4) =
-          make_float4(acc[ab][0], acc[ab][1], acc[ab][2], acc[ab][3]);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const float d = acc[ab][k] - bk[k];
-        s1[k] += d;
-        s2[k] = fmaf(d, d, s2[k]);
+      for (int r = 0; r < 4; ++r) {
+        dst[r * a.c2] = acc[r] + bias;
+        s1 += acc[r];
+        s2 = fmaf(acc[r], acc[r], s2);
       }
     }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) { part[item * 8 + k] = s1[k]; part[item * 8 + 4 + k] = s2[k]; }
   }
-  __syncthreads();
-  // channel sums over the blocks in index order
-  if ((int)threadIdx.x < 2 * COB) {
-    const int q = threadIdx.x / COB, kk = threadIdx.x % COB;
-    float t = 0.0f;
-    for (int blk = 0; blk < nblk; ++blk) t += part[(blk + nblk * (kk >> 2)) * 8 + q * 4 + (kk & 3)];
-    if (co0 + kk < a.c2) a.part2[((int64_t)b * 2 + q) * a.c2 + co0 + kk] = t;
+  store_channel_sums(s1, s2, red, a.part2 + (int64_t)b * 2 * a.c2, a.c2, co0);
+}
+
+template <int NCO>
+__device__ __forceinline__ void last_conv(const SmallArgs& a, const float* a3, const float* wl, float* __restrict__ yb, int h2, int w2) {
+  const int q = threadIdx.x & 3;
+  for (int blk = threadIdx.x >> 2; blk < h2 * w2; blk += NT / 4) {          // (the lanes of a quad stay together)
+    const int by = blk / w2, bx = blk - by * w2;
+    float acc[4][NCO];
+#pragma unroll
+    for (int ab = 0; ab < 4; ++ab)
+#pragma unroll
+      for (int k = 0; k < NCO; ++k) acc[ab][k] = 0.0f;
+    conv3_up_block<NCO>(a3, a.plane3, wl, q, a.c3, h2, w2, by, bx, acc);
+#pragma unroll
+    for (int k = 0; k < NCO; ++k) {
+      float v = 0.0f;
+#pragma unroll
+      for (int ab = 0; ab < 4; ++ab) {
+        const float t = quad_sum(acc[ab][k]);
+        v = ab == q ? t : v;
+      }
+      if (k < a.c4) yb[(int64_t)k * a.h * a.w + (2 * by + (q >> 1)) * a.w + 2 * bx + (q & 1)] = apply_act(v + a.params[a.b4 + k], ACT_SIGMOID);
+    }
   }
 }
 
@@ -349,20 +343,27 @@ __global__ __launch_bounds__(NT_MAX) void k_small_tail(SmallArgs a) {
   extern __shared__ float lds[];
   const int h2 = a.h / 2, w2 = a.w / 2, h4 = a.h / 4, w4 = a.w / 4, hw4 = h4 * w4, hw2 = h2 * w2, hw = a.h * a.w;
   const int F = a.c2 * hw4, FD = a.cr * hw4;      // flattened encoder output; decoder fc output
+  const int cr4 = (a.cr + 3) & ~3;
   double* tmp = reinterpret_cast<double*>(lds);   // [2*256] scratch of the statistics
   float* a2 = lds + 1024;                         // [c2][hw4]   (flatten order)
-  float* dec = a2 + F;                            // [cr][hw4]   (reshape order)
-  float* a3 = dec + FD;                           // [c3][hw2]
-  float* lat = a3 + a.c3 * hw2;                   // [n] z, then the channel output
+  float* dec = a2 + F;                            // [cr][plane_d]   (reshape order)
+  float* a3 = dec + cr4 * a.plane_d;              // [c3][plane3]
+  float* lat = a3 + a.c3 * a.plane3;              // [n] z, then the channel output
   float* scale = lat + a.n;                       // [c2]
   float* shift = scale + a.c2;
-  float* red = shift + a.c2;                      // [NT/64 + 1]
-  float* wl = reinterpret_cast<float*>((reinterpret_cast<uintptr_t>(red + NT / 64 + 4) + 15) & ~(uintptr_t)15);   // weights of the decoder convs (16-byte aligned: read four at a time)
+  float* red = lds;                               // [NT/64 + 1], over the scratch of the statistics
+  float* wl = reinterpret_cast<float*>((reinterpret_cast<uintptr_t>(shift + a.c2) + 15) & ~(uintptr_t)15);   // weights of the decoder convs (16-byte aligned: read four at a time)
   const int b = blockIdx.x;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  stage_tile_weights(a.params + a.w3, a.cr, 0, wl);
   bn_vectors(a.part2, a.B, a.c2, 1.0 / ((double)a.B * hw2), a.params + a.b2, a.params + a.bn2, scale, shift, tmp);
   __syncthreads();
-  bn_relu_pool_to_lds(a.raw2 + (int64_t)b * hw2 * a.c2, h2, w2, a.c2, scale, shift, a2);
+  bn_relu_pool_to_lds(a.raw2 + (int64_t)b * hw2 * a.c2, h2, w2, a.c2, scale, shift, a2, hw4);
+  // weights of the last conv: over the scratch of the statistics where they fit, else over those of the conv before it once it is done
+  const int nco4 = a.c4 == 1 ? 1 : 4;
+  const bool w4_early = a.c3 * 9 * nco4 <= 1024 - 32;
+  float* wl4 = w4_early ? lds + 32 : wl;
+  if (w4_early) stage_weights(a.params + a.w4, a.c4, a.c3, 0, nco4, wl4);
   __syncthreads();
   // fc to the latent: one wavefront per output row, lanes stride over the inputs
   {
@@ -405,7 +406,9 @@ __global__ __launch_bounds__(NT_MAX) void k_small_tail(SmallArgs a) {
       }
 #pragma unroll
       for (int r = 0; r < RB; ++r) {
-        const float t = wave_sum(acc[r]);
+        float t = row_sum(acc[r]);
+        t += __shfl_xor(t, 16, 64);
+        t += __shfl_xor(t, 32, 64);
         if (lane == 0 && o0 + r < a.n) lat[o0 + r] = t + a.params[a.bf1 + o0 + r];
       }
     }
@@ -431,101 +434,93 @@ __global__ __launch_bounds__(NT_MAX) void k_small_tail(SmallArgs a) {
     }
   }
   __syncthreads();
-  // decoder fc: one thread per output, the latent from LDS; a row is read in 16-byte pieces where the blob allows
+  // decoder fc: 16 lanes per output read a row in 16-byte pieces and add up over the lanes (one thread per output is bound by
+  // the vector cache, where every lane of a load touches a line of its own); one thread per output where rows have no such pieces
   {
     const float* wf = a.params + a.wf2;
     const bool vec = (a.n & 3) == 0 && (((uintptr_t)wf | (uintptr_t)lat) & 15) == 0;
-    for (int o = threadIdx.x; o < FD; o += NT) {
-      const float* row = wf + (int64_t)o * a.n;
-      float acc = a.params[a.bf2 + o];
-      if (vec) {
-#pragma unroll 8
-        for (int j = 0; j < a.n; j += 4) {
-          const float4 w4 = *reinterpret_cast<const float4*>(row + j);
+    if (vec) {
+      const int j0 = 4 * (threadIdx.x & 15);
+      constexpr int RB = 8;                       // outputs at a time: their loads are in flight together
+      const float inv_hw4 = 1.0f / (float)hw4;   // (o + 1/2) / hw4 rounds down to o / hw4: o < 2^14
+      for (int o0 = threadIdx.x >> 4; o0 < FD; o0 += NT / 16 * RB) {
+        float acc[RB];
+#pragma unroll
+        for (int r = 0; r < RB; ++r) acc[r] = 0.0f;
+        for (int j = j0; j < a.n; j += 64) {
           const float4 l4 = *reinterpret_cast<const float4*>(lat + j);
-          acc = fmaf(w4.w, l4.w, fmaf(w4.z, l4.z, fmaf(w4.y, l4.y, fmaf(w4.x, l4.x, acc))));
+          float4 w4[RB];
+#pragma unroll
+          for (int r = 0; r < RB; ++r) w4[r] = *reinterpret_cast<const float4*>(wf + (int64_t)min(o0 + r * (NT / 16), FD - 1) * a.n + j);
+#pragma unroll
+          for (int r = 0; r < RB; ++r) acc[r] = fmaf(w4[r].w, l4.w, fmaf(w4[r].z, l4.z, fmaf(w4[r].y, l4.y, fmaf(w4[r].x, l4.x, acc[r]))));
         }
-      } else {
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+          const int o = o0 + r * (NT / 16);
+          const float t = row_sum(acc[r]);
+          const int c = (int)(((float)o + 0.5f) * inv_hw4);
+          if ((threadIdx.x & 15) == 0 && o < FD) dec[c * a.plane_d + o - c * hw4] = t + a.params[a.bf2 + o];
+        }
+      }
+    } else {
+      for (int o = threadIdx.x; o < FD; o += NT) {
+        const float* row = wf + (int64_t)o * a.n;
+        float acc = a.params[a.bf2 + o];
 #pragma unroll 16
         for (int j = 0; j < a.n; ++j) acc = fmaf(row[j], lat[j], acc);
+        dec[(o / hw4) * a.plane_d + o % hw4] = acc;
       }
-      dec[o] = acc;
     }
   }
-  // first decoder conv: x2 upsample of dec [cr][h4 x w4], 3x3 to c3 channels at h2 x w2, ReLU, planar into a3.
-  // A thread owns a 2x2 block of output pixels and four channels; the threads of a wavefront share the channels
-  // (their weight reads are broadcasts).
+  // first decoder conv: x2 upsample of dec [cr][h4 x w4], 3x3 to c3 channels at h2 x w2, ReLU, planar into a3
   for (int co0 = 0; co0 < a.c3; co0 += COB) {
+    if (co0 > 0) {                                // (the first block's weights were staged before the statistics)
+      __syncthreads();
+      stage_tile_weights(a.params + a.w3, a.cr, co0, wl);
+    }
     __syncthreads();
-    stage_weights(a.params + a.w3, a.c3, a.cr, co0, COB, wl);
-    __syncthreads();
-    const int groups = (min(COB, a.c3 - co0) + 3) >> 2;
-    for (int item = threadIdx.x; item < hw4 * groups; item += NT) {
-      const int blk = item % hw4, g4 = item / hw4;
-      const int by = blk / w4, bx = blk % w4;
-      float acc[4][4];
+    const float bias = a.params[a.b3 + co0 + (lane & 15)];
+    for (int m0 = wave * 16; m0 < hw2; m0 += NT / 64 * 16) {
+      const floatx4 acc = conv3_tile<true>(dec, a.plane_d, a.cr, h4, w4, wl, m0, hw2);
+      const int px = m0 + (lane >> 4) * 4;
+      if (px < hw2) {
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const float bk = co0 + 4 * g4 + k < a.c3 ? a.params[a.b3 + co0 + 4 * g4 + k] : 0.0f;
-#pragma unroll
-        for (int ab = 0; ab < 4; ++ab) acc[ab][k] = bk;
+        for (int r = 0; r < 4; ++r) a3[(co0 + (lane & 15)) * a.plane3 + px + r] = fmaxf(acc[r] + bias, 0.0f);
       }
-      conv3_up_block<4>(dec, wl + 4 * g4, COB, a.cr, h4, w4, by, bx, acc);
-#pragma unroll
-      for (int k = 0; k < 4; ++k)
-        if (co0 + 4 * g4 + k < a.c3) {
-#pragma unroll
-          for (int ab = 0; ab < 4; ++ab)
-            a3[(co0 + 4 * g4 + k) * hw2 + (2 * by + (ab >> 1)) * w2 + 2 * bx + (ab & 1)] = fmaxf(acc[ab][k], 0.0f);
-        }
     }
   }
-  // last conv: x2 upsample of a3, 3x3 to c4 <= 4 channels at h x w, sigmoid, planar output; 2x2 blocks again
+  // last conv: x2 upsample of a3, 3x3 to c4 <= 4 channels at h x w, sigmoid, planar output: four lanes per 2x2 block of
+  // pixels take every fourth input channel each, add up, and store a pixel each
   __syncthreads();
+  if (!w4_early) {
+    stage_weights(a.params + a.w4, a.c4, a.c3, 0, nco4, wl4);
+    __syncthreads();
+  }
   float* yb = a.y + (int64_t)b * a.c4 * hw;
-  if (a.c4 == 1) {                                 // a single output channel: one accumulator per pixel, not four
-    stage_weights(a.params + a.w4, 1, a.c3, 0, 1, wl);
-    __syncthreads();
-    for (int blk = threadIdx.x; blk < hw2; blk += NT) {
-      const int by = blk / w2, bx = blk % w2;
-      float acc[4][1];
-#pragma unroll
-      for (int ab = 0; ab < 4; ++ab) acc[ab][0] = a.params[a.b4];
-      conv3_up_block<1>(a3, wl, 1, a.c3, h2, w2, by, bx, acc);
-#pragma unroll
-      for (int ab = 0; ab < 4; ++ab) yb[(2 * by + (ab >> 1)) * a.w + 2 * bx + (ab & 1)] = apply_act(acc[ab][0], ACT_SIGMOID);
-    }
-    return;
-  }
-  stage_weights(a.params + a.w4, a.c4, a.c3, 0, 4, wl);
-  __syncthreads();
-  for (int blk = threadIdx.x; blk < hw2; blk += NT) {
-    const int by = blk / w2, bx = blk % w2;
-    float acc[4][4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-#pragma unroll
-      for (int ab = 0; ab < 4; ++ab) acc[ab][k] = k < a.c4 ? a.params[a.b4 + k] : 0.0f;
-    conv3_up_block<4>(a3, wl, 4, a.c3, h2, w2, by, bx, acc);
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      if (k < a.c4) {
-#pragma unroll
-        for (int ab = 0; ab < 4; ++ab)
-          yb[(int64_t)k * hw + (2 * by + (ab >> 1)) * a.w + 2 * bx + (ab & 1)] = apply_act(acc[ab][k], ACT_SIGMOID);
-      }
-  }
+  if (nco4 == 1) last_conv<1>(a, a3, wl4, yb, h2, w2);
+  else last_conv<4>(a, a3, wl4, yb, h2, w2);
 }
 
-size_t lds1(const SmallArgs& a) { return sizeof(float) * ((size_t)a.c0 * a.h * a.w + (size_t)a.c0 * 9 * COB + (size_t)NT_MAX * (2 * COB + 1)); }
-size_t lds2(const SmallArgs& a) {
-  return sizeof(float) * (1024 + (size_t)a.c1 * (a.h / 2) * (a.w / 2) + (size_t)a.c1 * 9 * COB + 2 * a.c1 + NT_CONV2 / 64 * 2 * COB +
-                          (size_t)(a.h / 4) * (a.w / 4) * (COB / 4) * 8);
-}
+// LDS of the three launches in bytes
+size_t lds1(const SmallArgs& a) { return sizeof(float) * ((size_t)a.c0 * a.h * a.w + NT_MAX / 64 * 2 * COB); }
+size_t lds2(const SmallArgs& a) { return sizeof(float) * (1024 + (size_t)a.c1 * a.plane2 + (size_t)a.c1 * 9 * COB + 2 * a.c1 + NT_MAX / 64 * 2 * COB); }
 size_t lds3(const SmallArgs& a) {
-  const size_t F = (size_t)(a.c2 + a.cr) * (a.h / 4) * (a.w / 4);
-  const size_t wmax = (size_t)a.cr * 9 * COB > (size_t)a.c3 * 9 * 4 ? (size_t)a.cr * 9 * COB : (size_t)a.c3 * 9 * 4;
-  return sizeof(float) * (1024 + F + (size_t)a.c3 * (a.h / 2) * (a.w / 2) + a.n + 2 * a.c2 + NT_MAX / 64 + 4 + 4 + wmax);
+  const size_t cr4 = (a.cr + 3) & ~3;
+  const size_t wmax = cr4 * 9 * COB > (size_t)a.c3 * 9 * 4 ? cr4 * 9 * COB : (size_t)a.c3 * 9 * 4;
+  return sizeof(float) * (1024 + (size_t)a.c2 * (a.h / 4) * (a.w / 4) + cr4 * a.plane_d + (size_t)a.c3 * a.plane3 + a.n + 2 * a.c2 + 4 + wmax);
+}
+constexpr size_t kLds = 65536;
+// Plane strides of 16 floats more than a multiple of the 64 banks: the four lane groups of an MFMA read four neighbouring
+// planes at the same 16 pixels.  Planes without padding where a launch would not fit its LDS otherwise.
+void choose_planes(SmallArgs& a) {
+  auto pad = [](int n) { return (n + 47) / 64 * 64 + 16; };
+  const int hw2 = (a.h / 2) * (a.w / 2), hw4 = (a.h / 4) * (a.w / 4);
+  a.plane2 = pad(hw2);
+  if (lds2(a) > kLds) a.plane2 = hw2;
+  a.plane_d = pad(hw4); a.plane3 = pad(hw2);
+  if (lds3(a) > kLds) a.plane_d = hw4;
+  if (lds3(a) > kLds) a.plane3 = hw2;
 }
 
 #undef NT
@@ -557,7 +552,8 @@ bool fused_small_match(const Plan& P, FusedSmall* f) {
   if (S[3].cin != a.c2 * (a.h / 4) * (a.w / 4) || S[5].cin != a.n || S[7].hin != a.h / 4 || S[7].win != a.w / 4 ||
       a.cr * (a.h / 4) * (a.w / 4) != S[5].cout || S[8].cin != a.c3 || S[8].hin != a.h / 2)
     return false;
-  if (lds1(a) > 65536 || lds2(a) > 65536 || lds3(a) > 65536) return false;
+  choose_planes(a);
+  if (lds1(a) > kLds || lds2(a) > kLds || lds3(a) > kLds) return false;
   if ((int64_t)P.batch * 2 * (a.c1 + a.c2) > P.max_partial_floats) return false;   // the per-sample statistics live in the partial-sum buffer
   if (f) {
     f->w1 = S[0].w_off; f->b1 = S[0].b_off; f->bn1 = S[0].bn_off; f->w2 = S[1].w_off; f->b2 = S[1].b_off; f->bn2 = S[1].bn_off;
@@ -578,9 +574,14 @@ int launch_fused_small(const Plan& P, const FusedSmall& f, const float* params, 
   a.w1 = f.w1; a.b1 = f.b1; a.bn1 = f.bn1; a.w2 = f.w2; a.b2 = f.b2; a.bn2 = f.bn2;
   a.wf1 = f.wf1; a.bf1 = f.bf1; a.wf2 = f.wf2; a.bf2 = f.bf2; a.w3 = f.w3; a.b3 = f.b3; a.w4 = f.w4; a.b4 = f.b4;
   a.sigma = sigma; a.seed = seed; a.first_sample = first_sample;
-  hipLaunchKernelGGL(k_small_conv1, dim3(P.batch), dim3(NT_MAX), lds1(a), s, a);
-  hipLaunchKernelGGL(k_small_conv2, dim3(P.batch, f.c2 / COB), dim3(NT_CONV2), lds2(a), s, a);
-  hipLaunchKernelGGL(k_small_tail, dim3(P.batch), dim3(NT_MAX), lds3(a), s, a);
+  choose_planes(a);
+  // Sixteen wavefronts per sample while every sample has a compute unit to itself; beyond that eight, so that two workgroups
+  // fit the registers of one (28 x 28, 128 / 256 / 300 / 512 samples: 50 / 68 / 122 / 135 us with sixteen, 59 / 77 / 104 / 116 us
+  // with eight)
+  const dim3 nt(P.batch <= 256 ? NT_MAX : NT_MAX / 2);
+  hipLaunchKernelGGL(k_small_conv1, dim3(P.batch), nt, lds1(a), s, a);
+  hipLaunchKernelGGL(k_small_conv2, dim3(P.batch, f.c2 / COB), nt, lds2(a), s, a);
+  hipLaunchKernelGGL(k_small_tail, dim3(P.batch), nt, lds3(a), s, a);
   return launch_status("fused_small");
 }
 
