@@ -422,7 +422,7 @@ int build_plan(const char* spec, int batch, int dtype, int bn_mode, Plan* plan) 
                                         : st.thin == 2 ? thin_out_wz_bytes(st.cout, st.cin) : (int64_t)0));
       st.off_wpack_d = take(std::max(wpk, st.thin == 2 ? thin_wfrag_bytes(st.cin) : (int64_t)0));
       if (st.has_bn) st.off_bn = take(6 * (int64_t)st.cout * 4);
-      int64_t blocks = std::max<int64_t>((rows + 127) / 128, reduce_blocks(rows));  // finest partial-sum granularity
+      int64_t blocks = std::max<int64_t>((rows + 127) / 128, reduce_blocks_bound(rows));  // finest partial-sum granularity
       if (st.thin == 1) blocks = std::max<int64_t>(blocks, thin_in_mfma_blocks(batch, st.hc, st.wc));
       plan->max_partial_floats = std::max(plan->max_partial_floats, blocks * 2 * std::max(st.cout, st.cin));
       WgradArgs wa;
