@@ -424,40 +424,56 @@ __device__ __forceinline__ void igemm_epilogue(floatx16 (&acc)[BM / WGM / 32][BN
     else if (p.act == ACT_RELU) igemm_store_interior<T, MI, NJ, WN, SW, false, true>(acc, bias, stage, yrow, p.N, lane, s1, s2, p, mrow0, phase, ycol);
     else igemm_store_interior<T, MI, NJ, WN, SW, false, false>(acc, bias, stage, yrow, p.N, lane, s1, s2, p, mrow0, phase, ycol);
   } else {
+    // Checked tiles: the conv results are rounded and staged without looking at M, N or the activation; a rolled loop then
+    // applies the activation and stores what lies inside.  (With the checks, the activation and the output row formed per
+    // accumulator this was 30 to 40 KiB of straight-line code that every workgroup of a launch of a few slabs fetched once: bf16, 24 x
+    // 72 x 120 pixels, 3 -> 48 channels 35 -> 30 us, 48 -> 80 at half the side 26 -> 21, 48 -> 3 behind an upsample 27 -> 16.)
+    constexpr int EPC = 16 / ES;                 // elements per 16-byte chunk
+    constexpr int CPRO = WN / EPC;               // chunks per staged row
+    const int cols = min(WN, p.N - (n0 + wn * WN));       // of this wave's part, those inside (may be negative)
+    const int64_t mw = m0 + wm * WM;
+    float bias[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) bias[j] = p.bias && j * 32 + col_lane < cols ? p.bias[n0 + wn * WN + j * 32 + col_lane] : 0.0f;
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
+      const int rows = (int)min((int64_t)32, p.M - (mw + i * 32));
 #pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        const int col = n0 + wn * WN + j * 32 + col_lane;
-        const bool col_ok = col < p.N;
-        const float bias = (p.bias && col_ok) ? p.bias[col] : 0.0f;
+      for (int j = 0; j < NJ; ++j)
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
           const int lr = (e >> 2) * 8 + row_lane + (e & 3);
-          const int64_t m = m0 + wm * WM + i * 32 + lr;
-          const float v = round_to_storage<T>(acc[i][j][e] + bias);   // the stored conv result
-          if (p.partial && m < p.M && col_ok) { const float d = v - bias; s1[j] += d; s2[j] = fmaf(d, d, s2[j]); }
-          const float a = apply_act(v, p.act);
-          if (wide_store) {
-            Store<T>::st(&stage[lr * SW + j * 32 + col_lane], a);
-          } else if (m < p.M && col_ok) {
-            const int64_t o = (PHASED ? igemm_out_row(p, m, phase, 0) : m) * p.N + col;   // (column strips: interior tiles only)
-            Store<T>::st(&Y[o], a);
-            if (p.y_aux) p.y_aux[o] = a;
+          const float v = round_to_storage<T>(acc[i][j][e] + bias[j]);   // the stored conv result
+          if (p.partial) {                       // (columns past N are not stored)
+            const float d = lr < rows ? v - bias[j] : 0.0f;
+            s1[j] += d;
+            s2[j] = fmaf(d, d, s2[j]);
           }
+          Store<T>::st(&stage[lr * SW + j * 32 + col_lane], v);
         }
-      }
+      auto out_row = [&](int lr) {               // (column strips: interior tiles only)
+        const int64_t m = mw + i * 32 + lr;
+        return PHASED ? igemm_out_row(p, m, phase, 0) : m;
+      };
       if (wide_store) {
-        constexpr int EPC = 16 / ES;               // elements per 16-byte chunk
-        constexpr int CPRO = WN / EPC;             // chunks per staged row
-#pragma unroll
-        for (int c = 0; c < (32 * CPRO) / 64; ++c) {
-          const int idx = c * 64 + lane;
+#pragma unroll 1
+        for (int idx = lane; idx < 32 * CPRO; idx += 64) {
           const int lr = idx / CPRO, ch = idx % CPRO;
-          const int64_t m = m0 + wm * WM + i * 32 + lr;
-          const int col0 = n0 + wn * WN + ch * EPC;
-          if (m < p.M && col0 < p.N)
-            *reinterpret_cast<uint4v*>(Y + (PHASED ? igemm_out_row(p, m, phase, 0) : m) * p.N + col0) = *reinterpret_cast<const uint4v*>(&stage[lr * SW + ch * EPC]);
+          if (lr >= rows || ch * EPC >= cols) continue;
+          float f[EPC];
+          Store<T>::ldv(&stage[lr * SW + ch * EPC], f);
+#pragma unroll
+          for (int t = 0; t < EPC; ++t) f[t] = apply_act(f[t], p.act);
+          Store<T>::stv(Y + out_row(lr) * p.N + n0 + wn * WN + ch * EPC, f);
+        }
+      } else if (cols > 0) {
+#pragma unroll 1
+        for (int idx = lane; idx < rows * cols; idx += 64) {
+          const int lr = (int)((unsigned)idx / (unsigned)cols), c = idx - lr * cols;
+          const int64_t o = out_row(lr) * p.N + n0 + wn * WN + c;
+          const float a = apply_act(Store<T>::ld(&stage[lr * SW + c]), p.act);
+          Store<T>::st(&Y[o], a);
+          if (p.y_aux) p.y_aux[o] = a;
         }
       }
     }
