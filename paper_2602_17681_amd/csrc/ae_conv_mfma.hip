@@ -627,9 +627,22 @@ __device__ __forceinline__ IgemmTileId igemm_tile_id(const IgemmParams& p) {
     t.n = r <= sh ? sh : r - sh - 1;
   }
   if (p.tri >= 8) {                             // only the tiles of one off-diagonal block per pair are launched
-    const int tbm = p.tri_b / BM, tbn = p.tri_b / BN, per_pair = tbm * tbn;
-    const int pair = lb / per_pair, in_pair = lb - pair * per_pair;
-    const int tr = in_pair / tbn, tc = in_pair - tr * tbn;
+    const int tbm = p.tri_b / BM, tbn = p.tri_b / BN;
+    int tr, col;                                // tile row of its block; column among those of all pairs
+    if (gridDim.x > 256) {
+      // Several workgroups per compute unit: rows of equal K range together, the longest first, their columns spread over
+      // the XCDs.  (With a contiguous range of tiles each, one XCD gets the longest rows alone: two merges of 2048-blocks
+      // side by side, LU step of d = 4096, 1.23 against 1.15 ms.)
+      const int per_row = (int)gridDim.x / tbm, rank = (int)blockIdx.x / per_row;
+      col = xcd_logical_block((int)blockIdx.x - rank * per_row, per_row);
+      tr = p.tri == 9 ? tbm - 1 - rank : rank;
+    } else {
+      // one each: the longest K range decides, so neighbours share an L2 (d = 2048, 1536: 0.5 to 0.8 % of the step)
+      const int pair = lb / (tbm * tbn), in_pair = lb - pair * (tbm * tbn);
+      tr = in_pair / tbn;
+      col = pair * tbn + in_pair - tr * tbn;
+    }
+    const int pair = col / tbn, tc = col - pair * tbn;
     t.m = (2 * pair + (p.tri == 9 ? 1 : 0)) * tbm + tr;
     t.n = (2 * pair + (p.tri == 9 ? 0 : 1)) * tbn + tc;
   }
@@ -1833,7 +1846,10 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
     // units of a full round of 512 of the first kind: 256 of them 0.63, 512 halves 0.69, 256 halves 0.45, 256 tall ones 0.89.
     // Measured (QR step, 30 products): d = 512, 768, 1024 0.71, 0.97, 1.21 ms with halves, 0.94, 1.29, 1.63 without; d = 1536 the same;
     // d = 2048 3.66 with, 3.34 without; d = 4096 19.9 ms with tall tiles, 22.7 without.  Triangular K ranges gain from halves
-    // up to 256 tiles (d = 2048, LU step: 0.56 against 0.71 ms).
+    // up to 256 tiles (d = 2048, LU step: 0.56 against 0.71 ms), and the merges of the blocked inverse, launches that wait for
+    // one another, from quarters of 64 x 64 up to 128 tiles, two workgroups per compute unit: the longest K range is a chain of slabs, and
+    // a slab of a quarter is shorter (LU step in binary32, d = 1024 / 2048 / 3072: 0.321 / 0.562 / 1.189 ms with halves alone, 0.301 / 0.520 / 1.152
+    // with quarters; on another box 1.184 at d = 3072, 1.197 with quarters throughout, and at d = 2048 0.532, 0.537 with tiles of 64 x 32 up to 32 tiles).
     auto rounds = [](int64_t n, int64_t slots, double half, double full) {
       const int64_t rem = n % slots;
       return (double)(n / slots) * full + (rem == 0 ? 0.0 : rem <= slots / 2 ? half : full);
@@ -1846,6 +1862,10 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
     if (choice && tall < c128 && tall < c64) {
       p.tiles_mn /= 2;
       hipLaunchKernelGGL((k_gemm_split<256, 128, 4, 2, true>), dim3(grid.x / 2), dim3(512), 0, s, p);
+    } else if (choice && a0.tri >= 8 && n128 <= 128) {
+      p.tiles_n *= 2;
+      p.tiles_mn *= 4;
+      hipLaunchKernelGGL((k_gemm_split<64, 64, 2, 2, true>), dim3(grid.x * 4), dim3(256), 0, s, p);
     } else if (choice && (a0.tri != 0 ? n128 <= 256 : c64 < c128)) {
       p.tiles_n *= 2;
       p.tiles_mn *= 2;

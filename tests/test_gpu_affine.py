@@ -227,6 +227,18 @@ def test_inverse_at_a_width_of_three_blocks_of_1024(ae):
     assert np.abs(a @ got32 - np.eye(d)).max() < 1e-4
 
 
+@pytest.mark.parametrize("d", [1152, 2176])
+def test_inverse_merges_that_are_mostly_padding(ae, d):
+    """One block of 128 behind 1 024 and 2 048: the last merge has 64 x 64 tiles, one per compute unit (d = 1 152), or
+    128 x 64 tiles in the order for two of them (2 176), and most of its tiles lie in the identity padding.  The bound of the
+    sizes above, for the same reason."""
+    params = wl.make_lu_params(d, seed=d + 7, kind="random", noise=0.0)
+    a = ao.lu_compose(*params)
+    got = _inverse(ae, params, d, "f32")
+    assert _close(got, np.linalg.inv(a), TOL["f32"])
+    assert np.abs(a @ got - np.eye(d)).max() < 1e-4
+
+
 def test_largest_size_exercised(ae):
     """d = 8 192 (the widest residual stream of the model family the paper evaluates): A in full against the oracle, and
     the inverse through the residual A A^-1 = I on sampled columns."""
