@@ -292,6 +292,25 @@ def test_transform_mse_full_size(ae, dtype):
     assert np.all(np.abs(eb - eb_o) <= 2 * tol * eb_o + 1e-30)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d", [4, 8, 12, 260, 512, 520, 2050, 2056])
+def test_inverse_shift_by_pieces(ae, d, dtype):
+    """Rows of whole 16-byte pieces, around a wavefront's pass, and an entry off the border: the sum is formed in double, so the
+    result is the float64 product rounded once."""
+    import torch
+    g = torch.Generator().manual_seed(d)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    a, v = torch.randn(d, d, generator=g).to(td), torch.randn(d, generator=g)
+    ref = -(a.double() @ v.double())
+    for off_a, off_v in ((0, 0), (1, 0), (0, 1)):
+        at = torch.empty(d * d + 1, dtype=td, device="cuda")[off_a:off_a + d * d].view(d, d).copy_(a)
+        vt = torch.empty(d + 1, device="cuda")[off_v:off_v + d].copy_(v)
+        out = torch.full((d,), float("nan"), device="cuda")
+        ae.model_inverse_shift(at, vt, d, out)
+        # half a unit of the last place, and d roundings of double sums
+        assert ((out.cpu().double() - ref).abs() <= 2.0 ** -24 * ref.abs() + d * 2.0 ** -53 * (a.double().abs() @ v.double().abs())).all()
+
+
 def test_inverse_shift(ae):
     """The constant term -A^-1 v of the inverse map against a float64 product, and its argument checks."""
     import torch
