@@ -21,6 +21,7 @@
 //   k_wgrad_row3   weight gradient, three taps per workgroup from one input patch (bf16)
 //   k_wgrad_rows, k_wgrad   weight gradient, one tap per workgroup (1x1, odd shapes)
 //   k_wgrad_chunks          weight gradient of any channel counts, columns (tap, ci) walked across tap borders; binary32: k_wgrad_split
+//   k_dense                 dense bf16 products in check-free tiles
 //   k_gemm_split            binary32 products and convolutions by bf16 parts
 // The shared epilogue adds the bias, rounds to the storage type, optionally reduces per-channel
 // sum / sum of squares of the tile (batch-norm statistics), applies the activation and stores [M][N].
@@ -57,7 +58,7 @@ struct IgemmParams {
   // stored input (one per output parity (a, b) = (phase>>1, phase&1), pads 1-a and 1-b, weights
   // w + phase*N*K); row (n, i, j) of phase (a, b) is output pixel (2i+a, 2j+b) of a 2Hc x 2Wc image
   int phases;
-  // epilogue variants of the dense-GEMM use (EPI template parameter of k_dense and k_gemm_split):
+  // epilogue variants of the dense-GEMM use (EPI template parameter of k_dense, k_igemm and k_gemm_split):
   //   1: the stored output is MX block-quantised (blocks of mx_block output columns: a power of two from one 16-byte
   //      chunk up to the 64 columns of a wave tile; FP4 E2M1 elements);
   //   2: nothing is stored; the epilogue forms resid[m][n] - (acc + bias) and leaves per-tile column sums of it
@@ -993,7 +994,8 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
       return;
     }
   }
-  igemm_epilogue<T, BM, BN, WGM, WGN, INTERIOR, EPI, CHUNKS>(acc, p, smem, sRed, m0, n0, tile_m, phase);
+  static_assert(EPI != 2 || BM * BN * ES <= SLAB_BYTES, "resid");
+  igemm_epilogue<T, BM, BN, WGM, WGN, INTERIOR, EPI, CHUNKS, EPI == 2>(acc, p, smem, sRed, m0, n0, tile_m, phase);
 }
 
 // ---------------------------------------------------------------------------
@@ -1010,13 +1012,14 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
 // Measured against k_igemm's schedule with the same tiles (which read a slab's fragments behind the barrier that the slab's
 // MFMAs wait for): 4 096^3 143 -> 126 us, the quantising product of 16 384 x 4 096 x 4 096 683 -> 594 us, the one that only sums
 // its deviations 586 -> 537 us.  1 us a slab of 256 x 256 outputs, 0.55 us of it MFMAs at the full clock.
+// Which tiles come here, and with how many stages: dense_stages and launch_conv_mfma.
 // ---------------------------------------------------------------------------
-template <int BM, int BN, int WGM, int WGN, int EPI = 0>
+template <int BM, int BN, int WGM, int WGN, int NSTAGE, int EPI = 0>
 __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(2))) void k_dense(IgemmParams p) {
   constexpr int NT = WGM * WGN * 64, BKB = 64, BK = 32;
   constexpr int WM = BM / WGM, WN = BN / WGN, MI = WM / 32, NJ = WN / 32;
   constexpr int RSTEP = NT / 4, AC = BM / RSTEP, BC = BN / RSTEP, L = AC + BC;   // loads per thread and slab
-  constexpr int NSTAGE = (BM + BN) * BKB * 8 <= 160 * 1024 || NT == 512 ? 4 : 3;   // (four wavefronts: two workgroups share a compute unit's LDS)
+  static_assert(NSTAGE == 3 || NSTAGE == 4, "the waits below");
   constexpr int SA = BM * BKB, SB = BN * BKB, SW = WN + 8;
   constexpr int SLAB_BYTES = NSTAGE * (SA + SB), STAGE_BYTES = (NT / 64) * 32 * SW * 2;
   __shared__ __attribute__((aligned(16))) char smem[SLAB_BYTES > STAGE_BYTES ? SLAB_BYTES : STAGE_BYTES];
@@ -1610,8 +1613,33 @@ IgemmTile pick_tile(int64_t M, int cout, int cin, int es, bool wide = true, int 
   int bm = es == 2 ? 256 : 128;                 // 256-row tiles: bf16 only (register budget)
   if (((M + 255) / 256) * tiles_n < 512) bm = 128;
   (void)cin;
-  const int bkb = 64;                           // three LDS stages of 64-byte slabs: 2-3 workgroups per compute unit
+  const int bkb = 64;                           // slabs of 64 bytes: with three LDS stages two (256 x 128) or three (128 x 128) workgroups per compute unit
   return IgemmTile{bm, bn, bkb};
+}
+
+// LDS stages of k_dense with 128 x 128 tiles.  Three (50 KiB) let a compute unit hold three workgroups, four (67 KiB) two whose
+// loads run a slab further ahead.  Three where the compute units share the tiles unevenly (from 352) and where they save a round of
+// workgroups (513 to 768); four where there is at most one workgroup per compute unit or little more, beyond 768, where a few
+// columns of tiles stream their rows from memory and there is no round to save, and for triangular K ranges.  us with three /
+// four stages / k_igemm (three):
+//   256 tiles, 2 048^3: 33.2 / 28.2 / 29.4.             324, 2 304^3: 46.8 / 45.2 / 45.6.  352, 2 048 x 2 816 x 4 096: 65.9 / 67.7 / 70.0
+//   512, 4 096 x 2 048 x 4 096: 79.3 / 86.1 / 87.7.     576, 3 072^3: 84.2 / 94.4 / 89.2.  676, 3 328^3: 100.6 / 105.3 / 102.6
+//   768, 98 304 x 128 x 256: 23.4 / 26.0 / 23.9.        784, 3 584^3: 153 / 138 / 139
+//   512 in one column, K = 4 096: 144 / 135 / 134; in two: 108 / 104 / 109; 510 in three 89.3 / 87.5 / 89.4; 512 in four 79.5 / 85.1 / 86.5
+//   LU steps of d = 2 048 and 3 072: 392 and 833 / 381 and 797 / 426 and 854
+int dense_stages(int64_t tiles, int tiles_n, int tri) {
+  return tri == 0 && tiles >= 352 && tiles <= 768 && (tiles_n > 3 || tiles > 512) ? 3 : 4;
+}
+
+// Does k_dense take 256 x 128 tiles?  They leave it three stages at two workgroups per compute unit, like k_igemm, and its waits
+// let one slab's loads be in flight instead of two: it gains where K is short and the weights stay in the caches, and for
+// triangular K ranges.  us with k_dense / k_igemm, rows x columns x K:
+//   131 072 x 128 x 128 24.7 / 25.7, x 768 52.3 / 54.3, x 1 024 72.5 / 71.3;  65 536 x 384 x 128 34.2 / 34.9, x 256 41.0 / 41.2,
+//   x 512 53.5 / 53.3, x 2 048 149 / 144;  32 768 x 640 x 512 48.3 / 46.9, x 1 024 70.8 / 67.6;  32 768 x 1 152 x 64 43.3 / 44.6,
+//   x 256 60.8 / 59.1;  16 384 x 1 152 x 4 096 206 / 202.  Both products of a transformation error: 65 536 x 384 107 / 111,
+//   32 768 x 640 116 / 114, 32 768 x 896 162 / 170, 16 384 x 1 152 157 / 154, 8 192 x 2 176 249 / 245.  LU step of d = 4 096 1 158 / 1 164.
+bool dense_tall(int64_t N, int64_t K, int epi, int tri) {
+  return tri != 0 || (epi != CONV_EPI_NONE ? K < 1024 : N * K < (1 << 17));
 }
 
 }  // namespace
@@ -1892,6 +1920,8 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
     else IGEMM_LAUNCH_T(float, BMV, BNV, GM, GN);                              \
   } while (0)
   const bool dense_bf16 = a.dtype == AE_BF16 && dense && interior;
+  const int stages = dense_stages(grid.x, p.tiles_n, a0.tri);
+  const bool tall = dense_tall(p.N, p.K, a0.epi, a0.tri);
   if (a0.comp_mode != 0) {
     // (conv_comp_blocks: bfloat16, interior tiles, no split, not the eight-wavefront tile)
 #define IGEMM_LAUNCH_COMP(BMV, BNV, GM, GN)                                                                           \
@@ -1909,20 +1939,23 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
   if (a0.epi != CONV_EPI_NONE) {
     // (conv_epi_usable: interior tiles, BN = 128, no split; binary32 went to k_gemm_split above: a dense product of 128 columns or more)
     if (a.dtype != AE_BF16) return fail(AE_EINVAL, "conv_mfma: no such epilogue on the binary32 MFMA");
-#define IGEMM_LAUNCH_EPI(BMV, E) hipLaunchKernelGGL((k_dense<BMV, 128, 2, 2, E>), grid, dim3(256), 0, s, p)
-    if (t.bn == 256) {
-      if (a0.epi == CONV_EPI_MXQ) hipLaunchKernelGGL((k_dense<256, 256, 2, 4, 1>), grid, dim3(512), 0, s, p);
-      else hipLaunchKernelGGL((k_dense<256, 256, 2, 4, 2>), grid, dim3(512), 0, s, p);
-    } else {
-      if (t.bm == 256) { if (a0.epi == CONV_EPI_MXQ) IGEMM_LAUNCH_EPI(256, 1); else IGEMM_LAUNCH_EPI(256, 2); }
-      else { if (a0.epi == CONV_EPI_MXQ) IGEMM_LAUNCH_EPI(128, 1); else IGEMM_LAUNCH_EPI(128, 2); }
-    }
-#undef IGEMM_LAUNCH_EPI
+#define EPI_LAUNCH(E)                                                                                                        \
+  do {                                                                                                                       \
+    if (t.bn == 256) hipLaunchKernelGGL((k_dense<256, 256, 2, 4, 4, E>), grid, dim3(512), 0, s, p);                            \
+    else if (t.bm == 256 && tall) hipLaunchKernelGGL((k_dense<256, 128, 2, 2, 3, E>), grid, dim3(256), 0, s, p);                \
+    else if (t.bm == 256) hipLaunchKernelGGL((k_igemm<bf16_t, 256, 128, 2, 2, 64, true, true, E>), grid, dim3(256), 0, s, p);   \
+    else if (stages == 3) hipLaunchKernelGGL((k_dense<128, 128, 2, 2, 3, E>), grid, dim3(256), 0, s, p);                        \
+    else hipLaunchKernelGGL((k_dense<128, 128, 2, 2, 4, E>), grid, dim3(256), 0, s, p);                                         \
+  } while (0)
+    if (a0.epi == CONV_EPI_MXQ) EPI_LAUNCH(1);
+    else EPI_LAUNCH(2);
+#undef EPI_LAUNCH
     return launch_status("conv_mfma_epi");
   }
-  if (dense_bf16 && t.bn == 256) hipLaunchKernelGGL((k_dense<256, 256, 2, 4>), grid, dim3(512), 0, s, p);
-  else if (dense_bf16 && t.bm == 256 && t.bn == 128) hipLaunchKernelGGL((k_dense<256, 128, 2, 2>), grid, dim3(256), 0, s, p);
-  else if (dense_bf16 && t.bm == 128 && t.bn == 128) hipLaunchKernelGGL((k_dense<128, 128, 2, 2>), grid, dim3(256), 0, s, p);
+  if (dense_bf16 && t.bn == 256) hipLaunchKernelGGL((k_dense<256, 256, 2, 4, 4>), grid, dim3(512), 0, s, p);
+  else if (dense_bf16 && t.bm == 256 && t.bn == 128 && tall) hipLaunchKernelGGL((k_dense<256, 128, 2, 2, 3>), grid, dim3(256), 0, s, p);
+  else if (dense_bf16 && t.bm == 128 && t.bn == 128 && stages == 3) hipLaunchKernelGGL((k_dense<128, 128, 2, 2, 3>), grid, dim3(256), 0, s, p);
+  else if (dense_bf16 && t.bm == 128 && t.bn == 128) hipLaunchKernelGGL((k_dense<128, 128, 2, 2, 4>), grid, dim3(256), 0, s, p);
   else if (t.bn == 256) hipLaunchKernelGGL((k_igemm<bf16_t, 256, 256, 2, 4, 64, true, true>), grid, dim3(512), 0, s, p);   // (pick_tile: interior only)
   else if (t.bm == 256 && t.bn == 128) IGEMM_LAUNCH_K(bf16_t, 256, 128, 2, 2, 64);
   else if (t.bm == 256) IGEMM_LAUNCH_K(bf16_t, 256, 64, 4, 1, 64);

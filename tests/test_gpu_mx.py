@@ -292,6 +292,23 @@ def test_transform_mse_full_size(ae, dtype):
     assert np.all(np.abs(eb - eb_o) <= 2 * tol * eb_o + 1e-30)
 
 
+# 400 tiles of 128 x 128 (three stages of slabs), 576 and 768 of 256 x 128 (either kernel)
+@pytest.mark.parametrize("rows,d", [(3200, 2048), (16384, 1152), (65536, 384)])
+def test_transform_mse_tile_shapes(ae, rows, d):
+    """Both epilogues on the tile shapes that the sizes above do not reach, with the same bounds, and every element format
+    under the identity map, whose result is plain Q(x), bit for bit, and its error."""
+    test_transform_mse_matches_oracle(ae, "bf16", rows, d, "affine")
+    x = wl.make_activations(rows, d, seed=d, bf16=True)
+    eye = np.eye(d, dtype=np.float32)
+    for elem in ("fp4", "int4", "fp8"):
+        e, eb, yq = _run_tmse(ae, x, eye, np.zeros(d, np.float32), eye, "bf16", 32, elem)
+        q = mxo.mx_quantize(x.astype(np.float64), 32, elem)
+        assert _same_bits(yq, q.astype(np.float32))
+        # x - Q(x) is exact in binary32; rows x 32 squares are added in binary32 over 256 rows, then in double
+        own = ((x.astype(np.float64) - q) ** 2).reshape(rows, d // 32, 32).mean(axis=(0, 2))
+        assert np.all(np.abs(eb - own) <= 256 * 2.0 ** -24 * own) and abs(e - own.mean()) <= 257 * 2.0 ** -24 * own.mean()
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("d", [4, 8, 12, 260, 512, 520, 2050, 2056])
 def test_inverse_shift_by_pieces(ae, d, dtype):
