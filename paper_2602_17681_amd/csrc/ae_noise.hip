@@ -186,12 +186,10 @@ __global__ void k_noise(uint64_t seed, uint64_t first_sample, int64_t batch, int
 }
 
 // Message bits: one Philox call yields the 128 bits of a unit (sample, group of 128 positions).  A workgroup generates
-// GEN_UNITS units, one per lane of its first wavefront, into LDS and then all its threads stream out the units' outputs,
-// which are contiguous in x.  (One call per output, the earlier form, was bound by the generator's integer multiplies:
-// 65 536 x 64 bits, 17 MB, 20.1 us; now 9.)  VEC: k % 4 == 0 and x on a 16-byte border: a quad never leaves its word.
-constexpr int GEN_UNITS = 64;
-
-template <bool VEC>
+// GEN_UNITS units, one per thread, into LDS and then all its threads stream out the units' outputs, which are contiguous
+// in x.  (One call per output, the earliest form, was bound by the generator's integer multiplies: 65 536 x 64 bits, 17 MB,
+// 20.1 us; now 9.)  VEC: k % 4 == 0 and x on a 16-byte border: a quad never leaves its word.
+template <int GEN_UNITS, bool VEC>
 __global__ __launch_bounds__(NT) void k_gen_bits(uint64_t seed, uint64_t first_sample, int64_t batch, int k, float* __restrict__ x) {
   constexpr int W = VEC ? 4 : 1;
   __shared__ uint32_t words[GEN_UNITS * 4];
@@ -225,6 +223,16 @@ __global__ __launch_bounds__(NT) void k_gen_bits(uint64_t seed, uint64_t first_s
       else
         x[e0 + r] = (word & 1u) ? 1.0f : -1.0f;
     }
+  }
+}
+
+// Rows of a few bits: a thread per row, which needs a part of one word.  (2^22 rows of 1 / 2 / 4 bits: 11.6 / 12.4 / 22.6 us, 25.7 /
+// 28.4 / 26.8 through LDS, 13.7 / 24.1 / 43.9 with one generator call per output.)
+__global__ __launch_bounds__(NT) void k_gen_bits_few(uint64_t seed, uint64_t first_sample, int64_t batch, int k, float* __restrict__ x) {
+  for (int64_t b = (int64_t)blockIdx.x * NT + threadIdx.x; b < batch; b += (int64_t)gridDim.x * NT) {
+    const uint64_t sample = first_sample + (uint64_t)b;
+    const uint32_t word = philox4x32_10((uint32_t)sample, (uint32_t)(sample >> 32), 0u, 1u, (uint32_t)seed, (uint32_t)(seed >> 32)).x;
+    for (int j = 0; j < k; ++j) x[b * k + j] = ((word >> j) & 1u) ? 1.0f : -1.0f;
   }
 }
 
@@ -365,13 +373,22 @@ int launch_noise(uint64_t seed, uint64_t first_sample, int64_t batch, int64_t n,
 }
 
 int launch_gen_bits(uint64_t seed, uint64_t first_sample, int64_t batch, int k, float* x, hipStream_t s) {
+  if (k <= 4) {
+    hipLaunchKernelGGL(k_gen_bits_few, dim3(grid_for(batch, 1 << 20)), dim3(NT), 0, s, seed, first_sample, batch, k, x);
+    return launch_status("gen_bits");
+  }
   const int64_t units = batch * (((int64_t)k + 127) >> 7);
-  const int64_t groups = (units + GEN_UNITS - 1) / GEN_UNITS;
+  // A unit per thread while units are short, a wavefront of units beyond: 64 units leave three wavefronts idle while the first
+  // calls the generator (2^20 rows of 5 / 16 / 32 bits 20.6 / 20.8 / 22.8 us, with 256 11.3 / 12.4 / 21.4), 256 make few workgroups of
+  // large batches (65 536 x 63: 7.9 and 10.4 us; 4 096 x 4 099: 19.3 and 26.7).
+  const bool vec = k % 4 == 0 && ((uintptr_t)x & 15) == 0, few = k <= 32;
+  const int per_group = few ? 256 : 64;
+  const int64_t groups = (units + per_group - 1) / per_group;
   const dim3 grid((unsigned)(groups < (1 << 20) ? groups : (1 << 20)));
-  if (k % 4 == 0 && ((uintptr_t)x & 15) == 0)
-    hipLaunchKernelGGL((k_gen_bits<true>), grid, dim3(NT), 0, s, seed, first_sample, batch, k, x);
-  else
-    hipLaunchKernelGGL((k_gen_bits<false>), grid, dim3(NT), 0, s, seed, first_sample, batch, k, x);
+#define GEN_BITS(U, V) hipLaunchKernelGGL((k_gen_bits<U, V>), grid, dim3(NT), 0, s, seed, first_sample, batch, k, x)
+  if (few) { if (vec) GEN_BITS(256, true); else GEN_BITS(256, false); }
+  else { if (vec) GEN_BITS(64, true); else GEN_BITS(64, false); }
+#undef GEN_BITS
   return launch_status("gen_bits");
 }
 

@@ -33,3 +33,10 @@ def test_bits_and_counts(batch, k, off):
     ae.model_count_errors(yd, x, batch, k, be, ke)
     bad = (y > 0.5) != (ref > 0)
     assert (int(be.item()) - 5, int(ke.item()) - 6) == (int(bad.sum()), int(bad.any(axis=1).sum()))
+
+
+@pytest.mark.parametrize("off", [0, 1])
+@pytest.mark.parametrize("batch,k", [(257, 1), (300, 2), (513, 4), (255, 5), (256, 8), (515, 31), (257, 32), (65, 33)])
+def test_bits_of_short_rows(batch, k, off):
+    """Row lengths around the kernels for few bits, batches around their workgroups."""
+    test_bits_and_counts(batch, k, off)
