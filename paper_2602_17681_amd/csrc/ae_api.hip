@@ -152,8 +152,6 @@ int join_side(ae_model* m, int sel, hipStream_t s) {
   return AE_OK;
 }
 
-int nblocks_for(int64_t rows) { return reduce_blocks(rows); }
-
 // input tensor of step i: the previous step's saved output, or the caller's x
 const void* step_input(const ae_model* m, size_t i, const void* x) { return i == 0 ? x : m->plan.steps[i - 1].out; }
 
@@ -374,7 +372,7 @@ int forward_conv(ae_model* m, int si, Step& st, const float* params, const void*
       const float* about = a.bias;    // the conv epilogues take their column statistics about the bias
       if (!a.partial) {
         TIMED(si, "fwd.col_stats", 0.0, raw_el * es, launch_col_stats(st.raw, rows, st.cout, P.dtype, m->partial, s));
-        nblk = nblocks_for(rows);
+        nblk = reduce_blocks(rows, st.cout, P.dtype);
         about = nullptr;
       }
       TIMED(si, "fwd.bn_finalize", 0.0, (double)nblk * 2 * st.cout * 4,
@@ -453,7 +451,7 @@ int backward_conv(ae_model* m, int si, Step& st, const float* params, const void
               launch_post_bwd_reduce(st.raw, g, st.out, st.bn_vec, P.batch, st.hc, st.wc, st.cout, st.act, st.pool,
                                      P.dtype, m->partial, s));
         TIMED(si, "bwd.bn_finalize", 0.0, 0.0,
-              launch_bn_bwd_finalize(m->partial, nblocks_for(prow), rows, st.cout, grads + st.b_off, st.bn_vec,
+              launch_bn_bwd_finalize(m->partial, reduce_blocks(prow, st.cout, P.dtype), rows, st.cout, grads + st.b_off, st.bn_vec,
                                      grads + st.bn_off, P.bn_mode == 0, s));
       }
     }
@@ -478,7 +476,7 @@ int backward_conv(ae_model* m, int si, Step& st, const float* params, const void
     dr = m->draw;
     bias_done = true;
     TIMED(si, "bwd.bias_finalize", 0.0, 0.0,
-          launch_colsum_finalize(m->partial, nblocks_for(rows), st.cout, grads + st.b_off, s));
+          launch_colsum_finalize(m->partial, reduce_blocks(rows, st.cout, P.dtype), st.cout, grads + st.b_off, s));
   }
   // the conv-output gradient in whole chunks, where the kernels below want it; its buffer is guarded like the draw buffer beside it
   const void* dr_p = dr;
@@ -574,7 +572,7 @@ int backward_conv(ae_model* m, int si, Step& st, const float* params, const void
   if (!bias_done) {
     TIMED(si, "bwd.bias_colsum", 0.0, raw_el * es, launch_col_stats(dr, rows, st.cout, P.dtype, m->partial, s));
     TIMED(si, "bwd.bias_finalize", 0.0, 0.0,
-          launch_colsum_finalize(m->partial, nblocks_for(rows), st.cout, grads + st.b_off, s));
+          launch_colsum_finalize(m->partial, reduce_blocks(rows, st.cout, P.dtype), st.cout, grads + st.b_off, s));
   }
   if (st.thin == 1) {
     if (thin_wgrad_mfma_supported(st.cin, st.cout, st.wc, P.dtype))

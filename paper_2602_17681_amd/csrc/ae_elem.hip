@@ -224,7 +224,8 @@ __global__ void k_pack_weights_batch(PackBatch pb) {
 // ---------------------------------------------------------------------------
 // Block-level helper: every thread holds NQ x VEC partial sums for channel group
 // `cg` (channels cbase + cg*VEC ...) accumulated over the rows of its row lane
-// `rl`; combine over row lanes and write partial_blk[q][channel].
+// `rl`; combine over row lanes, in double, and write partial_blk[q][channel].  Where there are fewer sums than threads,
+// 2^g neighbouring lanes share the row lanes of one.
 // ---------------------------------------------------------------------------
 template <int VEC, int NQ>
 __device__ __forceinline__ void block_col_combine(const float (&acc)[NQ][VEC], int cg, int rl, int nrl, int tpr,
@@ -237,14 +238,16 @@ __device__ __forceinline__ void block_col_combine(const float (&acc)[NQ][VEC], i
       for (int v = 0; v < VEC; ++v) smem[((rl * tpr + cg) * NQ + q) * VEC + v] = acc[q][v];
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < tpr * NQ * VEC; i += NT) {
-    int v = i % VEC, q = (i / VEC) % NQ, g = i / (VEC * NQ);
-    int c = cbase + g * VEC + v;
-    if (c < C) {
-      float t = 0.0f;
-      for (int r = 0; r < nrl; ++r) t += smem[((r * tpr + g) * NQ + q) * VEC + v];
-      partial_blk[(int64_t)q * C + c] = t;
-    }
+  const int items = tpr * NQ * VEC;
+  int g = 0;
+  while (g < 6 && (items << (g + 1)) <= NT) ++g;
+  for (int i = threadIdx.x; i < items << g; i += NT) {         // (one pass if g > 0: the lanes of a sum stay together)
+    const int it = i >> g, sub = i & ((1 << g) - 1);
+    double t = 0.0;
+    for (int r = sub; r < nrl; r += 1 << g) t += (double)smem[r * items + it];
+    for (int off = (1 << g) >> 1; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+    const int v = it % VEC, q = (it / VEC) % NQ, c = cbase + it / (VEC * NQ) * VEC + v;
+    if (sub == 0 && c < C) partial_blk[(int64_t)q * C + c] = (float)t;
   }
 }
 
@@ -922,8 +925,8 @@ int launch_pack_weights_up(const float* w, void* wp, int cout, int cin, int dtyp
 }
 
 int launch_col_stats(const void* x, int64_t rows, int c, int dtype, float* partial, hipStream_t s) {
-  const int rpb = reduce_rows_per_block(rows);
-  const int nblocks = reduce_blocks(rows);
+  const int rpb = reduce_rows_per_block(rows, c, dtype);
+  const int nblocks = reduce_blocks(rows, c, dtype);
   DISPATCH_T_VEC(dtype, c, {
     const int groups = (c + VEC - 1) / VEC;
     const int tpr = groups < NT ? groups : NT;
@@ -958,8 +961,8 @@ int launch_post_bwd_reduce(const void* raw, const void* dout, const void* out_ac
   if (act != ACT_RELU || !bn_vec) out_act = nullptr;
   int64_t rows = n * (h >> pool) * (w >> pool);
   if (rows >= 0x7FFFFFFF) return fail(AE_EINVAL, "post_bwd_reduce: tensor too large");
-  const int rpb = reduce_rows_per_block(rows);
-  const int nblocks = reduce_blocks(rows);
+  const int rpb = reduce_rows_per_block(rows, c, dtype);
+  const int nblocks = reduce_blocks(rows, c, dtype);
   DISPATCH_T_VEC(dtype, c, {
     if (pool)
       hipLaunchKernelGGL((k_post_bwd_reduce<T, VEC, true>), dim3(nblocks), dim3(NT), 0, s, (const T*)raw,
@@ -1006,8 +1009,8 @@ int launch_act_bwd(const void* out, const float* out_f32, const void* dout, void
 
 int launch_act_bwd_colsum(const void* out, const float* out_f32, const void* dout, void* draw, int64_t rows, int c,
                           int act, int dtype, float* partial, hipStream_t s) {
-  const int rpb = reduce_rows_per_block(rows);
-  const int nblocks = reduce_blocks(rows);
+  const int rpb = reduce_rows_per_block(rows, c, dtype);
+  const int nblocks = reduce_blocks(rows, c, dtype);
   DISPATCH_T_VEC(dtype, c, hipLaunchKernelGGL((k_act_bwd_colsum<T, VEC>), dim3(nblocks), dim3(NT), 0, s, (const T*)out,
                                               out_f32, (const T*)dout, (T*)draw, rows, rpb, c, act, partial));
   return launch_status("act_bwd_colsum");

@@ -120,15 +120,26 @@ int launch_fused_small(const Plan& P, const FusedSmall& f, const float* params, 
 // large tensors, fewer when that would leave the machine with too few blocks.  Three blocks per
 // compute unit are enough: every one ends in a combination through LDS and leaves a row of partial
 // sums for the finalizing kernel (51 840 pooled rows of 48 channels, 810 blocks instead of 3 240: 23 -> 12 us
-// for the sums of a batch-norm backward, 9.8 -> 4.8 for their finalizing).
+// for the sums of a batch-norm backward, 9.8 -> 4.8 for their finalizing).  But a thread adds in binary32: no more than
+// eight rows to a thread for the sake of fewer blocks (column sums of a standard normal, error over the root of the rows,
+// with blocks as small as for eight per compute unit, as large as for three, and by this rule; combined in binary32, binary32 and
+// double: 51 840 x 48 7.2e-8, 8.6e-8, 4.9e-8; 32 768 x 1 024 7.8e-8, 1.0e-7, 7.8e-8; 65 536 x 16 1.3e-7, 1.7e-7, 2.4e-8).
 constexpr int kReduceRows = 256;
-inline int reduce_rows_per_block(int64_t rows, int min_blocks = 768) {
+inline int reduce_rows_per_block(int64_t rows, int min_blocks) {
   int rpb = kReduceRows;
   while (rpb > 16 && rows / rpb < min_blocks) rpb >>= 1;
   return rpb;
 }
-inline int reduce_blocks(int64_t rows) {
-  const int rpb = reduce_rows_per_block(rows);
+inline int reduce_rows_per_block(int64_t rows, int c, int dtype) {
+  const int vec = dtype == AE_BF16 ? (c % 8 == 0 ? 8 : 1) : (c % 4 == 0 ? 4 : 1);      // columns per thread, as the kernels take them
+  const int row_lanes = c / vec < 256 ? 256 / (c / vec) : 1;
+  int rpb = reduce_rows_per_block(rows, 768);
+  const int fine = reduce_rows_per_block(rows, 2048);
+  while (rpb > fine && rpb > 8 * row_lanes) rpb >>= 1;
+  return rpb;
+}
+inline int reduce_blocks(int64_t rows, int c, int dtype) {
+  const int rpb = reduce_rows_per_block(rows, c, dtype);
   return (int)((rows + rpb - 1) / rpb);
 }
 // what the partial-sum buffer has room for (the statistics of the three-launch path of small images live there too)
