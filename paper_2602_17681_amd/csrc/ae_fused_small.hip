@@ -94,11 +94,11 @@ __device__ __forceinline__ void bn_vectors(const float* __restrict__ partial, in
 // 16 output pixels x 16 channels of a 3x3 convolution (zero padding) of a planar LDS image src[cin][hs x ws] (planes `plane`
 // floats apart), UP: read through a x2 nearest-neighbour upsample.  Lane l multiplies input channel c + l/16 of pixel
 // `m0 + l % 16` (v_mfma_f32_16x16x4); results: channel l % 16 of pixels m0 + 4 (l/16) + 0..3.  Pixels past n_px are those of
-// pixel 0 (nobody stores them).  wl: [tap][cin rounded up to 4][16].
+// pixel 0 (nobody stores them).  wl: [tap][cin][16].
 template <bool UP>
 __device__ __forceinline__ floatx4 conv3_tile(const float* src, int plane, int cin, int hs, int ws, const float* wl, int m0, int n_px) {
   const int lane = threadIdx.x & 63, g = lane >> 4;
-  const int hc = UP ? 2 * hs : hs, wc = UP ? 2 * ws : ws, cin4 = (cin + 3) & ~3;
+  const int hc = UP ? 2 * hs : hs, wc = UP ? 2 * ws : ws, whole = cin & ~3;
   const int px = m0 + (lane & 15) < n_px ? m0 + (lane & 15) : 0;
   const int y = px / wc, x = px - y * wc;
   floatx4 even = {0.f, 0.f, 0.f, 0.f}, odd = {0.f, 0.f, 0.f, 0.f};   // two chains: an MFMA waits for the one before the last
@@ -107,41 +107,39 @@ __device__ __forceinline__ floatx4 conv3_tile(const float* src, int plane, int c
     const int yy = y + t / 3 - 1, xx = x + t % 3 - 1;
     const bool ok = yy >= 0 && yy < hc && xx >= 0 && xx < wc;
     const float* sp = src + g * plane + (ok ? (UP ? (yy >> 1) * ws + (xx >> 1) : yy * ws + xx) : 0);
-    const float* wp = wl + (t * cin4 + g) * COB + (lane & 15);
-    const int c_end = ok ? cin - g : 0;          // this lane's channels g, g + 4, ... below cin
-    int c = 0;
-    for (; c + 32 <= cin4; c += 32) {            // all reads of 32 channels ahead of their MFMAs
+    const float* wp = wl + (t * cin + g) * COB + (lane & 15);
+    int c = 0;                                   // this lane's channels: g, g + 4, ...
+    for (; c + 32 <= whole; c += 32) {           // all reads of 32 channels ahead of their MFMAs
       float v[8], w[8];
 #pragma unroll
       for (int u = 0; u < 8; ++u) { v[u] = sp[(c + 4 * u) * plane]; w[u] = wp[(c + 4 * u) * COB]; }
 #pragma unroll
       for (int u = 0; u < 8; u += 2) {
-        even = __builtin_amdgcn_mfma_f32_16x16x4f32(c + 4 * u < c_end ? v[u] : 0.0f, w[u], even, 0, 0, 0);
-        odd = __builtin_amdgcn_mfma_f32_16x16x4f32(c + 4 * u + 4 < c_end ? v[u + 1] : 0.0f, w[u + 1], odd, 0, 0, 0);
+        even = __builtin_amdgcn_mfma_f32_16x16x4f32(ok ? v[u] : 0.0f, w[u], even, 0, 0, 0);
+        odd = __builtin_amdgcn_mfma_f32_16x16x4f32(ok ? v[u + 1] : 0.0f, w[u + 1], odd, 0, 0, 0);
       }
     }
-    for (; c + 8 <= cin4; c += 8) {
-      const float v0 = c < c_end ? sp[c * plane] : 0.0f, v1 = c + 4 < c_end ? sp[(c + 4) * plane] : 0.0f;
+    for (; c + 8 <= whole; c += 8) {
+      const float v0 = ok ? sp[c * plane] : 0.0f, v1 = ok ? sp[(c + 4) * plane] : 0.0f;
       even = __builtin_amdgcn_mfma_f32_16x16x4f32(v0, wp[c * COB], even, 0, 0, 0);
       odd = __builtin_amdgcn_mfma_f32_16x16x4f32(v1, wp[(c + 4) * COB], odd, 0, 0, 0);
     }
-    if (c < cin4) even = __builtin_amdgcn_mfma_f32_16x16x4f32(c < c_end ? sp[c * plane] : 0.0f, wp[c * COB], even, 0, 0, 0);
+    if (c < whole) even = __builtin_amdgcn_mfma_f32_16x16x4f32(ok ? sp[c * plane] : 0.0f, wp[c * COB], even, 0, 0, 0);
+    if (whole < cin) {                           // up to three channels more: what is not there is neither read nor multiplied
+      const bool in = whole + g < cin;
+      odd = __builtin_amdgcn_mfma_f32_16x16x4f32(in && ok ? sp[whole * plane] : 0.0f, in ? wp[whole * COB] : 0.0f, odd, 0, 0, 0);
+    }
   }
   return even + odd;
 }
-// canonical conv weights W[co][ci][3][3], channels co0 .. co0 + 15 -> wl[tap][cin rounded up to 4][16] (zero beyond cin)
+// canonical conv weights W[co][ci][3][3], channels co0 .. co0 + 15 -> wl[tap][cin][16]
 __device__ __forceinline__ void stage_tile_weights(const float* __restrict__ w, int cin, int co0, float* wl) {
-  const int cin4 = (cin + 3) & ~3, row = cin * 9;
+  const int row = cin * 9;
   const float* src = w + (int64_t)co0 * row;
   for (int i = threadIdx.x; i < COB * row; i += NT) {
     const int co = i / row, r = i - co * row, ci = r / 9, t = r - ci * 9;
-    wl[(t * cin4 + ci) * COB + co] = src[i];
+    wl[(t * cin + ci) * COB + co] = src[i];
   }
-  if (cin4 != cin)
-    for (int i = threadIdx.x; i < 9 * (cin4 - cin) * COB; i += NT) {
-      const int co = i % COB, t = i / COB;
-      wl[((t % 9) * cin4 + cin + t / 9) * COB + co] = 0.0f;
-    }
 }
 // Sum and sum of squares of a channel over the workgroup's tiles, lane l holding channel l % 16: over the four lane groups,
 // then the wavefronts in order.  red: [NT / 64][2][COB]; the first 2 COB threads store.
@@ -343,16 +341,15 @@ __global__ __launch_bounds__(NT_MAX) void k_small_tail(SmallArgs a) {
   extern __shared__ float lds[];
   const int h2 = a.h / 2, w2 = a.w / 2, h4 = a.h / 4, w4 = a.w / 4, hw4 = h4 * w4, hw2 = h2 * w2, hw = a.h * a.w;
   const int F = a.c2 * hw4, FD = a.cr * hw4;      // flattened encoder output; decoder fc output
-  const int cr4 = (a.cr + 3) & ~3;
   double* tmp = reinterpret_cast<double*>(lds);   // [2*256] scratch of the statistics
   float* a2 = lds + 1024;                         // [c2][hw4]   (flatten order)
-  float* dec = a2 + F;                            // [cr][plane_d]   (reshape order)
-  float* a3 = dec + cr4 * a.plane_d;              // [c3][plane3]
-  float* lat = a3 + a.c3 * a.plane3;              // [n] z, then the channel output
+  float* lat = a2 + F;                            // [n] z, then the channel output (F is a multiple of 16: read four at a time)
   float* scale = lat + a.n;                       // [c2]
   float* shift = scale + a.c2;
+  float* dec = shift + a.c2;                      // [cr][plane_d]   (reshape order)
+  float* a3 = dec + a.cr * a.plane_d;             // [c3][plane3]
   float* red = lds;                               // [NT/64 + 1], over the scratch of the statistics
-  float* wl = reinterpret_cast<float*>((reinterpret_cast<uintptr_t>(shift + a.c2) + 15) & ~(uintptr_t)15);   // weights of the decoder convs (16-byte aligned: read four at a time)
+  float* wl = reinterpret_cast<float*>((reinterpret_cast<uintptr_t>(a3 + a.c3 * a.plane3) + 15) & ~(uintptr_t)15);   // weights of the decoder convs (16-byte aligned: read four at a time)
   const int b = blockIdx.x;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   stage_tile_weights(a.params + a.w3, a.cr, 0, wl);
@@ -506,9 +503,8 @@ __global__ __launch_bounds__(NT_MAX) void k_small_tail(SmallArgs a) {
 size_t lds1(const SmallArgs& a) { return sizeof(float) * ((size_t)a.c0 * a.h * a.w + NT_MAX / 64 * 2 * COB); }
 size_t lds2(const SmallArgs& a) { return sizeof(float) * (1024 + (size_t)a.c1 * a.plane2 + (size_t)a.c1 * 9 * COB + 2 * a.c1 + NT_MAX / 64 * 2 * COB); }
 size_t lds3(const SmallArgs& a) {
-  const size_t cr4 = (a.cr + 3) & ~3;
-  const size_t wmax = cr4 * 9 * COB > (size_t)a.c3 * 9 * 4 ? cr4 * 9 * COB : (size_t)a.c3 * 9 * 4;
-  return sizeof(float) * (1024 + (size_t)a.c2 * (a.h / 4) * (a.w / 4) + cr4 * a.plane_d + (size_t)a.c3 * a.plane3 + a.n + 2 * a.c2 + 4 + wmax);
+  const size_t wmax = (size_t)a.cr * 9 * COB > (size_t)a.c3 * 9 * 4 ? (size_t)a.cr * 9 * COB : (size_t)a.c3 * 9 * 4;
+  return sizeof(float) * (1024 + (size_t)a.c2 * (a.h / 4) * (a.w / 4) + (size_t)a.cr * a.plane_d + (size_t)a.c3 * a.plane3 + a.n + 2 * a.c2 + 4 + wmax);
 }
 constexpr size_t kLds = 65536;
 // Plane strides of 16 floats more than a multiple of the 64 banks: the four lane groups of an MFMA read four neighbouring

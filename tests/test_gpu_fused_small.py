@@ -32,3 +32,11 @@ def test_small_image_forward(dims, batch):
     m.model_forward(to_dev(params, "f32", torch), to_dev(x, "f32", torch), 7.0, batch, y)
     assert [t["name"] for t in m.model_timing_read() if t["launches"]] == ["step00.fwd.fused_small"]
     assert_close(y.cpu().numpy(), y_ref, 1e-4, "y")          # the binary32 tolerance of the whole-network tests
+
+
+@pytest.mark.parametrize("dims,batch", [((1, 16, 32, 16, 16, 64, 37, 64, 1), 2), ((1, 16, 28, 16, 48, 64, 38, 64, 1), 300),
+                                        ((3, 12, 32, 32, 128, 64, 33, 64, 4), 2), ((1, 20, 12, 16, 16, 8, 3, 16, 1), 5),
+                                        ((1, 8, 8, 16, 16, 4, 2, 16, 1), 20), ((1, 8, 4, 16, 16, 4, 7, 16, 1), 33)])
+def test_small_image_forward_any_reshape(dims, batch):
+    """Channels after the reshape off multiples of 4, up to networks that just fit the LDS of the third launch."""
+    test_small_image_forward(dims, batch)
