@@ -429,54 +429,87 @@ __device__ __forceinline__ void igemm_epilogue(floatx16 (&acc)[BM / WGM / 32][BN
     // applies the activation and stores what lies inside.  (With the checks, the activation and the output row formed per
     // accumulator this was 30 to 40 KiB of straight-line code that every workgroup of a launch of a few slabs fetched once: bf16, 24 x
     // 72 x 120 pixels, 3 -> 48 channels 35 -> 30 us, 48 -> 80 at half the side 26 -> 21, 48 -> 3 behind an upsample 27 -> 16.)
+    // Rows of no whole 16 bytes are stored from the accumulators where most of the columns are inside: through LDS they cost
+    // two LDS accesses per value (bf16, 16 x 96 x 96 pixels, 100 -> 99 channels, 3x3: 84 us, with all the checks formed per
+    // accumulator 77, so 66; 36 -> 99, 1x1: 38, 36, 17).  Few columns and the phases, whose output rows take divisions, use the loop.
     constexpr int EPC = 16 / ES;                 // elements per 16-byte chunk
     constexpr int CPRO = WN / EPC;               // chunks per staged row
     const int cols = min(WN, p.N - (n0 + wn * WN));       // of this wave's part, those inside (may be negative)
     const int64_t mw = m0 + wm * WM;
+    const bool direct = !wide_store && !p.y_aux && p.act != ACT_SIGMOID && 2 * cols > WN && p.phases == 1 && p.N < (1 << 20);   // (32-bit offsets)
     float bias[NJ];
 #pragma unroll
     for (int j = 0; j < NJ; ++j) bias[j] = p.bias && j * 32 + col_lane < cols ? p.bias[n0 + wn * WN + j * 32 + col_lane] : 0.0f;
+    auto out_row = [&](int64_t m) { return PHASED ? igemm_out_row(p, m, phase, 0) : m; };   // (column strips: interior tiles only)
+    auto conv_result = [&](int i, int j, int e, bool row_ok) {
+      const float v = round_to_storage<T>(acc[i][j][e] + bias[j]);   // the stored conv result
+      if (p.partial) {                           // (columns past N are not stored)
+        const float d = row_ok ? v - bias[j] : 0.0f;
+        s1[j] += d;
+        s2[j] = fmaf(d, d, s2[j]);
+      }
+      return v;
+    };
+    if (__builtin_expect(!direct, 1)) {
 #pragma unroll
-    for (int i = 0; i < MI; ++i) {
-      const int rows = (int)min((int64_t)32, p.M - (mw + i * 32));
+      for (int i = 0; i < MI; ++i) {
+        const int rows = (int)min((int64_t)32, p.M - (mw + i * 32));
 #pragma unroll
-      for (int j = 0; j < NJ; ++j)
+        for (int j = 0; j < NJ; ++j)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int lr = (e >> 2) * 8 + row_lane + (e & 3);
-          const float v = round_to_storage<T>(acc[i][j][e] + bias[j]);   // the stored conv result
-          if (p.partial) {                       // (columns past N are not stored)
-            const float d = lr < rows ? v - bias[j] : 0.0f;
-            s1[j] += d;
-            s2[j] = fmaf(d, d, s2[j]);
+          for (int e = 0; e < 16; ++e) {
+            const int lr = (e >> 2) * 8 + row_lane + (e & 3);
+            Store<T>::st(&stage[lr * SW + j * 32 + col_lane], conv_result(i, j, e, lr < rows));
           }
-          Store<T>::st(&stage[lr * SW + j * 32 + col_lane], v);
-        }
-      auto out_row = [&](int lr) {               // (column strips: interior tiles only)
-        const int64_t m = mw + i * 32 + lr;
-        return PHASED ? igemm_out_row(p, m, phase, 0) : m;
-      };
-      if (wide_store) {
+        if (wide_store) {
 #pragma unroll 1
-        for (int idx = lane; idx < 32 * CPRO; idx += 64) {
-          const int lr = idx / CPRO, ch = idx % CPRO;
-          if (lr >= rows || ch * EPC >= cols) continue;
-          float f[EPC];
-          Store<T>::ldv(&stage[lr * SW + ch * EPC], f);
+          for (int idx = lane; idx < 32 * CPRO; idx += 64) {
+            const int lr = idx / CPRO, ch = idx % CPRO;
+            if (lr >= rows || ch * EPC >= cols) continue;
+            float f[EPC];
+            Store<T>::ldv(&stage[lr * SW + ch * EPC], f);
 #pragma unroll
-          for (int t = 0; t < EPC; ++t) f[t] = apply_act(f[t], p.act);
-          Store<T>::stv(Y + out_row(lr) * p.N + n0 + wn * WN + ch * EPC, f);
-        }
-      } else if (cols > 0) {
+            for (int t = 0; t < EPC; ++t) f[t] = apply_act(f[t], p.act);
+            Store<T>::stv(Y + out_row(mw + i * 32 + lr) * p.N + n0 + wn * WN + ch * EPC, f);
+          }
+        } else if (cols > 0) {
+          const int step_r = 64 / cols, step_c = 64 - step_r * cols;
+          int lr = lane / cols, c = lane - lr * cols;
 #pragma unroll 1
-        for (int idx = lane; idx < rows * cols; idx += 64) {
-          const int lr = (int)((unsigned)idx / (unsigned)cols), c = idx - lr * cols;
-          const int64_t o = out_row(lr) * p.N + n0 + wn * WN + c;
-          const float a = apply_act(Store<T>::ld(&stage[lr * SW + c]), p.act);
-          Store<T>::st(&Y[o], a);
-          if (p.y_aux) p.y_aux[o] = a;
+          for (int idx = lane; idx < rows * cols; idx += 64) {
+            const int64_t o = out_row(mw + i * 32 + lr) * p.N + n0 + wn * WN + c;
+            const float a = apply_act(Store<T>::ld(&stage[lr * SW + c]), p.act);
+            Store<T>::st(&Y[o], a);
+            if (p.y_aux) p.y_aux[o] = a;
+            lr += step_r;
+            c += step_c;
+            if (c >= cols) { c -= cols; ++lr; }
+          }
         }
       }
+    } else {
+      // (the buffer's range drops the rows past M, an offset past it the columns past N: one instruction per store)
+      const int uw = __builtin_amdgcn_readfirstlane(wave), row_bytes = p.N * ES;
+      const int64_t um = m0 + uw / WGN * WM;
+      const int un = n0 + uw % WGN * WN, inside = (int)min((int64_t)WM, p.M - um);
+      const __amdgpu_buffer_rsrc_t rY = make_rsrc(Y + um * p.N + un, inside > 0 ? (inside - 1) * row_bytes + min(WN, p.N - un) * ES : 0);
+      unsigned off[NJ];
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) off[j] = j * 32 + col_lane < cols ? (unsigned)(row_lane * row_bytes + (j * 32 + col_lane) * ES) : kOob;
+      const bool relu = p.act == ACT_RELU;
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const int lr = i * 32 + (e >> 2) * 8 + (e & 3);
+#pragma unroll
+          for (int j = 0; j < NJ; ++j) {
+            float v = conv_result(i, j, e, lr + row_lane < inside);
+            v = relu ? apply_act(v, ACT_RELU) : v;
+            if constexpr (ES == 2) __builtin_amdgcn_raw_buffer_store_b16(f32_to_bf16(v), rY, off[j] + (unsigned)(lr * row_bytes), 0, 0);
+            else __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rY, off[j] + (unsigned)(lr * row_bytes), 0, 0);
+          }
+        }
     }
   }
   if (p.partial && EPI != 3 && EPI != 4) {

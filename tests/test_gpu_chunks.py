@@ -44,6 +44,16 @@ def test_tall_tiles_and_many_splits(dtype):
     run_case("in:12x64x43,conv3:20,relu,conv3:12,relu,conv1:3", 12, dtype=dtype, seed=431, flips=(dtype == "bf16"))
 
 
+# rows of no whole 16 bytes: more and less than half of a wavefront's columns, a ragged last row tile (of 128 and of 256
+# rows), statistics of a batch-norm, the four phases behind an upsample, a sigmoid and its binary32 copy
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("spec,batch", [("in:9x11x13,conv3:99,relu,conv3:101,bn,relu,conv1:57,relu,conv1:35,relu,conv1:27,relu,conv1:3", 3),
+                                        ("in:5x64x43,conv3:33,relu,conv1:61,bn,relu,conv1:21,conv1:2", 12),
+                                        ("in:6x5x7,up2,conv3:99,relu,up2,conv3:51,sigmoid", 2), ("in:12x7x5,conv1:99,sigmoid,conv1:2", 4)])
+def test_stores_of_odd_rows(spec, batch, dtype):
+    run_case(spec, batch, dtype=dtype, seed=440 + batch, flips=(dtype == "bf16"))
+
+
 @pytest.mark.parametrize("tail", ["", ",awgn"])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_tensors_of_the_caller_off_a_16_byte_border(dtype, tail):
