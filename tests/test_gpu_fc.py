@@ -52,3 +52,35 @@ def test_input_gradient(batch, k, latent):
     # a binary32 sum in another order moves a stored bfloat16 value by one place (2^-8) now and then: far below one place in the 2-norm
     for a, b in zip(*out):
         assert float((a - b).norm()) <= 2.0 ** -9 * float(b.norm())
+
+
+@pytest.mark.parametrize("batch,k,latent", [(1, 8192, 128), (37, 8192, 256), (130, 2048, 640), (512, 1024, 1024)])
+def test_input_gradient_itself(batch, k, latent):
+    """Noise hands the second layer's input gradient on unchanged, and with unit vectors as inputs the first layer's weight
+    gradient holds it column by column: against float64; and that it was the kernels for the parameters themselves, which
+    static parameters do not take."""
+    import torch
+    from paper_2602_17681_amd import binding as ae
+    spec = "in:%dx1x1,fc:%d,awgn,fc:%d" % (k, latent, k)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(latent)
+    x = torch.eye(batch, k, device="cuda").bfloat16()
+    dy = torch.randn(batch, k, device="cuda", generator=gen).bfloat16()
+    for static in (False, True):
+        m = ae.Model(spec, batch, ae.DTYPES["bf16"])
+        m.model_set_params_static(static)
+        gen.manual_seed(1)
+        p = torch.randn(m.n_params, device="cuda", generator=gen)
+        y, g = torch.empty_like(x), torch.empty(m.n_params, device="cuda")
+        m.model_timing_enable(True)
+        m.model_forward(p, x, 10.0, 1, y)
+        m.model_backward(p, x, dy, g)
+        names = [t["name"].split(".", 1)[1] for t in m.model_timing_read() if t["launches"]]
+        assert (names.count("fwd.fc"), names.count("bwd.fc_dgrad")) == ((0, 0) if static else (2, 1)), names
+        w2 = p[k * latent + latent:][:k * latent].view(k, latent).bfloat16().double()
+        ref = dy.double() @ w2
+        dz = g[:k * latent].view(latent, k)[:, :batch].t().double()
+        # one rounding to bfloat16 (2^-9, twice for the binary32 sum between two of its values), k + 1 binary32 roundings of partial sums
+        mag = dy.double().abs() @ w2.abs()
+        assert bool(((dz - ref).abs() <= 2.0 ** -8 * ref.abs() + (k + 1) * 2.0 ** -24 * mag).all())
+        assert bool((g[:k * latent].view(latent, k)[:, batch:] == 0).all())
