@@ -203,7 +203,10 @@ int model_set_inference(ae_model* m, int on);
  * calls).  on = 1 is the caller's promise that the CONTENTS of params stay the same from call to call (repeated
  * evaluation, Monte-Carlo launches): the conversion then runs only in the first forward and the first backward
  * pass after this call, and again whenever a different params pointer is passed.  Call it again (on = 1) after
- * changing the values in place, or with on = 0 to return to converting in every pass (the default). */
+ * changing the values in place, or with on = 0 to return to converting in every pass (the default).
+ * Big fully-connected layers of bfloat16 models (2^20 weights or more, both sides multiples of 128, up to 512 rows) are not
+ * converted while the flag is off: their kernels read the blob itself.  The operands are rounded alike either way, but the
+ * binary32 sums run in another order, so their results with and without the flag need not be the same bits. */
 int model_set_params_static(ae_model* m, int on);
 /* Recomputation instead of storage (an execution detail, not part of the method).  When the first layer is a 3x3
  * convolution of at most 4 input channels into 32 or 64 channels followed by batch-norm, ReLU and 2x2 max-pooling

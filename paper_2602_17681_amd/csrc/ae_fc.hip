@@ -8,7 +8,7 @@
 //     input gradient   dx[m][n] = sum_k a[m][k] w[k][n]     (TRANS: a thread takes 8 rows x 4 columns and turns them in registers)
 //
 // A workgroup of four wavefronts computes 128 x 64 outputs over a range of K in slabs of 128: the next slab's loads are in
-// flight (48 KiB per workgroup, three of them on a compute unit) while the present one is multiplied from LDS, which holds
+// flight (48 KiB per workgroup; a compute unit has room for three) while the present one is multiplied from LDS, which holds
 // both operands in MFMA fragment order: octet o (8 of the slab's 128 k's) of row r at 16-byte slot (r % 32) ^ o of block
 // (r / 32, o / 2), half o % 2, so that the 16 octets of a row that neighbouring lanes store fall into 16 different columns
 // of the banks.  The matrix cores are a fifth busy: 64-column tiles and splits of K for bytes in flight, nothing else.
@@ -162,7 +162,7 @@ int launch_fc_direct(const FcArgs& a, hipStream_t s) {
   p.a = (const bf16_t*)a.a; p.w = a.w; p.bias = a.bias; p.y = (bf16_t*)a.y; p.act = a.act;
   p.M = a.m; p.N = a.n; p.K = a.k;
   p.tiles_n = a.n / BN; p.tiles_m = (a.m + BM - 1) / BM;
-  // two to three workgroups per compute unit, each over two slabs at least
+  // where K is split, at most 512 workgroups (two per compute unit), each over two slabs at least; more than that without a split only
   const int tiles = p.tiles_n * p.tiles_m, slabs = a.k / BK;
   int64_t splits = 512 / tiles;
   if (splits > slabs / 2) splits = slabs / 2;

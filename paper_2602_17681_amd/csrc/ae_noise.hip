@@ -305,7 +305,9 @@ inline int grid_for(int64_t items, int cap) {
 
 // small batches of long vectors get a whole workgroup per sample
 static bool block_per_sample(int64_t batch, int64_t n) { return batch < 1024 && n >= 1024; }
-// workgroups per sample then: two per compute unit in all, at least two of each thread's quads to a share
+// workgroups per sample then: two per compute unit in all, at least 512 values (128 quads of noise) to a share.  Every share
+// forms the whole sum for itself, which costs less than its noise saves at any length: binary32, one sample of 2^22 / 2^26 values 3.2 ->
+// 0.53 / 68 -> 12 ms against one workgroup, 64 samples of 2^20 1.10 -> 0.40 ms, 1 024 to 4 096 values the same.
 static unsigned shares_of_sample(int64_t batch, int64_t n) {
   int64_t s = 512 / batch;
   if (s > n / 512) s = n / 512;
