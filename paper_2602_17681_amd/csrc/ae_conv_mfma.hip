@@ -473,8 +473,9 @@ __device__ __forceinline__ void igemm_epilogue(floatx16 (&acc)[BM / WGM / 32][BN
             Store<T>::stv(Y + out_row(mw + i * 32 + lr) * p.N + n0 + wn * WN + ch * EPC, f);
           }
         } else if (cols > 0) {
-          const int step_r = 64 / cols, step_c = 64 - step_r * cols;
-          int lr = lane / cols, c = lane - lr * cols;
+          const float inv = __builtin_amdgcn_rcpf((float)cols);       // (n + 1/2) inv rounds down to n / cols: n <= 64, cols <= WN
+          const int step_r = (int)(64.5f * inv), step_c = 64 - step_r * cols;
+          int lr = (int)(((float)lane + 0.5f) * inv), c = lane - lr * cols;
 #pragma unroll 1
           for (int idx = lane; idx < rows * cols; idx += 64) {
             const int64_t o = out_row(mw + i * 32 + lr) * p.N + n0 + wn * WN + c;
