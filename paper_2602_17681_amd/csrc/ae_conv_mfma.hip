@@ -339,8 +339,8 @@ __device__ __forceinline__ void igemm_resid_stats(const floatx16 (&acc)[MI][NJ],
 // ended on a barrier) so that global stores are 16 bytes wide and each instruction covers
 // whole row segments.  smem: at least 4*32*(WN + 16/sizeof(T))*sizeof(T) bytes; sRed: [WGM][2][BN].
 // PHASED: a checked tile may belong to an output parity of an upsampled convolution (interior tiles always may).
-// RESID_LDS: smem holds the whole tile in the storage type.
-template <typename T, int BM, int BN, int WGM, int WGN, bool INTERIOR, int EPI = 0, bool PHASED = false, bool RESID_LDS = false>
+// RESID_LDS: smem holds the whole tile in the storage type.  DIRECT: the checked tiles of direct_stores.
+template <typename T, int BM, int BN, int WGM, int WGN, bool INTERIOR, int EPI = 0, bool PHASED = false, bool RESID_LDS = false, bool DIRECT = false>
 __device__ __forceinline__ void igemm_epilogue(floatx16 (&acc)[BM / WGM / 32][BN / WGN / 32], const IgemmParams& p,
                                                char* smem, float (*sRed)[2][BN], int64_t m0, int n0, int64_t tile_m,
                                                int phase = 0) {
@@ -424,93 +424,93 @@ __device__ __forceinline__ void igemm_epilogue(floatx16 (&acc)[BM / WGM / 32][BN
     else if (p.partial) igemm_store_interior<T, MI, NJ, WN, SW, true, false>(acc, bias, stage, yrow, p.N, lane, s1, s2, p, mrow0, phase, ycol);
     else if (p.act == ACT_RELU) igemm_store_interior<T, MI, NJ, WN, SW, false, true>(acc, bias, stage, yrow, p.N, lane, s1, s2, p, mrow0, phase, ycol);
     else igemm_store_interior<T, MI, NJ, WN, SW, false, false>(acc, bias, stage, yrow, p.N, lane, s1, s2, p, mrow0, phase, ycol);
+  } else if constexpr (DIRECT) {
+    // Checked tiles of rows of no whole 16 bytes, most of the columns inside: from the accumulators to memory.  The buffer's range
+    // drops the rows past M, an offset past it the columns past N, so a store is one instruction.  (The loop below costs such
+    // rows two LDS accesses per value: bf16, 16 x 96 x 96 pixels, 100 -> 99 channels, 3x3: 84 us, with all the checks formed per
+    // accumulator 77, so 64; 36 -> 99, 1x1: 38, 37, 14.  A kernel of its own: in the same one the others pay up to 2 % for the code.)
+    const int uw = __builtin_amdgcn_readfirstlane(wave), row_bytes = p.N * ES;
+    const int64_t um = m0 + uw / WGN * WM;
+    const int un = n0 + uw % WGN * WN, cols = min(WN, p.N - un), inside = (int)min((int64_t)WM, p.M - um);
+    const __amdgpu_buffer_rsrc_t rY = make_rsrc(Y + um * p.N + un, inside > 0 && cols > 0 ? (inside - 1) * row_bytes + cols * ES : 0);
+    unsigned off[NJ];
+    float bias[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const bool ok = j * 32 + col_lane < cols;
+      off[j] = ok ? (unsigned)(row_lane * row_bytes + (j * 32 + col_lane) * ES) : kOob;
+      bias[j] = p.bias && ok ? p.bias[un + j * 32 + col_lane] : 0.0f;
+    }
+    const bool relu = p.act == ACT_RELU;
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int lr = i * 32 + (e >> 2) * 8 + (e & 3);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          const float v = round_to_storage<T>(acc[i][j][e] + bias[j]);   // the stored conv result
+          if (p.partial) {                       // (columns past N are not stored)
+            const float d = lr + row_lane < inside ? v - bias[j] : 0.0f;
+            s1[j] += d;
+            s2[j] = fmaf(d, d, s2[j]);
+          }
+          __builtin_amdgcn_raw_buffer_store_b16(f32_to_bf16(relu ? apply_act(v, ACT_RELU) : v), rY, off[j] + (unsigned)(lr * row_bytes), 0, 0);
+        }
+      }
   } else {
     // Checked tiles: the conv results are rounded and staged without looking at M, N or the activation; a rolled loop then
     // applies the activation and stores what lies inside.  (With the checks, the activation and the output row formed per
     // accumulator this was 30 to 40 KiB of straight-line code that every workgroup of a launch of a few slabs fetched once: bf16, 24 x
     // 72 x 120 pixels, 3 -> 48 channels 35 -> 30 us, 48 -> 80 at half the side 26 -> 21, 48 -> 3 behind an upsample 27 -> 16.)
-    // Rows of no whole 16 bytes are stored from the accumulators where most of the columns are inside: through LDS they cost
-    // two LDS accesses per value (bf16, 16 x 96 x 96 pixels, 100 -> 99 channels, 3x3: 84 us, with all the checks formed per
-    // accumulator 77, so 66; 36 -> 99, 1x1: 38, 36, 17).  Few columns and the phases, whose output rows take divisions, use the loop.
     constexpr int EPC = 16 / ES;                 // elements per 16-byte chunk
     constexpr int CPRO = WN / EPC;               // chunks per staged row
     const int cols = min(WN, p.N - (n0 + wn * WN));       // of this wave's part, those inside (may be negative)
     const int64_t mw = m0 + wm * WM;
-    const bool direct = !wide_store && !p.y_aux && p.act != ACT_SIGMOID && 2 * cols > WN && p.phases == 1 && p.N < (1 << 20);   // (32-bit offsets)
     float bias[NJ];
 #pragma unroll
     for (int j = 0; j < NJ; ++j) bias[j] = p.bias && j * 32 + col_lane < cols ? p.bias[n0 + wn * WN + j * 32 + col_lane] : 0.0f;
-    auto out_row = [&](int64_t m) { return PHASED ? igemm_out_row(p, m, phase, 0) : m; };   // (column strips: interior tiles only)
-    auto conv_result = [&](int i, int j, int e, bool row_ok) {
-      const float v = round_to_storage<T>(acc[i][j][e] + bias[j]);   // the stored conv result
-      if (p.partial) {                           // (columns past N are not stored)
-        const float d = row_ok ? v - bias[j] : 0.0f;
-        s1[j] += d;
-        s2[j] = fmaf(d, d, s2[j]);
-      }
-      return v;
-    };
-    if (__builtin_expect(!direct, 1)) {
 #pragma unroll
-      for (int i = 0; i < MI; ++i) {
-        const int rows = (int)min((int64_t)32, p.M - (mw + i * 32));
+    for (int i = 0; i < MI; ++i) {
+      const int rows = (int)min((int64_t)32, p.M - (mw + i * 32));
 #pragma unroll
-        for (int j = 0; j < NJ; ++j)
-#pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            const int lr = (e >> 2) * 8 + row_lane + (e & 3);
-            Store<T>::st(&stage[lr * SW + j * 32 + col_lane], conv_result(i, j, e, lr < rows));
-          }
-        if (wide_store) {
-#pragma unroll 1
-          for (int idx = lane; idx < 32 * CPRO; idx += 64) {
-            const int lr = idx / CPRO, ch = idx % CPRO;
-            if (lr >= rows || ch * EPC >= cols) continue;
-            float f[EPC];
-            Store<T>::ldv(&stage[lr * SW + ch * EPC], f);
-#pragma unroll
-            for (int t = 0; t < EPC; ++t) f[t] = apply_act(f[t], p.act);
-            Store<T>::stv(Y + out_row(mw + i * 32 + lr) * p.N + n0 + wn * WN + ch * EPC, f);
-          }
-        } else if (cols > 0) {
-          const float inv = __builtin_amdgcn_rcpf((float)cols);       // (n + 1/2) inv rounds down to n / cols: n <= 64, cols <= WN
-          const int step_r = (int)(64.5f * inv), step_c = 64 - step_r * cols;
-          int lr = (int)(((float)lane + 0.5f) * inv), c = lane - lr * cols;
-#pragma unroll 1
-          for (int idx = lane; idx < rows * cols; idx += 64) {
-            const int64_t o = out_row(mw + i * 32 + lr) * p.N + n0 + wn * WN + c;
-            const float a = apply_act(Store<T>::ld(&stage[lr * SW + c]), p.act);
-            Store<T>::st(&Y[o], a);
-            if (p.y_aux) p.y_aux[o] = a;
-            lr += step_r;
-            c += step_c;
-            if (c >= cols) { c -= cols; ++lr; }
-          }
-        }
-      }
-    } else {
-      // (the buffer's range drops the rows past M, an offset past it the columns past N: one instruction per store)
-      const int uw = __builtin_amdgcn_readfirstlane(wave), row_bytes = p.N * ES;
-      const int64_t um = m0 + uw / WGN * WM;
-      const int un = n0 + uw % WGN * WN, inside = (int)min((int64_t)WM, p.M - um);
-      const __amdgpu_buffer_rsrc_t rY = make_rsrc(Y + um * p.N + un, inside > 0 ? (inside - 1) * row_bytes + min(WN, p.N - un) * ES : 0);
-      unsigned off[NJ];
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) off[j] = j * 32 + col_lane < cols ? (unsigned)(row_lane * row_bytes + (j * 32 + col_lane) * ES) : kOob;
-      const bool relu = p.act == ACT_RELU;
-#pragma unroll
-      for (int i = 0; i < MI; ++i)
+      for (int j = 0; j < NJ; ++j)
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-          const int lr = i * 32 + (e >> 2) * 8 + (e & 3);
-#pragma unroll
-          for (int j = 0; j < NJ; ++j) {
-            float v = conv_result(i, j, e, lr + row_lane < inside);
-            v = relu ? apply_act(v, ACT_RELU) : v;
-            if constexpr (ES == 2) __builtin_amdgcn_raw_buffer_store_b16(f32_to_bf16(v), rY, off[j] + (unsigned)(lr * row_bytes), 0, 0);
-            else __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rY, off[j] + (unsigned)(lr * row_bytes), 0, 0);
+          const int lr = (e >> 2) * 8 + row_lane + (e & 3);
+          const float v = round_to_storage<T>(acc[i][j][e] + bias[j]);   // the stored conv result
+          if (p.partial) {                       // (columns past N are not stored)
+            const float d = lr < rows ? v - bias[j] : 0.0f;
+            s1[j] += d;
+            s2[j] = fmaf(d, d, s2[j]);
           }
+          Store<T>::st(&stage[lr * SW + j * 32 + col_lane], v);
         }
+      auto out_row = [&](int lr) {               // (column strips: interior tiles only)
+        const int64_t m = mw + i * 32 + lr;
+        return PHASED ? igemm_out_row(p, m, phase, 0) : m;
+      };
+      if (wide_store) {
+#pragma unroll 1
+        for (int idx = lane; idx < 32 * CPRO; idx += 64) {
+          const int lr = idx / CPRO, ch = idx % CPRO;
+          if (lr >= rows || ch * EPC >= cols) continue;
+          float f[EPC];
+          Store<T>::ldv(&stage[lr * SW + ch * EPC], f);
+#pragma unroll
+          for (int t = 0; t < EPC; ++t) f[t] = apply_act(f[t], p.act);
+          Store<T>::stv(Y + out_row(lr) * p.N + n0 + wn * WN + ch * EPC, f);
+        }
+      } else if (cols > 0) {
+#pragma unroll 1
+        for (int idx = lane; idx < rows * cols; idx += 64) {
+          const int lr = (int)((unsigned)idx / (unsigned)cols), c = idx - lr * cols;
+          const int64_t o = out_row(lr) * p.N + n0 + wn * WN + c;
+          const float a = apply_act(Store<T>::ld(&stage[lr * SW + c]), p.act);
+          Store<T>::st(&Y[o], a);
+          if (p.y_aux) p.y_aux[o] = a;
+        }
+      }
     }
   }
   if (p.partial && EPI != 3 && EPI != 4) {
@@ -762,10 +762,11 @@ __device__ __forceinline__ void replace_bits(floatx16 (&acc)[MI][NJ], uint64_t b
 // offsets are formed for every slab, not once per tap, a dozen VALU instructions per 16 bytes loaded.
 // Measured (bf16, 24 x 36 x 60 pixels): 48 -> 80 channels, 3x3, 25 us = 143 TFLOP/s, where one thread per output on the
 // vector ALUs took 3.4 ms; two such layers at 64 x 64 x 8 forward and backward 140 us against 11.4 ms.
-template <typename T, int BM, int BN, int WGM, int WGN, int BKB, bool INTERIOR, bool DMA, int EPI = 0, bool CHUNKS = false>
+template <typename T, int BM, int BN, int WGM, int WGN, int BKB, bool INTERIOR, bool DMA, int EPI = 0, bool CHUNKS = false, bool DIRECT = false>
 __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(2))) void k_igemm(IgemmParams p) {
   static_assert(!CHUNKS || (!INTERIOR && DMA && EPI == 0), "the chunk walk exists for checked tiles through the DMA pipeline");
   static_assert(EPI == 0 || INTERIOR, "the special epilogues exist for check-free tiles only");
+  static_assert(!DIRECT || (!INTERIOR && sizeof(T) == 2), "bf16, checked tiles");
   static_assert(WGM * WGN == 4 || WGM * WGN == 8, "four or eight wavefronts per workgroup");
   constexpr int NT = WGM * WGN * 64;            // threads: all of them load, each wavefront owns a WM x WN part of the tile
   static_assert(BKB == 64 || BKB == 128, "slab row bytes");
@@ -1029,7 +1030,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
     }
   }
   static_assert(EPI != 2 || BM * BN * ES <= SLAB_BYTES, "resid");
-  igemm_epilogue<T, BM, BN, WGM, WGN, INTERIOR, EPI, CHUNKS, EPI == 2>(acc, p, smem, sRed, m0, n0, tile_m, phase);
+  igemm_epilogue<T, BM, BN, WGM, WGN, INTERIOR, EPI, CHUNKS, EPI == 2, DIRECT>(acc, p, smem, sRed, m0, n0, tile_m, phase);
 }
 
 // ---------------------------------------------------------------------------
@@ -1816,6 +1817,13 @@ static int launch_splitk_finish(const ConvArgs& a, int splits, int64_t M, int N,
   return launch_status("splitk_finish");
 }
 
+// Checked bf16 tiles whose rows are stored from the accumulators (DIRECT): rows of no whole 16 bytes, most of a tile's columns
+// inside, 32-bit offsets.  (Phases, whose output rows take divisions, the sigmoid and its binary32 copy use the loop: 48 -> 3 channels behind
+// an upsample 27 -> 16 us with it.)
+static bool direct_stores(const IgemmParams& p, int dtype, int bn) {
+  return dtype == AE_BF16 && !p.split_out && p.N % 8 != 0 && p.N < (1 << 20) && 2 * p.N > bn && !p.y_aux && p.act != ACT_SIGMOID && p.phases == 1;
+}
+
 int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
   if (!conv_mfma_supported(a0)) return fail(AE_EINVAL, "conv_mfma: shape not supported");
   if (a0.w_frag != conv3_patch_usable(a0)) return fail(AE_EINVAL, "conv_mfma: the order of the packed weights does not fit the kernel of this launch (conv_weights_frag_order)");
@@ -1894,8 +1902,10 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
 #define IGEMM_LAUNCH_K(T, BMV, BNV, GM, GN, KB)                                                        \
   do {                                                                                                 \
     if (interior) hipLaunchKernelGGL((k_igemm<T, BMV, BNV, GM, GN, KB, true, true>), grid, dim3(256), 0, s, p); \
+    else if (sizeof(T) == 2 && direct) hipLaunchKernelGGL((k_igemm<T, BMV, BNV, GM, GN, KB, false, true, 0, false, sizeof(T) == 2>), grid, dim3(256), 0, s, p); \
     else hipLaunchKernelGGL((k_igemm<T, BMV, BNV, GM, GN, KB, false, true>), grid, dim3(256), 0, s, p); \
   } while (0)
+  const bool direct = direct_stores(p, a.dtype, t.bn);
   // Binary32: three bf16 parts (k_gemm_split), unless the caller asks for the binary32 MFMA or there are few columns and a
   // short K, where both only move the operands (65,536 rows, 64 -> 64 channels: 13.6 and 12.8 us; 131,072 rows, 48 -> 64 -> 48: 18.7
   // and 18.6, 22.4 and 22.9; from there on the parts win: 64 -> 512 -> 64 channels 60.5 against 45.6 and 45.0 against 37.4)
@@ -2020,8 +2030,12 @@ int launch_conv_chunks(const ConvArgs& a0, hipStream_t s) {
   splits = (c.KT + p.slabs_per_split - 1) / p.slabs_per_split;
   p.split_out = splits > 1 ? a.splitk_ws : nullptr;
   const dim3 grid((unsigned)(c.tiles * splits * p.phases));
-#define CHUNKS_LAUNCH(T, BMV, BNV, GM, GN) \
-  hipLaunchKernelGGL((k_igemm<T, BMV, BNV, GM, GN, 64, false, true, 0, true>), grid, dim3(256), 0, s, p)
+  const bool direct = direct_stores(p, a.dtype, c.bn);
+#define CHUNKS_LAUNCH(T, BMV, BNV, GM, GN)                                                                                           \
+  do {                                                                                                                               \
+    if (direct) hipLaunchKernelGGL((k_igemm<T, BMV, BNV, GM, GN, 64, false, true, 0, true, sizeof(T) == 2>), grid, dim3(256), 0, s, p); \
+    else hipLaunchKernelGGL((k_igemm<T, BMV, BNV, GM, GN, 64, false, true, 0, true>), grid, dim3(256), 0, s, p);                        \
+  } while (0)
 #define CHUNKS_TILE(T)                                                              \
   do {                                                                              \
     if (c.bn == 128) CHUNKS_LAUNCH(T, 128, 128, 2, 2);                            \

@@ -49,7 +49,8 @@ def test_tall_tiles_and_many_splits(dtype):
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("spec,batch", [("in:9x11x13,conv3:99,relu,conv3:101,bn,relu,conv1:57,relu,conv1:35,relu,conv1:27,relu,conv1:3", 3),
                                         ("in:5x64x43,conv3:33,relu,conv1:61,bn,relu,conv1:21,conv1:2", 12),
-                                        ("in:6x5x7,up2,conv3:99,relu,up2,conv3:51,sigmoid", 2), ("in:12x7x5,conv1:99,sigmoid,conv1:2", 4)])
+                                        ("in:6x5x7,up2,conv3:99,relu,up2,conv3:51,sigmoid", 2), ("in:12x7x5,conv1:99,sigmoid,conv1:2", 4),
+                                        ("in:64x9x11,conv3:99,relu,conv1:64,relu,conv3:70,bn,relu,conv1:2", 3), ("in:32x64x64,conv1:101,relu,conv1:3", 33)])
 def test_stores_of_odd_rows(spec, batch, dtype):
     run_case(spec, batch, dtype=dtype, seed=440 + batch, flips=(dtype == "bf16"))
 
