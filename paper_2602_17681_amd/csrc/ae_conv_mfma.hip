@@ -58,6 +58,9 @@ struct IgemmParams {
   // stored input (one per output parity (a, b) = (phase>>1, phase&1), pads 1-a and 1-b, weights
   // w + phase*N*K); row (n, i, j) of phase (a, b) is output pixel (2i+a, 2j+b) of a 2Hc x 2Wc image
   int phases;
+  // k_dense with its second operand [k][n] (KN): output rows are groups of kn_group, each a product of its own with the x of
+  // kn_group rows and K rows of w (group g: rows K g .. of w)
+  int kn_group = 0;
   // epilogue variants of the dense-GEMM use (EPI template parameter of k_dense, k_igemm and k_gemm_split):
   //   1: the stored output is MX block-quantised (blocks of mx_block output columns: a power of two from one 16-byte
   //      chunk up to the 64 columns of a wave tile; FP4 E2M1 elements);
@@ -1033,6 +1036,31 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
   igemm_epilogue<T, BM, BN, WGM, WGN, INTERIOR, EPI, CHUNKS, EPI == 2, DIRECT>(acc, p, smem, sRed, m0, n0, tile_m, phase);
 }
 
+// Operands that lie in LDS with K outermost, read transposed (ds_read_b64_tr_b16: within 16 lanes, lane 4j+q addresses 4 columns
+// of k-row j, lane i receives column i of k-rows 0..3): k-rows 0..3 and 4..7 of a lane's column
+typedef unsigned uint2v __attribute__((ext_vector_type(2)));
+struct TrFrag { uint2v lo, hi; };
+
+template <int OFF>
+__device__ __forceinline__ void tr_read(TrFrag& f, unsigned addr, int row_bytes4 /* = 4 k-rows */) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.lo) : "v"(addr), "n"(OFF));
+  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.hi) : "v"(addr + (unsigned)row_bytes4), "n"(OFF));
+#endif
+}
+__device__ __forceinline__ void tr_tie(TrFrag& f) {   // (as TieFrags)
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("" : "+v"(f.lo), "+v"(f.hi));
+#endif
+}
+template <int OFF, int STEP>                     // STEP: bytes of four k-rows
+__device__ __forceinline__ void tr_read_at(TrFrag& f, unsigned addr) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.lo) : "v"(addr), "n"(OFF));
+  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.hi) : "v"(addr), "n"(OFF + STEP));
+#endif
+}
+
 // ---------------------------------------------------------------------------
 // Dense bf16 products, check-free tiles: y[m][n] = x[m][:] w[n][:]^T, without the taps of k_igemm.
 //
@@ -1049,7 +1077,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
 // its deviations 586 -> 537 us.  1 us a slab of 256 x 256 outputs, 0.55 us of it MFMAs at the full clock.
 // Which tiles come here, and with how many stages: dense_stages and launch_conv_mfma.
 // ---------------------------------------------------------------------------
-template <int BM, int BN, int WGM, int WGN, int NSTAGE, int EPI = 0>
+template <int BM, int BN, int WGM, int WGN, int NSTAGE, int EPI = 0, bool KN = false>
 __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(2))) void k_dense(IgemmParams p) {
   constexpr int NT = WGM * WGN * 64, BKB = 64, BK = 32;
   constexpr int WM = BM / WGM, WN = BN / WGN, MI = WM / 32, NJ = WN / 32;
@@ -1069,16 +1097,26 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
   if (!igemm_k_range<BM, BN>(p, m0, n0, k_lo, k_hi)) return;
   const int kt0 = k_lo / BK, KT = (k_hi + BK - 1) / BK - kt0;
   const unsigned row_bytes = (unsigned)p.K * 2u;
-  const __amdgpu_buffer_rsrc_t rX = make_rsrc((const char*)p.x + m0 * row_bytes, BM * row_bytes);
-  const __amdgpu_buffer_rsrc_t rW = make_rsrc((const char*)p.w + (int64_t)n0 * row_bytes, BN * row_bytes);
+  const unsigned w_row = KN ? (unsigned)p.N * 2u : row_bytes;
+  const int grp = KN ? (int)(m0 / p.kn_group) : 0;
+  const __amdgpu_buffer_rsrc_t rX = make_rsrc((const char*)p.x + (m0 - (int64_t)grp * p.kn_group) * row_bytes, BM * row_bytes);
+  const __amdgpu_buffer_rsrc_t rW = KN ? make_rsrc((const char*)p.w + (int64_t)grp * p.K * w_row + n0 * 2, (unsigned)(p.K - 1) * w_row + BN * 2u)
+                                       : make_rsrc((const char*)p.w + (int64_t)n0 * row_bytes, BN * row_bytes);
   const int lrow = tid >> 2;
   const unsigned off0 = (unsigned)lrow * row_bytes + (unsigned)(((tid & 3) ^ ((lrow >> 2) & 3)) * 16);   // rows lrow + i RSTEP: the same swizzle
   unsigned kbyte = (unsigned)kt0 * BKB;          // of the next slab to load
+  // KN: a slab is 32 k-rows of BN values, 16-byte chunk c of row k in slot c ^ 4 (k & 3), so that the four rows of a
+  // transposing read lie in different banks; 64 bytes of a row stay together
+  constexpr int CPN = BN / 8, KROWS = NT / CPN;  // chunks per k-row; k-rows per pass
+  static_assert(!KN || (KROWS % 4 == 0 && (BN == 128 || BN == 256)), "the swizzle is the same in every pass");
+  const int krow = tid / CPN;
+  const unsigned offw = KN ? (unsigned)krow * w_row + (unsigned)(((tid % CPN) ^ (4 * (krow & 3))) * 16) : off0;
+  unsigned wbyte = (unsigned)kt0 * (KN ? BK * w_row : (unsigned)BKB);
   auto load = [&](auto c_, int stg) {            // load c of a slab into stage stg
     constexpr int c = decltype(c_)::value;
     if constexpr (c < AC) dma_load16s(rX, smem + stg * SA + c * (NT * 16) + wave * 1024, off0 + (unsigned)(c * RSTEP) * row_bytes, kbyte);
-    else dma_load16s(rW, sB + stg * SB + (c - AC) * (NT * 16) + wave * 1024, off0 + (unsigned)((c - AC) * RSTEP) * row_bytes, kbyte);
-    if constexpr (c == L - 1) kbyte += BKB;
+    else dma_load16s(rW, sB + stg * SB + (c - AC) * (NT * 16) + wave * 1024, offw + (unsigned)((c - AC) * (KN ? KROWS : RSTEP)) * w_row, wbyte);
+    if constexpr (c == L - 1) { kbyte += BKB; wbyte += KN ? BK * w_row : (unsigned)BKB; }
   };
   const int fr = lane & 31, fsw = (fr >> 2) & 3;
   unsigned fa_addr[2], fb_addr[2];               // of this lane's fragments of either K-step, stage 0
@@ -1088,6 +1126,14 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
     fa_addr[ks] = (unsigned)(size_t)(lds_char*)smem + (unsigned)(wm * WM * BKB) + o;
     fb_addr[ks] = (unsigned)(size_t)(lds_char*)sB + (unsigned)(wn * WN * BKB) + o;
   }
+  unsigned tr_addr[KN ? NJ : 1];                 // KN: of this lane's transposing reads, K-step 0, stage 0 (wave column 32 j: 64 bytes)
+  if constexpr (KN) {
+    const int kr = (lane & 15) >> 2;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+      tr_addr[j] = (unsigned)(size_t)(lds_char*)sB + (unsigned)(((lane >> 5) * 8 + kr) * (BN * 2) + (((wn * WN / 32 + j) ^ kr) * 64) +
+                                                                ((lane >> 4) & 1) * 32 + (lane & 3) * 8);
+  }
   floatx16 acc[MI][NJ];
 #pragma unroll
   for (int i = 0; i < MI; ++i)
@@ -1095,23 +1141,41 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
     for (int j = 0; j < NJ; ++j)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
-  uint4v fa[2][MI], fb[2][NJ];
+  uint4v fa[2][MI], fb[KN ? 1 : 2][NJ];
+  TrFrag ft[2][KN ? NJ : 1];
+  auto read_b = [&](auto ks_, auto j0_, auto j1_, int stg) {   // fragments j0 .. j1 - 1 of K-step ks
+    constexpr int ks = decltype(ks_)::value, j0 = decltype(j0_)::value, j1 = decltype(j1_)::value;
+    if constexpr (KN) unroll<j1 - j0>([&](auto j_) {
+      constexpr int j = j0 + decltype(j_)::value;
+      tr_read_at<ks * 16 * BN * 2, 4 * BN * 2>(ft[ks][j], tr_addr[j] + (unsigned)(stg * SB));
+    });
+    else LdsReadFrags<j0, j1, 32 * BKB>::run(fb[ks], fb_addr[ks] + (unsigned)(stg * SB));
+  };
+  auto wait_frags = [&](auto ks_) {
+    constexpr int ks = decltype(ks_)::value;
+    lds_wait_tie_a<0, MI>(fa[ks]);
+    if constexpr (KN) unroll<NJ>([&](auto j_) { tr_tie(ft[ks][decltype(j_)::value]); });
+    else lds_wait_tie_a<0, NJ>(fb[ks]);
+  };
   // K-step ks: between its MFMAs the fragment reads of the other K-step (stage rstg; waited for behind the last MFMA, so
   // that nothing is in flight where the loop turns) and its half of a slab's loads (stage lstg; none if negative)
   auto step = [&](auto ks_, auto read_, int rstg, int lstg) {
     constexpr int ks = decltype(ks_)::value;
     constexpr bool read = decltype(read_)::value;
     constexpr int MM = MI * NJ, H = NSTAGE == 3 ? L : (L + 1) / 2, C0 = ks == 1 ? 0 : H, NL = ks == 1 ? H : L - H;
-    const unsigned ra = fa_addr[ks ^ 1] + (unsigned)(rstg * SA), rb = fb_addr[ks ^ 1] + (unsigned)(rstg * SB);
+    const unsigned ra = fa_addr[ks ^ 1] + (unsigned)(rstg * SA);
     __builtin_amdgcn_sched_barrier(0);
     unroll<MM>([&](auto q_) {
       constexpr int q = decltype(q_)::value;
-      mma_step<bf16_t>(fa[ks][q / NJ], fb[ks][q % NJ], acc[q / NJ][q % NJ]);
+      if constexpr (KN) {
+        const TrFrag& t = ft[ks][q % NJ];
+        mma_step<bf16_t>(fa[ks][q / NJ], uint4v{t.lo.x, t.lo.y, t.hi.x, t.hi.y}, acc[q / NJ][q % NJ]);
+      } else mma_step<bf16_t>(fa[ks][q / NJ], fb[ks][q % NJ], acc[q / NJ][q % NJ]);
       if constexpr (read) {                      // two reads behind each of the first MFMAs
         constexpr int r0 = 2 * q, r1 = 2 * q + 2;
         constexpr int b0 = r0 < NJ ? r0 : NJ, b1 = r1 < NJ ? r1 : NJ;
         constexpr int a0 = r0 < NJ ? 0 : (r0 - NJ < MI ? r0 - NJ : MI), a1 = r1 < NJ ? 0 : (r1 - NJ < MI ? r1 - NJ : MI);
-        LdsReadFrags<b0, b1, 32 * BKB>::run(fb[ks ^ 1], rb);
+        read_b(std::integral_constant<int, ks ^ 1>{}, std::integral_constant<int, b0>{}, std::integral_constant<int, b1>{}, rstg);
         LdsReadFrags<a0, a1, 32 * BKB>::run(fa[ks ^ 1], ra);
       }
       if constexpr (NL > 0) {
@@ -1123,7 +1187,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
       }
       __builtin_amdgcn_sched_barrier(0);
     });
-    if constexpr (read) { lds_wait_tie_a<0, MI>(fa[ks ^ 1]); lds_wait_tie_a<0, NJ>(fb[ks ^ 1]); }
+    if constexpr (read) wait_frags(std::integral_constant<int, ks ^ 1>{});
   };
   constexpr std::integral_constant<int, 0> k0{};
   constexpr std::integral_constant<int, 1> k1{};
@@ -1138,10 +1202,9 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
   else if (KT > 1) __builtin_amdgcn_s_waitcnt(vm_imm(L));
   else __builtin_amdgcn_s_waitcnt(vm_imm(0));
   __builtin_amdgcn_s_barrier();
-  LdsReadFrags<0, NJ, 32 * BKB>::run(fb[0], fb_addr[0]);
+  read_b(k0, k0, std::integral_constant<int, NJ>{}, 0);
   LdsReadFrags<0, MI, 32 * BKB>::run(fa[0], fa_addr[0]);
-  lds_wait_tie_a<0, MI>(fa[0]);
-  lds_wait_tie_a<0, NJ>(fb[0]);
+  wait_frags(k0);
   int cur = 0, pend = -1;                        // stage of slab kt; stage whose loads are half issued
   for (int kt = 0; kt + 1 < KT; ++kt) {
     step(k0, yes, cur, pend);
@@ -2012,6 +2075,28 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
   return splits > 1 ? launch_splitk_finish(a, splits, p.M, p.N, s) : AE_OK;
 }
 
+// y[m][n] = sum over k of x[m mod group][k] w[K (m div group) + k][n], bf16, check-free tiles: products whose second operand lies
+// [k][n] (KN of k_dense), in groups of `group` output rows with the same x (one group: group = rows)
+bool dense_kn_supported(int64_t rows, int64_t k, int64_t n, int64_t group) {
+  return rows % group == 0 && group % 128 == 0 && n % 128 == 0 && k % 32 == 0 && k > 0 && (rows / 128) * (n / 128) < 0x7FFFFFFF &&
+         group * k * 2 < 0x7FFFFFFF && k * n * 2 < 0x7FFFFFFF;
+}
+int launch_dense_kn(const void* x, const void* w, void* y, int64_t rows, int64_t k, int64_t n, int64_t group, hipStream_t s) {
+  if (!dense_kn_supported(rows, k, n, group)) return fail(AE_EINVAL, "dense_kn: shape not supported");
+  IgemmParams p = {};
+  p.x = x; p.w = w; p.y = y;
+  p.M = rows; p.N = (int)n; p.K = (int)k; p.phases = 1; p.act = ACT_NONE; p.kn_group = (int)group;
+  const bool wide = rows % 256 == 0 && group % 256 == 0 && n % 256 == 0 && (rows / 256) * (n / 256) >= 256;
+  const int bt = wide ? 256 : 128;
+  p.tiles_n = (int)(n / bt);
+  p.tiles_mn = (int)((rows / bt) * (n / bt));
+  const dim3 grid((unsigned)p.tiles_mn);
+  if (wide) hipLaunchKernelGGL((k_dense<256, 256, 2, 4, 4, 0, true>), grid, dim3(512), 0, s, p);
+  else if (dense_stages(grid.x, p.tiles_n, 0) == 3) hipLaunchKernelGGL((k_dense<128, 128, 2, 2, 3, 0, true>), grid, dim3(256), 0, s, p);
+  else hipLaunchKernelGGL((k_dense<128, 128, 2, 2, 4, 0, true>), grid, dim3(256), 0, s, p);
+  return launch_status("dense_kn");
+}
+
 // ---- any channel counts: the chunk walk of k_igemm ---------------------------------------------------------------
 // a.x holds whole 16-byte chunks per pixel and a.w per tap (chan_pad channels, zeros behind the layer's own)
 int launch_conv_chunks(const ConvArgs& a0, hipStream_t s) {
@@ -2738,16 +2823,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 // the loads of the slab after that, then four K-steps of 16 pixels with the fragments of the
 // next K-step (the first of the next slab included) in flight behind the MFMAs.
 // ---------------------------------------------------------------------------
-typedef unsigned uint2v __attribute__((ext_vector_type(2)));
-struct TrFrag { uint2v lo, hi; };               // pixels 0..3 and 4..7 of a lane's channel
-
-template <int OFF>
-__device__ __forceinline__ void tr_read(TrFrag& f, unsigned addr, int row_bytes4 /* = 4 pixel rows */) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.lo) : "v"(addr), "n"(OFF));
-  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.hi) : "v"(addr + (unsigned)row_bytes4), "n"(OFF));
-#endif
-}
 // The patch operand of a K-step for all taps of a filter row at once: pixels 0..11 of a lane's channel, from the
 // lane's cell on.  Tap s of pixel j reads cell j + s, so the operand of tap s is pixels s .. s+7 of this run: the taps
 // are cut out of one 12-pixel read in registers (funnel shifts for the odd tap) instead of being read from LDS once

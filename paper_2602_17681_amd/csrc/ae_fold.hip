@@ -196,22 +196,31 @@ extern "C" int model_fold_linear(const void* w, const float* b, int64_t out, int
   void* wtt = (char*)zt + out * in * es;               // (A_l W A_r^-1)^T   [in][out]
   const void* cur = w;                                 // [out][in]
   if (a_right_inv) {
-    transpose(a_right_inv, q, q, art, dtype, s);
-    AE_TRY(launch_status("fold_transpose"));
     void* dst = a_left ? z : w_out;
-    const ConvArgs a = product_args(cur, art, nullptr, dst, out * (in / q), q, q, dtype);
+    const int64_t rows = out * (in / q);
+    const ConvArgs a = product_args(cur, art, nullptr, dst, rows, q, q, dtype);
     if (!conv_mfma_supported(a)) return fail(AE_EINVAL, "model_fold_linear: shape not supported by the matrix-core kernel");
-    AE_TRY(launch_conv_mfma(a, s));
+    if (dtype == AE_BF16 && dense_kn_supported(rows, q, q, rows)) {
+      AE_TRY(launch_dense_kn(cur, a_right_inv, dst, rows, q, q, rows, s));
+    } else {
+      transpose(a_right_inv, q, q, art, dtype, s);
+      AE_TRY(launch_status("fold_transpose"));
+      AE_TRY(launch_conv_mfma(a, s));
+    }
     cur = dst;
   }
   if (a_left) {
-    transpose(cur, out, in, zt, dtype, s);
-    AE_TRY(launch_status("fold_transpose"));
     const ConvArgs a = product_args(zt, a_left, nullptr, wtt, in * (out / p), p, p, dtype);
     if (!conv_mfma_supported(a)) return fail(AE_EINVAL, "model_fold_linear: shape not supported by the matrix-core kernel");
-    AE_TRY(launch_conv_mfma(a, s));
-    transpose(wtt, in, out, w_out, dtype, s);
-    AE_TRY(launch_status("fold_transpose"));
+    if (dtype == AE_BF16 && dense_kn_supported(out, p, in, p)) {
+      AE_TRY(launch_dense_kn(a_left, cur, w_out, out, p, in, p, s));
+    } else {
+      transpose(cur, out, in, zt, dtype, s);
+      AE_TRY(launch_status("fold_transpose"));
+      AE_TRY(launch_conv_mfma(a, s));
+      transpose(wtt, in, out, w_out, dtype, s);
+      AE_TRY(launch_status("fold_transpose"));
+    }
   } else if (!a_right_inv) {
     AE_HIP(hipMemcpyAsync(w_out, w, out * in * es, hipMemcpyDeviceToDevice, s));
   }

@@ -238,6 +238,9 @@ int launch_conv_direct(const ConvArgs& a, hipStream_t s);
 bool conv_mfma_supported(const ConvArgs& a);
 ConvArgs conv_effective(const ConvArgs& a);   // the GEMM that a.geom runs as
 int launch_conv_mfma(const ConvArgs& a, hipStream_t s);
+// bf16 products whose second operand lies [k][n], in groups of output rows: y[m][n] = sum_k x[m mod group][k] w[K (m div group) + k][n], K = the k of the call
+bool dense_kn_supported(int64_t rows, int64_t k, int64_t n, int64_t group);
+int launch_dense_kn(const void* x, const void* w, void* y, int64_t rows, int64_t k, int64_t n, int64_t group, hipStream_t s);
 // The matrix-core kernel for any channel counts: a.x and a.w hold chan_pad(cin) channels per pixel and per tap, zeros
 // behind the layer's own (launch_pad_channels, the packing kernels); a.y has plain rows of cout.
 bool conv_chunks_supported(const ConvArgs& a);
