@@ -1076,26 +1076,30 @@ __device__ __forceinline__ void tr_read_at(TrFrag& f, unsigned addr) {
 // MFMAs wait for): 4 096^3 143 -> 126 us, the quantising product of 16 384 x 4 096 x 4 096 683 -> 594 us, the one that only sums
 // its deviations 586 -> 537 us.  1 us a slab of 256 x 256 outputs, 0.55 us of it MFMAs at the full clock.
 // Which tiles come here, and with how many stages: dense_stages and launch_conv_mfma.
+// KN: the second operand lies [k][n] (launch_dense_kn): a slab is 32 k-rows of it, read with the transposing LDS reads; same sums in
+// the same order.  d = 4 096: 126 us as well.  KG = 2: dense_halves.
 // ---------------------------------------------------------------------------
-template <int BM, int BN, int WGM, int WGN, int NSTAGE, int EPI = 0, bool KN = false>
-__global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(2))) void k_dense(IgemmParams p) {
+template <int BM, int BN, int WGM, int WGN, int NSTAGE, int EPI = 0, bool KN = false, int KG = 1>
+__global__ __launch_bounds__(WGM * WGN * 64 * KG) __attribute__((amdgpu_waves_per_eu(2))) void k_dense(IgemmParams p) {
   constexpr int NT = WGM * WGN * 64, BKB = 64, BK = 32;
   constexpr int WM = BM / WGM, WN = BN / WGN, MI = WM / 32, NJ = WN / 32;
   constexpr int RSTEP = NT / 4, AC = BM / RSTEP, BC = BN / RSTEP, L = AC + BC;   // loads per thread and slab
   static_assert(NSTAGE == 3 || NSTAGE == 4, "the waits below");
   constexpr int SA = BM * BKB, SB = BN * BKB, SW = WN + 8;
   constexpr int SLAB_BYTES = NSTAGE * (SA + SB), STAGE_BYTES = (NT / 64) * 32 * SW * 2;
-  __shared__ __attribute__((aligned(16))) char smem[SLAB_BYTES > STAGE_BYTES ? SLAB_BYTES : STAGE_BYTES];
+  __shared__ __attribute__((aligned(16))) char smem_all[KG == 1 && SLAB_BYTES < STAGE_BYTES ? STAGE_BYTES : KG * SLAB_BYTES];
   __shared__ float sRed[WGM][2][BN];
+  const int kg = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / NT);
+  char* const smem = smem_all + kg * SLAB_BYTES;
   char* const sB = smem + NSTAGE * SA;
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tid = KG == 1 ? (int)threadIdx.x : (int)threadIdx.x - kg * NT, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
   const IgemmTileId tile = igemm_tile_id<BM, BN, true>(p);
   const int64_t m0 = tile.m * BM;
   const int n0 = tile.n * BN;
   int k_lo, k_hi;
   if (!igemm_k_range<BM, BN>(p, m0, n0, k_lo, k_hi)) return;
-  const int kt0 = k_lo / BK, KT = (k_hi + BK - 1) / BK - kt0;
+  const int KT = ((k_hi + BK - 1) / BK - k_lo / BK) / KG, kt0 = k_lo / BK + kg * KT;
   const unsigned row_bytes = (unsigned)p.K * 2u;
   const unsigned w_row = KN ? (unsigned)p.N * 2u : row_bytes;
   const int grp = KN ? (int)(m0 / p.kn_group) : 0;
@@ -1220,6 +1224,25 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
   step(k0, yes, cur, -1);
   step(k1, no, 0, -1);
   __syncthreads();                               // every wave is done with the slabs: the epilogue reuses the memory
+  if constexpr (KG == 2) {                       // the second half's sums, 16 bytes a lane at once, to the first
+    static_assert(BM * BN * 4 <= SLAB_BYTES && EPI == 0, "the second half's own stages hold its sums; no barrier follows");
+    float4v* const sum = reinterpret_cast<float4v*>(smem_all + SLAB_BYTES) + wave * (MI * NJ * 4 * 64) + lane;
+    if (kg == 1) {
+#pragma unroll
+      for (int t = 0; t < MI * NJ * 4; ++t) {
+        const floatx16& c = acc[t / 4 / NJ][t / 4 % NJ];
+        sum[t * 64] = float4v{c[4 * (t % 4)], c[4 * (t % 4) + 1], c[4 * (t % 4) + 2], c[4 * (t % 4) + 3]};
+      }
+    }
+    __syncthreads();
+    if (kg == 1) return;
+#pragma unroll
+    for (int t = 0; t < MI * NJ * 4; ++t) {
+      const float4v v = sum[t * 64];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[t / 4 / NJ][t / 4 % NJ][4 * (t % 4) + e] += v[e];
+    }
+  }
   static_assert(EPI != 2 || BM * BN * 2 <= SLAB_BYTES, "resid");
   igemm_epilogue<bf16_t, BM, BN, WGM, WGN, true, EPI, false, true>(acc, p, smem, sRed, m0, n0, tile.m);
 }
@@ -1729,6 +1752,13 @@ int dense_stages(int64_t tiles, int tiles_n, int tri) {
   return tri == 0 && tiles >= 352 && tiles <= 768 && (tiles_n > 3 || tiles > 512) ? 3 : 4;
 }
 
+// With the second operand [k][n] and at most one 128 x 128 tile per compute unit: do two groups of four wavefronts take half of K each?
+// Twice the loads in flight, at the price of handing 64 KiB of sums over.  us of the product (operands in the caches / from memory), whole
+// K / halves, rows x K x columns: 1 024 x 4 096^2 45.8 / 39.9 (62.6 / 57.7), 512 x 4 096^2 42.0 / 33.1, 1 024 x 2 048^2 24.4 / 20.2, 1 024^3
+// 14.1 / 12.4, 768^3 11.0 / 10.0, 512^3 8.8 / 8.3, 2 048 x 512^2 9.2 / 8.9, 4 096 x 256^2 6.8 / 7.3.  (With both operands k-contiguous it gains nothing:
+// 1 024 x 4 096^2 44.8 / 45.4.)
+bool dense_halves(int64_t tiles, int64_t K) { return tiles <= 256 && K % 64 == 0 && K >= 512; }
+
 // Does k_dense take 256 x 128 tiles?  They leave it three stages at two workgroups per compute unit, like k_igemm, and its waits
 // let one slab's loads be in flight instead of two: it gains where K is short and the weights stay in the caches, and for
 // triangular K ranges.  us with k_dense / k_igemm, rows x columns x K:
@@ -2092,6 +2122,7 @@ int launch_dense_kn(const void* x, const void* w, void* y, int64_t rows, int64_t
   p.tiles_mn = (int)((rows / bt) * (n / bt));
   const dim3 grid((unsigned)p.tiles_mn);
   if (wide) hipLaunchKernelGGL((k_dense<256, 256, 2, 4, 4, 0, true>), grid, dim3(512), 0, s, p);
+  else if (dense_halves(grid.x, p.K)) hipLaunchKernelGGL((k_dense<128, 128, 2, 2, 4, 0, true, 2>), grid, dim3(512), 0, s, p);
   else if (dense_stages(grid.x, p.tiles_n, 0) == 3) hipLaunchKernelGGL((k_dense<128, 128, 2, 2, 3, 0, true>), grid, dim3(256), 0, s, p);
   else hipLaunchKernelGGL((k_dense<128, 128, 2, 2, 4, 0, true>), grid, dim3(256), 0, s, p);
   return launch_status("dense_kn");

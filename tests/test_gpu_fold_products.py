@@ -5,8 +5,9 @@ pytestmark = pytest.mark.gpu
 
 
 # (out, in, p, q), 0 = that side absent: one and three groups of 128 and of 256 rows, K of 128 and more, 128 x 128 tiles (four stages of
-# slabs; 384 tiles in three columns and 352 in eleven, three) and 256 x 256 (256 tiles); 192 rows of a group stay with the transposing form
-@pytest.mark.parametrize("out,inn,p,q", [(128, 128, 128, 0), (384, 256, 128, 128), (768, 384, 256, 384), (4096, 1408, 128, 1408), (384, 768, 192, 256),
+# slabs; 384 tiles in three columns and 352 in eleven, three; K of 512 and more on few tiles in halves) and 256 x 256 (256 tiles); 192 rows
+# of a group stay with the transposing form
+@pytest.mark.parametrize("out,inn,p,q", [(128, 128, 128, 0), (256, 512, 0, 512), (512, 256, 512, 0), (128, 608, 0, 608), (128, 1152, 128, 1152), (384, 256, 128, 128), (768, 384, 256, 384), (4096, 1408, 128, 1408), (384, 768, 192, 256),
                                          (16384, 384, 128, 0), (4096, 4096, 4096, 256), (4096, 4096, 256, 4096), (65536, 256, 0, 256)])
 def test_fold_bf16(out, inn, p, q):
     import torch
