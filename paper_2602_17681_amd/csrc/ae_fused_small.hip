@@ -13,13 +13,16 @@
 //                   fc, reshape, both upsampled convolutions, sigmoid — all in LDS, y written once.
 // Arithmetic is binary32: the first three convolutions on the binary32 matrix instruction (16 pixels x 16 channels x 4 input
 // channels, one wavefront per 16 pixels), whose accumulators hold one channel per lane so that the batch statistics are
-// a few adds, the rest as fused multiply-adds on the vector ALUs.  Sixteen wavefronts per sample: a batch of 64 samples
-// occupies 64 of 256 compute units, so what counts is the length of one sample's chain of loads and LDS reads.  (Four
-// wavefronts and vector ALUs throughout: 10 + 18 + 50 us for the three launches at 64 samples of 28 x 28.  Now
-// 6 + 11 + 33; of the 33: statistics and pooling 4, fc 4.5, channel 1.5, fc 7.6, convolutions 9.5 and 4.3.)
+// a few adds, the rest as fused multiply-adds on the vector ALUs.  Sixteen wavefronts per workgroup, and where samples leave
+// compute units idle several workgroups share the pixels of one (bands: launch 3 repeats what all its pixels need, the decoder's
+// layers are computed for the band's rows and those around them): what counts is the length of one workgroup's chain of loads, LDS
+// reads and MFMAs.  64 samples of 28 x 28: 6 + 11 + 32 us for the three launches with one workgroup per sample, in all 51 and
+// now 39; of launch 3: statistics and pooling 4, fc 5, channel 1.7, fc 6, convolutions 3.5 and 1.7 (one workgroup: 7.6 and 7).
 // Definitions as in aemodel.h.  No activation is kept for a backward pass: the executor takes this path only for a
 // model in inference mode.
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 
 #include "ae_device.h"
 #include "ae_internal.h"
@@ -66,7 +69,7 @@ __device__ __forceinline__ void bn_vectors(const float* __restrict__ partial, in
   const int c = threadIdx.x % C, g = threadIdx.x / C;
   double s1 = 0.0, s2 = 0.0;
   if (g < G) {
-#pragma unroll 4
+#pragma unroll 8
     for (int b = g; b < B; b += G) {
       s1 += (double)partial[((int64_t)b * 2) * C + c];
       s2 += (double)partial[((int64_t)b * 2 + 1) * C + c];
@@ -93,13 +96,13 @@ __device__ __forceinline__ void bn_vectors(const float* __restrict__ partial, in
 
 // 16 output pixels x 16 channels of a 3x3 convolution (zero padding) of a planar LDS image src[cin][hs x ws] (planes `plane`
 // floats apart), UP: read through a x2 nearest-neighbour upsample.  Lane l multiplies input channel c + l/16 of pixel
-// `m0 + l % 16` (v_mfma_f32_16x16x4); results: channel l % 16 of pixels m0 + 4 (l/16) + 0..3.  Pixels past n_px are those of
-// pixel 0 (nobody stores them).  wl: [tap][cin][16].
+// `m0 + l % 16` (v_mfma_f32_16x16x4); results: channel l % 16 of pixels m0 + 4 (l/16) + 0..3.  Pixels from hi on are those of
+// pixel lo (nobody stores them).  wl: [tap][cin][16].
 template <bool UP>
-__device__ __forceinline__ floatx4 conv3_tile(const float* src, int plane, int cin, int hs, int ws, const float* wl, int m0, int n_px) {
+__device__ __forceinline__ floatx4 conv3_tile(const float* src, int plane, int cin, int hs, int ws, const float* wl, int m0, int lo, int hi) {
   const int lane = threadIdx.x & 63, g = lane >> 4;
   const int hc = UP ? 2 * hs : hs, wc = UP ? 2 * ws : ws, whole = cin & ~3;
-  const int px = m0 + (lane & 15) < n_px ? m0 + (lane & 15) : 0;
+  const int px = m0 + (lane & 15) < hi ? m0 + (lane & 15) : lo;
   const int y = px / wc, x = px - y * wc;
   floatx4 even = {0.f, 0.f, 0.f, 0.f}, odd = {0.f, 0.f, 0.f, 0.f};   // two chains: an MFMA waits for the one before the last
 #pragma unroll
@@ -218,6 +221,7 @@ struct SmallArgs {
   int B, c0, h, w, c1, c2, n, cr, c3, c4;       // cr: channels after the reshape (input of the first decoder conv)
   int64_t w1, b1, bn1, w2, b2, bn2, wf1, bf1, wf2, bf2, w3, b3, w4, b4;   // offsets into params
   float sigma; uint64_t seed, first_sample;
+  int bands1, bands2, bands;                      // workgroups per sample (launch 2: and block of channels) that share its pixels
   int plane2, plane_d, plane3;                    // plane strides in LDS of conv 2's input, the decoder fc's output, the last conv's input
 };
 
@@ -228,7 +232,7 @@ __global__ __launch_bounds__(NT_MAX) void k_small_conv1(SmallArgs a) {
   const int hw = a.h * a.w, K = a.c0 * 9, K4 = (K + 3) & ~3;
   float* img = lds;                               // [c0][h*w]
   float* red = img + a.c0 * hw;                   // [NT/64][2][COB]
-  const int b = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4;
+  const int b = blockIdx.x, band = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 4;
   const float* xb = a.x + (int64_t)b * a.c0 * hw;
   for (int i = threadIdx.x; i < a.c0 * hw; i += NT) img[i] = xb[i];
   for (int co0 = 0; co0 < a.c1; co0 += COB) {
@@ -239,7 +243,8 @@ __global__ __launch_bounds__(NT_MAX) void k_small_conv1(SmallArgs a) {
     for (int s = 0; s < 9; ++s) wk[s] = 4 * s + g < K ? a.params[a.w1 + (int64_t)co * K + 4 * s + g] : 0.0f;
     __syncthreads();                              // the image is there; the sums of the block before have been read
     float s1 = 0.0f, s2 = 0.0f;
-    for (int m0 = wave * 16; m0 < hw; m0 += NT / 64 * 16) {       // (hw is a multiple of 16)
+    const int t_hi = (band + 1) * (hw / 16) / a.bands1;
+    for (int m0 = (band * (hw / 16) / a.bands1 + wave) * 16; m0 < t_hi * 16; m0 += NT / 64 * 16) {       // (hw is a multiple of 16)
       const int px = m0 + (lane & 15), y = px / a.w, x = px - y * a.w;
       floatx4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -258,15 +263,15 @@ __global__ __launch_bounds__(NT_MAX) void k_small_conv1(SmallArgs a) {
         s2 = fmaf(acc[r], acc[r], s2);
       }
     }
-    store_channel_sums(s1, s2, red, a.part1 + (int64_t)b * 2 * a.c1, a.c1, co0);
+    store_channel_sums(s1, s2, red, a.part1 + ((int64_t)b * a.bands1 + band) * 2 * a.c1, a.c1, co0);
   }
 }
 
-// batch-norm + ReLU + 2x2 max-pool of a [pixels][C] conv output of one sample into a planar LDS image dst[C][hp*wp]
-__device__ __forceinline__ void bn_relu_pool_to_lds(const float* __restrict__ raw, int hc, int wc, int C, const float* scale,
+// batch-norm + ReLU + 2x2 max-pool of a [pixels][C] conv output of one sample into a planar LDS image dst[C][hp*wp], rows lo .. hi - 1 of it
+__device__ __forceinline__ void bn_relu_pool_to_lds(const float* __restrict__ raw, int wc, int lo, int hi, int C, const float* scale,
                                                     const float* shift, float* dst, int plane) {
-  const int hp = hc / 2, wp = wc / 2;
-  for (int i = threadIdx.x; i < hp * wp * C; i += NT) {
+  const int wp = wc / 2;
+  for (int i = lo * wp * C + threadIdx.x; i < hi * wp * C; i += NT) {
     const int c = i % C, q = i / C;
     const int yy = q / wp, xx = q % wp;
     const float sc = scale[c], sh = shift[c];
@@ -287,19 +292,20 @@ __global__ __launch_bounds__(NT_MAX) void k_small_conv2(SmallArgs a) {
   float* scale = wl + a.c1 * 9 * COB;             // [c1]
   float* shift = scale + a.c1;                    // [c1]
   float* red = shift + a.c1;                      // [NT/64][2][COB]
-  const int b = blockIdx.x, co0 = blockIdx.y * COB, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int b = blockIdx.x, co0 = blockIdx.y * COB, band = blockIdx.z, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int tiles = (hw2 + 15) / 16, m_lo = band * tiles / a.bands2 * 16, m_hi = min((band + 1) * tiles / a.bands2 * 16, hw2);   // pixels of the band
   stage_tile_weights(a.params + a.w2, a.c1, co0, wl);
-  bn_vectors(a.part1, a.B, a.c1, 1.0 / ((double)a.B * a.h * a.w), a.params + a.b1, a.params + a.bn1, scale, shift, tmp);
+  bn_vectors(a.part1, a.B * a.bands1, a.c1, 1.0 / ((double)a.B * a.h * a.w), a.params + a.b1, a.params + a.bn1, scale, shift, tmp);
   __syncthreads();
-  bn_relu_pool_to_lds(a.raw1 + (int64_t)b * a.h * a.w * a.c1, a.h, a.w, a.c1, scale, shift, a1, a.plane2);
+  bn_relu_pool_to_lds(a.raw1 + (int64_t)b * a.h * a.w * a.c1, a.w, max(m_lo / w2 - 1, 0), min((m_hi - 1) / w2 + 2, h2), a.c1, scale, shift, a1, a.plane2);
   __syncthreads();
   const int co = co0 + (lane & 15);
   const float bias = a.params[a.b2 + co];
   float s1 = 0.0f, s2 = 0.0f;
-  for (int m0 = wave * 16; m0 < hw2; m0 += NT / 64 * 16) {
-    const floatx4 acc = conv3_tile<false>(a1, a.plane2, a.c1, h2, w2, wl, m0, hw2);
+  for (int m0 = m_lo + wave * 16; m0 < m_hi; m0 += NT / 64 * 16) {
+    const floatx4 acc = conv3_tile<false>(a1, a.plane2, a.c1, h2, w2, wl, m0, m_lo, m_hi);
     const int px = m0 + (lane >> 4) * 4;
-    if (px < hw2) {                               // (hw2 is a multiple of 4)
+    if (px < m_hi) {                              // (m_hi is a multiple of 4)
       float* dst = a.raw2 + ((int64_t)b * hw2 + px) * a.c2 + co;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
@@ -309,13 +315,13 @@ __global__ __launch_bounds__(NT_MAX) void k_small_conv2(SmallArgs a) {
       }
     }
   }
-  store_channel_sums(s1, s2, red, a.part2 + (int64_t)b * 2 * a.c2, a.c2, co0);
+  store_channel_sums(s1, s2, red, a.part2 + ((int64_t)b * a.bands2 + band) * 2 * a.c2, a.c2, co0);
 }
 
 template <int NCO>
-__device__ __forceinline__ void last_conv(const SmallArgs& a, const float* a3, const float* wl, float* __restrict__ yb, int h2, int w2) {
+__device__ __forceinline__ void last_conv(const SmallArgs& a, const float* a3, const float* wl, float* __restrict__ yb, int h2, int w2, int y_lo, int y_hi) {
   const int q = threadIdx.x & 3;
-  for (int blk = threadIdx.x >> 2; blk < h2 * w2; blk += NT / 4) {          // (the lanes of a quad stay together)
+  for (int blk = y_lo * w2 + (threadIdx.x >> 2); blk < y_hi * w2; blk += NT / 4) {          // (the lanes of a quad stay together)
     const int by = blk / w2, bx = blk - by * w2;
     float acc[4][NCO];
 #pragma unroll
@@ -340,7 +346,12 @@ __device__ __forceinline__ void last_conv(const SmallArgs& a, const float* a3, c
 __global__ __launch_bounds__(NT_MAX) void k_small_tail(SmallArgs a) {
   extern __shared__ float lds[];
   const int h2 = a.h / 2, w2 = a.w / 2, h4 = a.h / 4, w4 = a.w / 4, hw4 = h4 * w4, hw2 = h2 * w2, hw = a.h * a.w;
-  const int F = a.c2 * hw4, FD = a.cr * hw4;      // flattened encoder output; decoder fc output
+  const int F = a.c2 * hw4;                       // flattened encoder output
+  // A workgroup has the 2x2 blocks of output pixels y_lo .. y_hi - 1 of its sample: the rows c_lo .. c_hi - 1 of the convolution before
+  // and d_lo .. d_hi - 1 of the decoder fc's output are what they read.  What lies before is the same in every band.
+  const int band = blockIdx.y, y_lo = band * h2 / a.bands, y_hi = (band + 1) * h2 / a.bands;
+  const int c_lo = max(y_lo - 1, 0), c_hi = min(y_hi + 1, h2), d_lo = max(c_lo - 1, 0) >> 1, d_hi = (min(c_hi, h2 - 1) >> 1) + 1;
+  const int n_d = (d_hi - d_lo) * w4, FD = a.cr * n_d;               // decoder fc outputs of the band: n_d pixels of every channel
   double* tmp = reinterpret_cast<double*>(lds);   // [2*256] scratch of the statistics
   float* a2 = lds + 1024;                         // [c2][hw4]   (flatten order)
   float* lat = a2 + F;                            // [n] z, then the channel output (F is a multiple of 16: read four at a time)
@@ -349,13 +360,15 @@ __global__ __launch_bounds__(NT_MAX) void k_small_tail(SmallArgs a) {
   float* dec = shift + a.c2;                      // [cr][plane_d]   (reshape order)
   float* a3 = dec + a.cr * a.plane_d;             // [c3][plane3]
   float* red = lds;                               // [NT/64 + 1], over the scratch of the statistics
-  float* wl = reinterpret_cast<float*>((reinterpret_cast<uintptr_t>(a3 + a.c3 * a.plane3) + 15) & ~(uintptr_t)15);   // weights of the decoder convs (16-byte aligned: read four at a time)
+  // weights of the decoder convs, 16-byte aligned: read four at a time.  (Rounded as an offset: a pointer made of an integer is no LDS
+  // pointer to the compiler, and its flat loads tripled the time of the convolution.)
+  float* wl = lds + ((a3 + a.c3 * a.plane3 - lds + 3) & ~(int64_t)3);
   const int b = blockIdx.x;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   stage_tile_weights(a.params + a.w3, a.cr, 0, wl);
-  bn_vectors(a.part2, a.B, a.c2, 1.0 / ((double)a.B * hw2), a.params + a.b2, a.params + a.bn2, scale, shift, tmp);
+  bn_vectors(a.part2, a.B * a.bands2, a.c2, 1.0 / ((double)a.B * hw2), a.params + a.b2, a.params + a.bn2, scale, shift, tmp);
   __syncthreads();
-  bn_relu_pool_to_lds(a.raw2 + (int64_t)b * hw2 * a.c2, h2, w2, a.c2, scale, shift, a2, hw4);
+  bn_relu_pool_to_lds(a.raw2 + (int64_t)b * hw2 * a.c2, w2, 0, h4, a.c2, scale, shift, a2, hw4);
   // weights of the last conv: over the scratch of the statistics where they fit, else over those of the conv before it once it is done
   const int nco4 = a.c4 == 1 ? 1 : 4;
   const bool w4_early = a.c3 * 9 * nco4 <= 1024 - 32;
@@ -438,8 +451,10 @@ __global__ __launch_bounds__(NT_MAX) void k_small_tail(SmallArgs a) {
     const bool vec = (a.n & 3) == 0 && (((uintptr_t)wf | (uintptr_t)lat) & 15) == 0;
     if (vec) {
       const int j0 = 4 * (threadIdx.x & 15);
-      constexpr int RB = 8;                       // outputs at a time: their loads are in flight together
-      const float inv_hw4 = 1.0f / (float)hw4;   // (o + 1/2) / hw4 rounds down to o / hw4: o < 2^14
+      constexpr int RB = 6;                       // outputs at a time: their loads are in flight together (28 x 28, four bands: 6 39.2 us in all, 8 40.4, 12 40.9)
+      const float inv_nd = 1.0f / (float)n_d;    // (o + 1/2) / n_d rounds down to o / n_d: o < 2^14
+      auto channel = [&](int o) { return (int)(((float)o + 0.5f) * inv_nd); };
+      auto row_of = [&](int o) { const int c = channel(o); return c * hw4 + d_lo * w4 + o - c * n_d; };
       for (int o0 = threadIdx.x >> 4; o0 < FD; o0 += NT / 16 * RB) {
         float acc[RB];
 #pragma unroll
@@ -448,7 +463,7 @@ __global__ __launch_bounds__(NT_MAX) void k_small_tail(SmallArgs a) {
           const float4 l4 = *reinterpret_cast<const float4*>(lat + j);
           float4 w4[RB];
 #pragma unroll
-          for (int r = 0; r < RB; ++r) w4[r] = *reinterpret_cast<const float4*>(wf + (int64_t)min(o0 + r * (NT / 16), FD - 1) * a.n + j);
+          for (int r = 0; r < RB; ++r) w4[r] = *reinterpret_cast<const float4*>(wf + (int64_t)row_of(min(o0 + r * (NT / 16), FD - 1)) * a.n + j);
 #pragma unroll
           for (int r = 0; r < RB; ++r) acc[r] = fmaf(w4[r].w, l4.w, fmaf(w4[r].z, l4.z, fmaf(w4[r].y, l4.y, fmaf(w4[r].x, l4.x, acc[r]))));
         }
@@ -456,12 +471,13 @@ __global__ __launch_bounds__(NT_MAX) void k_small_tail(SmallArgs a) {
         for (int r = 0; r < RB; ++r) {
           const int o = o0 + r * (NT / 16);
           const float t = row_sum(acc[r]);
-          const int c = (int)(((float)o + 0.5f) * inv_hw4);
-          if ((threadIdx.x & 15) == 0 && o < FD) dec[c * a.plane_d + o - c * hw4] = t + a.params[a.bf2 + o];
+          const int c = channel(o), w = row_of(o);
+          if ((threadIdx.x & 15) == 0 && o < FD) dec[c * a.plane_d + w - c * hw4] = t + a.params[a.bf2 + w];
         }
       }
     } else {
-      for (int o = threadIdx.x; o < FD; o += NT) {
+      for (int o1 = threadIdx.x; o1 < FD; o1 += NT) {
+        const int o = o1 / n_d * hw4 + d_lo * w4 + o1 % n_d;
         const float* row = wf + (int64_t)o * a.n;
         float acc = a.params[a.bf2 + o];
 #pragma unroll 16
@@ -478,13 +494,12 @@ __global__ __launch_bounds__(NT_MAX) void k_small_tail(SmallArgs a) {
     }
     __syncthreads();
     const float bias = a.params[a.b3 + co0 + (lane & 15)];
-    for (int m0 = wave * 16; m0 < hw2; m0 += NT / 64 * 16) {
-      const floatx4 acc = conv3_tile<true>(dec, a.plane_d, a.cr, h4, w4, wl, m0, hw2);
+    for (int m0 = c_lo * w2 + wave * 16; m0 < c_hi * w2; m0 += NT / 64 * 16) {
+      const floatx4 acc = conv3_tile<true>(dec, a.plane_d, a.cr, h4, w4, wl, m0, c_lo * w2, c_hi * w2);
       const int px = m0 + (lane >> 4) * 4;
-      if (px < hw2) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) a3[(co0 + (lane & 15)) * a.plane3 + px + r] = fmaxf(acc[r] + bias, 0.0f);
-      }
+      for (int r = 0; r < 4; ++r)
+        if (px + r < c_hi * w2) a3[(co0 + (lane & 15)) * a.plane3 + px + r] = fmaxf(acc[r] + bias, 0.0f);
     }
   }
   // last conv: x2 upsample of a3, 3x3 to c4 <= 4 channels at h x w, sigmoid, planar output: four lanes per 2x2 block of
@@ -495,8 +510,8 @@ __global__ __launch_bounds__(NT_MAX) void k_small_tail(SmallArgs a) {
     __syncthreads();
   }
   float* yb = a.y + (int64_t)b * a.c4 * hw;
-  if (nco4 == 1) last_conv<1>(a, a3, wl4, yb, h2, w2);
-  else last_conv<4>(a, a3, wl4, yb, h2, w2);
+  if (nco4 == 1) last_conv<1>(a, a3, wl4, yb, h2, w2, y_lo, y_hi);
+  else last_conv<4>(a, a3, wl4, yb, h2, w2, y_lo, y_hi);
 }
 
 // LDS of the three launches in bytes
@@ -575,9 +590,17 @@ int launch_fused_small(const Plan& P, const FusedSmall& f, const float* params, 
   // fit the registers of one (28 x 28, 128 / 256 / 300 / 512 samples: 50 / 68 / 122 / 135 us with sixteen, 59 / 77 / 104 / 116 us
   // with eight)
   const dim3 nt(P.batch <= 256 ? NT_MAX : NT_MAX / 2);
-  hipLaunchKernelGGL(k_small_conv1, dim3(P.batch), nt, lds1(a), s, a);
-  hipLaunchKernelGGL(k_small_conv2, dim3(P.batch, f.c2 / COB), nt, lds2(a), s, a);
-  hipLaunchKernelGGL(k_small_tail, dim3(P.batch), nt, lds3(a), s, a);
+  // Bands: as many workgroups per sample as leave at most one per compute unit.  us in all, 28 x 28, bands of the launches 1 / 1 / 1 and as
+  // chosen: 1 sample 45 -> 33, 64 46 -> 39, 128 47 -> 43; more of them than compute units lose (128 samples, 4 / 2 / 2: 56).
+  const int per = P.batch < 256 ? 256 / P.batch : 1;
+  a.bands1 = std::min(per, 4);
+  a.bands2 = std::min(std::max(per / (f.c2 / COB), 1), 4);
+  a.bands = std::min(per, a.h / 4);
+  if ((int64_t)P.batch * 2 * (a.bands1 * f.c1 + a.bands2 * f.c2) > P.max_partial_floats) a.bands1 = a.bands2 = 1;
+  a.part2 = partial + (int64_t)P.batch * a.bands1 * 2 * f.c1;
+  hipLaunchKernelGGL(k_small_conv1, dim3(P.batch, a.bands1), nt, lds1(a), s, a);
+  hipLaunchKernelGGL(k_small_conv2, dim3(P.batch, f.c2 / COB, a.bands2), nt, lds2(a), s, a);
+  hipLaunchKernelGGL(k_small_tail, dim3(P.batch, a.bands), nt, lds3(a), s, a);
   return launch_status("fused_small");
 }
 
