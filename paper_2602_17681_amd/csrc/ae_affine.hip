@@ -1012,12 +1012,11 @@ int dense_product(const void* x, const void* w, void* y, int d, int dtype, int t
   a.x = x; a.w = w; a.bias = nullptr; a.y = y;
   a.n = d; a.hc = a.wc = 1; a.cin = a.cout = d; a.k = 1; a.up = 0; a.act = ACT_NONE; a.dtype = dtype;
   a.tri = tri;
-  // Products of matrices close to the identity (the exponential and its squarings, the only ones without a triangular
-  // operand) keep the binary32 MFMA up to d = 480: a bf16 dot of 16 products is rounded at its largest one, a bias of 1.6e-7 at the
+  // Products of matrices close to the identity (the exponential and its squarings) and those of the QR calls with a triangle keep the binary32 MFMA up to d = 480: a bf16 dot of 16 products is rounded at its largest one, a bias of 1.6e-7 at the
   // diagonal that five squarings carry along coherently, while the binary32 MFMA's error grows with d.  A after compose, 2-norm
   // against float64: d = 256 4.0e-6 by parts against 3.6e-6, d = 1024 4.2e-6 against 1.4e-5, d = 2048 4.6e-6 against 3.7e-5;
   // dG 3.5e-6 against 2.5e-6, 3.4e-6 against 1.1e-5, 3.5e-6 against 3.1e-5.
-  a.f32_mfma = tri == CONV_TRI_NONE && d < 512;
+  a.f32_mfma = (tri == CONV_TRI_NONE || tri == CONV_TRI_LOWER_W_FULL || tri == CONV_TRI_UPPER_W_FULL) && d < 512;
   if (!g_timing) return launch_conv_mfma(a, s);
   AE_HIP(hipEventRecord(g_ev0, s));
   AE_TRY(launch_conv_mfma(a, s));
@@ -1090,14 +1089,20 @@ int tri_inverse(const LuSrc& q, int dp, float* mneg, float* tt, float* x, float*
 //     X2 = X X,  Y = X2 X,   B0 = I + X + X2/2,  B1 = I/3! + X/4! + X2/5!,  B2 = I/6! + X/7! + X2/8!,
 //     U = B1 + B2 Y,   Q_0 = B0 + U Y.
 // The product kernel computes y = x w^T; X is exactly skew-symmetric, so X^T = -X, X2^T = X2, Y^T = -Y and none of
-// these factors needs a transposed copy (x X = -(x X^T)).  The backward pass is the adjoint of this chain, step by
-// step, with the stored X, X2, Y, U, U^T, B2, B2^T and Q_i, Q_i^T (eight products for the polynomial, two per
-// squaring); one fused element-wise pass (k_qr_combine) forms sums, scalings and transposes.
+// these factors needs a transposed copy (x X = -(x X^T)); -X2 is what is stored, as the product leaves it.  The backward pass is the
+// adjoint of this chain, step by step, with the stored X, -X2, Y, U, U^T, B2, B2^T and Q_i, Q_i^T (seven products for the
+// polynomial, where the two of X2 = X X are one for the skew part that is asked for; two per squaring); few element-wise passes
+// form sums, scalings and transposes.  The three products with a triangle: the two whose zeros bound K walk half of it (0.66 ->
+// 0.35 ms at d = 4096).  d = 4096: 30 products and 33 passes 21.2 ms, 29 and 23 now 19.7; d = 1024 1.23 and 1.14, d = 2048 3.48 and 3.26.
 constexpr int kQrOrder = 8;
 
-// out = ident * I + alpha * y (+ beta * y2), out_t = out^T; 32 x 32 tiles.  y2, out, out_t may be null.
-__global__ __launch_bounds__(256) void k_qr_combine(const float* __restrict__ y, const float* __restrict__ y2, float alpha, float beta,
-                                                    float ident, int d, float* __restrict__ out, float* __restrict__ out_t) {
+// Element-wise passes of the exponential and its adjoint: 32 x 32 tiles, sums of up to three matrices, read once, and the result's
+// transpose through LDS.  Bound by HBM.
+
+// out = ident I + c[0] a0 + c[1] a1 + c[2] a2, out_t = out^T.  Absent matrices are null; so may be out or out_t.
+struct QrSum { const float* a[3]; float c[3]; float ident; };
+template <typename T>
+__global__ __launch_bounds__(256) void k_qr_combine(QrSum q, const T* __restrict__ first, int d, float* __restrict__ out, float* __restrict__ out_t) {
   __shared__ float tile[32][33];
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
   const int r0 = blockIdx.y * 32, c0 = blockIdx.x * 32;
@@ -1105,8 +1110,10 @@ __global__ __launch_bounds__(256) void k_qr_combine(const float* __restrict__ y,
   for (int j = 0; j < 4; ++j) {
     const int r = r0 + ty + 8 * j, c = c0 + tx;
     const int64_t i = (int64_t)r * d + c;
-    float v = alpha * y[i] + (r == c ? ident : 0.0f);
-    if (y2) v += beta * y2[i];
+    float v = q.c[0] * Store<T>::ld(first + i) + (r == c ? q.ident : 0.0f);
+#pragma unroll
+    for (int t = 1; t < 3; ++t)
+      if (q.a[t]) v += q.c[t] * q.a[t][i];
     if (out) out[i] = v;
     tile[ty + 8 * j][tx] = v;
   }
@@ -1117,18 +1124,38 @@ __global__ __launch_bounds__(256) void k_qr_combine(const float* __restrict__ y,
   }
 }
 
-// out = scale * (g - g^T): the scaled skew part (scale = 1 / (2 * 2^J) forward; the same form gives dG from dX)
-__global__ __launch_bounds__(256) void k_qr_skew(const float* __restrict__ g, float scale, int d, float* __restrict__ out) {
+// out = scale (s + sign s^T), s = a + b - c (b, c may be null): the skew (sign -1) and symmetric parts
+__global__ __launch_bounds__(256) void k_qr_skew(const float* __restrict__ a, const float* __restrict__ b, const float* __restrict__ c, float scale, float sign,
+                                                 int d, float* __restrict__ out) {
   __shared__ float tile[32][33];
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
   const int r0 = blockIdx.y * 32, c0 = blockIdx.x * 32;
+  auto at = [&](int r, int col) {
+    const int64_t i = (int64_t)r * d + col;
+    float v = a[i];
+    if (b) v += b[i];
+    if (c) v -= c[i];
+    return v;
+  };
 #pragma unroll
-  for (int j = 0; j < 4; ++j) tile[ty + 8 * j][tx] = g[(int64_t)(c0 + ty + 8 * j) * d + r0 + tx];   // g[c][r]
+  for (int j = 0; j < 4; ++j) tile[ty + 8 * j][tx] = at(c0 + ty + 8 * j, r0 + tx);
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    const int r = r0 + ty + 8 * j, c = c0 + tx;
-    out[(int64_t)r * d + c] = scale * (g[(int64_t)r * d + c] - tile[tx][ty + 8 * j]);
+    const int r = r0 + ty + 8 * j, col = c0 + tx;
+    out[(int64_t)r * d + col] = scale * (at(r, col) + sign * tile[tx][ty + 8 * j]);
+  }
+}
+
+// x = a + b/4! + c/7!,  x2 = a/2 + b/5! + c/8!: the gradients of X and X2 through B0, B1 and B2 (16-byte vectors)
+__global__ __launch_bounds__(256) void k_qr_powers_grad(const float4* __restrict__ a, const float4* __restrict__ b, const float4* __restrict__ c, int64_t n4,
+                                                        float4* __restrict__ x, float4* __restrict__ x2) {
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (int64_t)gridDim.x * 256) {
+    const float4 p = a[i], q = b[i], r = c[i];
+    auto s = [](float u, float v, float w, float cu, float cv, float cw) { return cu * u + cv * v + cw * w; };
+    constexpr float f4 = 1.0f / 24.0f, f5 = 1.0f / 120.0f, f7 = 1.0f / 5040.0f, f8 = 1.0f / 40320.0f;
+    x[i] = make_float4(s(p.x, q.x, r.x, 1.0f, f4, f7), s(p.y, q.y, r.y, 1.0f, f4, f7), s(p.z, q.z, r.z, 1.0f, f4, f7), s(p.w, q.w, r.w, 1.0f, f4, f7));
+    x2[i] = make_float4(s(p.x, q.x, r.x, 0.5f, f5, f8), s(p.y, q.y, r.y, 0.5f, f5, f8), s(p.z, q.z, r.z, 0.5f, f5, f8), s(p.w, q.w, r.w, 0.5f, f5, f8));
   }
 }
 
@@ -1155,24 +1182,18 @@ __global__ __launch_bounds__(256) void k_vec_max(const float* __restrict__ v, in
   if (threadIdx.x == 0) out[0] = sm[0];
 }
 
-// acc = (first ? 0 : acc) + alpha * y
-__global__ __launch_bounds__(256) void k_qr_axpy(float* __restrict__ acc, const float* __restrict__ y, float alpha, int first, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
-    acc[i] = (first ? 0.0f : acc[i]) + alpha * y[i];
-}
-
-// binary32 <-> storage type
-template <typename T>
-__global__ __launch_bounds__(256) void k_to_f32(const T* __restrict__ in, float* __restrict__ out, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) out[i] = Store<T>::ld(in + i);
-}
+// binary32 -> storage type
 template <typename T>
 __global__ __launch_bounds__(256) void k_from_f32(const float* __restrict__ in, T* __restrict__ out, int64_t n) {
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) Store<T>::st(out + i, in[i]);
 }
 
-void qr_combine(const float* y, const float* y2, float alpha, float beta, float ident, int d, float* out, float* out_t, hipStream_t s) {
-  hipLaunchKernelGGL(k_qr_combine, dim3(d / 32, d / 32), dim3(256), 0, s, y, y2, alpha, beta, ident, d, out, out_t);
+void qr_combine(const QrSum& q, int d, float* out, float* out_t, hipStream_t s) {
+  hipLaunchKernelGGL((k_qr_combine<float>), dim3(d / 32, d / 32), dim3(256), 0, s, q, q.a[0], d, out, out_t);
+}
+void qr_transpose(const float* y, int d, float* out_t, hipStream_t s) { qr_combine(QrSum{{y, nullptr, nullptr}, {1.0f, 0.0f, 0.0f}, 0.0f}, d, nullptr, out_t, s); }
+void qr_skew(const float* a, const float* b, const float* c, float scale, float sign, int d, float* out, hipStream_t s) {
+  hipLaunchKernelGGL(k_qr_skew, dim3(d / 32, d / 32), dim3(256), 0, s, a, b, c, scale, sign, d, out);
 }
 
 // workspace of the QR calls: binary32 d x d matrices
@@ -1180,7 +1201,7 @@ struct QrSlots {
   float* base; int64_t dd; int J;
   float* x() const { return base; }                                  // S / 2^J
   float* h(int k) const { return base + (int64_t)(k - 1) * dd; }     // slots 1 .. kQrOrder-1 (k = 2 .. kQrOrder):
-  float* x2() const { return h(2); }                                 //   X X (symmetric)
+  float* nx2() const { return h(2); }                                //   -X X (symmetric)
   float* y3() const { return h(3); }                                 //   X^3 (skew-symmetric)
   float* u() const { return h(4); }                                  //   U = B1 + B2 Y
   float* ut() const { return h(5); }
@@ -1375,7 +1396,7 @@ extern "C" int model_qr_squarings(const float* g, int64_t d, void* workspace, in
   const int n = (int)d;
   float* skew = reinterpret_cast<float*>(workspace);          // S = (G - G^T) / 2
   float* rowsum = skew + d * d;                               // then d row sums and the maximum
-  hipLaunchKernelGGL(k_qr_skew, dim3(n / 32, n / 32), dim3(256), 0, s, g, 0.5f, n, skew);
+  qr_skew(g, nullptr, nullptr, 0.5f, -1.0f, n, skew, s);
   hipLaunchKernelGGL(k_row_abs_sum, dim3((n + 3) / 4), dim3(256), 0, s, (const float*)skew, n, rowsum);
   hipLaunchKernelGGL(k_vec_max, dim3(1), dim3(256), 0, s, (const float*)rowsum, n, rowsum + d);
   AE_TRY(launch_status("qr_squarings"));
@@ -1400,36 +1421,30 @@ extern "C" int model_qr_compose(const float* g, const float* rp, const float* lo
   hipStream_t s = (hipStream_t)stream;
   const int n = (int)d, J = squarings;
   const QrSlots w{reinterpret_cast<float*>(workspace), d * d, J};
-  const dim3 tgrid(n / 32, n / 32);
-  hipLaunchKernelGGL(k_qr_skew, tgrid, dim3(256), 0, s, g, 0.5f / (float)(1 << J), n, w.x());
+  qr_skew(g, nullptr, nullptr, 0.5f / (float)(1 << J), -1.0f, n, w.x(), s);
   float* y = w.tmp(1);
-  float* b = w.tmp(0);
   // (dense_product(x, w, out) = x w^T; with w skew-symmetric that is -(x w))
-  AE_TRY(dense_product(w.x(), w.x(), y, n, AE_F32, CONV_TRI_NONE, s));                      // X X^T = -X2
-  qr_combine(y, nullptr, -1.0f, 0.0f, 0.0f, n, w.x2(), nullptr, s);
-  AE_TRY(dense_product(w.x2(), w.x(), y, n, AE_F32, CONV_TRI_NONE, s));                     // X2 X^T = -Y
-  qr_combine(y, nullptr, -1.0f, 0.0f, 0.0f, n, w.y3(), nullptr, s);
-  qr_combine(w.x(), w.x2(), 1.0f / 5040.0f, 1.0f / 40320.0f, 1.0f / 720.0f, n, w.b2(), w.b2t(), s);
+  AE_TRY(dense_product(w.x(), w.x(), w.nx2(), n, AE_F32, CONV_TRI_NONE, s));                // X X^T = -X2
+  AE_TRY(dense_product(w.nx2(), w.x(), w.y3(), n, AE_F32, CONV_TRI_NONE, s));               // -X2 X^T = Y
+  qr_combine(QrSum{{w.x(), w.nx2(), nullptr}, {1.0f / 5040.0f, -1.0f / 40320.0f, 0.0f}, 1.0f / 720.0f}, n, w.b2(), w.b2t(), s);
   AE_TRY(launch_status("qr_powers"));
   AE_TRY(dense_product(w.b2(), w.y3(), y, n, AE_F32, CONV_TRI_NONE, s));                    // B2 Y^T = -B2 Y
-  qr_combine(w.x(), w.x2(), 1.0f / 24.0f, 1.0f / 120.0f, 1.0f / 6.0f, n, b, nullptr, s);    // B1
-  qr_combine(y, b, -1.0f, 1.0f, 0.0f, n, w.u(), w.ut(), s);                                 // U = B1 + B2 Y
+  qr_combine(QrSum{{y, w.x(), w.nx2()}, {-1.0f, 1.0f / 24.0f, -1.0f / 120.0f}, 1.0f / 6.0f}, n, w.u(), w.ut(), s);       // U = B1 + B2 Y
   AE_TRY(launch_status("qr_u"));
   AE_TRY(dense_product(w.u(), w.y3(), y, n, AE_F32, CONV_TRI_NONE, s));                     // U Y^T = -U Y
-  qr_combine(w.x(), w.x2(), 1.0f, 0.5f, 1.0f, n, b, nullptr, s);                            // B0
-  qr_combine(y, b, -1.0f, 1.0f, 0.0f, n, w.q(0), w.qt(0), s);                               // Q_0 = B0 + U Y
+  qr_combine(QrSum{{y, w.x(), w.nx2()}, {-1.0f, 1.0f, -0.5f}, 1.0f}, n, w.q(0), w.qt(0), s);   // Q_0 = B0 + U Y
   AE_TRY(launch_status("qr_polynomial"));
   for (int i = 0; i < J; ++i) {
     AE_TRY(dense_product(w.q(i), w.qt(i), w.q(i + 1), n, AE_F32, CONV_TRI_NONE, s));        // Q_{i+1} = Q_i Q_i
-    qr_combine(w.q(i + 1), nullptr, 1.0f, 0.0f, 0.0f, n, nullptr, w.qt(i + 1), s);
+    qr_transpose(w.q(i + 1), n, w.qt(i + 1), s);
     AE_TRY(launch_status("qr_square"));
   }
   float* rdt = w.tmp(2);                                                                     // (R + diag s)^T
   LuSrc q{nullptr, rp, log_s, sign_s, nullptr, nullptr, n};
   launch_build_transposed<float, LU_UD>(q, rdt, s);
   AE_TRY(launch_status("qr_build"));
-  if (dtype == AE_F32) return dense_product(w.q(J), rdt, a_out, n, AE_F32, CONV_TRI_NONE, s);
-  AE_TRY(dense_product(w.q(J), rdt, y, n, AE_F32, CONV_TRI_NONE, s));
+  if (dtype == AE_F32) return dense_product(w.q(J), rdt, a_out, n, AE_F32, CONV_TRI_LOWER_W_FULL, s);
+  AE_TRY(dense_product(w.q(J), rdt, y, n, AE_F32, CONV_TRI_LOWER_W_FULL, s));
   hipLaunchKernelGGL((k_from_f32<bf16_t>), dim3(lu_grid(d * d)), dim3(256), 0, s, (const float*)y, (bf16_t*)a_out, d * d);
   return launch_status("qr_compose");
 }
@@ -1448,9 +1463,10 @@ extern "C" int model_qr_backward(const void* g_a, const float* rp, const float* 
   const QrSlots w{reinterpret_cast<float*>(workspace), dd, J};
   float *t0 = w.tmp(0), *t1 = w.tmp(1), *t2 = w.tmp(2), *t3 = w.tmp(3), *t4 = w.tmp(4), *t5 = w.tmp(5);
   // dA in binary32 (t0) and its transpose (t1)
-  if (dtype == AE_BF16) hipLaunchKernelGGL((k_to_f32<bf16_t>), dim3(lu_grid(dd)), dim3(256), 0, s, (const bf16_t*)g_a, t0, dd);
-  else hipLaunchKernelGGL((k_to_f32<float>), dim3(lu_grid(dd)), dim3(256), 0, s, (const float*)g_a, t0, dd);
-  qr_combine(t0, nullptr, 1.0f, 0.0f, 0.0f, n, nullptr, t1, s);
+  const QrSum one{{nullptr, nullptr, nullptr}, {1.0f, 0.0f, 0.0f}, 0.0f};
+  const dim3 tgrid(n / 32, n / 32);
+  if (dtype == AE_BF16) hipLaunchKernelGGL((k_qr_combine<bf16_t>), tgrid, dim3(256), 0, s, one, (const bf16_t*)g_a, n, t0, t1);
+  else hipLaunchKernelGGL((k_qr_combine<float>), tgrid, dim3(256), 0, s, one, (const float*)g_a, n, t0, t1);
   AE_TRY(launch_status("qr_backward_in"));
   // d(R + diag s) = Q^T dA: strictly upper part and diagonal
   AE_TRY(dense_product(w.qt(J), t1, t2, n, AE_F32, CONV_TRI_NONE, s));
@@ -1459,47 +1475,37 @@ extern "C" int model_qr_backward(const void* g_a, const float* rp, const float* 
   LuSrc q{nullptr, rp, log_s, sign_s, nullptr, nullptr, n};
   launch_build_rows<float, LU_UD>(q, t2, s);
   AE_TRY(launch_status("qr_build"));
-  AE_TRY(dense_product(t0, t2, t3, n, AE_F32, CONV_TRI_NONE, s));
-  qr_combine(t3, nullptr, 1.0f, 0.0f, 0.0f, n, nullptr, t4, s);
+  AE_TRY(dense_product(t0, t2, t3, n, AE_F32, CONV_TRI_UPPER_W_FULL, s));
+  qr_transpose(t3, n, t4, s);
   float *cur = t3, *cur_t = t4;
   // squarings in reverse: dQ_i = dQ_{i+1} Q_i^T + Q_i^T dQ_{i+1}
   for (int i = J - 1; i >= 0; --i) {
     AE_TRY(dense_product(cur, w.q(i), t0, n, AE_F32, CONV_TRI_NONE, s));
     AE_TRY(dense_product(w.qt(i), cur_t, t1, n, AE_F32, CONV_TRI_NONE, s));
-    qr_combine(t0, t1, 1.0f, 1.0f, 0.0f, n, cur, cur_t, s);
+    qr_combine(QrSum{{t0, t1, nullptr}, {1.0f, 1.0f, 0.0f}, 0.0f}, n, cur, cur_t, s);
     AE_TRY(launch_status("qr_backward_square"));
   }
   // the polynomial in reverse; A = dQ_0, B = its transpose, C .. G free
   float *A = cur, *B = cur_t, *C = t0, *D = t1, *E = t2, *F = w.spare(), *G = t5;
-  const dim3 eg(lu_grid(dd)), eb(256);
   AE_TRY(dense_product(A, w.y3(), C, n, AE_F32, CONV_TRI_NONE, s));                         // dU = dQ_0 Y^T
-  qr_combine(C, nullptr, 1.0f, 0.0f, 0.0f, n, nullptr, D, s);                               // dU^T
+  qr_transpose(C, n, D, s);                                                                 // dU^T
   AE_TRY(dense_product(w.ut(), B, E, n, AE_F32, CONV_TRI_NONE, s));                         // U^T dQ_0        (Q_0 = B0 + U Y)
   AE_TRY(dense_product(w.b2t(), D, F, n, AE_F32, CONV_TRI_NONE, s));                        // B2^T dU         (U = B1 + B2 Y)
-  qr_combine(E, F, 1.0f, 1.0f, 0.0f, n, E, D, s);                                           // dY = their sum (E) and dY^T (D)
+  qr_combine(QrSum{{E, F, nullptr}, {1.0f, 1.0f, 0.0f}, 0.0f}, n, E, D, s);                 // dY = their sum (E) and dY^T (D)
   AE_TRY(launch_status("qr_backward_dy"));
   AE_TRY(dense_product(C, w.y3(), F, n, AE_F32, CONV_TRI_NONE, s));                         // dB2 = dU Y^T
   // dX  = dB0 + dB1/4! + dB2/7!  + ...,   dX2 = dB0/2 + dB1/5! + dB2/8! + ...   with dB0 = dQ_0, dB1 = dU
-  hipLaunchKernelGGL(k_qr_axpy, eg, eb, 0, s, G, (const float*)A, 1.0f, 1, dd);
-  hipLaunchKernelGGL(k_qr_axpy, eg, eb, 0, s, G, (const float*)C, 1.0f / 24.0f, 0, dd);
-  hipLaunchKernelGGL(k_qr_axpy, eg, eb, 0, s, G, (const float*)F, 1.0f / 5040.0f, 0, dd);
-  hipLaunchKernelGGL(k_qr_axpy, eg, eb, 0, s, B, (const float*)A, 0.5f, 1, dd);
-  hipLaunchKernelGGL(k_qr_axpy, eg, eb, 0, s, B, (const float*)C, 1.0f / 120.0f, 0, dd);
-  hipLaunchKernelGGL(k_qr_axpy, eg, eb, 0, s, B, (const float*)F, 1.0f / 40320.0f, 0, dd);
+  hipLaunchKernelGGL(k_qr_powers_grad, dim3(lu_grid(dd)), dim3(256), 0, s, (const float4*)A, (const float4*)C, (const float4*)F, dd / 4, (float4*)G, (float4*)B);
   AE_TRY(launch_status("qr_backward_db"));
   AE_TRY(dense_product(E, w.x(), A, n, AE_F32, CONV_TRI_NONE, s));                          // Y = X2 X:  dX2 += dY X^T
-  hipLaunchKernelGGL(k_qr_axpy, eg, eb, 0, s, B, (const float*)A, 1.0f, 0, dd);
-  AE_TRY(dense_product(w.x2(), D, C, n, AE_F32, CONV_TRI_NONE, s));                         //            dX  += X2^T dY = X2 dY
-  hipLaunchKernelGGL(k_qr_axpy, eg, eb, 0, s, G, (const float*)C, 1.0f, 0, dd);
-  qr_combine(B, nullptr, 1.0f, 0.0f, 0.0f, n, nullptr, F, s);                               // dX2^T
+  AE_TRY(dense_product(w.nx2(), D, C, n, AE_F32, CONV_TRI_NONE, s));                        //            dX  += X2^T dY = X2 dY = -C
+  // X2 = X X:  dX += dX2 X^T + X^T dX2.  Only the skew part of dX is asked for, and that of these two terms is the skew part of
+  // (dX2 + dX2^T) X^T:  X^T = -X, so the transpose of the second is -dX2^T X^T, and skew parts of a matrix and of its negative transpose agree
+  qr_skew(B, A, nullptr, 1.0f, 1.0f, n, F, s);
   AE_TRY(launch_status("qr_backward_dx2"));
-  AE_TRY(dense_product(B, w.x(), A, n, AE_F32, CONV_TRI_NONE, s));                          // X2 = X X:  dX += dX2 X^T
-  hipLaunchKernelGGL(k_qr_axpy, eg, eb, 0, s, G, (const float*)A, 1.0f, 0, dd);
-  AE_TRY(dense_product(w.x(), F, C, n, AE_F32, CONV_TRI_NONE, s));                          //            dX += X^T dX2 = -(X dX2)
-  hipLaunchKernelGGL(k_qr_axpy, eg, eb, 0, s, G, (const float*)C, -1.0f, 0, dd);
-  float* dx = G;
+  AE_TRY(dense_product(F, w.x(), A, n, AE_F32, CONV_TRI_NONE, s));
   // X = (G - G^T) / (2 * 2^J):  dG = (dX - dX^T) / (2 * 2^J)
-  hipLaunchKernelGGL(k_qr_skew, dim3(n / 32, n / 32), dim3(256), 0, s, (const float*)dx, 0.5f / (float)(1 << J), n, d_g);
+  qr_skew(G, A, C, 0.5f / (float)(1 << J), -1.0f, n, d_g, s);
   return launch_status("qr_backward");
 }
 

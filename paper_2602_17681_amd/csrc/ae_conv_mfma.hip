@@ -74,6 +74,8 @@ struct IgemmParams {
   //   3: w[n][k] = 0 for k < n, wanted outputs n < m: K starts at the tile's first column; tiles above the diagonal return
   //   4: x[m][k] = 0 for k < m and w[n][k] = 0 for k < n (upper times lower): K starts at max(first row, first column)
   //   5: x[m][k] = 0 for k < m: K starts at the tile's first row
+  //   6: w[n][k] = 0 for k > n: K ends at the tile's last column
+  //   7: w[n][k] = 0 for k < n: K starts at the tile's first column
   // Blocked triangular inverse, all pairs of neighbouring tri_b x tri_b diagonal blocks in one launch (tile sizes divide
   // tri_b): only the tiles of one off-diagonal block per pair are computed, over the K range of one block:
   //   8: tile rows in an even block r, columns in block r+1, K = block r, x upper triangular: from the tile's first row on;
@@ -649,10 +651,11 @@ __device__ __forceinline__ IgemmTileId igemm_tile_id(const IgemmParams& p) {
   const int gm = min(p.tiles_mn / p.tiles_n - grp * kGroupM, kGroupM);
   t.n = in_grp / gm;
   t.m = grp * kGroupM + in_grp % gm;
-  if (p.tri == 3) {                             // K range [column, K): walk column by column, the longest first
+  if (p.tri == 3 || p.tri == 6 || p.tri == 7) { // K range [column, K) or [0, column]: walk column by column, the longest first
     const int tiles_m = p.tiles_mn / p.tiles_n;
     t.n = lb / tiles_m;
     t.m = lb - t.n * tiles_m;
+    if (p.tri == 6) t.n = p.tiles_n - 1 - t.n;
   }
   if (p.tri == 4 && p.tiles_mn == p.tiles_n * p.tiles_n) {
     // K range [max(row, column), K): on a square tile grid walk the L-shaped shells max(tile row, tile column) = 0, 1, ...
@@ -695,6 +698,8 @@ __device__ __forceinline__ bool igemm_k_range(const IgemmParams& p, int64_t m0, 
   else if (p.tri == 3) { if ((int64_t)n0 >= m0 + BM) return false; k_lo = n0; }
   else if (p.tri == 4) k_lo = (int)max(m0, (int64_t)n0);
   else if (p.tri == 5) k_lo = (int)m0;
+  else if (p.tri == 6) k_hi = min(p.K, n0 + BN);
+  else if (p.tri == 7) k_lo = n0;
   else if (p.tri >= 8) {
     const int rb = (int)(m0 / p.tri_b), cb = n0 / p.tri_b;
     if (p.tri == 9 ? !((rb & 1) == 1 && cb == rb - 1) : !((rb & 1) == 0 && cb == rb + 1)) return false;
@@ -1945,7 +1950,7 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
   if (a0.tri >= 8 && (a0.tri > 9 || a.dtype != AE_F32 || a0.tri_b < 128 || a0.tri_b % 128 != 0 || a.n % (2 * a0.tri_b) != 0 ||
                       a0.tri_d < 0 || a0.tri_d > a.n || a0.tri_d % 128 != 0))
     return fail(AE_EINVAL, "conv_mfma: bad block size for the blocked triangular inverse");
-  if (a0.tri != 0 && (a0.tri < 0 || (a0.tri > 5 && a0.tri < 8) || a0.tri > 9 || a.k != 1 || a.hc != 1 || a.wc != 1 || a.up != 0 || a.n != a.cout || a.cin != a.cout ||
+  if (a0.tri != 0 && (a0.tri < 0 || a0.tri > 9 || a.k != 1 || a.hc != 1 || a.wc != 1 || a.up != 0 || a.n != a.cout || a.cin != a.cout ||
                       a0.epi != CONV_EPI_NONE || a.partial))
     return fail(AE_EINVAL, "conv_mfma: triangular K ranges are for square dense products only");
   if (conv3_patch_usable(a0)) {
@@ -2023,7 +2028,8 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
     const bool choice = dense && interior && t.bn == 128 && a0.epi == CONV_EPI_NONE;
     const double c128 = rounds(n128, 512, 0.63, 1.0), c64 = rounds(2 * n128, 512, 0.45, 0.69);
     // (not with column sums: the caller counts one block of them per 128 rows)
-    const double tall = a0.tri == 0 && !p.partial && p.M % 256 == 0 && p.K >= 1024 ? rounds(n128 / 2, 256, 0.89, 0.89) : 1e30;
+    const bool whole = a0.tri == 0 || a0.tri == 6 || a0.tri == 7;      // every output, K ranges that make rounds of equal sums: as without them
+    const double tall = whole && !p.partial && p.M % 256 == 0 && p.K >= 1024 ? rounds(n128 / 2, 256, 0.89, 0.89) : 1e30;
     if (choice && tall < c128 && tall < c64) {
       p.tiles_mn /= 2;
       hipLaunchKernelGGL((k_gemm_split<256, 128, 4, 2, true>), dim3(grid.x / 2), dim3(512), 0, s, p);
@@ -2031,7 +2037,7 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
       p.tiles_n *= 2;
       p.tiles_mn *= 4;
       hipLaunchKernelGGL((k_gemm_split<64, 64, 2, 2, true>), dim3(grid.x * 4), dim3(256), 0, s, p);
-    } else if (choice && (a0.tri != 0 ? n128 <= 256 : c64 < c128)) {
+    } else if (choice && (!whole ? n128 <= 256 : c64 < c128)) {
       p.tiles_n *= 2;
       p.tiles_mn *= 2;
       hipLaunchKernelGGL((k_gemm_split<128, 64, 4, 1, true>), dim3(grid.x * 2), dim3(256), 0, s, p);

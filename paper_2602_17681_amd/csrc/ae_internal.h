@@ -208,6 +208,7 @@ struct ConvArgs {
   //   CONV_TRI_UPPER_W      w upper triangular (w[n][k] = 0 for k < n); wanted: the outputs below the diagonal.
   //   CONV_TRI_UPPER_LOWER  x upper triangular, w^T lower triangular (w[n][k] = 0 for k < n): every output wanted;
   //   CONV_TRI_UPPER_X_FULL x upper triangular; every output wanted;
+  //   CONV_TRI_LOWER_W_FULL, CONV_TRI_UPPER_W_FULL  w[n][k] = 0 for k > n, for k < n; every output wanted;
   //   CONV_TRI_PAIR_*       one level of a blocked triangular inverse: all pairs of neighbouring tri_b x tri_b diagonal
   //                         blocks (r even, r+1) in one launch; only the tiles of the named off-diagonal block of
   //                         each pair are computed, over the K range of the named block:
@@ -222,7 +223,7 @@ struct ConvArgs {
   int tri_d = 0;
   bool f32_mfma = false;           // dense binary32 products: not through bf16 parts
 };
-enum { CONV_TRI_NONE = 0, CONV_TRI_LOWER_UPPER = 1, CONV_TRI_UPPER_X = 2, CONV_TRI_UPPER_W = 3, CONV_TRI_UPPER_LOWER = 4, CONV_TRI_UPPER_X_FULL = 5,
+enum { CONV_TRI_NONE = 0, CONV_TRI_LOWER_UPPER = 1, CONV_TRI_UPPER_X = 2, CONV_TRI_UPPER_W = 3, CONV_TRI_UPPER_LOWER = 4, CONV_TRI_UPPER_X_FULL = 5, CONV_TRI_LOWER_W_FULL = 6, CONV_TRI_UPPER_W_FULL = 7,
        CONV_TRI_PAIR_UPPER_K0 = 8, CONV_TRI_PAIR_LOWER_K1 = 9 };
 enum { CONV_PLAIN = 0, CONV_UP_PHASES = 1, CONV_UP_DGRAD = 2 };
 enum { CONV_EPI_NONE = 0, CONV_EPI_MXQ = 1, CONV_EPI_RESID = 2 };
