@@ -255,37 +255,14 @@ void launch_build(const LuSrc& q, void* out, hipStream_t s) {
 }
 
 // ---- inverse of the parametrised matrix ---------------------------------------------------------------------
-// A^-1 = (U + diag s)^-1 L^-1 P^T.  Both triangular inverses use the same blocked recursion on a LOWER triangular
-// matrix M (L itself; (U + diag s)^T for the upper factor): 128 x 128 diagonal blocks are inverted by substitution,
-// then neighbouring inverses X11, X22 of blocks of size b merge into the inverse of the 2b x 2b block,
-//     [[X11, 0], [-X22 M21 X11, X22]].
+// A^-1 = (U + diag s)^-1 L^-1 P^T.  Both triangular inverses are blocked recursions: 128 x 128 diagonal blocks are inverted by
+// substitution, then neighbouring inverses X11, X22 of blocks of size b merge into the inverse of the 2b x 2b block,
+//     L:  [[X11, 0], [-X22 L21 X11, X22]],      U:  [[X11, -X11 U12 X22], [0, X22]].
 // X and X^T live as full d x d binary32 matrices whose diagonal blocks come first and which fill level by level (the other
-// triangle is never written and never read: every product starts or ends its K range at the tile's own rows); one level is
-// two launches of the matrix-core kernel over ALL pairs at once (K-range modes CONV_TRI_PAIR_*) and a transposing copy:
-//     T' = -(M21 X11)^T  into the upper blocks of a scratch matrix,   X21 = X22 T'^T  in place into X,
-//     X21^T  into X^T.
-
-// mneg = -M in the 32 x 32 tiles below the 128 x 128 diagonal blocks, the only ones the merges read.  Of M = L (WHICH 0) or
-// (U + diag s)^T (1, through LDS: both sides of the transpose move whole rows) these tiles hold nothing but parameters, and
-// zeros beyond row d, where an identity block pads the matrix to the working size of the recursion.
-template <int WHICH>
-__global__ __launch_bounds__(256) void k_tri_prepare(LuSrc q, int dp, float* __restrict__ mneg) {
-  __shared__ float tile[32][33];
-  const int r0 = blockIdx.y * 32, c0 = blockIdx.x * 32;
-  if ((c0 >> 7) >= (r0 >> 7)) return;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  if (WHICH == 1) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) tile[ty + 8 * j][tx] = r0 + tx < q.d ? q.up[(int64_t)(c0 + ty + 8 * j) * q.d + r0 + tx] : 0.0f;
-    __syncthreads();
-  }
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int r = r0 + ty + 8 * j, c = c0 + tx;
-    const float v = WHICH == 0 ? (r < q.d ? q.lp[(int64_t)r * q.d + c] : 0.0f) : tile[tx][ty + 8 * j];
-    mneg[(int64_t)r * dp + c] = -v;
-  }
-}
+// triangle is never written and never read: every product starts or ends its K range at the tile's own rows).  The product kernel
+// computes x w^T, and the parameters themselves are what it wants as w, so that a level is two launches over ALL pairs of both factors:
+//     L:  T = X11^T L21^T = (L21 X11)^T,  X21 = -X22 T^T;      U:  T = X22^T U12^T = (U12 X22)^T,  X12 = -X11 T^T;
+// the second writes its block into X and the transpose into X^T.
 
 // ---- many small matrices at once (the per-block transformations: one d x d parameter set per transformer block, d the
 // head dimension) --------------------------------------------------------------------------------------------------
@@ -859,14 +836,15 @@ __global__ __launch_bounds__(512) void k_lu_small_solve(const float* __restrict_
   }
 }
 
-// X_bb = M_bb^-1 for every 128 x 128 diagonal block b of M = L (WHICH 0) or (U + diag s)^T (1) (one workgroup of 256 threads
-// each), inverted in place in LDS as above; the block and its transpose are written into the full matrices x and xt.
-template <int WHICH>
-__global__ __launch_bounds__(256) void k_tri_diag_inverse(LuSrc q, int dp, float* __restrict__ x, float* __restrict__ xt) {
+// X_bb = M_bb^-1 for every 128 x 128 diagonal block b of M = L (which 0) or (U + diag s)^T (1) (one workgroup of 256 threads
+// each; blockIdx.y + first: which), inverted in place in LDS as above; the block and its transpose are written into the full
+// matrices lo (lower triangular) and hi of the factor.
+struct TriOut { float* lo; float* hi; };
+__global__ __launch_bounds__(256) void k_tri_diag_inverse(LuSrc q, int dp, int first, TriOut l, TriOut u) {
   __shared__ float pk[128 * 129];
   __shared__ float tb[64 * 68];
-  const int tid = threadIdx.x, o = blockIdx.x * 128;
-  const float* src = WHICH == 0 ? q.lp : q.up;
+  const int tid = threadIdx.x, o = blockIdx.x * 128, which = first + (int)blockIdx.y;
+  const float* src = which == 0 ? q.lp : q.up;
   const bool vec = small_vec(src, q.d);
 #pragma unroll
   for (int b0 = 0; b0 < 16; b0 += 8) {                   // 128 x 32 chunks of four columns, eight per thread in flight
@@ -874,7 +852,7 @@ __global__ __launch_bounds__(256) void k_tri_diag_inverse(LuSrc q, int dp, float
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
       const int e = tid + (b0 + t) * 256, i = e >> 5, c = (e & 31) * 4;
-      const bool in = o + i < q.d && o + c < q.d && (WHICH == 0 ? c < i : c + 3 > i);
+      const bool in = o + i < q.d && o + c < q.d && (which == 0 ? c < i : c + 3 > i);
       v[t] = in ? small_load4<float>(src, q.d, o + i, o + c, vec) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     }
 #pragma unroll
@@ -886,27 +864,36 @@ __global__ __launch_bounds__(256) void k_tri_diag_inverse(LuSrc q, int dp, float
         if (c + s != i) pk[i * 129 + c + s] = w[s];
     }
   }
-  if (tid < 128) pk[tid * 129 + tid] = WHICH == 0 || o + tid >= q.d ? 1.0f : q.sign[o + tid] * expf(q.log_s[o + tid]);
+  if (tid < 128) pk[tid * 129 + tid] = which == 0 || o + tid >= q.d ? 1.0f : q.sign[o + tid] * expf(q.log_s[o + tid]);
   __syncthreads();
-  const SmallTri m = WHICH == 0 ? SmallTri{pk, 129, 1} : SmallTri{pk, 1, 129};
+  const SmallTri m = which == 0 ? SmallTri{pk, 129, 1} : SmallTri{pk, 1, 129};
   small_tri_diag(m, tid);
   small_tri_merge16(m, tb, tid);
   small_tri_merge<32>(m, tb, tid);
   small_tri_merge<64>(m, tb, tid);
+  const TriOut out = which == 0 ? l : u;
   for (int e = tid; e < 128 * 128; e += 256) {
     const int i = e >> 7, j = e & 127;
-    x[(int64_t)(o + i) * dp + o + j] = j <= i ? m.at(i, j) : 0.0f;
-    xt[(int64_t)(o + i) * dp + o + j] = i <= j ? m.at(j, i) : 0.0f;
+    out.lo[(int64_t)(o + i) * dp + o + j] = j <= i ? m.at(i, j) : 0.0f;
+    out.hi[(int64_t)(o + i) * dp + o + j] = i <= j ? m.at(j, i) : 0.0f;
+    if (blockIdx.x & 1) out.hi[(int64_t)(o + i) * dp + o - 128 + j] = 0.0f;   // 256 x 256 diagonal blocks hold zeros below the diagonal (launch_tri_last)
   }
 }
 
-// out[r][c] = z[r][perm[c]] in the storage type (z P^T); z is d x d, d % 8 == 0.  A row goes through LDS, so that global memory sees
+// out[r][c] = z[r][perm[c]] in the storage type (z P^T), z + z2 in rows and columns below `split`; z is d x d, d % 8 == 0.  A row goes through LDS, so that global memory sees
 // whole rows on both sides (gathered straight from memory, d = 4096 took 81 us; this way 18).
 template <typename T>
-__global__ __launch_bounds__(256) void k_lu_inverse_out(const float* __restrict__ z, const int* __restrict__ perm, int d, T* __restrict__ out) {
+__global__ __launch_bounds__(256) void k_lu_inverse_out(const float* __restrict__ z, const float* __restrict__ z2, int split, const int* __restrict__ perm, int d, T* __restrict__ out) {
   extern __shared__ __attribute__((aligned(16))) float row[];
   for (int r = blockIdx.x; r < d; r += gridDim.x) {
-    for (int c = 4 * threadIdx.x; c < d; c += 1024) *reinterpret_cast<float4*>(row + c) = *reinterpret_cast<const float4*>(z + (int64_t)r * d + c);
+    for (int c = 4 * threadIdx.x; c < d; c += 1024) {
+      float4 v = *reinterpret_cast<const float4*>(z + (int64_t)r * d + c);
+      if (r < split && c < split) {
+        const float4 w = *reinterpret_cast<const float4*>(z2 + (int64_t)r * d + c);
+        v = make_float4(v.x + w.x, v.y + w.y, v.z + w.z, v.w + w.w);
+      }
+      *reinterpret_cast<float4*>(row + c) = v;
+    }
     __syncthreads();
     for (int c0 = 8 * threadIdx.x; c0 < d; c0 += 2048) {
       float v[8];
@@ -1035,19 +1022,6 @@ unsigned lu_grid(int64_t items) {
   return (unsigned)(g < 4096 ? (g < 1 ? 1 : g) : 4096);
 }
 
-// xt[c][r] = x[r][c] over the lower off-diagonal block (rows in block 2p+1, columns in block 2p, blocks of b) of every
-// pair p = blockIdx.z: 32 x 32 tiles through LDS
-__global__ __launch_bounds__(256) void k_tri_pair_transpose(const float* __restrict__ x, float* __restrict__ xt, int dp, int b) {
-  __shared__ float tile[32][33];
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  const int r0 = (2 * (int)blockIdx.z + 1) * b + (int)blockIdx.y * 32, c0 = 2 * (int)blockIdx.z * b + (int)blockIdx.x * 32;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) tile[ty + 8 * j][tx] = x[(int64_t)(r0 + ty + 8 * j) * dp + c0 + tx];
-  __syncthreads();
-#pragma unroll
-  for (int j = 0; j < 4; ++j) xt[(int64_t)(c0 + ty + 8 * j) * dp + r0 + tx] = tile[tx][ty + 8 * j];
-}
-
 // 128 times the smallest power of two that reaches d: the working size of the recursion
 int64_t tri_padded_size(int64_t d) {
   int64_t dp = 128;
@@ -1055,29 +1029,18 @@ int64_t tri_padded_size(int64_t d) {
   return dp;
 }
 
-// the blocked recursion above for one lower triangular matrix, padded with an identity block to the working size
-// d = dp (128 times a power of two, at least q.d): x = M^-1 and xt = its transpose ([dp][dp] binary32 each);
-// mneg and tt are scratch of the same size
-template <int WHICH>
-int tri_inverse(const LuSrc& q, int dp, float* mneg, float* tt, float* x, float* xt, hipStream_t s) {
-  const int d = dp;
-  hipLaunchKernelGGL((k_tri_prepare<WHICH>), dim3(d / 32, d / 32), dim3(256), 0, s, q, d, mneg);
-  hipLaunchKernelGGL((k_tri_diag_inverse<WHICH>), dim3(d / 128), dim3(256), 0, s, q, d, x, xt);
+// The recursion above for L (first 0, count 2 for both) or U + diag s alone (first 1), padded with an identity block to the working size
+// dp (128 times a power of two, at least q.d): lo and hi of a factor are its inverse and the inverse's transpose, whichever is
+// lower and upper triangular; tt is scratch; all [dp][dp] binary32.
+struct TriWork { float* lo; float* hi; float* tt; };
+int tri_inverse(const LuSrc& q, int dp, int first, int count, const TriWork& l, const TriWork& u, hipStream_t s) {
+  hipLaunchKernelGGL(k_tri_diag_inverse, dim3(dp / 128, count), dim3(256), 0, s, q, dp, first, TriOut{l.lo, l.hi}, TriOut{u.lo, u.hi});
   AE_TRY(launch_status("tri_diag_inverse"));
-  for (int b = 128; b < d; b *= 2) {
-    ConvArgs a;
-    memset(&a, 0, sizeof(a));
-    a.n = d; a.hc = a.wc = 1; a.cin = a.cout = d; a.k = 1; a.up = 0; a.act = ACT_NONE; a.dtype = AE_F32;
-    a.tri_b = b;
-    a.tri_pairs = (q.d + 2 * b - 1) / (2 * b);                            // pairs wholly inside the identity padding stay as they are
-    a.tri_d = q.d < d ? q.d : 0;                                          // ... and so do the zero parts of the last pair
-    a.x = xt; a.w = mneg; a.y = tt; a.tri = CONV_TRI_PAIR_UPPER_K0;       // T' = X11^T (-M21)^T = -(M21 X11)^T
-    AE_TRY(launch_conv_mfma(a, s));
-    a.x = x; a.w = tt; a.y = x; a.tri = CONV_TRI_PAIR_LOWER_K1;           // X21 = X22 T'^T (reads the diagonal blocks of x, writes below them)
-    AE_TRY(launch_conv_mfma(a, s));
-    // X21^T into X^T: a transposing copy (a third product would give the same block at fifteen times the cost)
-    hipLaunchKernelGGL(k_tri_pair_transpose, dim3(b / 32, b / 32, a.tri_pairs), dim3(256), 0, s, (const float*)x, xt, d, b);
-    AE_TRY(launch_status("tri_pair_transpose"));
+  for (int b = 128; b < dp; b *= 2) {
+    const TriProduct t[2] = {{l.hi, q.lp, q.d, l.tt, nullptr, false}, {u.lo, q.up, q.d, u.tt, nullptr, true}};
+    const TriProduct x[2] = {{l.lo, l.tt, dp, l.lo, l.hi, true}, {u.hi, u.tt, dp, u.hi, u.lo, false}};   // (reads diagonal blocks, writes beside them)
+    AE_TRY(launch_tri_pairs(t + first, count, dp, b, q.d, false, s));
+    AE_TRY(launch_tri_pairs(x + first, count, dp, b, q.d, true, s));
   }
   return AE_OK;
 }
@@ -1521,13 +1484,13 @@ extern "C" int model_qr_inverse(const float* rp, const float* log_s, const float
   const int64_t dd = d * d, dp = tri_padded_size(d), pp = dp * dp;
   const QrSlots w{const_cast<float*>(reinterpret_cast<const float*>(qr_workspace)), dd, squarings};
   float* f = reinterpret_cast<float*>(workspace);
-  float *mneg = f, *tt = f + pp, *rdinv_t = f + 2 * pp, *rdinv = f + 3 * pp, *z = f + 4 * pp;
+  float *compact = f, *tt = f + pp, *rdinv_t = f + 2 * pp, *rdinv = f + 3 * pp, *z = f + 4 * pp;
   LuSrc q{nullptr, rp, log_s, sign_s, nullptr, nullptr, (int)d};
-  AE_TRY(tri_inverse<1>(q, (int)dp, mneg, tt, rdinv_t, rdinv, s));        // ((R + diag s)^T)^-1 and its transpose (R + diag s)^-1
+  AE_TRY(tri_inverse(q, (int)dp, 1, 1, TriWork{}, TriWork{rdinv_t, rdinv, tt}, s));
   if (dp != d) {                                                          // drop the identity padding
-    hipLaunchKernelGGL(k_tri_compact, dim3(lu_grid(dd)), dim3(256), 0, s, (const float*)rdinv, (int)dp, (int)d, mneg);
+    hipLaunchKernelGGL(k_tri_compact, dim3(lu_grid(dd)), dim3(256), 0, s, (const float*)rdinv, (int)dp, (int)d, compact);
     AE_TRY(launch_status("tri_compact"));
-    rdinv = mneg;
+    rdinv = compact;
   }
   // A^-1 = (R + diag s)^-1 Q^T = x w^T with w = Q, x upper triangular (its lower triangle is not written)
   if (dtype == AE_F32) return dense_product(rdinv, w.q(squarings), a_inv_out, (int)d, AE_F32, CONV_TRI_UPPER_X_FULL, s);
@@ -1553,35 +1516,18 @@ extern "C" int model_lu_inverse(const float* lp, const float* up, const float* l
   if (d < 128 || d > 16384 || d % 128 != 0) return fail(AE_EINVAL, "model_lu_inverse: d must be a multiple of 128, at most 16384");
   if ((reinterpret_cast<uintptr_t>(workspace) & 15) != 0) return fail(AE_EINVAL, "model_lu_inverse: the workspace must be 16-byte aligned");
   hipStream_t s = (hipStream_t)stream;
-  const int64_t dd = d * d, dp = tri_padded_size(d), pp = dp * dp;
+  const int64_t dp = tri_padded_size(d), pp = dp * dp;
   float* f = reinterpret_cast<float*>(workspace);
-  float* mneg = f;                  // -M of the factor being inverted and the scratch of its recursion: for L ...
-  float* tt = f + pp;
-  float* linv = f + 2 * pp;         // L^-1 and its transpose; afterwards (U + diag s)^-1 L^-1
-  float* linv_t = f + 3 * pp;
-  float* udinv_t = f + 4 * pp;      // ((U + diag s)^T)^-1 = ((U + diag s)^-1)^T and its transpose (U + diag s)^-1
-  float* udinv = f + 5 * pp;
-  float* mneg_u = f + 6 * pp;       // ... and for (U + diag s)^T: the two inversions run side by side on two streams
-  float* tt_u = f + 7 * pp;         // (the lower levels of the recursion have too few tiles to fill the chip alone)
+  const TriWork l{f, f + pp, f + 4 * pp};                  // L^-1 and its transpose
+  const TriWork u{f + 2 * pp, f + 3 * pp, f + 5 * pp};     // the transpose of (U + diag s)^-1 and itself
+  float *z = f + 6 * pp, *z2 = f + 7 * pp;                 // (U + diag s)^-1 L^-1, the second halves of its long sums
   LuSrc q{lp, up, log_s, sign_s, nullptr, nullptr, (int)d};
-  SideBranch br;
-  AE_TRY(br.begin(s, !g_timing, "model_lu_inverse"));
-  int rc = tri_inverse<0>(q, (int)dp, mneg, tt, linv, linv_t, s);
-  if (rc == AE_OK) rc = tri_inverse<1>(q, (int)dp, mneg_u, tt_u, udinv_t, udinv, br.side);
-  rc = br.end(rc, "model_lu_inverse");
-  if (rc != AE_OK) return rc;
-  if (dp != d) {                    // drop the identity padding: the two factors of the last product as d x d matrices
-    hipLaunchKernelGGL(k_tri_compact, dim3(lu_grid(dd)), dim3(256), 0, s, (const float*)udinv, (int)dp, (int)d, mneg);
-    hipLaunchKernelGGL(k_tri_compact, dim3(lu_grid(dd)), dim3(256), 0, s, (const float*)linv_t, (int)dp, (int)d, tt);
-    AE_TRY(launch_status("tri_compact"));
-    udinv = mneg;
-    linv_t = tt;
-  }
-  float* z = linv;
-  AE_TRY(dense_product(udinv, linv_t, z, (int)d, AE_F32, CONV_TRI_UPPER_LOWER, s));
+  AE_TRY(tri_inverse(q, (int)dp, 0, 2, l, u, s));
+  AE_TRY(launch_tri_last(u.hi, l.hi, (int)dp, z, z2, (int)d, s));
+  const int split = tri_last_split((int)d);
   const dim3 og((unsigned)(d < 2048 ? d : 2048));
-  if (dtype == AE_BF16) hipLaunchKernelGGL((k_lu_inverse_out<bf16_t>), og, dim3(256), (size_t)d * 4, s, (const float*)z, perm, (int)d, (bf16_t*)a_inv_out);
-  else hipLaunchKernelGGL((k_lu_inverse_out<float>), og, dim3(256), (size_t)d * 4, s, (const float*)z, perm, (int)d, (float*)a_inv_out);
+  if (dtype == AE_BF16) hipLaunchKernelGGL((k_lu_inverse_out<bf16_t>), og, dim3(256), (size_t)d * 4, s, (const float*)z, (const float*)z2, split, perm, (int)d, (bf16_t*)a_inv_out);
+  else hipLaunchKernelGGL((k_lu_inverse_out<float>), og, dim3(256), (size_t)d * 4, s, (const float*)z, (const float*)z2, split, perm, (int)d, (float*)a_inv_out);
   return launch_status("lu_inverse_out");
 }
 

@@ -25,6 +25,7 @@
 //   k_gemm_split            binary32 products and convolutions by bf16 parts
 // The shared epilogue adds the bias, rounds to the storage type, optionally reduces per-channel
 // sum / sum of squares of the tile (batch-norm statistics), applies the activation and stores [M][N].
+#include <algorithm>
 #include <type_traits>
 
 #include "ae_device.h"
@@ -76,13 +77,19 @@ struct IgemmParams {
   //   5: x[m][k] = 0 for k < m: K starts at the tile's first row
   //   6: w[n][k] = 0 for k > n: K ends at the tile's last column
   //   7: w[n][k] = 0 for k < n: K starts at the tile's first column
-  // Blocked triangular inverse, all pairs of neighbouring tri_b x tri_b diagonal blocks in one launch (tile sizes divide
-  // tri_b): only the tiles of one off-diagonal block per pair are computed, over the K range of one block:
-  //   8: tile rows in an even block r, columns in block r+1, K = block r, x upper triangular: from the tile's first row on;
-  //   9: tile rows in an odd block r, columns in block r-1, K = block r, x lower triangular: up to the tile's last row
-  // tri_d > 0 (modes 8, 9): the matrices are an identity block beyond row and column tri_d; tiles of the odd block that
-  // lie wholly beyond it return (their outputs are zero and stay unwritten) and K ranges over the odd block end at tri_d.
-  int tri, tri_b, tri_d;
+  int tri;
+  // k_gemm_split<..., TRI_PAIRS>: one product of one level of the blocked triangular inverse, for all pairs of neighbouring tri_b x tri_b diagonal
+  // blocks (r even, r + 1) of one or two matrices in one launch: only the tiles of one off-diagonal block per pair, K the block of their rows
+  //   upper: rows in block r, columns in block r + 1, x upper triangular: K from the tile's first row on;
+  //   lower: rows in block r + 1, columns in block r, x lower triangular: K up to the tile's last row
+  // tri_d: the matrices are an identity block beyond row and column tri_d; tiles of the odd block that lie wholly beyond it return
+  // (their outputs are zero and stay unwritten) and K ranges over the odd block end there.  negate: -(x w^T), and its transpose into yt.
+  // TRI_LAST: x upper, w^T lower triangular (as mode 4); 128 x 128 outputs whose K range is longer than half of K are two
+  // workgroups, of which the second leaves its sums in the other matrix's y.
+  // Row lengths ldx and ldw (elements) of the operands, N of the outputs.
+  struct Tri { const void* x; const void* w; void* y; float* yt; bool lower; } tm[2];
+  int tri_b, tri_d, tri_pairs, ldx, ldw;
+  bool negate;
   // k_conv3_patch on images wider than its tile: a tile is TH rows x Wt columns of one of `strips` column strips
   // of the image (Wt = Wc / strips, TH = 256 / Wt); GEMM row m = tile * 256 + th * Wt + tw then is pixel
   // (row block * TH + th, strip * Wt + tw) of its image.  1: a tile spans the image width and rows are pixels in order.
@@ -635,7 +642,7 @@ __device__ __forceinline__ IgemmTileId igemm_tile_id(const IgemmParams& p) {
   int lb0 = xcd_logical_block((int)blockIdx.x, (int)gridDim.x);
   // triangular products: tile rows differ in work by an order of magnitude, so neighbouring tiles go to different
   // XCDs (the hardware's own round-robin) instead of one contiguous range per XCD, the longest K ranges first
-  if (p.tri != 0 && p.tri < 8) lb0 = p.tri == 1 ? (int)gridDim.x - 1 - (int)blockIdx.x : (int)blockIdx.x;
+  if (p.tri != 0) lb0 = p.tri == 1 ? (int)gridDim.x - 1 - (int)blockIdx.x : (int)blockIdx.x;
   if (p.tri == 4 && (gridDim.x & 63) == 0) {    // runs of eight consecutive tiles per XCD (they share an operand panel in its L2), runs interleaved
     const int i = (int)blockIdx.x >> 3, x = (int)blockIdx.x & 7;
     lb0 = ((((i >> 3) << 3) + x) << 3) + (i & 7);
@@ -667,26 +674,6 @@ __device__ __forceinline__ IgemmTileId igemm_tile_id(const IgemmParams& p) {
     t.m = r <= sh ? r : sh;
     t.n = r <= sh ? sh : r - sh - 1;
   }
-  if (p.tri >= 8) {                             // only the tiles of one off-diagonal block per pair are launched
-    const int tbm = p.tri_b / BM, tbn = p.tri_b / BN;
-    int tr, col;                                // tile row of its block; column among those of all pairs
-    if (gridDim.x > 256) {
-      // Several workgroups per compute unit: rows of equal K range together, the longest first, their columns spread over
-      // the XCDs.  (With a contiguous range of tiles each, one XCD gets the longest rows alone: two merges of 2048-blocks
-      // side by side, LU step of d = 4096, 1.23 against 1.15 ms.)
-      const int per_row = (int)gridDim.x / tbm, rank = (int)blockIdx.x / per_row;
-      col = xcd_logical_block((int)blockIdx.x - rank * per_row, per_row);
-      tr = p.tri == 9 ? tbm - 1 - rank : rank;
-    } else {
-      // one each: the longest K range decides, so neighbours share an L2 (d = 2048, 1536: 0.5 to 0.8 % of the step)
-      const int pair = lb / (tbm * tbn), in_pair = lb - pair * (tbm * tbn);
-      tr = in_pair / tbn;
-      col = pair * tbn + in_pair - tr * tbn;
-    }
-    const int pair = col / tbn, tc = col - pair * tbn;
-    t.m = (2 * pair + (p.tri == 9 ? 1 : 0)) * tbm + tr;
-    t.n = (2 * pair + (p.tri == 9 ? 0 : 1)) * tbn + tc;
-  }
   return t;
 }
 // its K range (triangular operands: see IgemmParams::tri); false: no output of the tile is wanted
@@ -700,16 +687,63 @@ __device__ __forceinline__ bool igemm_k_range(const IgemmParams& p, int64_t m0, 
   else if (p.tri == 5) k_lo = (int)m0;
   else if (p.tri == 6) k_hi = min(p.K, n0 + BN);
   else if (p.tri == 7) k_lo = n0;
-  else if (p.tri >= 8) {
-    const int rb = (int)(m0 / p.tri_b), cb = n0 / p.tri_b;
-    if (p.tri == 9 ? !((rb & 1) == 1 && cb == rb - 1) : !((rb & 1) == 0 && cb == rb + 1)) return false;
-    k_lo = p.tri == 8 ? (int)m0 : rb * p.tri_b;
-    k_hi = p.tri == 8 ? (rb + 1) * p.tri_b : (int)m0 + BM;
-    if (p.tri_d > 0) {
-      if ((p.tri == 9 ? m0 : (int64_t)n0) >= p.tri_d) return false;
-      if (p.tri == 9) k_hi = min(k_hi, p.tri_d);
-    }
+  return true;
+}
+
+// Tiles and K ranges of the triangular inverse's products (IgemmParams::tm)
+enum { TRI_NO = 0, TRI_PAIRS = 1, TRI_LAST = 2 };
+struct TriTile { int which, m0, n0, k_lo, k_hi; bool second; };      // matrix; second half of a K range
+template <int BM, int BN>
+__device__ __forceinline__ bool tri_pair_tile(const IgemmParams& p, TriTile& t) {
+  const int tbm = p.tri_b / BM, tbn = p.tri_b / BN;
+  int tr, col;                                  // rank of the tile's row in its block, longest K first; column among those of all pairs
+  if (gridDim.x > 256) {
+    // Several workgroups per compute unit: rows of equal K range together, the longest first, their columns spread over
+    // the XCDs.  (With a contiguous range of tiles each, one XCD gets the longest rows alone: two merges of 2048-blocks
+    // side by side, LU step of d = 4096, 1.23 against 1.15 ms.)
+    const int per_row = (int)gridDim.x / tbm;
+    tr = (int)blockIdx.x / per_row;
+    col = xcd_logical_block((int)blockIdx.x - tr * per_row, per_row);
+    // Two each at most, all resident at once: the second half the other way round, so that a long range shares its compute unit with a short one
+    if (gridDim.x <= 512 && tr >= tbm / 2) tr = tbm / 2 + tbm - 1 - tr;
+  } else {
+    // one each: the longest K range decides, so neighbours share an L2 (d = 2048, 1536: 0.5 to 0.8 % of the step)
+    const int lb = xcd_logical_block((int)blockIdx.x, (int)gridDim.x), pair = lb / (tbm * tbn), in_pair = lb - pair * (tbm * tbn);
+    tr = in_pair / tbn;
+    col = pair * tbn + in_pair - tr * tbn;
   }
+  int pair = col / tbn;
+  const int tc = col - pair * tbn;
+  t.which = pair >= p.tri_pairs ? 1 : 0;
+  pair -= t.which * p.tri_pairs;
+  const bool lower = t.which ? p.tm[1].lower : p.tm[0].lower;
+  const int even = 2 * pair * p.tri_b, odd = even + p.tri_b;
+  t.m0 = lower ? odd + (tbm - 1 - tr) * BM : even + tr * BM;
+  t.n0 = (lower ? even : odd) + tc * BN;
+  t.k_lo = lower ? odd : t.m0;
+  t.k_hi = lower ? min(t.m0 + BM, p.tri_d) : odd;
+  t.second = false;
+  return (lower ? t.m0 : t.n0) < p.tri_d;
+}
+// The L-shaped shells max(row, column) = 0, 1, ... of BM x BM outputs (two tiles where BN is half of it): those whose range [max, K) is longer than half, two halves each, then
+// the others, so that the ranges of either kind are dispatched longest first and the hardware's in-order dispatch balances the rest
+template <int BM, int BN>
+__device__ __forceinline__ bool tri_last_tile(const IgemmParams& p, TriTile& t) {
+  const int sub = BN < BM ? (int)blockIdx.x & 1 : 0, lb = BN < BM ? (int)blockIdx.x >> 1 : (int)blockIdx.x;
+  const int half = p.K / BM / 2, n2 = 2 * half * half;
+  const bool two = lb < n2;
+  const int i = two ? lb >> 1 : lb - n2 / 2;
+  int sh = (int)sqrtf((float)i);
+  while (sh * sh > i) --sh;
+  while ((sh + 1) * (sh + 1) <= i) ++sh;
+  const int r = i - sh * sh;                    // 0 .. 2 sh
+  t.m0 = (r <= sh ? r : sh) * BM;
+  t.n0 = (r <= sh ? sh : r - sh - 1) * BM + sub * BN;
+  t.which = two && (lb & 1) ? 1 : 0;
+  t.second = t.which == 1;
+  const int lo = sh * BM, mid = two ? lo + (p.K - lo) / 64 * 32 : p.K;
+  t.k_lo = t.second ? mid : lo;
+  t.k_hi = t.second ? p.K : mid;
   return true;
 }
 
@@ -1278,7 +1312,7 @@ __global__ __launch_bounds__(WGM * WGN * 64 * KG) __attribute__((amdgpu_waves_pe
 // lie beyond the range where the product of the values does not, and where both accumulators leave it with different signs
 // their sum would be NaN for an infinity.
 // ---------------------------------------------------------------------------
-template <int BM, int BN, int WGM, int WGN, bool INTERIOR, int EPI = 0, bool CONV = false>
+template <int BM, int BN, int WGM, int WGN, bool INTERIOR, int EPI = 0, bool CONV = false, int TRI = TRI_NO>
 __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_split(IgemmParams p) {
   constexpr int NT = WGM * WGN * 64;
   constexpr int WM = BM / WGM, WN = BN / WGN, MI = WM / 32, NJ = WN / 32;
@@ -1290,11 +1324,26 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
   __shared__ float sRed[WGM][2][BN];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WGN, wn = wave % WGN;
-  const IgemmTileId tile = igemm_tile_id<BM, BN, INTERIOR>(p);
-  const int64_t m0 = tile.m * BM;
-  const int n0 = tile.n * BN;
-  int k_lo, k_hi;
-  if (!igemm_k_range<BM, BN>(p, m0, n0, k_lo, k_hi)) return;
+  static_assert(TRI == TRI_NO || (INTERIOR && EPI == 0 && !CONV), "dense products");
+  IgemmTileId tile = {};
+  int64_t m0;
+  int n0, k_lo, k_hi;
+  const int ldx = TRI != TRI_NO ? p.ldx : p.K, ldw = TRI != TRI_NO ? p.ldw : p.K;
+  float* yt = nullptr;
+  if constexpr (TRI != TRI_NO) {
+    TriTile t;
+    if (!(TRI == TRI_PAIRS ? tri_pair_tile<BM, BN>(p, t) : tri_last_tile<BM, BN>(p, t))) return;
+    m0 = t.m0; n0 = t.n0; k_lo = t.k_lo; k_hi = t.k_hi;
+    p.x = t.which ? p.tm[1].x : p.tm[0].x;
+    p.w = t.which ? p.tm[1].w : p.tm[0].w;
+    p.y = t.which ? p.tm[1].y : p.tm[0].y;
+    yt = t.which ? p.tm[1].yt : p.tm[0].yt;
+  } else {
+    tile = igemm_tile_id<BM, BN, INTERIOR>(p);
+    m0 = tile.m * BM;
+    n0 = tile.n * BN;
+    if (!igemm_k_range<BM, BN>(p, m0, n0, k_lo, k_hi)) return;
+  }
   // slabs of 16 (K ranges start at multiples of 32)
   const int kt0 = INTERIOR ? k_lo / 16 : max(k_lo / 16, tile.split * p.slabs_per_split);
   const int KT = INTERIOR ? (k_hi + 15) / 16 - kt0 : min((k_hi + 15) / 16 - kt0, p.slabs_per_split);
@@ -1313,7 +1362,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
         x.h = (int)(t - n * (unsigned)p.Hc);
         x.img = n * (unsigned)((p.Hv >> p.up) * (p.Wv >> p.up)) * (unsigned)p.Cin * 4u;
       } else {
-        x.img = (unsigned)m * (unsigned)p.K * 4u;
+        x.img = (unsigned)m * (unsigned)ldx * 4u;
       }
     }
     return x;
@@ -1336,7 +1385,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
   for (int i = 0; i < BC; ++i) {
     const int n = n0 + lrow + i * RSTEP;
-    off[AC + i] = n < p.N ? (unsigned)(tile.phase * p.N + n) * (unsigned)p.K * 4u + (unsigned)(kt0 * 64 + kq * 16) : kOob;
+    off[AC + i] = n < p.N ? (unsigned)(tile.phase * p.N + n) * (unsigned)ldw * 4u + (unsigned)(kt0 * 64 + kq * 16) : kOob;
   }
   auto next_slab = [&]() {                       // CONV: behind the loads of a slab
     if constexpr (CONV) {
@@ -1463,7 +1512,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
         const int n = n0 + wn * WN + j * 32 + (lane & 31);
-        const unsigned o = n < p.N ? (unsigned)(tile.phase * p.N + n) * (unsigned)p.K * 4u + (unsigned)(k * 4 + (lane >> 5) * 16) : kOob;
+        const unsigned o = n < p.N ? (unsigned)(tile.phase * p.N + n) * (unsigned)ldw * 4u + (unsigned)(k * 4 + (lane >> 5) * 16) : kOob;
         f[MI + j] = __builtin_amdgcn_raw_buffer_load_b128(rW, o, 0, 0);
       }
 #pragma unroll
@@ -1487,6 +1536,24 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
           }
         }
       return;
+    }
+  }
+  if constexpr (TRI == TRI_PAIRS) {
+    if (p.negate) {
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) acc[i][j] = -acc[i][j];
+    }
+    if (yt) {                                    // four rows of a column are 16 bytes of the transpose
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+          for (int g = 0; g < 4; ++g)
+            *reinterpret_cast<float4v*>(yt + (int64_t)(n0 + wn * WN + j * 32 + (lane & 31)) * p.N + m0 + wm * WM + i * 32 + g * 8 + (lane >> 5) * 4) =
+                float4v{acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
     }
   }
   igemm_epilogue<float, BM, BN, WGM, WGN, INTERIOR, EPI>(acc, p, smem, sRed, m0, n0, tile.m, tile.phase);
@@ -1945,12 +2012,7 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
   p.mx_block = a0.mx_block;
   p.mx_elem = a0.mx_elem;
   p.tri = a0.tri;
-  p.tri_b = a0.tri_b;
-  p.tri_d = a0.tri >= 8 ? a0.tri_d : 0;
-  if (a0.tri >= 8 && (a0.tri > 9 || a.dtype != AE_F32 || a0.tri_b < 128 || a0.tri_b % 128 != 0 || a.n % (2 * a0.tri_b) != 0 ||
-                      a0.tri_d < 0 || a0.tri_d > a.n || a0.tri_d % 128 != 0))
-    return fail(AE_EINVAL, "conv_mfma: bad block size for the blocked triangular inverse");
-  if (a0.tri != 0 && (a0.tri < 0 || a0.tri > 9 || a.k != 1 || a.hc != 1 || a.wc != 1 || a.up != 0 || a.n != a.cout || a.cin != a.cout ||
+  if (a0.tri != 0 && (a0.tri < 0 || a0.tri > 7 || a.k != 1 || a.hc != 1 || a.wc != 1 || a.up != 0 || a.n != a.cout || a.cin != a.cout ||
                       a0.epi != CONV_EPI_NONE || a.partial))
     return fail(AE_EINVAL, "conv_mfma: triangular K ranges are for square dense products only");
   if (conv3_patch_usable(a0)) {
@@ -1990,11 +2052,6 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
   splits = (KT + p.slabs_per_split - 1) / p.slabs_per_split;
   p.split_out = splits > 1 ? a.splitk_ws : nullptr;
   dim3 grid((unsigned)(tiles_m * p.tiles_n * splits * p.phases));
-  if (a0.tri >= 8) {
-    const int64_t all_pairs = p.M / (2 * a0.tri_b);
-    const int64_t pairs = a0.tri_pairs > 0 && a0.tri_pairs < all_pairs ? a0.tri_pairs : all_pairs;
-    grid = dim3((unsigned)(pairs * (a0.tri_b / t.bm) * (a0.tri_b / t.bn)));
-  }
   const bool interior = splits == 1 && p.M % t.bm == 0 && p.N % t.bn == 0 && !a.y_aux && a.act != ACT_SIGMOID &&
                         !(a.partial && a.act != ACT_NONE);
 #define IGEMM_LAUNCH_K(T, BMV, BNV, GM, GN, KB)                                                        \
@@ -2016,10 +2073,7 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
     // units of a full round of 512 of the first kind: 256 of them 0.63, 512 halves 0.69, 256 halves 0.45, 256 tall ones 0.89.
     // Measured (QR step, 30 products): d = 512, 768, 1024 0.71, 0.97, 1.21 ms with halves, 0.94, 1.29, 1.63 without; d = 1536 the same;
     // d = 2048 3.66 with, 3.34 without; d = 4096 19.9 ms with tall tiles, 22.7 without.  Triangular K ranges gain from halves
-    // up to 256 tiles (d = 2048, LU step: 0.56 against 0.71 ms), and the merges of the blocked inverse, launches that wait for
-    // one another, from quarters of 64 x 64 up to 128 tiles, two workgroups per compute unit: the longest K range is a chain of slabs, and
-    // a slab of a quarter is shorter (LU step in binary32, d = 1024 / 2048 / 3072: 0.321 / 0.562 / 1.189 ms with halves alone, 0.301 / 0.520 / 1.152
-    // with quarters; on another box 1.184 at d = 3072, 1.197 with quarters throughout, and at d = 2048 0.532, 0.537 with tiles of 64 x 32 up to 32 tiles).
+    // up to 256 tiles (d = 2048, LU step: 0.56 against 0.71 ms).
     auto rounds = [](int64_t n, int64_t slots, double half, double full) {
       const int64_t rem = n % slots;
       return (double)(n / slots) * full + (rem == 0 ? 0.0 : rem <= slots / 2 ? half : full);
@@ -2033,10 +2087,6 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
     if (choice && tall < c128 && tall < c64) {
       p.tiles_mn /= 2;
       hipLaunchKernelGGL((k_gemm_split<256, 128, 4, 2, true>), dim3(grid.x / 2), dim3(512), 0, s, p);
-    } else if (choice && a0.tri >= 8 && n128 <= 128) {
-      p.tiles_n *= 2;
-      p.tiles_mn *= 4;
-      hipLaunchKernelGGL((k_gemm_split<64, 64, 2, 2, true>), dim3(grid.x * 4), dim3(256), 0, s, p);
     } else if (choice && (!whole ? n128 <= 256 : c64 < c128)) {
       p.tiles_n *= 2;
       p.tiles_mn *= 2;
@@ -2132,6 +2182,46 @@ int launch_dense_kn(const void* x, const void* w, void* y, int64_t rows, int64_t
   else if (dense_stages(grid.x, p.tiles_n, 0) == 3) hipLaunchKernelGGL((k_dense<128, 128, 2, 2, 3, 0, true>), grid, dim3(256), 0, s, p);
   else hipLaunchKernelGGL((k_dense<128, 128, 2, 2, 4, 0, true>), grid, dim3(256), 0, s, p);
   return launch_status("dense_kn");
+}
+
+// ---- the triangular inverse's products -----------------------------------------------------------------------------------
+int launch_tri_pairs(const TriProduct* f, int count, int dp, int b, int d, bool negate, hipStream_t s) {
+  if (count < 1 || count > 2 || b < 128 || b % 128 != 0 || dp % (2 * b) != 0 || d < 1 || d > dp || d % 128 != 0 || (int64_t)dp * dp * 4 >= 0x7FFFFFFF)
+    return fail(AE_EINVAL, "tri_pairs: bad sizes");
+  IgemmParams p = {};
+  p.M = dp; p.N = p.K = dp; p.phases = 1; p.act = ACT_NONE;
+  p.ldx = dp; p.ldw = f[0].ldw; p.tri_b = b; p.tri_d = d; p.tri_pairs = (d + 2 * b - 1) / (2 * b);   // pairs wholly inside the identity padding stay as they are
+  p.negate = negate;
+  p.x_bytes = (unsigned)((int64_t)dp * dp * 4);
+  p.w_bytes = (unsigned)((int64_t)p.ldw * p.ldw * 4);
+  for (int i = 0; i < count; ++i) p.tm[i] = IgemmParams::Tri{f[i].x, f[i].w, f[i].y, f[i].yt, f[i].lower};
+  // Tiles: launches that wait for one another; the longest K range of a tile is a chain of slabs, and a slab of a smaller tile is shorter, so quarters
+  // of 64 x 64 while those that lie inside are at most 256 of 128 x 128 (of the last pair, only columns or rows up to d do).  us of a binary32 inverse with
+  // quarters up to 64, 128 and 256: d = 2 048 222, 206, 206; 2 176 395, 387, 375; 3 072 532, 524, 514; with halves between 256 and 512, d = 4 096 718, without 708.
+  const int64_t t = b / 128, tiles = count * p.tri_pairs * t * t, inside = count * ((p.tri_pairs - 1) * t * t + t * std::max(0, std::min((int)t, (d - (2 * p.tri_pairs - 1) * b) / 128)));
+  if (inside <= 256) hipLaunchKernelGGL((k_gemm_split<64, 64, 2, 2, true, 0, false, TRI_PAIRS>), dim3((unsigned)tiles * 4), dim3(256), 0, s, p);
+  else hipLaunchKernelGGL((k_gemm_split<128, 128, 2, 2, true, 0, false, TRI_PAIRS>), dim3((unsigned)tiles), dim3(256), 0, s, p);
+  return launch_status("tri_pairs");
+}
+// side of the square of outputs that share a K range, which starts at its first row: x and w hold zeros in the other triangle of
+// the diagonal blocks of that size: 256 (tiles of 256 x 128) where they fill the chip for long enough (d = 4 096 717 -> 706 us of an
+// inverse, 3 072 497 and 505)
+static int tri_last_side(int d) { return d % 256 == 0 && d >= 4096 ? 256 : 128; }
+int tri_last_split(int d) { return d / tri_last_side(d) / 2 * tri_last_side(d); }
+int launch_tri_last(const float* x, const float* w, int ld, float* y, float* y2, int d, hipStream_t s) {
+  if (d < 128 || d % 128 != 0 || ld < d || (int64_t)ld * ld * 4 >= 0x7FFFFFFF) return fail(AE_EINVAL, "tri_last: bad sizes");
+  IgemmParams p = {};
+  p.M = d; p.N = p.K = d; p.phases = 1; p.act = ACT_NONE;
+  p.ldx = p.ldw = ld;
+  p.x_bytes = p.w_bytes = (unsigned)((int64_t)ld * ld * 4);
+  p.tm[0] = IgemmParams::Tri{x, w, y, nullptr, false};
+  p.tm[1] = IgemmParams::Tri{x, w, y2, nullptr, false};
+  const int side = tri_last_side(d), t = d / side, half = t / 2;
+  const unsigned n = (unsigned)(t * t + half * half);
+  if (side == 256) hipLaunchKernelGGL((k_gemm_split<256, 128, 4, 2, true, 0, false, TRI_LAST>), dim3(n * 2), dim3(512), 0, s, p);
+  else if (t * t <= 256) hipLaunchKernelGGL((k_gemm_split<128, 64, 4, 1, true, 0, false, TRI_LAST>), dim3(n * 2), dim3(256), 0, s, p);
+  else hipLaunchKernelGGL((k_gemm_split<128, 128, 2, 2, true, 0, false, TRI_LAST>), dim3(n), dim3(256), 0, s, p);
+  return launch_status("tri_last");
 }
 
 // ---- any channel counts: the chunk walk of k_igemm ---------------------------------------------------------------

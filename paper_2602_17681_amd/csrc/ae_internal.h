@@ -209,22 +209,10 @@ struct ConvArgs {
   //   CONV_TRI_UPPER_LOWER  x upper triangular, w^T lower triangular (w[n][k] = 0 for k < n): every output wanted;
   //   CONV_TRI_UPPER_X_FULL x upper triangular; every output wanted;
   //   CONV_TRI_LOWER_W_FULL, CONV_TRI_UPPER_W_FULL  w[n][k] = 0 for k > n, for k < n; every output wanted;
-  //   CONV_TRI_PAIR_*       one level of a blocked triangular inverse: all pairs of neighbouring tri_b x tri_b diagonal
-  //                         blocks (r even, r+1) in one launch; only the tiles of the named off-diagonal block of
-  //                         each pair are computed, over the K range of the named block:
-  //                           UPPER_K0: rows in block r, columns in block r+1, K = block r (x upper triangular: from the row on);
-  //                           LOWER_K1: rows in block r+1, columns in block r, K = block r+1 (x lower triangular: up to the row).
-  //                         tri_pairs > 0 limits the launch to the first tri_pairs pairs (the rest keep their contents).
   int tri = 0;
-  int tri_b = 0;
-  //                         tri_d > 0 (a multiple of 128): the matrices are an identity block beyond row and column
-  //                         tri_d; tiles and K ranges beyond it are skipped (outputs there are zero, left unwritten).
-  int tri_pairs = 0;
-  int tri_d = 0;
   bool f32_mfma = false;           // dense binary32 products: not through bf16 parts
 };
-enum { CONV_TRI_NONE = 0, CONV_TRI_LOWER_UPPER = 1, CONV_TRI_UPPER_X = 2, CONV_TRI_UPPER_W = 3, CONV_TRI_UPPER_LOWER = 4, CONV_TRI_UPPER_X_FULL = 5, CONV_TRI_LOWER_W_FULL = 6, CONV_TRI_UPPER_W_FULL = 7,
-       CONV_TRI_PAIR_UPPER_K0 = 8, CONV_TRI_PAIR_LOWER_K1 = 9 };
+enum { CONV_TRI_NONE = 0, CONV_TRI_LOWER_UPPER = 1, CONV_TRI_UPPER_X = 2, CONV_TRI_UPPER_W = 3, CONV_TRI_UPPER_LOWER = 4, CONV_TRI_UPPER_X_FULL = 5, CONV_TRI_LOWER_W_FULL = 6, CONV_TRI_UPPER_W_FULL = 7 };
 enum { CONV_PLAIN = 0, CONV_UP_PHASES = 1, CONV_UP_DGRAD = 2 };
 enum { CONV_EPI_NONE = 0, CONV_EPI_MXQ = 1, CONV_EPI_RESID = 2 };
 bool conv_epi_usable(const ConvArgs& a);         // can launch_conv_mfma run a.epi for this shape?
@@ -241,6 +229,15 @@ ConvArgs conv_effective(const ConvArgs& a);   // the GEMM that a.geom runs as
 int launch_conv_mfma(const ConvArgs& a, hipStream_t s);
 // bf16 products whose second operand lies [k][n], in groups of output rows: y[m][n] = sum_k x[m mod group][k] w[K (m div group) + k][n], K = the k of the call
 bool dense_kn_supported(int64_t rows, int64_t k, int64_t n, int64_t group);
+// One product of one level of the blocked triangular inverse (ae_affine.hip), binary32: for all pairs of neighbouring b x b diagonal blocks
+// (r even, r + 1) of one or two dp x dp matrices, y = +-x w^T in one off-diagonal block, K the block of its rows: lower: rows r + 1, columns
+// r, x lower triangular; else rows r, columns r + 1, x upper triangular.  yt (may be null): the transpose.  ldw: w's row length, d or dp.
+// The matrices are an identity block beyond row and column d (a multiple of 128): nothing there is read from w or written.
+struct TriProduct { const float* x; const float* w; int ldw; float* y; float* yt; bool lower; };
+int launch_tri_pairs(const TriProduct* f, int count, int dp, int b, int d, bool negate, hipStream_t s);
+// y [d][d] = x w^T, x upper and w^T lower triangular (rows of ld); the entries in rows and columns below tri_last_split(d) are y + y2
+int tri_last_split(int d);
+int launch_tri_last(const float* x, const float* w, int ld, float* y, float* y2, int d, hipStream_t s);
 int launch_dense_kn(const void* x, const void* w, void* y, int64_t rows, int64_t k, int64_t n, int64_t group, hipStream_t s);
 // The matrix-core kernel for any channel counts: a.x and a.w hold chan_pad(cin) channels per pixel and per tap, zeros
 // behind the layer's own (launch_pad_channels, the packing kernels); a.y has plain rows of cout.
