@@ -1080,13 +1080,6 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
 typedef unsigned uint2v __attribute__((ext_vector_type(2)));
 struct TrFrag { uint2v lo, hi; };
 
-template <int OFF>
-__device__ __forceinline__ void tr_read(TrFrag& f, unsigned addr, int row_bytes4 /* = 4 k-rows */) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.lo) : "v"(addr), "n"(OFF));
-  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.hi) : "v"(addr + (unsigned)row_bytes4), "n"(OFF));
-#endif
-}
 __device__ __forceinline__ void tr_tie(TrFrag& f) {   // (as TieFrags)
 #if defined(__HIP_DEVICE_COMPILE__)
   asm volatile("" : "+v"(f.lo), "+v"(f.hi));
@@ -2959,8 +2952,8 @@ template <int OFF>
 __device__ __forceinline__ void tr_read_run(TrRun& f, unsigned addr) {
 #if defined(__HIP_DEVICE_COMPILE__)
   asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.lo) : "v"(addr), "n"(OFF));
-  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.hi) : "v"(addr + 4u * 128u), "n"(OFF));
-  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.ex) : "v"(addr + 8u * 128u), "n"(OFF));
+  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.hi) : "v"(addr), "n"(OFF + 4 * 128));
+  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(f.ex) : "v"(addr), "n"(OFF + 8 * 128));
 #endif
 }
 template <int NTAP>
@@ -3011,8 +3004,8 @@ __device__ __forceinline__ void wgrad3_reads(TrFrag (&fa)[BM / 64], TrRun& fb, u
 #pragma unroll
   for (int i = 0; i < G::MI; ++i) {
     // column i of the wave's co range: the swizzled column differs from a_addr's by (i << 6) XORed in
-    if (i == 0) tr_read<KS * 16 * G::RBA>(fa[0], a_addr, 4 * G::RBA);
-    else tr_read<KS * 16 * G::RBA>(fa[i], a_addr ^ 64u, 4 * G::RBA);
+    if (i == 0) tr_read_at<KS * 16 * G::RBA, 4 * G::RBA>(fa[0], a_addr);
+    else tr_read_at<KS * 16 * G::RBA, 4 * G::RBA>(fa[i], a_addr ^ 64u);
   }
   tr_read_run<G::cell_base(KS) * 128>(fb, b_addr);
 }
@@ -3142,42 +3135,56 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   }
 #define LGKM_WAIT(N) asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N))
 
-  // prologue: slabs 0 and 1 in flight, fragments of (slab 0, K-step 0)
+  // Three slabs in flight before the loop.  A slab's last fragments are in registers when its last MFMAs have yet to run: there the
+  // workgroup waits for the next slab and gives the stage to the slab after the next two, so that a load has two slabs' time.  (Waiting where the
+  // slab begins gave it one: steps of the wide and of the large network 1 468 -> 1 454 and 2 322 -> 2 305 us.)
+  const bool full = __builtin_amdgcn_readfirstlane(wave) + 4 * (G::XU - 1) < G::X_UNITS;   // (loads per slab and wave: L, or one less)
+  constexpr int L = G::A_PASSES + G::XU;
+  auto landed = [&](int behind) {                // all loads but those of the last `behind` slabs
+    if (behind >= 2) { if (full) __builtin_amdgcn_s_waitcnt(vm_imm(2 * L)); else __builtin_amdgcn_s_waitcnt(vm_imm(2 * L - 2)); }
+    else if (behind == 1) { if (full) __builtin_amdgcn_s_waitcnt(vm_imm(L)); else __builtin_amdgcn_s_waitcnt(vm_imm(L - 1)); }
+    else __builtin_amdgcn_s_waitcnt(vm_imm(0));
+  };
   WGRAD3_DMA(0);
   if (KT > 1) WGRAD3_DMA(1);
-  __builtin_amdgcn_s_waitcnt(vm_imm(0));
+  if (KT > 2) WGRAD3_DMA(2);
+  landed(KT - 1);
   __builtin_amdgcn_s_barrier();
   wgrad3_reads<BM, SW, 0>(fa0, fb0, lds0 + a_lane, lds0 + b_lane);
-  int cur = 0;
-  for (int t = 0; t < KT; ++t) {
-    // the loads of slab t+1 (issued one slab ago) are the only ones outstanding
-    __builtin_amdgcn_s_waitcnt(vm_imm(0));
-    __builtin_amdgcn_s_barrier();
-    const int nxt = cur == 2 ? 0 : cur + 1;
-    if (t + 2 < KT) { const int st2 = nxt == 2 ? 0 : nxt + 1; WGRAD3_DMA(st2); }
-    [[maybe_unused]] const unsigned sa = lds0 + (unsigned)(cur * G::STAGE) + a_lane;
-    [[maybe_unused]] const unsigned sb = lds0 + (unsigned)(cur * G::STAGE) + b_lane, nb = lds0 + (unsigned)(nxt * G::STAGE) + b_lane;
-    [[maybe_unused]] const unsigned na = lds0 + (unsigned)(nxt * G::STAGE) + a_lane;
 #if defined(__HIP_DEVICE_COMPILE__)
-    wgrad3_reads<BM, SW, 1>(fa1, fb1, sa, sb);
-    LGKM_WAIT(NR);
-    WGRAD3_MMA(fa0, fb0)
-    wgrad3_reads<BM, SW, 2>(fa0, fb0, sa, sb);
-    LGKM_WAIT(NR);
+#define WGRAD3_STEPS(CUR)                                                                                    \
+  {                                                                                                          \
+    const unsigned sa = lds0 + (unsigned)((CUR) * G::STAGE) + a_lane, sb = lds0 + (unsigned)((CUR) * G::STAGE) + b_lane; \
+    wgrad3_reads<BM, SW, 1>(fa1, fb1, sa, sb);                                                               \
+    LGKM_WAIT(NR);                                                                                           \
+    WGRAD3_MMA(fa0, fb0)                                                                                     \
+    wgrad3_reads<BM, SW, 2>(fa0, fb0, sa, sb);                                                               \
+    LGKM_WAIT(NR);                                                                                           \
+    WGRAD3_MMA(fa1, fb1)                                                                                     \
+    wgrad3_reads<BM, SW, 3>(fa1, fb1, sa, sb);                                                               \
+    LGKM_WAIT(NR);                                                                                           \
+    WGRAD3_MMA(fa0, fb0)                                                                                     \
+    LGKM_WAIT(0);                                                                                            \
+  }
+  int cur = 0;
+  for (int t = 0; t + 1 < KT; ++t) {
+    const int nxt = cur == 2 ? 0 : cur + 1;
+    WGRAD3_STEPS(cur)
+    landed(t + 2 < KT ? 1 : 0);
+    __builtin_amdgcn_s_barrier();
+    wgrad3_reads<BM, SW, 0>(fa0, fb0, lds0 + (unsigned)(nxt * G::STAGE) + a_lane, lds0 + (unsigned)(nxt * G::STAGE) + b_lane);
+    if (t + 3 < KT) WGRAD3_DMA(cur);
     WGRAD3_MMA(fa1, fb1)
-    wgrad3_reads<BM, SW, 3>(fa1, fb1, sa, sb);
-    LGKM_WAIT(NR);
-    WGRAD3_MMA(fa0, fb0)
-    if (t + 1 < KT) {
-      wgrad3_reads<BM, SW, 0>(fa0, fb0, na, nb);
-      LGKM_WAIT(NR);
-    } else {
-      LGKM_WAIT(0);
-    }
-    WGRAD3_MMA(fa1, fb1)
-#endif
+    LGKM_WAIT(0);                                // (nothing is in flight where the loop turns)
+#pragma unroll
+    for (int i = 0; i < MI; ++i) tr_tie(fa0[i]);
+    asm volatile("" : "+v"(fb0.lo), "+v"(fb0.hi), "+v"(fb0.ex));
     cur = nxt;
   }
+  WGRAD3_STEPS(cur)
+  WGRAD3_MMA(fa1, fb1)
+#undef WGRAD3_STEPS
+#endif
 #undef WGRAD3_DMA
 #undef WGRAD3_MMA
 #undef LGKM_WAIT
