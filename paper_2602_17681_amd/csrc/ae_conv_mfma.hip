@@ -2065,7 +2065,8 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
     // enough to outweigh their prologue and epilogue, which nothing runs beside.  The costs are rounds of workgroups, in
     // units of a full round of 512 of the first kind: 256 of them 0.63, 512 halves 0.69, 256 halves 0.45, 256 tall ones 0.89.
     // Measured (QR step, 30 products): d = 512, 768, 1024 0.71, 0.97, 1.21 ms with halves, 0.94, 1.29, 1.63 without; d = 1536 the same;
-    // d = 2048 3.66 with, 3.34 without; d = 4096 19.9 ms with tall tiles, 22.7 without.  Triangular K ranges gain from halves
+    // d = 2048 3.66 with, 3.34 without; d = 4096 19.9 ms with tall tiles, 22.7 without.  Tall ones from K = 512 on: 65 536 rows,
+    // 512 -> 512 channels 208 -> 190 us, 512 -> 128 59 -> 52.  Triangular K ranges gain from halves
     // up to 256 tiles (d = 2048, LU step: 0.56 against 0.71 ms).
     auto rounds = [](int64_t n, int64_t slots, double half, double full) {
       const int64_t rem = n % slots;
@@ -2076,7 +2077,7 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
     const double c128 = rounds(n128, 512, 0.63, 1.0), c64 = rounds(2 * n128, 512, 0.45, 0.69);
     // (not with column sums: the caller counts one block of them per 128 rows)
     const bool whole = a0.tri == 0 || a0.tri == 6 || a0.tri == 7;      // every output, K ranges that make rounds of equal sums: as without them
-    const double tall = whole && !p.partial && p.M % 256 == 0 && p.K >= 1024 ? rounds(n128 / 2, 256, 0.89, 0.89) : 1e30;
+    const double tall = whole && !p.partial && p.M % 256 == 0 && p.K >= 512 ? rounds(n128 / 2, 256, 0.89, 0.89) : 1e30;
     if (choice && tall < c128 && tall < c64) {
       p.tiles_mn /= 2;
       hipLaunchKernelGGL((k_gemm_split<256, 128, 4, 2, true>), dim3(grid.x / 2), dim3(512), 0, s, p);
