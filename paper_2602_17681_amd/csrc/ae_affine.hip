@@ -132,15 +132,14 @@ __global__ __launch_bounds__(256) void k_lu_build_rows(LuSrc q, T* __restrict__ 
   }
 }
 
-// inv[i] = i, then inv[perm[i]] = i (two launches): entries of perm outside 0..d-1 are ignored, so every inv[r]
-// stays inside 0..d-1 whatever perm holds
-__global__ void k_lu_iota(int* __restrict__ inv, int d) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < d) inv[i] = i;
-}
-__global__ void k_lu_invert_perm(const int* __restrict__ perm, int* __restrict__ inv, int d) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i < d && (unsigned)perm[i] < (unsigned)d) inv[perm[i]] = i;
+// inv[i] = i, then inv[perm[i]] = i: entries of perm outside 0..d-1 are ignored, so every inv[r] stays inside 0..d-1 whatever
+// perm holds.  One workgroup: d is at most 16 384, and a launch costs more.
+__global__ __launch_bounds__(1024) void k_lu_invert_perm(const int* __restrict__ perm, int* __restrict__ inv, int d) {
+  for (int i = threadIdx.x; i < d; i += 1024) inv[i] = i;
+  __syncthreads();
+#pragma unroll 4
+  for (int i = threadIdx.x; i < d; i += 1024)
+    if ((unsigned)perm[i] < (unsigned)d) inv[perm[i]] = i;
 }
 
 // A[i][:] = Y[perm[i]][:], 16 bytes per lane (row bytes are a multiple of 64)
@@ -242,7 +241,8 @@ __global__ __launch_bounds__(256) void k_vol_penalty(const float* __restrict__ l
   __shared__ double sm[256 / 64 + 1];
   __shared__ float total;
   double acc = 0.0;
-  for (int i = threadIdx.x; i < d; i += 256) acc += (double)log_s[i];
+#pragma unroll 16
+  for (int i = threadIdx.x; i < d; i += 256) acc += (double)log_s[i];      // (sixteen loads in flight: 4 096 entries 8 -> 4.8 us)
   acc = block_sum<256>(acc, sm);
   if (threadIdx.x == 0) { total = (float)acc; *value = (float)(acc * acc); }
   __syncthreads();
@@ -1270,13 +1270,18 @@ extern "C" int model_lu_compose(const float* lp, const float* up, const float* l
   const int64_t mat = lu_mat_bytes(d, dtype);
   char* ws = reinterpret_cast<char*>(workspace);
   void* l = ws;                 // L                 [i][k]
-  void* udt = ws + mat;         // (U + diag s)^T    [n][k]   (binary32: U^T, the diagonal follows in k_lu_permute_rows_diag)
+  void* udt = ws + mat;         // (U + diag s)^T    [n][k]   (binary32: U^T, the diagonal follows in k_lu_permute_rows_diag; kn: U + diag s [k][n])
   void* y = ws + 2 * mat;       // L (U + diag s)    [i][n]
   LuSrc q{lp, up, log_s, sign_s, nullptr, nullptr, (int)d};
-  if (dtype == AE_BF16) { launch_build_rows<bf16_t, LU_L>(q, l, s); launch_build_transposed<bf16_t, LU_UD>(q, udt, s); }
-  else { launch_build_rows<float, LU_L>(q, l, s); launch_build_transposed<float, LU_U>(q, udt, s); }
+  const bool kn = dtype == AE_BF16 && !g_timing && dense_kn_supported(d, d, d, d);     // w as it lies: [k][n]
+  if (dtype == AE_BF16) {
+    launch_build_rows<bf16_t, LU_L>(q, l, s);
+    if (kn) launch_build_rows<bf16_t, LU_UD>(q, udt, s);
+    else launch_build_transposed<bf16_t, LU_UD>(q, udt, s);
+  } else { launch_build_rows<float, LU_L>(q, l, s); launch_build_transposed<float, LU_U>(q, udt, s); }
   AE_TRY(launch_status("lu_build"));
-  AE_TRY(dense_product(l, udt, y, (int)d, dtype, CONV_TRI_LOWER_UPPER, s));
+  if (kn) AE_TRY(launch_dense_kn(l, udt, y, d, d, d, d, s, CONV_TRI_LOWER_UPPER));
+  else AE_TRY(dense_product(l, udt, y, (int)d, dtype, CONV_TRI_LOWER_UPPER, s));
   if (dtype == AE_F32) {
     const dim3 grid((unsigned)((d + 1023) / 1024), (unsigned)((d + 15) / 16));
     hipLaunchKernelGGL(k_lu_permute_rows_diag, grid, dim3(256), 0, s, (const float*)y, (const float*)l, q, perm, (float*)a_out);
@@ -1307,27 +1312,30 @@ extern "C" int model_lu_backward(const void* g, const float* lp, const float* up
   void* dud = ws + 4 * mat;     // L^T B             [k][n]  (on and above the diagonal)
   void* dl = ws + 5 * mat;      // B (U + diag s)^T  [r][k]  (below the diagonal)
   int* inv = reinterpret_cast<int*>(ws + 6 * mat);
-  const unsigned pg = (unsigned)((d + 255) / 256);
-  hipLaunchKernelGGL(k_lu_iota, dim3(pg), dim3(256), 0, s, inv, (int)d);
-  hipLaunchKernelGGL(k_lu_invert_perm, dim3(pg), dim3(256), 0, s, perm, inv, (int)d);
+  hipLaunchKernelGGL(k_lu_invert_perm, dim3(1), dim3(1024), 0, s, perm, inv, (int)d);
   LuSrc q{lp, up, log_s, sign_s, inv, g, (int)d};
   // The two gradient branches share nothing but their inputs, and a product with triangular K ranges ends on a few long
   // tiles that leave most of the chip idle: the lower-triangle branch runs on a stream of the library's own beside the
   // upper-triangle branch (not while model_lu_timing brackets every product with events on one stream).
   SideBranch br;
-  AE_TRY(br.begin(s, !g_timing, "model_lu_backward"));
+  // (Smaller matrices stay on one stream, where the kernels are shorter than the fork and the join: us of the call with and without it, bf16 d = 256
+  // 75 / 33, 1 024 74 / 46, 1 536 69 / 63, 2 048 74 / 73, 3 072 116 / 133, 4 096 212 / 257; binary32 256 75 / 42, 1 024 84 / 99.)
+  const bool kn = dtype == AE_BF16 && !g_timing && dense_kn_supported(d, d, d, d);     // both products read B as it lies: [k][n] and [m][k]
+  if (kn) launch_build_rows<bf16_t, LU_B>(q, b, s);
+  AE_TRY(br.begin(s, !g_timing && d >= (dtype == AE_BF16 ? 2048 : 1024), "model_lu_backward"));
   hipStream_t s2 = br.side;
   int rc = AE_OK;
   const unsigned grid = lu_grid(d * d / 8 * 4);
   if (dtype == AE_BF16) {
-    launch_build_transposed<bf16_t, LU_L>(q, lt, s); launch_build_transposed<bf16_t, LU_B>(q, bt, s);
-    launch_build_rows<bf16_t, LU_UD>(q, ud, s2); launch_build_rows<bf16_t, LU_B>(q, b, s2);
+    launch_build_transposed<bf16_t, LU_L>(q, lt, s);
+    launch_build_rows<bf16_t, LU_UD>(q, ud, s2);
+    if (!kn) { launch_build_transposed<bf16_t, LU_B>(q, bt, s); launch_build_rows<bf16_t, LU_B>(q, b, s2); }
   } else {
     launch_build_transposed<float, LU_L>(q, lt, s); launch_build_transposed<float, LU_B>(q, bt, s);
     launch_build_rows<float, LU_UD>(q, ud, s2); launch_build_rows<float, LU_B>(q, b, s2);
   }
   rc = launch_status("lu_build");
-  if (rc == AE_OK) rc = dense_product(lt, bt, dud, (int)d, dtype, CONV_TRI_UPPER_X, s);
+  if (rc == AE_OK) rc = kn ? launch_dense_kn(lt, b, dud, d, d, d, d, s, CONV_TRI_UPPER_X) : dense_product(lt, bt, dud, (int)d, dtype, CONV_TRI_UPPER_X, s);
   if (rc == AE_OK) rc = dense_product(b, ud, dl, (int)d, dtype, CONV_TRI_UPPER_W, s2);
   if (rc == AE_OK) {
     if (dtype == AE_BF16) {

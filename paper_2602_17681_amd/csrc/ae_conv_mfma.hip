@@ -2161,19 +2161,22 @@ bool dense_kn_supported(int64_t rows, int64_t k, int64_t n, int64_t group) {
   return rows % group == 0 && group % 128 == 0 && n % 128 == 0 && k % 32 == 0 && k > 0 && (rows / 128) * (n / 128) < 0x7FFFFFFF &&
          group * k * 2 < 0x7FFFFFFF && k * n * 2 < 0x7FFFFFFF;
 }
-int launch_dense_kn(const void* x, const void* w, void* y, int64_t rows, int64_t k, int64_t n, int64_t group, hipStream_t s) {
+int launch_dense_kn(const void* x, const void* w, void* y, int64_t rows, int64_t k, int64_t n, int64_t group, hipStream_t s, int tri) {
   if (!dense_kn_supported(rows, k, n, group)) return fail(AE_EINVAL, "dense_kn: shape not supported");
+  if (tri != 0 && (rows != n || k != n || group != rows || (tri != CONV_TRI_LOWER_UPPER && tri != CONV_TRI_UPPER_X))) return fail(AE_EINVAL, "dense_kn: bad triangular product");
   IgemmParams p = {};
   p.x = x; p.w = w; p.y = y;
-  p.M = rows; p.N = (int)n; p.K = (int)k; p.phases = 1; p.act = ACT_NONE; p.kn_group = (int)group;
-  const bool wide = rows % 256 == 0 && group % 256 == 0 && n % 256 == 0 && (rows / 256) * (n / 256) >= 256;
-  const int bt = wide ? 256 : 128;
-  p.tiles_n = (int)(n / bt);
-  p.tiles_mn = (int)((rows / bt) * (n / bt));
+  p.M = rows; p.N = (int)n; p.K = (int)k; p.phases = 1; p.act = ACT_NONE; p.kn_group = (int)group; p.tri = tri;
+  // (tiles of very different K ranges: as in launch_conv_mfma)
+  const bool wide = rows % 256 == 0 && group % 256 == 0 && n % 256 == 0 && (rows / 256) * (n / 256) >= (tri != 0 ? 1024 : 256);
+  const bool tall = tri != 0 && !wide && rows % 256 == 0 && (rows / 256) * (n / 128) >= 512;
+  p.tiles_n = (int)(n / (wide ? 256 : 128));
+  p.tiles_mn = (int)((rows / (wide || tall ? 256 : 128)) * p.tiles_n);
   const dim3 grid((unsigned)p.tiles_mn);
   if (wide) hipLaunchKernelGGL((k_dense<256, 256, 2, 4, 4, 0, true>), grid, dim3(512), 0, s, p);
-  else if (dense_halves(grid.x, p.K)) hipLaunchKernelGGL((k_dense<128, 128, 2, 2, 4, 0, true, 2>), grid, dim3(512), 0, s, p);
-  else if (dense_stages(grid.x, p.tiles_n, 0) == 3) hipLaunchKernelGGL((k_dense<128, 128, 2, 2, 3, 0, true>), grid, dim3(256), 0, s, p);
+  else if (tall) hipLaunchKernelGGL((k_dense<256, 128, 2, 2, 3, 0, true>), grid, dim3(256), 0, s, p);
+  else if (tri == 0 && dense_halves(grid.x, p.K)) hipLaunchKernelGGL((k_dense<128, 128, 2, 2, 4, 0, true, 2>), grid, dim3(512), 0, s, p);
+  else if (dense_stages(grid.x, p.tiles_n, tri) == 3) hipLaunchKernelGGL((k_dense<128, 128, 2, 2, 3, 0, true>), grid, dim3(256), 0, s, p);
   else hipLaunchKernelGGL((k_dense<128, 128, 2, 2, 4, 0, true>), grid, dim3(256), 0, s, p);
   return launch_status("dense_kn");
 }

@@ -238,7 +238,7 @@ int launch_tri_pairs(const TriProduct* f, int count, int dp, int b, int d, bool 
 // y [d][d] = x w^T, x upper and w^T lower triangular (rows of ld); the entries in rows and columns below tri_last_split(d) are y + y2
 int tri_last_split(int d);
 int launch_tri_last(const float* x, const float* w, int ld, float* y, float* y2, int d, hipStream_t s);
-int launch_dense_kn(const void* x, const void* w, void* y, int64_t rows, int64_t k, int64_t n, int64_t group, hipStream_t s);
+int launch_dense_kn(const void* x, const void* w, void* y, int64_t rows, int64_t k, int64_t n, int64_t group, hipStream_t s, int tri = 0);   // tri: CONV_TRI_LOWER_UPPER, _UPPER_X of square products
 // The matrix-core kernel for any channel counts: a.x and a.w hold chan_pad(cin) channels per pixel and per tap, zeros
 // behind the layer's own (launch_pad_channels, the packing kernels); a.y has plain rows of cout.
 bool conv_chunks_supported(const ConvArgs& a);
