@@ -183,8 +183,8 @@ int model_get_conv_output(ae_model* m, int step, int64_t chw[3], float* out_nchw
  * floating-point operations and bytes of one launch (2*M*N*K for the convolution
  * family; bytes every operand must cross HBM at least once).  name may be NULL. */
 int model_timing_enable(ae_model* m, int on);
-/* Scheduling of the backward pass (an execution detail, not part of the method).  By
- * default (on = 1) model_backward enqueues the weight-gradient kernels on a second stream
+/* Scheduling of the backward pass (an execution detail, not part of the method).  With on = 1, and by default
+ * where the network's work outweighs the forks and joins, model_backward enqueues the weight-gradient kernels on a second stream
  * owned by the handle, ordered against the caller's stream by events in both directions:
  * everything enqueued on the caller's stream after model_backward returns sees all
  * gradients.  on = 0 keeps every kernel on the caller's stream in program order (also the

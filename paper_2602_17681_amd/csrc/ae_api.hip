@@ -24,7 +24,8 @@
 // handle: forked by an event once the layer's conv-output gradient exists, joined by an event
 // before that gradient's buffer is written again (two such buffers alternate between layers)
 // and at the end of the pass.  With per-kernel timing enabled, or overlap switched off,
-// everything runs on the caller's stream in program order.
+// everything runs on the caller's stream in program order; so does a network of little work unless overlap is
+// switched on (overlap_pays).
 struct TimeSlot {
   std::string name;
   double flops = 0.0, bytes = 0.0;  // algorithmic work of one launch
@@ -52,6 +53,8 @@ struct ae_model {
   float* splitk_ws = nullptr;
   char* dypad[3] = {nullptr, nullptr, nullptr};   // padded conv-output gradients: beside draw_buf[0], draw_buf[1], and of layers that stay in order
   bool overlap = true;
+  bool overlap_asked = false;      // model_set_overlap: whatever the size
+  bool overlap_pays = true;        // enough work behind the forks and joins (overlap_pays)
   hipStream_t side = nullptr;
   hipEvent_t ev_fork = nullptr;
   hipEvent_t ev_wdone[2] = {nullptr, nullptr};   // weight gradient reading draw_buf[i] has finished
@@ -130,9 +133,23 @@ class TimedScope {
   } while (0)
 #define TIMED(step, tag, flops, bytes, call) TIMED_ON(s, step, tag, flops, bytes, call)
 
+// Does the second stream pay?  A fork and a join take the host 15 to 20 us, as long as three launches, and each leaves the GPU waiting: a
+// network whose layers are that short is faster in order.  The line is drawn by the multiply-adds of a forward pass (binary32: six bf16
+// products each, at twice the time in practice).  us per training step with two streams / one, 10^9 multiply-adds of the step (three
+// times those of the forward pass), bf16: 0.01 372 / 238, 0.25 381 / 251, 3.5 730 / 706, 8.6 582 / 538, 8.8 486 / 446, 18.7 931 / 914, 29 724 / 742,
+// 52 905 / 928, 56 1 003 / 1 007, 75 1 046 / 1 069, 599 2 254 / 2 395; binary32: 0.01 368 / 244, 1.3 422 / 386, 6.6 716 / 702, 8.8 722 / 705, 11.7 699 / 711,
+// 47 1 283 / 1 311.
+bool overlap_pays(const Plan& P) {
+  double macs = 0.0;
+  for (const Step& st : P.steps)
+    if (st.kind == ST_CONV)       // (a 3x3 convolution behind an upsample: four products a channel)
+      macs += (double)P.batch * st.hc * st.wc * st.cout * st.cin * (st.up && st.k == 3 ? 4 : st.k * st.k);
+  return macs >= (P.dtype == AE_BF16 ? 8e9 : 3.4e9);
+}
+
 // Side stream of the backward pass: created on first use; null when the pass runs on one stream.
 hipStream_t side_stream(ae_model* m) {
-  if (!m->overlap || m->timing) return nullptr;
+  if (!m->overlap || m->timing || !(m->overlap_asked || m->overlap_pays)) return nullptr;
   if (!m->side) {
     if (hipStreamCreateWithFlags(&m->side, hipStreamNonBlocking) != hipSuccess) { m->side = nullptr; return nullptr; }
     bool ok = hipEventCreateWithFlags(&m->ev_fork, hipEventDisableTiming) == hipSuccess;
@@ -698,6 +715,7 @@ int model_create(const char* layer_spec, int batch, int dtype, int bn_mode, ae_m
                 (long long)m->plan.ws_bytes, hipGetErrorString(e));
   }
   Plan& P = m->plan;
+  m->overlap_pays = overlap_pays(P);
   for (Step& st : P.steps) {
     st.out = st.off_out >= 0 ? m->ws + st.off_out : nullptr;
     st.raw = st.off_raw >= 0 ? m->ws + st.off_raw : nullptr;
@@ -788,7 +806,7 @@ int model_timing_enable(ae_model* m, int on) {
 
 int model_set_overlap(ae_model* m, int on) {
   if (!m) return fail(AE_EINVAL, "model_set_overlap: null model");
-  m->overlap = on != 0;
+  m->overlap = m->overlap_asked = on != 0;
   return AE_OK;
 }
 
