@@ -275,7 +275,6 @@ void launch_build(const LuSrc& q, void* out, hipStream_t s) {
 // 32 (512) matrices of 128, bfloat16 in and out: four wavefronts of one 32 x 32 tile, operands one after the other, 11.1 (88) us composing
 // and 13.9 (240) backward; this way 10.7 (66) and 11.3 (168).
 // LDS rows are 132 floats: the 16-byte fragment reads of 16 rows and the 4-byte ones of two rows fall into different banks.
-typedef float floatx16 __attribute__((ext_vector_type(16)));
 constexpr int kSmallLd = 132;
 
 __device__ __forceinline__ LuSrc small_src(const float* lp, const float* up, const float* log_s, const float* sign_s, int d, int m) {
@@ -338,26 +337,7 @@ struct SmallStage {
   }
 };
 
-// c += the 32 x 32 product over k = k0 .. k1 - 1 (multiples of 8): a(h, k, t), b(h, k, t) give this lane's operand for the k's
-// k + 4 h + t, h = lane / 32 (the low lanes' k is paired with the high lanes' in one MFMA; both operands use the same pairing).
-// Two partial sums: half the roundings at the size of the whole, and two MFMA chains in flight.
-template <typename A, typename B>
-__device__ __forceinline__ void small_mma(floatx16& c, int k0, int k1, A a, B b) {
-  floatx16 c2 = {};
-#pragma unroll 2
-  for (int k = k0; k < k1; k += 8) {
-    float av[4], bv[4];
-    a(k, av);
-    b(k, bv);
-#pragma unroll
-    for (int t = 0; t < 4; t += 2) {
-      c = __builtin_amdgcn_mfma_f32_32x32x2f32(av[t], bv[t], c, 0, 0, 0);
-      c2 = __builtin_amdgcn_mfma_f32_32x32x2f32(av[t + 1], bv[t + 1], c2, 0, 0, 0);
-    }
-  }
-  c += c2;
-}
-// The same on tiles of 16 x 16, two of them side by side (columns lane % 16 and 16 on): a(k, v), b(k, h, v) give this lane's operands for
+// c += the product over k = k0 .. k1 - 1 on tiles of 16 x 16, two of them side by side (columns lane % 16 and 16 on): a(k, v), b(k, h, v) give this lane's operands for
 // the k's k + 8 (lane / 16) + 0 .. 7 (element e of a lane: row 4 (lane / 16) + e); k0 and k1 are multiples of 32.
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 template <typename A, typename B>
@@ -377,8 +357,6 @@ __device__ __forceinline__ void small_mma16(floatx4 (&c)[2], int k0, int k1, A a
 #pragma unroll
   for (int h = 0; h < 2; ++h) c[h] += (s[0][h] + s[1][h]) + (s[2][h] + s[3][h]);
 }
-// element e of a lane's accumulator: row 8 (e / 4) + 4 (lane / 32) + e % 4, column lane % 32
-__device__ __forceinline__ int small_row(int lane, int e) { return (e >> 2) * 8 + (lane >> 5) * 4 + (e & 3); }
 // sums that are NaN replaced by value(e): a zero of a triangle meets an infinity in a tile's K range, where the sum over the
 // triangle alone need not be NaN (nothing but infinities and NaN gets there; one fused multiply-add per sum otherwise)
 template <typename V, typename VALUE>
@@ -574,6 +552,11 @@ __device__ __forceinline__ void small_tri_merge16(const SmallTri& x, float* tb, 
   const int pr = tid >> 6, t = tid & 63, tr = t >> 3, tc = t & 7, o0 = 32 * pr, o1 = o0 + 16;
   float* tp = tb + pr * 256;
   float acc[2][2] = {};
+  if (tid >= 256) {                                    // (whole wavefronts, where one factor has 512 threads)
+    __syncthreads();
+    __syncthreads();
+    return;
+  }
 #pragma unroll
   for (int k = 0; k < 16; ++k)                         // T = M21 X11:  X11[k][c] = 0 for k < c
 #pragma unroll
@@ -624,52 +607,61 @@ __device__ __forceinline__ void small_tri_merge16(const SmallTri& x, float* tb, 
     for (int j = 0; j < 2; ++j) x.at(o1 + tr + 8 * i, o0 + tc + 8 * j) = -acc[i][j];   // (M21 was last read before the barrier)
   __syncthreads();
 }
+// (eight wavefronts: one or two 16 x 16 tiles each, as small_mma16)
 template <int B>
 __device__ __forceinline__ void small_tri_merge(const SmallTri& x, float* tb, int tid) {
-  constexpr int N = B / 32, LT = B + 4;                // tiles per side; row length of T
-  const int w = tid >> 6, lane = tid & 63, h = lane >> 5, pr = w / (N * N), ti = (w / N) % N, tj = w % N;
-  const int o0 = 2 * pr * B, o1 = o0 + B, r = ti * 32 + (lane & 31), c = tj * 32 + (lane & 31);
-  float* tp = tb + (pr & 1) * (B * LT);
-  const bool on = o1 < 128;
-  floatx16 acc = {};
-  if (on) {
-    small_mma(acc, tj * 32, B,                         // T = M21 X11:  X11[k][c] = 0 for k < c
-              [&](int k, float (&v)[4]) {
+  constexpr int NT = B / 32, LT = B + 4, COLS = B / (16 * NT), TASKS = B / 16 * COLS;   // tiles per wavefront; row length of T; wavefronts per row of tiles, per pair
+  static_assert(TASKS * (64 / B) == 8, "one task each");
+  const int w = tid >> 6, lane = tid & 63, lc = lane & 15, g8 = (lane >> 4) * 8, pr = w / TASKS, t = w % TASKS;
+  const int o0 = 2 * pr * B, o1 = o0 + B, r0 = t / COLS * 16, c0 = t % COLS * 16 * NT;
+  float* const tp = tb + pr * (B * LT);
+  auto product = [&](floatx4 (&c)[NT], int k0, int k1, auto a, auto b) {
+    floatx4 s[4][NT] = {};
+#pragma unroll 1
+    for (int k = k0; k < k1; k += 32) {
+      float av[8], bv[NT][8];
 #pragma unroll
-                for (int t = 0; t < 4; ++t) v[t] = x.at(o1 + r, o0 + k + 4 * h + t);
-              },
-              [&](int k, float (&v)[4]) {
+      for (int u = 0; u < 8; ++u) {
+        av[u] = a(k + g8 + u);
 #pragma unroll
-                for (int t = 0; t < 4; ++t) { const int kk = k + 4 * h + t; const float u = x.at(o0 + kk, o0 + c); v[t] = kk >= c ? u : 0.0f; }
-              });
-    small_resum_nan(acc, [&](int e) {
+        for (int h = 0; h < NT; ++h) bv[h][u] = b(k + g8 + u, c0 + 16 * h + lc);
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+#pragma unroll
+        for (int h = 0; h < NT; ++h) s[u & 3][h] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u], bv[h][u], s[u & 3][h], 0, 0, 0);
+    }
+#pragma unroll
+    for (int h = 0; h < NT; ++h) c[h] = (s[0][h] + s[1][h]) + (s[2][h] + s[3][h]);
+  };
+  floatx4 acc[NT];
+  product(acc, c0 & ~31, B, [&](int k) { return x.at(o1 + r0 + lc, o0 + k); },   // T = M21 X11:  X11[k][c] = 0 for k < c
+          [&](int k, int c) { const float u = x.at(o0 + k, o0 + c); return k >= c ? u : 0.0f; });
+#pragma unroll
+  for (int h = 0; h < NT; ++h) {
+    const int c = c0 + 16 * h + lc;
+    small_resum_nan(acc[h], [&](int e) {
       float v = 0.0f;
-      for (int k = c; k < B; ++k) v = fmaf(x.at(o1 + ti * 32 + small_row(lane, e), o0 + k), x.at(o0 + k, o0 + c), v);
+      for (int k = c; k < B; ++k) v = fmaf(x.at(o1 + r0 + 4 * (lane >> 4) + e, o0 + k), x.at(o0 + k, o0 + c), v);
       return v;
     });
 #pragma unroll
-    for (int e = 0; e < 16; ++e) tp[(ti * 32 + small_row(lane, e)) * LT + c] = acc[e];
+    for (int e = 0; e < 4; ++e) tp[(r0 + 4 * (lane >> 4) + e) * LT + c] = acc[h][e];
   }
   __syncthreads();
-  if (on) {
-    acc = floatx16{};
-    small_mma(acc, 0, ti * 32 + 32,                    // X21 = -X22 T:  X22[r][k] = 0 for k > r
-              [&](int k, float (&v)[4]) {
+  product(acc, 0, (r0 & ~31) + 32, [&](int k) { const float u = x.at(o1 + r0 + lc, o1 + k); return k <= r0 + lc ? u : 0.0f; },   // X21 = -X22 T:  X22[r][k] = 0 for k > r
+          [&](int k, int c) { return tp[k * LT + c]; });
 #pragma unroll
-                for (int t = 0; t < 4; ++t) { const int kk = k + 4 * h + t; const float u = x.at(o1 + r, o1 + kk); v[t] = kk <= r ? u : 0.0f; }
-              },
-              [&](int k, float (&v)[4]) {
-#pragma unroll
-                for (int t = 0; t < 4; ++t) v[t] = tp[(k + 4 * h + t) * LT + c];
-              });
-    small_resum_nan(acc, [&](int e) {
-      const int row = ti * 32 + small_row(lane, e);
+  for (int h = 0; h < NT; ++h) {
+    const int c = c0 + 16 * h + lc;
+    small_resum_nan(acc[h], [&](int e) {
+      const int row = r0 + 4 * (lane >> 4) + e;
       float v = 0.0f;
       for (int k = 0; k <= row; ++k) v = fmaf(x.at(o1 + row, o1 + k), tp[k * LT + c], v);
       return v;
     });
 #pragma unroll
-    for (int e = 0; e < 16; ++e) x.at(o1 + ti * 32 + small_row(lane, e), o0 + c) = -acc[e];   // (M21 was last read before the barrier)
+    for (int e = 0; e < 4; ++e) x.at(o1 + r0 + 4 * (lane >> 4) + e, o0 + c) = -acc[h][e];   // (M21 was last read before the barrier)
   }
   __syncthreads();
 }
@@ -747,7 +739,7 @@ __global__ __launch_bounds__(512) void k_lu_small_solve(const float* __restrict_
     float av[8];
 #pragma unroll
     for (int t = 0; t < 8; ++t) av[t] = a(lc, g8 + t);
-    floatx4 c = {}, c2 = {};                             // (as small_mma)
+    floatx4 c = {}, c2 = {};                             // (two partial sums)
 #pragma unroll
     for (int t = 0; t < 8; t += 2) {
       c = __builtin_amdgcn_mfma_f32_16x16x4f32(av[t], bv[t], c, 0, 0, 0);
@@ -836,33 +828,37 @@ __global__ __launch_bounds__(512) void k_lu_small_solve(const float* __restrict_
   }
 }
 
-// X_bb = M_bb^-1 for every 128 x 128 diagonal block b of M = L (which 0) or (U + diag s)^T (1) (one workgroup of 256 threads
+// X_bb = M_bb^-1 for every 128 x 128 diagonal block b of M = L (which 0) or (U + diag s)^T (1) (one workgroup of 512 threads
 // each; blockIdx.y + first: which), inverted in place in LDS as above; the block and its transpose are written into the full
 // matrices lo (lower triangular) and hi of the factor.
 struct TriOut { float* lo; float* hi; };
-__global__ __launch_bounds__(256) void k_tri_diag_inverse(LuSrc q, int dp, int first, TriOut l, TriOut u) {
+__global__ __launch_bounds__(512) void k_tri_diag_inverse(LuSrc q, int dp, int first, TriOut l, TriOut u) {
   __shared__ float pk[128 * 129];
   __shared__ float tb[64 * 68];
   const int tid = threadIdx.x, o = blockIdx.x * 128, which = first + (int)blockIdx.y;
   const float* src = which == 0 ? q.lp : q.up;
-  const bool vec = small_vec(src, q.d);
+  const float4 zero = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  auto get = [&](int e, bool wide) {                     // 128 x 32 chunks of four columns
+    const int i = e >> 5, c = (e & 31) * 4;
+    const bool in = o + i < q.d && o + c < q.d && (which == 0 ? c < i : c + 3 > i);
+    return in ? small_load4<float>(src, q.d, o + i, o + c, wide) : zero;
+  };
+  auto put = [&](int e, const float4& v) {
+    const int i = e >> 5, c = (e & 31) * 4;
+    const float w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-  for (int b0 = 0; b0 < 16; b0 += 8) {                   // 128 x 32 chunks of four columns, eight per thread in flight
+    for (int s = 0; s < 4; ++s)
+      if (c + s != i) pk[i * 129 + c + s] = w[s];
+  };
+  if (small_vec(src, q.d)) {
     float4 v[8];
 #pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      const int e = tid + (b0 + t) * 256, i = e >> 5, c = (e & 31) * 4;
-      const bool in = o + i < q.d && o + c < q.d && (which == 0 ? c < i : c + 3 > i);
-      v[t] = in ? small_load4<float>(src, q.d, o + i, o + c, vec) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-    }
+    for (int t = 0; t < 8; ++t) v[t] = get(tid + t * 512, true);
 #pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      const int e = tid + (b0 + t) * 256, i = e >> 5, c = (e & 31) * 4;
-      const float w[4] = {v[t].x, v[t].y, v[t].z, v[t].w};
-#pragma unroll
-      for (int s = 0; s < 4; ++s)
-        if (c + s != i) pk[i * 129 + c + s] = w[s];
-    }
+    for (int t = 0; t < 8; ++t) put(tid + t * 512, v[t]);
+  } else {
+#pragma unroll 1
+    for (int e = tid; e < 4096; e += 512) put(e, get(e, false));
   }
   if (tid < 128) pk[tid * 129 + tid] = which == 0 || o + tid >= q.d ? 1.0f : q.sign[o + tid] * expf(q.log_s[o + tid]);
   __syncthreads();
@@ -872,7 +868,8 @@ __global__ __launch_bounds__(256) void k_tri_diag_inverse(LuSrc q, int dp, int f
   small_tri_merge<32>(m, tb, tid);
   small_tri_merge<64>(m, tb, tid);
   const TriOut out = which == 0 ? l : u;
-  for (int e = tid; e < 128 * 128; e += 256) {
+#pragma unroll 4
+  for (int e = tid; e < 128 * 128; e += 512) {
     const int i = e >> 7, j = e & 127;
     out.lo[(int64_t)(o + i) * dp + o + j] = j <= i ? m.at(i, j) : 0.0f;
     out.hi[(int64_t)(o + i) * dp + o + j] = i <= j ? m.at(j, i) : 0.0f;
@@ -1034,7 +1031,7 @@ int64_t tri_padded_size(int64_t d) {
 // lower and upper triangular; tt is scratch; all [dp][dp] binary32.
 struct TriWork { float* lo; float* hi; float* tt; };
 int tri_inverse(const LuSrc& q, int dp, int first, int count, const TriWork& l, const TriWork& u, hipStream_t s) {
-  hipLaunchKernelGGL(k_tri_diag_inverse, dim3(dp / 128, count), dim3(256), 0, s, q, dp, first, TriOut{l.lo, l.hi}, TriOut{u.lo, u.hi});
+  hipLaunchKernelGGL(k_tri_diag_inverse, dim3(dp / 128, count), dim3(512), 0, s, q, dp, first, TriOut{l.lo, l.hi}, TriOut{u.lo, u.hi});
   AE_TRY(launch_status("tri_diag_inverse"));
   for (int b = 128; b < dp; b *= 2) {
     const TriProduct t[2] = {{l.hi, q.lp, q.d, l.tt, nullptr, false}, {u.lo, q.up, q.d, u.tt, nullptr, true}};
