@@ -747,9 +747,16 @@ __global__ __launch_bounds__(512) void k_lu_small_solve(const float* __restrict_
     }
     return c + c2;
   };
-  constexpr int G = 4 / NC;                              // wavefronts per 16 columns; one alone waits for nobody
+  constexpr int G = 4 / NC;                              // wavefronts per 16 columns; one alone waits for nobody, ...
   const int cc = wave / G * 16, g = wave % G;
-  auto sync = [&]() { if constexpr (G > 1) __syncthreads(); };
+  // ... but its lanes read what others of them have written: LDS serves a wavefront in order, and this keeps the compiler to it
+  auto wave_sync = [&]() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  auto sync = [&]() { if constexpr (G > 1) __syncthreads(); else wave_sync(); };
+  auto sync_same = [&]() { if constexpr (NC == 4) wave_sync(); };  // where y is z: rows that all lanes have read are overwritten
   // (a zero outside a triangle, or above the one of a column, may have met an infinity: NaN is summed again over k = first .. last(row))
   auto resum = [&](floatx4& c, auto a, const float* b, auto first, auto last) {
     if (fmaf(c[0], 0.0f, fmaf(c[1], 0.0f, fmaf(c[2], 0.0f, c[3] * 0.0f))) == 0.0f) return;
@@ -775,6 +782,7 @@ __global__ __launch_bounds__(512) void k_lu_small_solve(const float* __restrict_
         c[h] = product(a);
         resum(c[h], a, y + o * LY, [&](int) { return max(pc[cc + lc] - o, 0); }, [&](int row) { return r + row; });
       }
+      sync_same();
 #pragma unroll
       for (int h = 0; h < RT; ++h)
 #pragma unroll
@@ -806,6 +814,7 @@ __global__ __launch_bounds__(512) void k_lu_small_solve(const float* __restrict_
         c[h] = product(a);
         resum(c[h], a, z + o * LY, [&](int row) { return r + row; }, [](int) { return 31; });
       }
+      sync_same();
 #pragma unroll
       for (int h = 0; h < RT; ++h)
 #pragma unroll

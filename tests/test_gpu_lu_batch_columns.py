@@ -45,3 +45,24 @@ def test_an_infinity_stays_in_its_columns_and_rows(count, d, i, j, which):
         ae.model_lu_inverse_batch(lp, up, ls, sign, perm, count, d, ai)
         out.append(ai[:, :, perm[0].long() > j] if which == "L" else ai[:, j + 1:])
     assert ((out[0] - out[1]).norm() <= 1e-6 * out[1].norm()).item()
+
+
+# the infinity sends whole columns through the sums that are taken again
+@pytest.mark.parametrize("count,d", [(129, 128), (129, 97), (65, 128), (129, 64)])
+@pytest.mark.parametrize("special", [0.0, float("inf")])
+def test_a_matrix_does_not_depend_on_how_many_there_are(count, d, special):
+    """Two and four blocks of columns per workgroup (a wavefront or two per 16 columns) against one (four): the same sums, the same bits."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(count * d)
+    rnd = lambda *s: torch.randn(*s, device="cuda", generator=g)      # noqa: E731
+    lp, up, ls = rnd(count, d, d) * d ** -0.5, rnd(count, d, d) * d ** -0.5, 0.3 * rnd(count, d)
+    if special:
+        lp[:, d - 8, d // 3] = special
+    sign, perm = torch.where(rnd(count, d) < 0, -1.0, 1.0), torch.argsort(torch.rand(count, d, device="cuda", generator=g), dim=1).to(torch.int32)
+    many, few = torch.empty(count, d, d, device="cuda"), torch.empty(count, d, d, device="cuda")
+    ae.model_lu_inverse_batch(lp, up, ls, sign, perm, count, d, many)
+    for i in range(0, count, 32):
+        n, s = min(32, count - i), slice(i, min(count, i + 32))
+        ae.model_lu_inverse_batch(lp[s], up[s], ls[s], sign[s], perm[s], n, d, few[s])
+    assert torch.equal(torch.nan_to_num(many, nan=123.0), torch.nan_to_num(few, nan=123.0))
+    assert bool(torch.isfinite(many).all()) == (special == 0.0)
