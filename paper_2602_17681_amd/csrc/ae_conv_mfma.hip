@@ -634,16 +634,18 @@ struct SlabReads<KS, KS, MI, NJ, BKB> {
   static __device__ __forceinline__ void run(uint4v (&)[KS][MI], uint4v (&)[KS][NJ], unsigned, unsigned, const int (&)[KS]) {}
 };
 
-// Which tile a workgroup computes, in what order (ONE_SPLIT: the launch does not split K)
+// Which tile a workgroup computes, in what order (ONE_SPLIT: the launch does not split K; TRI: a triangular K range, p.tri).
+// The modes are decided at run time, but in instances of their own: every workgroup would pay for them before its first load
+// (Monte-Carlo estimates with the modes in every instance and without: batch 5 783 439 -> 427 us, 12 716 576 -> 566, 65 536 1 524 -> 1 516).
 struct IgemmTileId { int64_t m; int n, split, phase; };
-template <int BM, int BN, bool ONE_SPLIT>
+template <int BM, int BN, bool ONE_SPLIT, bool TRI>
 __device__ __forceinline__ IgemmTileId igemm_tile_id(const IgemmParams& p) {
   IgemmTileId t;
   int lb0 = xcd_logical_block((int)blockIdx.x, (int)gridDim.x);
   // triangular products: tile rows differ in work by an order of magnitude, so neighbouring tiles go to different
   // XCDs (the hardware's own round-robin) instead of one contiguous range per XCD, the longest K ranges first
-  if (p.tri != 0) lb0 = p.tri == 1 ? (int)gridDim.x - 1 - (int)blockIdx.x : (int)blockIdx.x;
-  if (p.tri == 4 && (gridDim.x & 63) == 0) {    // runs of eight consecutive tiles per XCD (they share an operand panel in its L2), runs interleaved
+  if (TRI) lb0 = p.tri == 1 ? (int)gridDim.x - 1 - (int)blockIdx.x : (int)blockIdx.x;
+  if (TRI && p.tri == 4 && (gridDim.x & 63) == 0) {    // runs of eight consecutive tiles per XCD (they share an operand panel in its L2), runs interleaved
     const int i = (int)blockIdx.x >> 3, x = (int)blockIdx.x & 7;
     lb0 = ((((i >> 3) << 3) + x) << 3) + (i & 7);
   }
@@ -658,13 +660,13 @@ __device__ __forceinline__ IgemmTileId igemm_tile_id(const IgemmParams& p) {
   const int gm = min(p.tiles_mn / p.tiles_n - grp * kGroupM, kGroupM);
   t.n = in_grp / gm;
   t.m = grp * kGroupM + in_grp % gm;
-  if (p.tri == 3 || p.tri == 6 || p.tri == 7) { // K range [column, K) or [0, column]: walk column by column, the longest first
+  if (TRI && (p.tri == 3 || p.tri == 6 || p.tri == 7)) { // K range [column, K) or [0, column]: walk column by column, the longest first
     const int tiles_m = p.tiles_mn / p.tiles_n;
     t.n = lb / tiles_m;
     t.m = lb - t.n * tiles_m;
     if (p.tri == 6) t.n = p.tiles_n - 1 - t.n;
   }
-  if (p.tri == 4 && p.tiles_mn == p.tiles_n * p.tiles_n) {
+  if (TRI && p.tri == 4 && p.tiles_mn == p.tiles_n * p.tiles_n) {
     // K range [max(row, column), K): on a square tile grid walk the L-shaped shells max(tile row, tile column) = 0, 1, ...
     // so that the workgroups are dispatched longest first and the hardware's in-order dispatch balances the rest
     int sh = (int)sqrtf((float)lb);
@@ -677,9 +679,10 @@ __device__ __forceinline__ IgemmTileId igemm_tile_id(const IgemmParams& p) {
   return t;
 }
 // its K range (triangular operands: see IgemmParams::tri); false: no output of the tile is wanted
-template <int BM, int BN>
+template <int BM, int BN, bool TRI>
 __device__ __forceinline__ bool igemm_k_range(const IgemmParams& p, int64_t m0, int n0, int& k_lo, int& k_hi) {
   k_lo = 0; k_hi = p.K;
+  if (!TRI) return true;
   if (p.tri == 1) k_hi = (int)min((int64_t)p.K, min(m0 + BM, (int64_t)n0 + BN));
   else if (p.tri == 2) { if ((int64_t)n0 + BN <= m0) return false; k_lo = (int)m0; }
   else if (p.tri == 3) { if ((int64_t)n0 >= m0 + BM) return false; k_lo = n0; }
@@ -690,8 +693,8 @@ __device__ __forceinline__ bool igemm_k_range(const IgemmParams& p, int64_t m0, 
   return true;
 }
 
-// Tiles and K ranges of the triangular inverse's products (IgemmParams::tm)
-enum { TRI_NO = 0, TRI_PAIRS = 1, TRI_LAST = 2 };
+// Tiles and K ranges of the triangular inverse's products (IgemmParams::tm); TRI_RANGE: those of IgemmParams::tri
+enum { TRI_NO = 0, TRI_PAIRS = 1, TRI_LAST = 2, TRI_RANGE = 3 };
 struct TriTile { int which, m0, n0, k_lo, k_hi; bool second; };      // matrix; second half of a K range
 template <int BM, int BN>
 __device__ __forceinline__ bool tri_pair_tile(const IgemmParams& p, TriTile& t) {
@@ -804,11 +807,12 @@ __device__ __forceinline__ void replace_bits(floatx16 (&acc)[MI][NJ], uint64_t b
 // offsets are formed for every slab, not once per tap, a dozen VALU instructions per 16 bytes loaded.
 // Measured (bf16, 24 x 36 x 60 pixels): 48 -> 80 channels, 3x3, 25 us = 143 TFLOP/s, where one thread per output on the
 // vector ALUs took 3.4 ms; two such layers at 64 x 64 x 8 forward and backward 140 us against 11.4 ms.
-template <typename T, int BM, int BN, int WGM, int WGN, int BKB, bool INTERIOR, bool DMA, int EPI = 0, bool CHUNKS = false, bool DIRECT = false>
+template <typename T, int BM, int BN, int WGM, int WGN, int BKB, bool INTERIOR, bool DMA, int EPI = 0, bool CHUNKS = false, bool DIRECT = false, bool TRI = false>
 __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(2))) void k_igemm(IgemmParams p) {
   static_assert(!CHUNKS || (!INTERIOR && DMA && EPI == 0), "the chunk walk exists for checked tiles through the DMA pipeline");
   static_assert(EPI == 0 || INTERIOR, "the special epilogues exist for check-free tiles only");
   static_assert(!DIRECT || (!INTERIOR && sizeof(T) == 2), "bf16, checked tiles");
+  static_assert(!TRI || (EPI == 0 && !CHUNKS && !DIRECT), "dense products");
   static_assert(WGM * WGN == 4 || WGM * WGN == 8, "four or eight wavefronts per workgroup");
   constexpr int NT = WGM * WGN * 64;            // threads: all of them load, each wavefront owns a WM x WN part of the tile
   static_assert(BKB == 64 || BKB == 128, "slab row bytes");
@@ -831,7 +835,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WGN, wn = wave % WGN;
-  const IgemmTileId tile = igemm_tile_id<BM, BN, INTERIOR>(p);
+  const IgemmTileId tile = igemm_tile_id<BM, BN, INTERIOR, TRI>(p);
   const int phase = tile.phase, split = tile.split;
   const int64_t tile_m = tile.m;
   const int tile_n = tile.n;
@@ -868,7 +872,7 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
   }
 
   int k_lo, k_hi;
-  if (!igemm_k_range<BM, BN>(p, m0, n0, k_lo, k_hi)) return;
+  if (!igemm_k_range<BM, BN, TRI>(p, m0, n0, k_lo, k_hi)) return;
   const int kt_lo = k_lo / BK, kt_hi = (k_hi + BK - 1) / BK;
   const int kt0 = INTERIOR ? kt_lo : max(kt_lo, split * p.slabs_per_split);   // first K slab of this workgroup
   // CHUNKS: the tap and the chunk within it of this lane's next load (q = chunk index along K)
@@ -1111,7 +1115,7 @@ __device__ __forceinline__ void tr_read_at(TrFrag& f, unsigned addr) {
 // KN: the second operand lies [k][n] (launch_dense_kn): a slab is 32 k-rows of it, read with the transposing LDS reads; same sums in
 // the same order.  d = 4 096: 126 us as well.  KG = 2: dense_halves.
 // ---------------------------------------------------------------------------
-template <int BM, int BN, int WGM, int WGN, int NSTAGE, int EPI = 0, bool KN = false, int KG = 1>
+template <int BM, int BN, int WGM, int WGN, int NSTAGE, int EPI = 0, bool TRI = false, bool KN = false, int KG = 1>
 __global__ __launch_bounds__(WGM * WGN * 64 * KG) __attribute__((amdgpu_waves_per_eu(2))) void k_dense(IgemmParams p) {
   constexpr int NT = WGM * WGN * 64, BKB = 64, BK = 32;
   constexpr int WM = BM / WGM, WN = BN / WGN, MI = WM / 32, NJ = WN / 32;
@@ -1126,11 +1130,11 @@ __global__ __launch_bounds__(WGM * WGN * 64 * KG) __attribute__((amdgpu_waves_pe
   char* const sB = smem + NSTAGE * SA;
   const int tid = KG == 1 ? (int)threadIdx.x : (int)threadIdx.x - kg * NT, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
-  const IgemmTileId tile = igemm_tile_id<BM, BN, true>(p);
+  const IgemmTileId tile = igemm_tile_id<BM, BN, true, TRI>(p);
   const int64_t m0 = tile.m * BM;
   const int n0 = tile.n * BN;
   int k_lo, k_hi;
-  if (!igemm_k_range<BM, BN>(p, m0, n0, k_lo, k_hi)) return;
+  if (!igemm_k_range<BM, BN, TRI>(p, m0, n0, k_lo, k_hi)) return;
   const int KT = ((k_hi + BK - 1) / BK - k_lo / BK) / KG, kt0 = k_lo / BK + kg * KT;
   const unsigned row_bytes = (unsigned)p.K * 2u;
   const unsigned w_row = KN ? (unsigned)p.N * 2u : row_bytes;
@@ -1317,13 +1321,15 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
   __shared__ float sRed[WGM][2][BN];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WGN, wn = wave % WGN;
-  static_assert(TRI == TRI_NO || (INTERIOR && EPI == 0 && !CONV), "dense products");
+  static_assert(TRI == TRI_NO || (EPI == 0 && !CONV), "dense products");
+  constexpr bool WALK = TRI == TRI_PAIRS || TRI == TRI_LAST;
+  static_assert(!WALK || INTERIOR, "check-free tiles");
   IgemmTileId tile = {};
   int64_t m0;
   int n0, k_lo, k_hi;
-  const int ldx = TRI != TRI_NO ? p.ldx : p.K, ldw = TRI != TRI_NO ? p.ldw : p.K;
+  const int ldx = WALK ? p.ldx : p.K, ldw = WALK ? p.ldw : p.K;
   float* yt = nullptr;
-  if constexpr (TRI != TRI_NO) {
+  if constexpr (WALK) {
     TriTile t;
     if (!(TRI == TRI_PAIRS ? tri_pair_tile<BM, BN>(p, t) : tri_last_tile<BM, BN>(p, t))) return;
     m0 = t.m0; n0 = t.n0; k_lo = t.k_lo; k_hi = t.k_hi;
@@ -1332,10 +1338,10 @@ __global__ __launch_bounds__(WGM * WGN * 64) __attribute__((amdgpu_waves_per_eu(
     p.y = t.which ? p.tm[1].y : p.tm[0].y;
     yt = t.which ? p.tm[1].yt : p.tm[0].yt;
   } else {
-    tile = igemm_tile_id<BM, BN, INTERIOR>(p);
+    tile = igemm_tile_id<BM, BN, INTERIOR, TRI == TRI_RANGE>(p);
     m0 = tile.m * BM;
     n0 = tile.n * BN;
-    if (!igemm_k_range<BM, BN>(p, m0, n0, k_lo, k_hi)) return;
+    if (!igemm_k_range<BM, BN, TRI == TRI_RANGE>(p, m0, n0, k_lo, k_hi)) return;
   }
   // slabs of 16 (K ranges start at multiples of 32)
   const int kt0 = INTERIOR ? k_lo / 16 : max(k_lo / 16, tile.split * p.slabs_per_split);
@@ -1806,15 +1812,15 @@ IgemmTile pick_tile(int64_t M, int cout, int cin, int es, bool wide = true, int 
 // LDS stages of k_dense with 128 x 128 tiles.  Three (50 KiB) let a compute unit hold three workgroups, four (67 KiB) two whose
 // loads run a slab further ahead.  Three where the compute units share the tiles unevenly (from 352) and where they save a round of
 // workgroups (513 to 768); four where there is at most one workgroup per compute unit or little more, beyond 768, where a few
-// columns of tiles stream their rows from memory and there is no round to save, and for triangular K ranges.  us with three /
+// columns of tiles stream their rows from memory and there is no round to save, and always for triangular K ranges.  us with three /
 // four stages / k_igemm (three):
 //   256 tiles, 2 048^3: 33.2 / 28.2 / 29.4.             324, 2 304^3: 46.8 / 45.2 / 45.6.  352, 2 048 x 2 816 x 4 096: 65.9 / 67.7 / 70.0
 //   512, 4 096 x 2 048 x 4 096: 79.3 / 86.1 / 87.7.     576, 3 072^3: 84.2 / 94.4 / 89.2.  676, 3 328^3: 100.6 / 105.3 / 102.6
 //   768, 98 304 x 128 x 256: 23.4 / 26.0 / 23.9.        784, 3 584^3: 153 / 138 / 139
 //   512 in one column, K = 4 096: 144 / 135 / 134; in two: 108 / 104 / 109; 510 in three 89.3 / 87.5 / 89.4; 512 in four 79.5 / 85.1 / 86.5
 //   LU steps of d = 2 048 and 3 072: 392 and 833 / 381 and 797 / 426 and 854
-int dense_stages(int64_t tiles, int tiles_n, int tri) {
-  return tri == 0 && tiles >= 352 && tiles <= 768 && (tiles_n > 3 || tiles > 512) ? 3 : 4;
+int dense_stages(int64_t tiles, int tiles_n) {
+  return tiles >= 352 && tiles <= 768 && (tiles_n > 3 || tiles > 512) ? 3 : 4;
 }
 
 // With the second operand [k][n] and at most one 128 x 128 tile per compute unit: do two groups of four wavefronts take half of K each?
@@ -1826,13 +1832,13 @@ bool dense_halves(int64_t tiles, int64_t K) { return tiles <= 256 && K % 64 == 0
 
 // Does k_dense take 256 x 128 tiles?  They leave it three stages at two workgroups per compute unit, like k_igemm, and its waits
 // let one slab's loads be in flight instead of two: it gains where K is short and the weights stay in the caches, and for
-// triangular K ranges.  us with k_dense / k_igemm, rows x columns x K:
+// triangular K ranges (always).  us with k_dense / k_igemm, rows x columns x K:
 //   131 072 x 128 x 128 24.7 / 25.7, x 768 52.3 / 54.3, x 1 024 72.5 / 71.3;  65 536 x 384 x 128 34.2 / 34.9, x 256 41.0 / 41.2,
 //   x 512 53.5 / 53.3, x 2 048 149 / 144;  32 768 x 640 x 512 48.3 / 46.9, x 1 024 70.8 / 67.6;  32 768 x 1 152 x 64 43.3 / 44.6,
 //   x 256 60.8 / 59.1;  16 384 x 1 152 x 4 096 206 / 202.  Both products of a transformation error: 65 536 x 384 107 / 111,
 //   32 768 x 640 116 / 114, 32 768 x 896 162 / 170, 16 384 x 1 152 157 / 154, 8 192 x 2 176 249 / 245.  LU step of d = 4 096 1 158 / 1 164.
-bool dense_tall(int64_t N, int64_t K, int epi, int tri) {
-  return tri != 0 || (epi != CONV_EPI_NONE ? K < 1024 : N * K < (1 << 17));
+bool dense_tall(int64_t N, int64_t K, int epi) {
+  return epi != CONV_EPI_NONE ? K < 1024 : N * K < (1 << 17);
 }
 
 }  // namespace
@@ -2054,6 +2060,7 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
     else hipLaunchKernelGGL((k_igemm<T, BMV, BNV, GM, GN, KB, false, true>), grid, dim3(256), 0, s, p); \
   } while (0)
   const bool direct = direct_stores(p, a.dtype, t.bn);
+  const bool tri = a0.tri != 0;
   // Binary32: three bf16 parts (k_gemm_split), unless the caller asks for the binary32 MFMA or there are few columns and a
   // short K, where both only move the operands (65,536 rows, 64 -> 64 channels: 13.6 and 12.8 us; 131,072 rows, 48 -> 64 -> 48: 18.7
   // and 18.6, 22.4 and 22.9; from there on the parts win: 64 -> 512 -> 64 channels 60.5 against 45.6 and 45.0 against 37.4)
@@ -2080,13 +2087,17 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
     const double tall = whole && !p.partial && p.M % 256 == 0 && p.K >= 512 ? rounds(n128 / 2, 256, 0.89, 0.89) : 1e30;
     if (choice && tall < c128 && tall < c64) {
       p.tiles_mn /= 2;
-      hipLaunchKernelGGL((k_gemm_split<256, 128, 4, 2, true>), dim3(grid.x / 2), dim3(512), 0, s, p);
+      if (tri) hipLaunchKernelGGL((k_gemm_split<256, 128, 4, 2, true, 0, false, TRI_RANGE>), dim3(grid.x / 2), dim3(512), 0, s, p);
+      else hipLaunchKernelGGL((k_gemm_split<256, 128, 4, 2, true>), dim3(grid.x / 2), dim3(512), 0, s, p);
     } else if (choice && (!whole ? n128 <= 256 : c64 < c128)) {
       p.tiles_n *= 2;
       p.tiles_mn *= 2;
-      hipLaunchKernelGGL((k_gemm_split<128, 64, 4, 1, true>), dim3(grid.x * 2), dim3(256), 0, s, p);
+      if (tri) hipLaunchKernelGGL((k_gemm_split<128, 64, 4, 1, true, 0, false, TRI_RANGE>), dim3(grid.x * 2), dim3(256), 0, s, p);
+      else hipLaunchKernelGGL((k_gemm_split<128, 64, 4, 1, true>), dim3(grid.x * 2), dim3(256), 0, s, p);
     } else if (a0.epi == CONV_EPI_MXQ) hipLaunchKernelGGL((k_gemm_split<128, 128, 2, 2, true, 1>), grid, dim3(256), 0, s, p);   // (conv_epi_usable: interior)
     else if (a0.epi == CONV_EPI_RESID) hipLaunchKernelGGL((k_gemm_split<128, 128, 2, 2, true, 2>), grid, dim3(256), 0, s, p);
+    else if (tri && interior) hipLaunchKernelGGL((k_gemm_split<128, 128, 2, 2, true, 0, false, TRI_RANGE>), grid, dim3(256), 0, s, p);
+    else if (tri) hipLaunchKernelGGL((k_gemm_split<128, 128, 2, 2, false, 0, false, TRI_RANGE>), grid, dim3(256), 0, s, p);   // (64 columns: not by parts)
 #define SPLIT_LAUNCH(BNV, GM, GN, IN, CV) hipLaunchKernelGGL((k_gemm_split<128, BNV, GM, GN, IN, 0, CV>), grid, dim3(256), 0, s, p)
 #define SPLIT_LAUNCH_T(BNV, GM, GN)                                                                                    \
   do {                                                                                                                 \
@@ -2107,8 +2118,8 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
     else IGEMM_LAUNCH_T(float, BMV, BNV, GM, GN);                              \
   } while (0)
   const bool dense_bf16 = a.dtype == AE_BF16 && dense && interior;
-  const int stages = dense_stages(grid.x, p.tiles_n, a0.tri);
-  const bool tall = dense_tall(p.N, p.K, a0.epi, a0.tri);
+  const int stages = dense_stages(grid.x, p.tiles_n);
+  const bool tall = dense_tall(p.N, p.K, a0.epi);
   if (a0.comp_mode != 0) {
     // (conv_comp_blocks: bfloat16, interior tiles, no split, not the eight-wavefront tile)
 #define IGEMM_LAUNCH_COMP(BMV, BNV, GM, GN)                                                                           \
@@ -2138,6 +2149,21 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
     else EPI_LAUNCH(2);
 #undef EPI_LAUNCH
     return launch_status("conv_mfma_epi");
+  }
+  if (tri) {
+    // square products: 64-column tiles (d = 32, 64) are never check-free, nor are those of bf16 here (k_dense takes them)
+#define TRI_LAUNCH(T, BMV, BNV, IN) hipLaunchKernelGGL((k_igemm<T, BMV, BNV, 2, 2, 64, IN, true, 0, false, false, true>), grid, dim3(256), 0, s, p)
+    if (dense_bf16 && t.bn == 256) hipLaunchKernelGGL((k_dense<256, 256, 2, 4, 4, 0, true>), grid, dim3(512), 0, s, p);
+    else if (dense_bf16 && t.bm == 256) hipLaunchKernelGGL((k_dense<256, 128, 2, 2, 3, 0, true>), grid, dim3(256), 0, s, p);
+    else if (dense_bf16) hipLaunchKernelGGL((k_dense<128, 128, 2, 2, 4, 0, true>), grid, dim3(256), 0, s, p);
+    else if (a.dtype == AE_BF16 && t.bm == 256) TRI_LAUNCH(bf16_t, 256, 128, false);
+    else if (a.dtype == AE_BF16 && t.bn == 128) TRI_LAUNCH(bf16_t, 128, 128, false);
+    else if (a.dtype == AE_BF16) TRI_LAUNCH(bf16_t, 128, 64, false);
+    else if (t.bn == 64) TRI_LAUNCH(float, 128, 64, false);
+    else if (interior) TRI_LAUNCH(float, 128, 128, true);
+    else TRI_LAUNCH(float, 128, 128, false);
+#undef TRI_LAUNCH
+    return launch_status("conv_mfma_tri");
   }
   if (dense_bf16 && t.bn == 256) hipLaunchKernelGGL((k_dense<256, 256, 2, 4, 4>), grid, dim3(512), 0, s, p);
   else if (dense_bf16 && t.bm == 256 && t.bn == 128 && tall) hipLaunchKernelGGL((k_dense<256, 128, 2, 2, 3>), grid, dim3(256), 0, s, p);
@@ -2173,11 +2199,14 @@ int launch_dense_kn(const void* x, const void* w, void* y, int64_t rows, int64_t
   p.tiles_n = (int)(n / (wide ? 256 : 128));
   p.tiles_mn = (int)((rows / (wide || tall ? 256 : 128)) * p.tiles_n);
   const dim3 grid((unsigned)p.tiles_mn);
-  if (wide) hipLaunchKernelGGL((k_dense<256, 256, 2, 4, 4, 0, true>), grid, dim3(512), 0, s, p);
-  else if (tall) hipLaunchKernelGGL((k_dense<256, 128, 2, 2, 3, 0, true>), grid, dim3(256), 0, s, p);
-  else if (tri == 0 && dense_halves(grid.x, p.K)) hipLaunchKernelGGL((k_dense<128, 128, 2, 2, 4, 0, true, 2>), grid, dim3(512), 0, s, p);
-  else if (dense_stages(grid.x, p.tiles_n, tri) == 3) hipLaunchKernelGGL((k_dense<128, 128, 2, 2, 3, 0, true>), grid, dim3(256), 0, s, p);
-  else hipLaunchKernelGGL((k_dense<128, 128, 2, 2, 4, 0, true>), grid, dim3(256), 0, s, p);
+  if (tri != 0) {
+    if (wide) hipLaunchKernelGGL((k_dense<256, 256, 2, 4, 4, 0, true, true>), grid, dim3(512), 0, s, p);
+    else if (tall) hipLaunchKernelGGL((k_dense<256, 128, 2, 2, 3, 0, true, true>), grid, dim3(256), 0, s, p);
+    else hipLaunchKernelGGL((k_dense<128, 128, 2, 2, 4, 0, true, true>), grid, dim3(256), 0, s, p);
+  } else if (wide) hipLaunchKernelGGL((k_dense<256, 256, 2, 4, 4, 0, false, true>), grid, dim3(512), 0, s, p);
+  else if (dense_halves(grid.x, p.K)) hipLaunchKernelGGL((k_dense<128, 128, 2, 2, 4, 0, false, true, 2>), grid, dim3(512), 0, s, p);
+  else if (dense_stages(grid.x, p.tiles_n) == 3) hipLaunchKernelGGL((k_dense<128, 128, 2, 2, 3, 0, false, true>), grid, dim3(256), 0, s, p);
+  else hipLaunchKernelGGL((k_dense<128, 128, 2, 2, 4, 0, false, true>), grid, dim3(256), 0, s, p);
   return launch_status("dense_kn");
 }
 

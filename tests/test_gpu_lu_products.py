@@ -4,8 +4,9 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-# d off 128: transposed operands; 128 .. : operands as they lie, 128 x 128 tiles; 4 096: 256 x 128; a second stream from 2 048 (binary32: 1 024) on
-@pytest.mark.parametrize("d,dtype", [(96, "bf16"), (128, "bf16"), (160, "bf16"), (640, "bf16"), (1024, "bf16"), (2048, "bf16"), (4096, "bf16"), (96, "f32"), (992, "f32"), (1024, "f32")])
+# d off 128: transposed operands, checked tiles (8 224: of 256 rows); 128 .. : operands as they lie, 128 x 128 tiles; 4 096: 256 x 128; 8 192:
+# 256 x 256; a second stream from 2 048 (binary32: 1 024) on
+@pytest.mark.parametrize("d,dtype", [(96, "bf16"), (128, "bf16"), (160, "bf16"), (640, "bf16"), (1024, "bf16"), (2048, "bf16"), (4096, "bf16"), (8192, "bf16"), (8224, "bf16"), (64, "f32"), (96, "f32"), (992, "f32"), (1024, "f32")])
 def test_lu_step(d, dtype):
     import torch
     from paper_2602_17681_amd import binding as ae
