@@ -343,6 +343,7 @@ __device__ __forceinline__ void last_conv(const SmallArgs& a, const float* a3, c
 }
 
 // ---- launch 3: everything from the second batch-norm to y ----------------------------------------------------------
+template <int DB>                                 // outputs of the decoder's fc at a time (launch_fused_small)
 __global__ __launch_bounds__(NT_MAX) void k_small_tail(SmallArgs a) {
   extern __shared__ float lds[];
   const int h2 = a.h / 2, w2 = a.w / 2, h4 = a.h / 4, w4 = a.w / 4, hw4 = h4 * w4, hw2 = h2 * w2, hw = a.h * a.w;
@@ -451,24 +452,23 @@ __global__ __launch_bounds__(NT_MAX) void k_small_tail(SmallArgs a) {
     const bool vec = (a.n & 3) == 0 && (((uintptr_t)wf | (uintptr_t)lat) & 15) == 0;
     if (vec) {
       const int j0 = 4 * (threadIdx.x & 15);
-      constexpr int RB = 6;                       // outputs at a time: their loads are in flight together (28 x 28, four bands: 6 39.2 us in all, 8 40.4, 12 40.9)
       const float inv_nd = 1.0f / (float)n_d;    // (o + 1/2) / n_d rounds down to o / n_d: o < 2^14
       auto channel = [&](int o) { return (int)(((float)o + 0.5f) * inv_nd); };
       auto row_of = [&](int o) { const int c = channel(o); return c * hw4 + d_lo * w4 + o - c * n_d; };
-      for (int o0 = threadIdx.x >> 4; o0 < FD; o0 += NT / 16 * RB) {
-        float acc[RB];
+      for (int o0 = threadIdx.x >> 4; o0 < FD; o0 += NT / 16 * DB) {
+        float acc[DB];
 #pragma unroll
-        for (int r = 0; r < RB; ++r) acc[r] = 0.0f;
+        for (int r = 0; r < DB; ++r) acc[r] = 0.0f;
         for (int j = j0; j < a.n; j += 64) {
           const float4 l4 = *reinterpret_cast<const float4*>(lat + j);
-          float4 w4[RB];
+          float4 w4[DB];
 #pragma unroll
-          for (int r = 0; r < RB; ++r) w4[r] = *reinterpret_cast<const float4*>(wf + (int64_t)row_of(min(o0 + r * (NT / 16), FD - 1)) * a.n + j);
+          for (int r = 0; r < DB; ++r) w4[r] = *reinterpret_cast<const float4*>(wf + (int64_t)row_of(min(o0 + r * (NT / 16), FD - 1)) * a.n + j);
 #pragma unroll
-          for (int r = 0; r < RB; ++r) acc[r] = fmaf(w4[r].w, l4.w, fmaf(w4[r].z, l4.z, fmaf(w4[r].y, l4.y, fmaf(w4[r].x, l4.x, acc[r]))));
+          for (int r = 0; r < DB; ++r) acc[r] = fmaf(w4[r].w, l4.w, fmaf(w4[r].z, l4.z, fmaf(w4[r].y, l4.y, fmaf(w4[r].x, l4.x, acc[r]))));
         }
 #pragma unroll
-        for (int r = 0; r < RB; ++r) {
+        for (int r = 0; r < DB; ++r) {
           const int o = o0 + r * (NT / 16);
           const float t = row_sum(acc[r]);
           const int c = channel(o), w = row_of(o);
@@ -587,12 +587,15 @@ int launch_fused_small(const Plan& P, const FusedSmall& f, const float* params, 
   a.sigma = sigma; a.seed = seed; a.first_sample = first_sample;
   choose_planes(a);
   // Sixteen wavefronts per sample while every sample has a compute unit to itself; beyond that eight, so that two workgroups
-  // fit the registers of one (28 x 28, 128 / 256 / 300 / 512 samples: 50 / 68 / 122 / 135 us with sixteen, 59 / 77 / 104 / 116 us
-  // with eight)
+  // fit the registers of one (28 x 28, 128 / 256 / 300 / 512 samples: 43 / 65 / 118 / 127 us with sixteen, 49 / 73 / 101 / 108
+  // with eight; 16 x 16: 30 / 39 / 68 / 75 and 32 / 36 / 49 / 53)
   const dim3 nt(P.batch <= 256 ? NT_MAX : NT_MAX / 2);
   // Bands: as many workgroups per sample as leave at most one per compute unit.  us in all, 28 x 28, bands of the launches 1 / 1 / 1 and as
-  // chosen: 1 sample 45 -> 33, 64 46 -> 39, 128 47 -> 43; more of them than compute units lose (128 samples, 4 / 2 / 2: 56).
-  const int per = P.batch < 256 ? 256 / P.batch : 1;
+  // chosen: 1 sample 48 -> 33, 64 50 -> 40, 128 51 -> 43; more of them than compute units lose (128 samples, 4 / 2 / 2: 56).  Two instead of
+  // three: their bounds fall between rows, and two have room (85 samples of 16 x 16 / 20 x 20 / 28 x 28 / 32 x 32: one band 32 / 38 / 52 / 62, three 34 / 37 / 48 /
+  // 55, two 31 / 36 / 45 / 53).
+  int per = P.batch < 256 ? 256 / P.batch : 1;
+  if (per == 3) per = 2;
   a.bands1 = std::min(per, 4);
   a.bands2 = std::min(std::max(per / (f.c2 / COB), 1), 4);
   a.bands = std::min(per, a.h / 4);
@@ -600,7 +603,11 @@ int launch_fused_small(const Plan& P, const FusedSmall& f, const float* params, 
   a.part2 = partial + (int64_t)P.batch * a.bands1 * 2 * f.c1;
   hipLaunchKernelGGL(k_small_conv1, dim3(P.batch, a.bands1), nt, lds1(a), s, a);
   hipLaunchKernelGGL(k_small_conv2, dim3(P.batch, f.c2 / COB, a.bands2), nt, lds2(a), s, a);
-  hipLaunchKernelGGL(k_small_tail, dim3(P.batch, a.bands), nt, lds3(a), s, a);
+  // The decoder's fc: the loads of 6 outputs per 16 threads in flight, of 8 where one workgroup's outputs are whole passes of as many (us in all
+  // with 6 / 8: 256 samples of 16 x 16 39.5 / 38.4, 32 x 32 75.0 / 73.8; others as fast or slower with 8: 20 x 20 45.4 / 45.6, 28 x 28 65.6 / 65.5,
+  // 64 samples in four bands, 28 x 28, 39.9 / 41.6).
+  if (a.bands == 1 && f.cr * (a.h / 4) * (a.w / 4) % (8 * (int)nt.x / 16) == 0) hipLaunchKernelGGL(k_small_tail<8>, dim3(P.batch, 1), nt, lds3(a), s, a);
+  else hipLaunchKernelGGL(k_small_tail<6>, dim3(P.batch, a.bands), nt, lds3(a), s, a);
   return launch_status("fused_small");
 }
 

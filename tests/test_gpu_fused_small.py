@@ -43,7 +43,9 @@ def test_small_image_forward_any_reshape(dims, batch):
 
 
 @pytest.mark.parametrize("dims,batch", [((1, 28, 28, 16, 32, 64, 32, 16, 1), 1), ((1, 28, 28, 16, 32, 64, 32, 16, 1), 64), ((1, 28, 28, 16, 32, 62, 32, 16, 1), 85),
-                                        ((2, 32, 20, 32, 64, 64, 9, 32, 2), 30), ((1, 8, 4, 16, 16, 4, 3, 16, 1), 7), ((1, 12, 24, 16, 128, 8, 4, 16, 1), 128)])
+                                        ((2, 32, 20, 32, 64, 64, 9, 32, 2), 30), ((1, 8, 4, 16, 16, 4, 3, 16, 1), 7), ((1, 12, 24, 16, 128, 8, 4, 16, 1), 128),
+                                        # the decoder's fc in whole passes of eight outputs: one of 1 024 threads, four of 512
+                                        ((1, 16, 16, 16, 32, 64, 32, 16, 1), 200), ((1, 32, 32, 16, 32, 64, 16, 16, 1), 257)])
 def test_small_image_forward_bands(dims, batch):
-    """Several workgroups per sample: one to eight bands of rows, of the first two launches up to four."""
+    """Several workgroups per sample: one to eight bands of rows, of the first two launches up to four (never three)."""
     test_small_image_forward(dims, batch)
