@@ -3167,7 +3167,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     }                                                                                                        \
     __builtin_amdgcn_sched_barrier(0);                                                                       \
   }
-#define LGKM_WAIT(N) asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N))
+  // waits until at most N LDS reads are outstanding and ties the fragments that have arrived to the wait: no MFMA of theirs may move ahead of it
+#define LGKM_WAIT(N, FA, FB)                                                                                 \
+  {                                                                                                          \
+    asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N));                                                          \
+    _Pragma("unroll") for (int i = 0; i < MI; ++i) tr_tie(FA[i]);                                            \
+    asm volatile("" : "+v"(FB.lo), "+v"(FB.hi), "+v"(FB.ex));                                                \
+  }
 
   // Three slabs in flight before the loop.  A slab's last fragments are in registers when its last MFMAs have yet to run: there the
   // workgroup waits for the next slab and gives the stage to the slab after the next two, so that a load has two slabs' time.  (Waiting where the
@@ -3190,15 +3196,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   {                                                                                                          \
     const unsigned sa = lds0 + (unsigned)((CUR) * G::STAGE) + a_lane, sb = lds0 + (unsigned)((CUR) * G::STAGE) + b_lane; \
     wgrad3_reads<BM, SW, 1>(fa1, fb1, sa, sb);                                                               \
-    LGKM_WAIT(NR);                                                                                           \
+    LGKM_WAIT(NR, fa0, fb0)                                                                                  \
     WGRAD3_MMA(fa0, fb0)                                                                                     \
     wgrad3_reads<BM, SW, 2>(fa0, fb0, sa, sb);                                                               \
-    LGKM_WAIT(NR);                                                                                           \
+    LGKM_WAIT(NR, fa1, fb1)                                                                                  \
     WGRAD3_MMA(fa1, fb1)                                                                                     \
     wgrad3_reads<BM, SW, 3>(fa1, fb1, sa, sb);                                                               \
-    LGKM_WAIT(NR);                                                                                           \
+    LGKM_WAIT(NR, fa0, fb0)                                                                                  \
     WGRAD3_MMA(fa0, fb0)                                                                                     \
-    LGKM_WAIT(0);                                                                                            \
+    LGKM_WAIT(0, fa1, fb1)                                                                                   \
   }
   int cur = 0;
   for (int t = 0; t + 1 < KT; ++t) {
@@ -3209,10 +3215,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     wgrad3_reads<BM, SW, 0>(fa0, fb0, lds0 + (unsigned)(nxt * G::STAGE) + a_lane, lds0 + (unsigned)(nxt * G::STAGE) + b_lane);
     if (t + 3 < KT) WGRAD3_DMA(cur);
     WGRAD3_MMA(fa1, fb1)
-    LGKM_WAIT(0);                                // (nothing is in flight where the loop turns)
-#pragma unroll
-    for (int i = 0; i < MI; ++i) tr_tie(fa0[i]);
-    asm volatile("" : "+v"(fb0.lo), "+v"(fb0.hi), "+v"(fb0.ex));
+    LGKM_WAIT(0, fa0, fb0)                       // (nothing is in flight where the loop turns)
     cur = nxt;
   }
   WGRAD3_STEPS(cur)
