@@ -998,6 +998,21 @@ struct SideBranch {
   }
 };
 
+// launch(), between two events while model_lu_timing is on
+template <typename LAUNCH>
+int timed_product(hipStream_t s, LAUNCH launch) {
+  if (!g_timing) return launch();
+  AE_HIP(hipEventRecord(g_ev0, s));
+  AE_TRY(launch());
+  AE_HIP(hipEventRecord(g_ev1, s));
+  AE_HIP(hipEventSynchronize(g_ev1));
+  float ms = 0.0f;
+  AE_HIP(hipEventElapsedTime(&ms, g_ev0, g_ev1));
+  g_timing_ms += ms;
+  ++g_timing_launches;
+  return AE_OK;
+}
+
 // y[m][n] = sum_k x[m][k] w[n][k], all d x d in the storage type; tri: which operand is triangular (CONV_TRI_*)
 int dense_product(const void* x, const void* w, void* y, int d, int dtype, int tri, hipStream_t s) {
   ConvArgs a;
@@ -1010,16 +1025,7 @@ int dense_product(const void* x, const void* w, void* y, int d, int dtype, int t
   // against float64: d = 256 4.0e-6 by parts against 3.6e-6, d = 1024 4.2e-6 against 1.4e-5, d = 2048 4.6e-6 against 3.7e-5;
   // dG 3.5e-6 against 2.5e-6, 3.4e-6 against 1.1e-5, 3.5e-6 against 3.1e-5.
   a.f32_mfma = (tri == CONV_TRI_NONE || tri == CONV_TRI_LOWER_W_FULL || tri == CONV_TRI_UPPER_W_FULL) && d < 512;
-  if (!g_timing) return launch_conv_mfma(a, s);
-  AE_HIP(hipEventRecord(g_ev0, s));
-  AE_TRY(launch_conv_mfma(a, s));
-  AE_HIP(hipEventRecord(g_ev1, s));
-  AE_HIP(hipEventSynchronize(g_ev1));
-  float ms = 0.0f;
-  AE_HIP(hipEventElapsedTime(&ms, g_ev0, g_ev1));
-  g_timing_ms += ms;
-  ++g_timing_launches;
-  return AE_OK;
+  return timed_product(s, [&]() { return launch_conv_mfma(a, s); });
 }
 
 int64_t lu_mat_bytes(int64_t d, int dtype) { return d * d * (int64_t)dtype_size(dtype); }
@@ -1279,14 +1285,14 @@ extern "C" int model_lu_compose(const float* lp, const float* up, const float* l
   void* udt = ws + mat;         // (U + diag s)^T    [n][k]   (binary32: U^T, the diagonal follows in k_lu_permute_rows_diag; kn: U + diag s [k][n])
   void* y = ws + 2 * mat;       // L (U + diag s)    [i][n]
   LuSrc q{lp, up, log_s, sign_s, nullptr, nullptr, (int)d};
-  const bool kn = dtype == AE_BF16 && !g_timing && dense_kn_supported(d, d, d, d);     // w as it lies: [k][n]
+  const bool kn = dtype == AE_BF16 && dense_kn_supported(d, d, d, d);     // w as it lies: [k][n]
   if (dtype == AE_BF16) {
     launch_build_rows<bf16_t, LU_L>(q, l, s);
     if (kn) launch_build_rows<bf16_t, LU_UD>(q, udt, s);
     else launch_build_transposed<bf16_t, LU_UD>(q, udt, s);
   } else { launch_build_rows<float, LU_L>(q, l, s); launch_build_transposed<float, LU_U>(q, udt, s); }
   AE_TRY(launch_status("lu_build"));
-  if (kn) AE_TRY(launch_dense_kn(l, udt, y, d, d, d, d, s, CONV_TRI_LOWER_UPPER));
+  if (kn) AE_TRY(timed_product(s, [&]() { return launch_dense_kn(l, udt, y, d, d, d, d, s, CONV_TRI_LOWER_UPPER); }));
   else AE_TRY(dense_product(l, udt, y, (int)d, dtype, CONV_TRI_LOWER_UPPER, s));
   if (dtype == AE_F32) {
     const dim3 grid((unsigned)((d + 1023) / 1024), (unsigned)((d + 15) / 16));
@@ -1326,7 +1332,7 @@ extern "C" int model_lu_backward(const void* g, const float* lp, const float* up
   SideBranch br;
   // (Smaller matrices stay on one stream, where the kernels are shorter than the fork and the join: us of the call with and without it, bf16 d = 256
   // 75 / 33, 1 024 74 / 46, 1 536 69 / 63, 2 048 74 / 73, 3 072 116 / 133, 4 096 212 / 257; binary32 256 75 / 42, 1 024 84 / 99.)
-  const bool kn = dtype == AE_BF16 && !g_timing && dense_kn_supported(d, d, d, d);     // both products read B as it lies: [k][n] and [m][k]
+  const bool kn = dtype == AE_BF16 && dense_kn_supported(d, d, d, d);     // both products read B as it lies: [k][n] and [m][k]
   if (kn) launch_build_rows<bf16_t, LU_B>(q, b, s);
   AE_TRY(br.begin(s, !g_timing && d >= (dtype == AE_BF16 ? 2048 : 1024), "model_lu_backward"));
   hipStream_t s2 = br.side;
@@ -1341,7 +1347,7 @@ extern "C" int model_lu_backward(const void* g, const float* lp, const float* up
     launch_build_rows<float, LU_UD>(q, ud, s2); launch_build_rows<float, LU_B>(q, b, s2);
   }
   rc = launch_status("lu_build");
-  if (rc == AE_OK) rc = kn ? launch_dense_kn(lt, b, dud, d, d, d, d, s, CONV_TRI_UPPER_X) : dense_product(lt, bt, dud, (int)d, dtype, CONV_TRI_UPPER_X, s);
+  if (rc == AE_OK) rc = kn ? timed_product(s, [&]() { return launch_dense_kn(lt, b, dud, d, d, d, d, s, CONV_TRI_UPPER_X); }) : dense_product(lt, bt, dud, (int)d, dtype, CONV_TRI_UPPER_X, s);
   if (rc == AE_OK) rc = dense_product(b, ud, dl, (int)d, dtype, CONV_TRI_UPPER_W, s2);
   if (rc == AE_OK) {
     if (dtype == AE_BF16) {
@@ -1537,7 +1543,7 @@ extern "C" int model_lu_inverse(const float* lp, const float* up, const float* l
   float *z = f + 6 * pp, *z2 = f + 7 * pp;                 // (U + diag s)^-1 L^-1, the second halves of its long sums
   LuSrc q{lp, up, log_s, sign_s, nullptr, nullptr, (int)d};
   AE_TRY(tri_inverse(q, (int)dp, 0, 2, l, u, s));
-  AE_TRY(launch_tri_last(u.hi, l.hi, (int)dp, z, z2, (int)d, s));
+  AE_TRY(timed_product(s, [&]() { return launch_tri_last(u.hi, l.hi, (int)dp, z, z2, (int)d, s); }));
   const int split = tri_last_split((int)d);
   const dim3 og((unsigned)(d < 2048 ? d : 2048));
   if (dtype == AE_BF16) hipLaunchKernelGGL((k_lu_inverse_out<bf16_t>), og, dim3(256), (size_t)d * 4, s, (const float*)z, (const float*)z2, split, perm, (int)d, (bf16_t*)a_inv_out);

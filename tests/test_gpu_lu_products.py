@@ -35,3 +35,30 @@ def test_lu_step(d, dtype):
     assert rel(a, (L @ U)[p]) <= tol
     assert rel(dup, torch.triu(dU, 1)) <= tol and rel(dlp, torch.tril(dL, -1)) <= tol and rel(dls, torch.diagonal(dU) * s) <= tol
     assert torch.equal(dup, torch.triu(dup, 1)) and torch.equal(dlp, torch.tril(dlp, -1))
+
+
+@pytest.mark.parametrize("d,dtype", [(96, "bf16"), (256, "bf16"), (2048, "bf16"), (256, "f32")])
+def test_timed_products_are_those_of_untimed_calls(d, dtype):
+    """While the products are timed the same kernels run on the same operands: the workspaces hold the same bits, operand for operand.  One
+    product of the inverse is timed, the last."""
+    import torch
+    from paper_2602_17681_amd import binding as ae
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(d)
+    rand = lambda *s: torch.randn(*s, device="cuda", generator=gen)      # noqa: E731
+    td = {"f32": torch.float32, "bf16": torch.bfloat16}[dtype]
+    lp, up, ls, sign, g = rand(d, d) * d ** -0.5, rand(d, d) * d ** -0.5, 0.3 * rand(d), torch.ones(d, device="cuda"), rand(d, d).to(td)
+    perm = torch.randperm(d, device="cuda", generator=gen).to(torch.int32)
+    a, dlp, dup, dls = torch.empty(d, d, device="cuda", dtype=td), torch.empty(d, d, device="cuda"), torch.empty(d, d, device="cuda"), torch.empty(d, device="cuda")
+    calls = [(1, ae.model_lu_workspace(d, ae.DTYPES[dtype]), lambda ws: ae.model_lu_compose(lp, up, ls, sign, perm, d, a, ws)),
+             (2, ae.model_lu_workspace(d, ae.DTYPES[dtype]), lambda ws: ae.model_lu_backward(g, lp, up, ls, sign, perm, d, dlp, dup, dls, ws))]
+    if d % 128 == 0:
+        calls.append((1, ae.model_lu_inverse_workspace(d), lambda ws: ae.model_lu_inverse(lp, up, ls, sign, perm, d, a, ws)))
+    for products, size, call in calls:
+        plain, timed = torch.zeros(size, dtype=torch.uint8, device="cuda"), torch.zeros(size, dtype=torch.uint8, device="cuda")
+        call(plain)
+        ae.model_lu_timing(True)
+        call(timed)
+        ms, n = ae.model_lu_timing(False)
+        assert n == products and ms > 0.0
+        assert torch.equal(plain, timed)
