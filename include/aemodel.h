@@ -189,7 +189,7 @@ int model_timing_enable(ae_model* m, int on);
  * everything enqueued on the caller's stream after model_backward returns sees all
  * gradients.  on = 0 keeps every kernel on the caller's stream in program order (also the
  * behaviour while per-kernel timing is enabled, so that each measured duration belongs to
- * one kernel alone).  Results are identical either way. */
+ * one kernel alone).  on = -1 returns to the default.  Results are identical either way. */
 int model_set_overlap(ae_model* m, int on);
 /* Inference mode (on = 1): forward passes keep nothing for a backward pass — model_backward, model_get_activation
  * and model_get_conv_output then return AE_ESTATE — which lets the executor take paths that never write the

@@ -192,7 +192,7 @@ class Model:
         _check(lib.model_timing_enable(self._h, 1 if on else 0))
 
     def model_set_overlap(self, on):
-        _check(lib.model_set_overlap(self._h, 1 if on else 0))
+        _check(lib.model_set_overlap(self._h, -1 if on == -1 else 1 if on else 0))
 
     def model_set_inference(self, on):
         _check(lib.model_set_inference(self._h, 1 if on else 0))

@@ -53,7 +53,7 @@ struct ae_model {
   float* splitk_ws = nullptr;
   char* dypad[3] = {nullptr, nullptr, nullptr};   // padded conv-output gradients: beside draw_buf[0], draw_buf[1], and of layers that stay in order
   bool overlap = true;
-  bool overlap_asked = false;      // model_set_overlap: whatever the size
+  bool overlap_asked = false;      // model_set_overlap(1): whatever the size
   bool overlap_pays = true;        // enough work behind the forks and joins (overlap_pays)
   hipStream_t side = nullptr;
   hipEvent_t ev_fork = nullptr;
@@ -806,7 +806,8 @@ int model_timing_enable(ae_model* m, int on) {
 
 int model_set_overlap(ae_model* m, int on) {
   if (!m) return fail(AE_EINVAL, "model_set_overlap: null model");
-  m->overlap = m->overlap_asked = on != 0;
+  m->overlap = on != 0;
+  m->overlap_asked = on > 0;
   return AE_OK;
 }
 

@@ -270,3 +270,22 @@ def run_case(spec, batch, dtype="f32", seed=0, snr_db=10.0, first_sample=0, bn_m
 def _feeds_batch_bn(spec, op, bn_mode):
     toks = [t.strip() for t in spec.split(",")][1:]
     return bn_mode == 0 and op + 1 < len(toks) and toks[op + 1] == "bn"
+
+
+def captured_branches(call):
+    """Does `call` enqueue work on more than the current stream?  Captured into a HIP graph (never replayed), every kernel is a node behind
+    the one before it on its stream: a node with two successors is a fork to another stream.  Call it once before (streams and
+    events are made on first use)."""
+    import ctypes
+    import torch
+    with open("/proc/self/maps") as f:
+        hip = ctypes.CDLL(next(line.split()[-1] for line in f if "libamdhip64" in line))
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+        call()
+    n, g = ctypes.c_size_t(), ctypes.c_void_p(graph.raw_cuda_graph())
+    assert hip.hipGraphGetEdges(g, None, None, ctypes.byref(n)) == 0
+    src, dst = (ctypes.c_void_p * n.value)(), (ctypes.c_void_p * n.value)()
+    assert hip.hipGraphGetEdges(g, src, dst, ctypes.byref(n)) == 0 and n.value > 0
+    return len(set(src)) < n.value
