@@ -136,17 +136,19 @@ def test_product_timing_counts_launches_and_changes_nothing(ae):
     assert ae.model_lu_timing(False) == (0.0, 0)
 
 
-def test_backward_on_two_streams_back_to_back_same_bits(ae):
-    """model_lu_backward runs its two branches on two streams.  Eight calls in a row on one workspace with changing
-    gradients, no synchronisation between them, against the same calls made one product at a time on one stream
-    (the timing mode): identical bits."""
+@pytest.mark.parametrize("d,dtype,two", [(1024, "bf16", False), (2048, "bf16", True), (1024, "f32", True)])
+def test_backward_on_two_streams_back_to_back_same_bits(ae, d, dtype, two):
+    """model_lu_backward runs its two branches on two streams (bf16 from d = 2 048 on, binary32 from 1 024).  Eight calls in a row on one
+    workspace with changing gradients, no synchronisation between them, against the same calls made one product at a time on one
+    stream (the timing mode): identical bits."""
     import torch
-    d = 1024
+    import parity_util as pu
+    td = {"f32": torch.float32, "bf16": torch.bfloat16}[dtype]
     params = wl.make_lu_params(d, seed=5)
     dev = _dev(ae, params)
     rng = np.random.default_rng(2)
-    gs = [torch.from_numpy(rng.standard_normal((d, d)).astype(np.float32)).cuda().to(torch.bfloat16) for _ in range(8)]
-    ws = torch.empty(ae.model_lu_workspace(d, ae.DTYPES["bf16"]), dtype=torch.uint8, device="cuda")
+    gs = [torch.from_numpy(rng.standard_normal((d, d)).astype(np.float32)).cuda().to(td) for _ in range(8)]
+    ws = torch.empty(ae.model_lu_workspace(d, ae.DTYPES[dtype]), dtype=torch.uint8, device="cuda")
 
     def run():
         outs = [[torch.full((d, d), float("nan"), device="cuda"), torch.full((d, d), float("nan"), device="cuda"),
@@ -156,14 +158,15 @@ def test_backward_on_two_streams_back_to_back_same_bits(ae):
         torch.cuda.synchronize()
         return outs
 
-    two = run()
+    many = run()
     ae.model_lu_timing(True)
     one = run()
     ae.model_lu_timing(False)
-    for a, b in zip(two, one):
+    for a, b in zip(many, one):
         for x, y in zip(a, b):
             assert torch.equal(x, y)
-    assert not torch.equal(two[0][0], two[1][0])
+    assert not torch.equal(many[0][0], many[1][0])
+    assert pu.captured_branches(lambda: ae.model_lu_backward(gs[0], *dev, d, *many[0], ws)) == two
 
 
 def test_full_size_compose_and_backward(ae):

@@ -577,7 +577,7 @@ def test_single_layers_bf16_gradients(ae, case):
     ("bf16", "in:64x32x32,conv3:128,relu,conv3:64,conv3:128,relu,conv3:64,relu,conv3:64", 16),
 ])
 def test_backward_two_streams_same_bits(ae, dtype, spec, batch):
-    """The weight gradients run on a second stream by default; with that switched off, and on
+    """The weight gradients run on a second stream where that is asked for; with that switched off, and on
     repeated calls, every gradient must come out bit for bit the same (the kernels are
     deterministic, so any difference is a missing ordering between the two streams)."""
     import torch
@@ -608,11 +608,13 @@ def test_forward_and_backward_replay_from_a_captured_graph(ae, name, dtype, batc
     """The calls make no allocation and no host synchronisation, and the library's second stream is forked from and
     joined into the caller's by events, so a caller may capture them into a HIP graph: four replays, with eager calls
     (same handle, other buffers) and synchronisations between them, each bit for bit the eager result.  The bf16
-    case takes the recomputing first layer and the fused backward epilogues."""
+    case takes the recomputing first layer and the fused backward epilogues.  (Two streams in both: the binary32 one would stay on one
+    by itself.)"""
     import torch
     spec = wl.CONFIGS[name]["spec"]
     bf = dtype == "bf16"
     m = ae.Model(spec, batch, ae.DTYPES[dtype])
+    m.model_set_overlap(True)
     params = torch.from_numpy(wl.make_params(spec, 11, bf16=bf)).cuda()
     x = to_dev(wl.make_input(spec, batch, 11, bf16=bf), dtype, torch)
     y0 = torch.empty((batch,) + m.out_shape, device="cuda", dtype=x.dtype)
