@@ -73,10 +73,9 @@ struct IgemmParams {
   //   1: x[m][k] = 0 for k > m and w[n][k] = 0 for k > n (lower times upper): K ends at min(last row, last column) + 1
   //   2: x[m][k] = 0 for k < m, wanted outputs n >= m: K starts at the tile's first row; tiles below the diagonal return
   //   3: w[n][k] = 0 for k < n, wanted outputs n < m: K starts at the tile's first column; tiles above the diagonal return
-  //   4: x[m][k] = 0 for k < m and w[n][k] = 0 for k < n (upper times lower): K starts at max(first row, first column)
-  //   5: x[m][k] = 0 for k < m: K starts at the tile's first row
-  //   6: w[n][k] = 0 for k > n: K ends at the tile's last column
-  //   7: w[n][k] = 0 for k < n: K starts at the tile's first column
+  //   4: x[m][k] = 0 for k < m: K starts at the tile's first row
+  //   5: w[n][k] = 0 for k > n: K ends at the tile's last column
+  //   6: w[n][k] = 0 for k < n: K starts at the tile's first column
   int tri;
   // k_gemm_split<..., TRI_PAIRS>: one product of one level of the blocked triangular inverse, for all pairs of neighbouring tri_b x tri_b diagonal
   // blocks (r even, r + 1) of one or two matrices in one launch: only the tiles of one off-diagonal block per pair, K the block of their rows
@@ -84,7 +83,7 @@ struct IgemmParams {
   //   lower: rows in block r + 1, columns in block r, x lower triangular: K up to the tile's last row
   // tri_d: the matrices are an identity block beyond row and column tri_d; tiles of the odd block that lie wholly beyond it return
   // (their outputs are zero and stay unwritten) and K ranges over the odd block end there.  negate: -(x w^T), and its transpose into yt.
-  // TRI_LAST: x upper, w^T lower triangular (as mode 4); 128 x 128 outputs whose K range is longer than half of K are two
+  // TRI_LAST: x upper, w^T lower triangular: K starts at max(first row, first column); 128 x 128 outputs whose K range is longer than half of K are two
   // workgroups, of which the second leaves its sums in the other matrix's y.
   // Row lengths ldx and ldw (elements) of the operands, N of the outputs.
   struct Tri { const void* x; const void* w; void* y; float* yt; bool lower; } tm[2];
@@ -645,10 +644,6 @@ __device__ __forceinline__ IgemmTileId igemm_tile_id(const IgemmParams& p) {
   // triangular products: tile rows differ in work by an order of magnitude, so neighbouring tiles go to different
   // XCDs (the hardware's own round-robin) instead of one contiguous range per XCD, the longest K ranges first
   if (TRI) lb0 = p.tri == 1 ? (int)gridDim.x - 1 - (int)blockIdx.x : (int)blockIdx.x;
-  if (TRI && p.tri == 4 && (gridDim.x & 63) == 0) {    // runs of eight consecutive tiles per XCD (they share an operand panel in its L2), runs interleaved
-    const int i = (int)blockIdx.x >> 3, x = (int)blockIdx.x & 7;
-    lb0 = ((((i >> 3) << 3) + x) << 3) + (i & 7);
-  }
   t.phase = 0;
   if (p.phases == 4) { t.phase = lb0 & 3; lb0 >>= 2; }   // the four phases of a tile run side by side: they read the same input
   t.split = ONE_SPLIT ? 0 : lb0 / p.tiles_mn;
@@ -660,21 +655,11 @@ __device__ __forceinline__ IgemmTileId igemm_tile_id(const IgemmParams& p) {
   const int gm = min(p.tiles_mn / p.tiles_n - grp * kGroupM, kGroupM);
   t.n = in_grp / gm;
   t.m = grp * kGroupM + in_grp % gm;
-  if (TRI && (p.tri == 3 || p.tri == 6 || p.tri == 7)) { // K range [column, K) or [0, column]: walk column by column, the longest first
+  if (TRI && (p.tri == 3 || p.tri >= 5)) {      // K range [column, K) or [0, column]: walk column by column, the longest first
     const int tiles_m = p.tiles_mn / p.tiles_n;
     t.n = lb / tiles_m;
     t.m = lb - t.n * tiles_m;
-    if (p.tri == 6) t.n = p.tiles_n - 1 - t.n;
-  }
-  if (TRI && p.tri == 4 && p.tiles_mn == p.tiles_n * p.tiles_n) {
-    // K range [max(row, column), K): on a square tile grid walk the L-shaped shells max(tile row, tile column) = 0, 1, ...
-    // so that the workgroups are dispatched longest first and the hardware's in-order dispatch balances the rest
-    int sh = (int)sqrtf((float)lb);
-    while (sh * sh > lb) --sh;
-    while ((sh + 1) * (sh + 1) <= lb) ++sh;
-    const int r = lb - sh * sh;                 // 0 .. 2 sh
-    t.m = r <= sh ? r : sh;
-    t.n = r <= sh ? sh : r - sh - 1;
+    if (p.tri == 5) t.n = p.tiles_n - 1 - t.n;
   }
   return t;
 }
@@ -686,10 +671,9 @@ __device__ __forceinline__ bool igemm_k_range(const IgemmParams& p, int64_t m0, 
   if (p.tri == 1) k_hi = (int)min((int64_t)p.K, min(m0 + BM, (int64_t)n0 + BN));
   else if (p.tri == 2) { if ((int64_t)n0 + BN <= m0) return false; k_lo = (int)m0; }
   else if (p.tri == 3) { if ((int64_t)n0 >= m0 + BM) return false; k_lo = n0; }
-  else if (p.tri == 4) k_lo = (int)max(m0, (int64_t)n0);
-  else if (p.tri == 5) k_lo = (int)m0;
-  else if (p.tri == 6) k_hi = min(p.K, n0 + BN);
-  else if (p.tri == 7) k_lo = n0;
+  else if (p.tri == 4) k_lo = (int)m0;
+  else if (p.tri == 5) k_hi = min(p.K, n0 + BN);
+  else if (p.tri == 6) k_lo = n0;
   return true;
 }
 
@@ -2011,7 +1995,7 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
   p.mx_block = a0.mx_block;
   p.mx_elem = a0.mx_elem;
   p.tri = a0.tri;
-  if (a0.tri != 0 && (a0.tri < 0 || a0.tri > 7 || a.k != 1 || a.hc != 1 || a.wc != 1 || a.up != 0 || a.n != a.cout || a.cin != a.cout ||
+  if (a0.tri != 0 && (a0.tri < 0 || a0.tri > CONV_TRI_UPPER_W_FULL || a.k != 1 || a.hc != 1 || a.wc != 1 || a.up != 0 || a.n != a.cout || a.cin != a.cout ||
                       a0.epi != CONV_EPI_NONE || a.partial))
     return fail(AE_EINVAL, "conv_mfma: triangular K ranges are for square dense products only");
   if (conv3_patch_usable(a0)) {
@@ -2038,7 +2022,7 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
   }
   // the wide tile exists without run-time checks only; tiles of very different K lengths (the triangular modes 1-3)
   // balance better when smaller unless there are at least four per compute unit (measured: d = 8192, not 4096)
-  const bool wide_ok = (a0.tri == 0 || a0.tri <= 3) && !a.y_aux && a.act != ACT_SIGMOID && !(a.partial && a.act != ACT_NONE) && a0.geom == CONV_PLAIN;
+  const bool wide_ok = a0.tri <= CONV_TRI_UPPER_W && !a.y_aux && a.act != ACT_SIGMOID && !(a.partial && a.act != ACT_NONE) && a0.geom == CONV_PLAIN;
   const IgemmTile t = pick_tile(p.M, a.cout, a.cin, es, wide_ok, a0.tri == 0 ? 256 : 1024);
   p.tiles_n = (a.cout + t.bn - 1) / t.bn;
   const int64_t tiles_m = (p.M + t.bm - 1) / t.bm;
@@ -2083,7 +2067,7 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
     const bool choice = dense && interior && t.bn == 128 && a0.epi == CONV_EPI_NONE;
     const double c128 = rounds(n128, 512, 0.63, 1.0), c64 = rounds(2 * n128, 512, 0.45, 0.69);
     // (not with column sums: the caller counts one block of them per 128 rows)
-    const bool whole = a0.tri == 0 || a0.tri == 6 || a0.tri == 7;      // every output, K ranges that make rounds of equal sums: as without them
+    const bool whole = a0.tri == CONV_TRI_NONE || a0.tri == CONV_TRI_LOWER_W_FULL || a0.tri == CONV_TRI_UPPER_W_FULL;      // every output, K ranges that make rounds of equal sums: as without them
     const double tall = whole && !p.partial && p.M % 256 == 0 && p.K >= 512 ? rounds(n128 / 2, 256, 0.89, 0.89) : 1e30;
     if (choice && tall < c128 && tall < c64) {
       p.tiles_mn /= 2;

@@ -206,13 +206,12 @@ struct ConvArgs {
   //   CONV_TRI_LOWER_UPPER  x lower triangular, w^T upper triangular (w[n][k] = 0 for k > n);
   //   CONV_TRI_UPPER_X      x upper triangular; wanted: the outputs on and above the diagonal;
   //   CONV_TRI_UPPER_W      w upper triangular (w[n][k] = 0 for k < n); wanted: the outputs below the diagonal.
-  //   CONV_TRI_UPPER_LOWER  x upper triangular, w^T lower triangular (w[n][k] = 0 for k < n): every output wanted;
   //   CONV_TRI_UPPER_X_FULL x upper triangular; every output wanted;
   //   CONV_TRI_LOWER_W_FULL, CONV_TRI_UPPER_W_FULL  w[n][k] = 0 for k > n, for k < n; every output wanted;
   int tri = 0;
   bool f32_mfma = false;           // dense binary32 products: not through bf16 parts
 };
-enum { CONV_TRI_NONE = 0, CONV_TRI_LOWER_UPPER = 1, CONV_TRI_UPPER_X = 2, CONV_TRI_UPPER_W = 3, CONV_TRI_UPPER_LOWER = 4, CONV_TRI_UPPER_X_FULL = 5, CONV_TRI_LOWER_W_FULL = 6, CONV_TRI_UPPER_W_FULL = 7 };
+enum { CONV_TRI_NONE = 0, CONV_TRI_LOWER_UPPER = 1, CONV_TRI_UPPER_X = 2, CONV_TRI_UPPER_W = 3, CONV_TRI_UPPER_X_FULL = 4, CONV_TRI_LOWER_W_FULL = 5, CONV_TRI_UPPER_W_FULL = 6 };
 enum { CONV_PLAIN = 0, CONV_UP_PHASES = 1, CONV_UP_DGRAD = 2 };
 enum { CONV_EPI_NONE = 0, CONV_EPI_MXQ = 1, CONV_EPI_RESID = 2 };
 bool conv_epi_usable(const ConvArgs& a);         // can launch_conv_mfma run a.epi for this shape?
