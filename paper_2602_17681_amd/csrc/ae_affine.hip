@@ -1412,10 +1412,10 @@ extern "C" int model_qr_compose(const float* g, const float* rp, const float* lo
   qr_combine(QrSum{{w.x(), w.nx2(), nullptr}, {1.0f / 5040.0f, -1.0f / 40320.0f, 0.0f}, 1.0f / 720.0f}, n, w.b2(), w.b2t(), s);
   AE_TRY(launch_status("qr_powers"));
   AE_TRY(dense_product(w.b2(), w.y3(), y, n, AE_F32, CONV_TRI_NONE, s));                    // B2 Y^T = -B2 Y
-  qr_combine(QrSum{{y, w.x(), w.nx2()}, {-1.0f, 1.0f / 24.0f, -1.0f / 120.0f}, 1.0f / 6.0f}, n, w.u(), w.ut(), s);       // U = B1 + B2 Y
+  qr_combine(QrSum{{w.x(), w.nx2(), y}, {1.0f / 24.0f, -1.0f / 120.0f, -1.0f}, 1.0f / 6.0f}, n, w.u(), w.ut(), s);       // U = B1 + B2 Y
   AE_TRY(launch_status("qr_u"));
   AE_TRY(dense_product(w.u(), w.y3(), y, n, AE_F32, CONV_TRI_NONE, s));                     // U Y^T = -U Y
-  qr_combine(QrSum{{y, w.x(), w.nx2()}, {-1.0f, 1.0f, -0.5f}, 1.0f}, n, w.q(0), w.qt(0), s);   // Q_0 = B0 + U Y
+  qr_combine(QrSum{{w.x(), w.nx2(), y}, {1.0f, -0.5f, -1.0f}, 1.0f}, n, w.q(0), w.qt(0), s);   // Q_0 = B0 + U Y
   AE_TRY(launch_status("qr_polynomial"));
   for (int i = 0; i < J; ++i) {
     AE_TRY(dense_product(w.q(i), w.qt(i), w.q(i + 1), n, AE_F32, CONV_TRI_NONE, s));        // Q_{i+1} = Q_i Q_i
