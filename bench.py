@@ -420,7 +420,7 @@ def bench_lu_param(torch, ae, args):
                    "inverse_ms_beside_the_step": inv_ms,
                    "per_block_matrices_32x128_compose_gradients_inverse_ms": small_ms},
         # the three GEMM launches of a step (62 % of its kernel time; twelve element-wise kernels are the rest)
-        "roofline": {"bound": "mfma", "kernel": "k_igemm (triangular K ranges)", "achieved": ach, "peak": PEAK[args.dtype],
+        "roofline": {"bound": "mfma", "kernel": "%s (triangular K ranges)" % ("k_dense" if args.dtype == "bf16" else "k_gemm_split"), "achieved": ach, "peak": PEAK[args.dtype],
                      "unit": "TFLOP/s", "frac": ach / PEAK[args.dtype], "achieved_whole_step": flops / step_ms / 1e9,
                      "traffic": LU_TRAFFIC_BYTES.get(args.dtype) if d == 4096 else None, "avg_ms": avg_ms, "launches_per_step": 3,
                      "flops_per_launch": flops / 3, "bytes_per_launch": 3.0 * d * d * es, "step_ms_under_events": step_ms},
@@ -858,7 +858,7 @@ def main():
         "dtype": cfg["dtype"], "data": "synthetic",
         "config": {"workload": "%s: %s" % (name, cfg["spec"]), "batch": st["B"], "snr_db": cfg["snr_db"],
                    "seed": cfg["seed"], "pass": "forward+loss+backward" if cfg["backward"] else "forward",
-                   "backward_streams": 1 if args.no_overlap else 2,
+                   "backward_streams": "1" if args.no_overlap else "2 where the network's work outweighs the forks, else 1",
                    "first_layer_conv_output": "stored" if args.no_recompute else "recomputed where the layer allows",
                    "inference_mode_and_static_params": not cfg["backward"]},
         "per_snr": per_snr,

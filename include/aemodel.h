@@ -296,9 +296,9 @@ int model_transform_mse_static(const void* x, const void* a_mat, const float* v,
  * model_lu_compose  writes a_out = A [d][d] in dtype.
  * model_lu_backward given g = dLoss/dA [d][d] in dtype, writes the gradients of the free parameters in binary32:
  *   d_lp [d][d] (strictly lower part, zero elsewhere), d_up [d][d] (strictly upper part, zero elsewhere),
- *   d_log_s [d].  The products are rounded to dtype before they are cut to the triangles.  The lower-triangle
- *   branch runs on a stream the library owns (default priority), forked from and joined back into `stream` inside
- *   the call: for the caller everything is ordered on `stream` as usual.
+ *   d_log_s [d].  The products are rounded to dtype before they are cut to the triangles.  From d = 2 048 on (binary32: 1 024) the
+ *   lower-triangle branch runs on a stream the library owns (default priority), forked from and joined back into `stream`
+ *   inside the call: for the caller everything is ordered on `stream` as usual.
  * model_vol_penalty the volume regulariser in the form used in practice (Eq. 6 and the paragraph after it):
  *   *value = (sum_i log_s[i])^2 (device pointer), d_log_s (device, nullable) its gradient 2 sum. */
 int model_lu_workspace(int64_t d, int dtype, int64_t* bytes);
@@ -310,13 +310,12 @@ int model_lu_backward(const void* g, const float* lp, const float* up, const flo
 int model_vol_penalty(const float* log_s, int64_t d, float* value, float* d_log_s, void* stream);
 /* The inverse of the parametrised matrix, A^-1 = (U + diag s)^-1 L^-1 P^T (what the transformation error and the
  * folding take beside A): a_inv_out [d][d] in dtype.  Both triangular factors are inverted by a blocked recursion
- * (128 x 128 diagonal blocks by substitution, then neighbouring blocks merged, two products and a transposing copy per level), all in
+ * (128 x 128 diagonal blocks by substitution, then neighbouring blocks merged, two products per level), all in
  * binary32 on the matrix cores; s must not contain zeros.  d: a multiple of 128, at most 16384.  The recursion works
  * at dp = 128 times the smallest power of two that reaches d, on the factors extended by an identity block (pairs,
  * tiles and K ranges wholly inside the padding are skipped); the last product and the output are d x d again.
- * workspace: model_lu_inverse_workspace bytes (eight dp x dp binary32 matrices), 16-byte aligned.  The two
- * triangular inversions run side by side, one of them on a stream the library owns, forked from and joined back
- * into `stream` inside the call. */
+ * workspace: model_lu_inverse_workspace bytes (eight dp x dp binary32 matrices), 16-byte aligned; lp and up, which are read in
+ * place, may lie at any 4-byte border.  Everything runs on `stream`: the two factors share each launch. */
 int model_lu_inverse_workspace(int64_t d, int64_t* bytes);
 int model_lu_inverse(const float* lp, const float* up, const float* log_s, const float* sign_s, const int* perm, int64_t d,
                      int dtype, void* a_inv_out, void* workspace, void* stream);
@@ -324,7 +323,8 @@ int model_lu_inverse(const float* lp, const float* up, const float* log_s, const
  * parameter set per transformer block, d the head dimension): `count` independent parameter sets stored one after
  * the other — lp, up [count][d][d], log_s, sign_s [count][d], perm [count][d] (each a permutation of 0..d-1) — and
  * results laid out the same way (a_out, a_inv_out, g: [count][d][d] in dtype; d_lp, d_up [count][d][d], d_log_s
- * [count][d] in binary32).  One workgroup owns one matrix, which lives in LDS; all arithmetic is binary32, only the
+ * [count][d] in binary32).  A workgroup owns 32 rows or columns of a result (all columns of an inverse where there are many
+ * matrices), its operands live in LDS; all arithmetic is binary32, only the
  * stored a_out / a_inv_out (and the given g) are in dtype.  1 <= d <= 128 (larger matrices take the calls above),
  * 1 <= count <= 2^20, no workspace, no alignment requirement beyond the element types'.  Same definitions, same
  * treatment of perm and of zeros in s as model_lu_compose / model_lu_backward / model_lu_inverse. */
@@ -336,7 +336,8 @@ int model_lu_backward_batch(const void* g, const float* lp, const float* up, con
 int model_lu_inverse_batch(const float* lp, const float* up, const float* log_s, const float* sign_s, const int* perm,
                            int64_t count, int64_t d, int dtype, void* a_inv_out, void* stream);
 /* Measurement aid (not thread safe): returns in *gemm_ms / *launches (host, nullable) the time and count of the
- * matrix-core products model_lu_compose / model_lu_backward launched since the last call, then clears both and
+ * matrix-core products model_lu_compose / model_lu_backward and the model_qr calls launched since the last call (of an inverse the
+ * last one), then clears both and
  * switches the timing on (enable != 0) or off.  While it is on, every product is bracketed by HIP events on its
  * stream and waited for, so the calls become synchronous. */
 int model_lu_timing(int enable, double* gemm_ms, int64_t* launches);

@@ -2056,8 +2056,9 @@ int launch_conv_mfma(const ConvArgs& a0, hipStream_t s) {
     // enough to outweigh their prologue and epilogue, which nothing runs beside.  The costs are rounds of workgroups, in
     // units of a full round of 512 of the first kind: 256 of them 0.63, 512 halves 0.69, 256 halves 0.45, 256 tall ones 0.89.
     // Measured (QR step, 30 products): d = 512, 768, 1024 0.71, 0.97, 1.21 ms with halves, 0.94, 1.29, 1.63 without; d = 1536 the same;
-    // d = 2048 3.66 with, 3.34 without; d = 4096 19.9 ms with tall tiles, 22.7 without.  Tall ones from K = 512 on: 65 536 rows,
-    // 512 -> 512 channels 208 -> 190 us, 512 -> 128 59 -> 52.  Triangular K ranges gain from halves
+    // d = 2048 3.66 with, 3.34 without; d = 4096 19.9 ms with tall tiles, 22.7 without.  Tall ones from K = 512 on: forward pass of
+    // one layer of K = 512 / 640 / 768 / 896, 128 to 1 024 columns, 2 048 to 65 536 rows: 1 to 14 % faster where the costs choose them (65 536 x 512 x 512 274 -> 267 us,
+    // 20 480 x 256 x 640 65 -> 57, 8 192 x 1 024 x 896 129 -> 121), nowhere slower.  Triangular K ranges gain from halves
     // up to 256 tiles (d = 2048, LU step: 0.56 against 0.71 ms).
     auto rounds = [](int64_t n, int64_t slots, double half, double full) {
       const int64_t rem = n % slots;
@@ -2214,8 +2215,9 @@ int launch_tri_pairs(const TriProduct* f, int count, int dp, int b, int d, bool 
   return launch_status("tri_pairs");
 }
 // side of the square of outputs that share a K range, which starts at its first row: x and w hold zeros in the other triangle of
-// the diagonal blocks of that size: 256 (tiles of 256 x 128) where they fill the chip for long enough (d = 4 096 717 -> 706 us of an
-// inverse, 3 072 497 and 505)
+// the diagonal blocks of that size: 256 (tiles of 256 x 128) where they fill the chip for long enough.  us of a binary32 inverse with 128 / 256: d = 1 024
+// 103 / 115, 2 304 383 / 396, 2 816 517 / 509, 3 072 578 / 576, 3 328 575 / 579, 3 840 668 / 661, 4 096 731 / 722, 4 352 1 350 / 1 361, 5 120 2 395 / 2 375, 6 144 3 034 / 2 998,
+// 8 192 4 365 / 4 261: even between 2 560 and 4 352, the larger squares win beyond
 static int tri_last_side(int d) { return d % 256 == 0 && d >= 4096 ? 256 : 128; }
 int tri_last_split(int d) { return d / tri_last_side(d) / 2 * tri_last_side(d); }
 int launch_tri_last(const float* x, const float* w, int ld, float* y, float* y2, int d, hipStream_t s) {
@@ -3161,7 +3163,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 
   // Three slabs in flight before the loop.  A slab's last fragments are in registers when its last MFMAs have yet to run: there the
   // workgroup waits for the next slab and gives the stage to the slab after the next two, so that a load has two slabs' time.  (Waiting where the
-  // slab begins gave it one: steps of the wide and of the large network 1 468 -> 1 454 and 2 322 -> 2 305 us.)
+  // slab begins gave it one: a launch of 128 <-> 256 channels over 32 images of 64 x 64 97.9 -> 95.0 us; of a training step under 1 %.)
   const bool full = __builtin_amdgcn_readfirstlane(wave) + 4 * (G::XU - 1) < G::X_UNITS;   // (loads per slab and wave: L, or one less)
   constexpr int L = G::A_PASSES + G::XU;
   auto landed = [&](int behind) {                // all loads but those of the last `behind` slabs
